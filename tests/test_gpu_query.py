@@ -63,3 +63,20 @@ def test_components_empty_and_invalid():
     with pytest.raises(binding.BtError) as ei:
         binding.bt_bitruss_components(d, torch.zeros(bad.m, dtype=torch.int64, device="cuda"), 1)
     assert ei.value.status == binding.BT_EINVAL
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_components_rows_of_wave_lengths(seed):
+    """Rows of 0 to 200 edges with arbitrary numbers, so that a row's first
+    edge of the k-bitruss lies in any of its 64-edge pieces or in none."""
+    rng = np.random.default_rng(900 + seed)
+    lens = [0, 1, 63, 64, 65, 127, 128, 129, 200, 0, 3]
+    edges = [(i, int(j)) for i, n in enumerate(lens) for j in rng.choice(220, n, replace=False)]
+    g = synth.from_edges(len(lens), 220, edges)
+    ph = np.where(rng.random(g.m) < (0.5, 0.05, 0.01, 0.9)[seed], rng.integers(0, 9, g.m), 0)
+    dg = upload(g)
+    phi = torch.from_numpy(ph.astype(np.int64)).cuda()
+    for k in (-1, 0, 1, 4, 9):
+        comp, c = binding.bt_bitruss_components(dg, phi, k)
+        ocomp, oc = bitruss_components(g.n_upper, g.n_lower, g.row_ptr, g.col, ph, k)
+        assert c == oc and np.array_equal(comp.cpu().numpy(), ocomp), k
