@@ -76,13 +76,14 @@ struct Events {
     }
 };
 
-// Sizes the index from the wedge bound and points `ix` at buffers.
+// Sizes the index from the wedge bound and points `ix` at buffers.  With
+// ix.n_graphs set (small graphs) it holds per-graph regions and no links.
 void alloc_index(const RankCSR &r, IndexArrays &ix, bool owned, Workspace &ws,
                  std::vector<void *> *own) {
     if (r.wedges_po >= (int64_t)UINT32_MAX)
         throw Error{BT_EOVERFLOW, "priority-obeyed wedges must be below 2^32"};
     ix.cap_w = r.wedges_po;
-    ix.cap_b = r.wedges_po / 2;
+    ix.cap_b = r.wedges_po / 2 + ix.n_graphs;
     const int64_t m = r.m;
     auto get = [&](const char *name, size_t bytes) -> void * {
         if (!owned) return ws.get(name, bytes);
@@ -96,6 +97,12 @@ void alloc_index(const RankCSR &r, IndexArrays &ix, bool owned, Workspace &ws,
     ix.web = (int32_t *)get("ix_web", sizeof(int32_t) * (ix.cap_w + 1));
     ix.wbl = (int32_t *)get("ix_wbl", sizeof(int32_t) * (ix.cap_w + 1));
     ix.supl = (uint64_t *)get("ix_supl", sizeof(uint64_t) * (m + 1));
+    if (ix.n_graphs > 0) {
+        ix.butterflies = (int64_t *)get("ix_small", sizeof(uint64_t) * (1 + 2 * (size_t)ix.n_graphs));
+        ix.cursor = (uint64_t *)(ix.butterflies + 1);
+        ix.base = ix.cursor + ix.n_graphs;
+        return;
+    }
     ix.link_off = (int64_t *)get("ix_link_off", sizeof(int64_t) * (m + 1));
     ix.link = (uint3 *)get("ix_link", sizeof(uint3) * (2 * ix.cap_w + 1));
     ix.cursor = (uint64_t *)get("ix_cursor", sizeof(uint64_t) * 2);
@@ -104,7 +111,7 @@ void alloc_index(const RankCSR &r, IndexArrays &ix, bool owned, Workspace &ws,
 
 int64_t index_bytes(const IndexArrays &ix, int64_t m) {
     return (int64_t)(sizeof(uint32_t) + 2 * sizeof(int32_t)) * (ix.n_b + 1) +
-           (int64_t)(3 * sizeof(int32_t) + 2 * sizeof(uint3)) * ix.n_w +
+           (int64_t)(3 * sizeof(int32_t) + 2 * (ix.base ? sizeof(uint2) : sizeof(uint3))) * ix.n_w +
            (int64_t)(sizeof(uint64_t) + sizeof(int64_t) + sizeof(int32_t) * 2) * m +
            (ix.n_w + 31) / 32 * 4;
 }
@@ -120,10 +127,12 @@ void build_all(const bt_csr &g, RankCSR &r, IndexArrays &ix, bool owned,
     if (ev) ev->mark(1);
     alloc_index(r, ix, owned, ws, own);
     zero_bytes(ix.supl, sizeof(uint64_t) * (r.m + 1), s);
-    zero_bytes(ix.cursor, sizeof(uint64_t) * 2, s);
-    build_index(r, t, ix, ws, s);
+    if (ix.n_graphs > 0) zero_bytes(ix.butterflies, sizeof(uint64_t) * (1 + ix.n_graphs), s);
+    else zero_bytes(ix.cursor, sizeof(uint64_t) * 2, s);
+    build_index(r, t, ix, ws, s, comps);
     if (ev) ev->mark(2);
     check_butterfly_total(ix.supl, r.m, ix.butterflies, ws, s);
+    if (ix.n_graphs > 0) return;  // the peel reads the sizes
     int64_t *hs = ws.host(4);
     BT_HIP(hipMemcpyAsync(hs, ix.cursor, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
@@ -172,6 +181,13 @@ bool reorder_single(int64_t m) {
     return m >= kReorderMinEdges && !(v && std::atoi(v) == 0);
 }
 
+// Whether a graph of m edges peels in one workgroup (peel_leaf).
+// BT_PEEL_MODE=graph keeps the grid-wide rounds, as replayed kernels.
+bool leaf_peel(int64_t m, const Workspace &ws) {
+    const char *mv = std::getenv("BT_PEEL_MODE");
+    return m < kLeafEdges && ws.coop && !(mv && std::strcmp(mv, "graph") == 0);
+}
+
 // out[perm[p]] = t[p]: results back to the caller's edge order.
 __global__ void k_unpermute(const uint32_t *perm, int64_t m, const int64_t *sup_t,
                             const int64_t *phi_t, int64_t *sup_out, int64_t *phi_out) {
@@ -208,6 +224,8 @@ void decompose_impl(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0, bt_s
     }
     RankCSR r;
     IndexArrays ix;
+    const bool leaf = g.m > 0 && leaf_peel(g.m, ws);
+    if (leaf) ix.n_graphs = 1;
     build_all(g, r, ix, false, nullptr, ws, stream, &ev);
     ev.mark(3);
     if (auto_pc && g.m > 0) {
@@ -224,7 +242,14 @@ void decompose_impl(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0, bt_s
     PeelCounters pc;
     PeelOptions o;
     o.unit_updates = unit_updates;
-    peel(r, ix, sup_out, phi_out, pc, ws, stream, &o);
+    if (leaf) {
+        int64_t *doff = ws.get<int64_t>("lf_off", 2);
+        const std::vector<int64_t> off{0, g.m};
+        BT_HIP(hipMemcpyAsync(doff, off.data(), 2 * sizeof(int64_t), hipMemcpyHostToDevice, stream));
+        peel_leaf(ix, off, doff, sup_out, phi_out, unit_updates, pc, ws, stream);
+    } else {
+        peel(r, ix, sup_out, phi_out, pc, ws, stream, &o);
+    }
     if (perm) {
         k_unpermute<<<grid_for(g0.m, 256, 16384), 256, 0, stream>>>(
             perm, g0.m, sup_out0 ? sup_out : nullptr, phi_out, sup_out0, phi_out0);
@@ -361,21 +386,29 @@ void decompose_union_impl(const bt_csr &u, const std::vector<int64_t> &off,
     ev.mark(0);
     RankCSR r;
     IndexArrays ix;
+    const char *mode = std::getenv("BT_BATCH_PEEL");
+    const bool as_union = mode && std::strcmp(mode, "union") == 0;
+    int64_t max_m = 0;
+    for (size_t g = 0; g + 1 < off.size(); ++g) max_m = std::max(max_m, off[g + 1] - off[g]);
+    const bool leaf = leaf_peel(max_m, ws) && !as_union;
+    if (leaf) ix.n_graphs = (int32_t)off.size() - 1;
     build_all(u, r, ix, false, nullptr, ws, s, &ev, off.size() > 2, &comps);
     ev.mark(3);
     PeelCounters pc;
     // Per-graph levels pay when there are several graphs, all small: its
     // gathers rescan a graph's whole edge range, where the shared-level peel
     // keeps a threshold active set.  BT_BATCH_PEEL=union forces the latter.
-    int64_t max_m = 0;
-    for (size_t g = 0; g + 1 < off.size(); ++g) max_m = std::max(max_m, off[g + 1] - off[g]);
-    const char *mode = std::getenv("BT_BATCH_PEEL");
-    const bool multi = ws.coop && off.size() > 2 && max_m <= kMultiMaxEdges &&
-                       !(mode && std::strcmp(mode, "union") == 0);
+    const bool multi = ws.coop && off.size() > 2 && max_m <= kMultiMaxEdges && !as_union;
     if (on_sized && *on_sized)
         (*on_sized)((int64_t)ws.bytes(),
-                    peel_state_bytes(u.m, ix.n_b, ix.n_w, (int64_t)off.size() - 1, multi));
-    if (multi)
+                    leaf ? peel_leaf_bytes(u.m, ix.cap_b, ix.cap_w, ix.n_graphs)
+                         : peel_state_bytes(u.m, ix.n_b, ix.n_w, (int64_t)off.size() - 1, multi));
+    if (leaf) {
+        int64_t *doff = ws.get<int64_t>("lf_off", (int64_t)off.size());
+        BT_HIP(hipMemcpyAsync(doff, off.data(), sizeof(int64_t) * off.size(),
+                              hipMemcpyHostToDevice, s));
+        peel_leaf(ix, off, doff, sup_out, phi_out, false, pc, ws, s);
+    } else if (multi)
         peel_multi(r, ix, sup_out, phi_out, off, pc, ws, s);
     else
         peel(r, ix, sup_out, phi_out, pc, ws, s);
@@ -607,7 +640,7 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
                  int64_t *const *phi_out, bt_stats *stats, Workspace &ws, hipStream_t s,
                  const SizedHook *on_sized = nullptr) {
     std::vector<BatchEntry> tab(b - a);
-    int64_t nu = 0, nl = 0, m = 0, max_span = 1;
+    int64_t nu = 0, nl = 0, m = 0, max_span = 1, max_m = 0;
     for (int32_t i = a; i < b; ++i) {
         BatchEntry &E = tab[i - a];
         E.row_ptr = gs[i].row_ptr;
@@ -624,6 +657,7 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
         nl += E.nl;
         m += E.m;
         max_span = std::max<int64_t>(max_span, std::max<int64_t>(E.m, (int64_t)E.nu + 1));
+        max_m = std::max(max_m, E.m);
     }
     const bool splittable = b - a > 1;
     if (splittable && (nu + nl >= INT32_MAX || m >= INT32_MAX)) {
@@ -669,10 +703,12 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     comps.n = b - a;
     comps.l_off = dvoff;
     comps.u_off = dvoff + (b - a + 1);
-    // BT_BATCH_REORDER=0 keeps the union in the callers' numbering.
+    // BT_BATCH_REORDER=0 keeps the union in the callers' numbering.  Graphs
+    // that peel in LDS gain nothing from the order.
     const char *ro = std::getenv("BT_BATCH_REORDER");
-    const uint32_t *perm =
-        ro && std::atoi(ro) == 0 ? nullptr : reorder_union(u, dvoff, b - a, ws, s);
+    const uint32_t *perm = (ro && std::atoi(ro) == 0) || leaf_peel(max_m, ws)
+                               ? nullptr
+                               : reorder_union(u, dvoff, b - a, ws, s);
     bt_stats st;
     try {
         decompose_union_impl(u, off, comps, sup_u, phi_u, stats ? &st : nullptr, ws, s,

@@ -88,15 +88,16 @@ __global__ void k_rank_keys_comp(const int32_t *deg, int32_t n_lower, int32_t n,
     }
 }
 
-// zbase[p]: the first rank of p's graph in p's layer.
+// zbase[p]: the first rank of p's graph in p's layer; vgraph[p]: the graph.
 __global__ void k_zbase(const int32_t *new2old, int32_t n_lower, int32_t n, Components cp,
-                        int32_t *zbase) {
+                        int32_t *zbase, int32_t *vgraph) {
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
          p += (int64_t)gridDim.x * blockDim.x) {
         const int32_t v = new2old[p];
         const bool up = v >= n_lower;
         const int32_t c = up ? comp_of(cp.u_off, cp.n, v - n_lower) : comp_of(cp.l_off, cp.n, v);
         zbase[p] = up ? n_lower + (int32_t)cp.u_off[c] : (int32_t)cp.l_off[c];
+        vgraph[p] = c;
     }
 }
 
@@ -233,7 +234,7 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     int32_t *new2old = ws.get<int32_t>("prep_new2old", n);
     int32_t *deg_new = ws.get<int32_t>("prep_degnew", n);
     const bool uni = comps && comps->n > 1;
-    r.zbase = nullptr;
+    r.zbase = r.vgraph = nullptr;
     if (n > 0) {
         if (uni) {
             const int cbits = bits_for((uint64_t)(comps->n - 1));
@@ -252,8 +253,9 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
         BT_CHECK_LAUNCH();
         if (uni) {
             r.zbase = ws.get<int32_t>("rank_zbase", n);
+            r.vgraph = ws.get<int32_t>("rank_vgraph", n);
             k_zbase<<<grid_for(n, 256, 8192), 256, 0, s>>>(new2old, nl, (int32_t)n, *comps,
-                                                           r.zbase);
+                                                           r.zbase, r.vgraph);
             BT_CHECK_LAUNCH();
         }
     }

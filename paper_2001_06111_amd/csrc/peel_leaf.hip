@@ -1,0 +1,630 @@
+// peel_leaf.hip - the peel of small edge sets, one workgroup each.
+//
+// A graph of fewer than kLeafEdges edges (in a batch: each such graph) peels
+// in one workgroup that keeps every edge's support, link range and state in
+// LDS.  Its rounds are the bulk-synchronous rounds of Algorithm 5, as in the
+// grid-wide peels, but what made those slow for small graphs is gone:
+//   - a round ends in a workgroup barrier (about 0.1 us) instead of two grid
+//     barriers (about 2.3 us each);
+//   - supports fall by LDS atomics; the grid-wide peels issue each decrement
+//     as a memory-side atomic (2.4e10/s for the whole chip);
+//   - a wedge is alive exactly while neither of its edges has been removed,
+//     which the edges' LDS states say, so there are no alive bits to clear.
+// Graphs are independent, so a batch's graphs peel side by side on all CUs,
+// pulled from a queue in decreasing size, and no graph waits for another's
+// rounds.  A round still takes 4.7 to 6.6 us (graphs of 14,000 edges, 350 to
+// 2,100 rounds; 9.4 us grid-wide): about 2 us in each phase, chains of work
+// item, link, bloom state (a returning memory atomic) in phase A and work
+// item, bloom state, wedge records in phase B, at 4 cycles an instruction.
+// Counting the kills in an LDS hash table instead of memory did not shorten
+// it.  512 graphs of 200 to 16,000 edges in one batch: 63.3 ms grid-wide,
+// 19.8 ms so; the 10k-edge uniform graph 0.67 ms and 0.46 ms.
+//
+// The workgroup makes its own link lists (twin and bloom of each wedge of an
+// edge) from the wedge records by counting in LDS, so the index build of
+// these graphs stops at the wedges.
+//
+// Work items are pieces of at most 64 links (phase A) or wedges (phase B).
+// Blooms of small graphs hold few wedges, so a wave takes up to 64 items at
+// once and spreads their elements over its lanes: item j of a lane's element
+// is found from a 64-bit mask of the items' first elements.
+#include <algorithm>
+#include <cstdlib>
+
+#include "peel_common.h"
+
+namespace bt {
+
+namespace {
+
+constexpr int kLeafBlock = 1024;
+constexpr uint32_t kNoTwin = 0xffffffffu;  // the twin is not peeled here
+// An edge's state, in the top bits of the word that holds the end of its
+// links: remaining, queued for an even or an odd round (1, 2), removed.
+enum : uint32_t { kRemaining = 0, kRemoved = 3 };
+constexpr int kStateShift = 30;
+constexpr uint32_t kEndMask = (1u << kStateShift) - 1;
+
+struct LeafArgs {
+    const LeafJob *jobs;
+    int32_t njobs;
+    int32_t *queue;
+    const int32_t *wea, *web, *wbl;
+    const uint32_t *bwoff;
+    const int32_t *bk;  // initial bloom numbers
+    u64 *bs;            // (live wedges at the round's start << 32) | kills this round
+    uint2 *link;        // {bloom, twin}: job's links at [2 w0, 2 (w0 + nw))
+    // Work lists past their part in LDS.
+    uint2 *front[2];    // {edge | (links - 1) << 16, first link}
+    uint2 *items;       // {bloom | multi << 31, first wedge << 6 | (wedges - 1)}
+    int64_t *phi_out;
+    int32_t *glevels;  // levels per graph
+    LeafCtl *ctl;
+};
+
+// First slots of the job's regions of the work lists: an edge has at most
+// one item more than its links / 64, a bloom one more than its wedges / 64.
+__device__ __forceinline__ int64_t front_base(const LeafJob &J, int32_t j) {
+    return (int64_t)J.e0 + J.w0 / 32 + j;
+}
+__device__ __forceinline__ int64_t items_base(const LeafJob &J, int32_t j) {
+    return (int64_t)J.b0 + J.w0 / 64 + j;
+}
+
+// Each lane asks for cnt consecutive slots of a counter in LDS.  Must be
+// called by all 64 lanes.
+__device__ __forceinline__ uint32_t lds_alloc(uint32_t cnt, uint32_t *ctr) {
+    const unsigned long long any = __ballot(cnt != 0);
+    if (!any) return 0;
+    uint32_t before, total;
+    if (!__ballot(cnt > 1)) {
+        before = (uint32_t)__popcll(any & lanemask_lt());
+        total = (uint32_t)__popcll(any);
+    } else {
+        const uint32_t inc = wave_inclusive_sum<uint32_t>(cnt);
+        total = wave_last(inc);
+        before = inc - cnt;
+    }
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(ctr, total);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + before;
+}
+
+// Writes a lane's n elements from lo as items of at most 64: {id | extra of
+// the piece's size, position}.  A lane writes its first piece, the whole wave the
+// others of a longer range.
+template <typename F>
+__device__ __forceinline__ void put_pieces(uint32_t n, uint32_t lo, uint32_t cnt, uint32_t slot,
+                                           uint32_t id, F &&put) {
+    if (cnt) put(slot, id, lo, min((uint32_t)kWave, n), cnt);
+    unsigned long long big = __ballot(cnt > 1);
+    while (big) {
+        const int l = __ffsll(big) - 1;
+        big &= big - 1;
+        const uint32_t bn = __shfl(n, l, kWave), blo = __shfl(lo, l, kWave);
+        const uint32_t bc = __shfl(cnt, l, kWave), bs = __shfl(slot, l, kWave);
+        const uint32_t bi = __shfl(id, l, kWave);
+        for (uint32_t c = 1 + lane_id(); c < bc; c += kWave)
+            put(bs + c, bi, blo + c * kWave, min((uint32_t)kWave, bn - c * kWave), bc);
+    }
+}
+
+// A bloom's state for the next round: its kills leave it.
+__device__ __forceinline__ u64 settle(u64 state) {
+    return (u64)((uint32_t)(state >> 32) - (uint32_t)state) << 32;
+}
+
+// The item of element t0 + lane when the lanes' items start at `start`
+// (increasing over the lanes with ok): the items that start before the
+// window, plus those that start in it at or before this element, less one.
+__device__ __forceinline__ int item_of(bool ok, uint32_t start, uint32_t t0, u64 *mask) {
+    const int before = (int)__popcll(__ballot(ok && start < t0));
+    if (lane_id() == 0) __hip_atomic_store(mask, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (ok && start >= t0 && start < t0 + kWave)
+        __hip_atomic_fetch_or(mask, 1ull << (start - t0), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP);
+    const u64 m = __hip_atomic_load(mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const u64 le = lanemask_lt() | (u64(1) << lane_id());
+    return before + (int)__popcll(m & le) - 1;
+}
+
+// Work lists keep their first entries in LDS (most rounds of a small graph
+// fit) and the rest in global memory at the same index.
+constexpr uint32_t kFrontLds = 512, kItemsLds = 1024;
+
+// LDS of a workgroup for jobs of up to ecap edges (a multiple of 4): the two
+// frontier lists and the bloom items; support and end of links of each edge.
+inline size_t leaf_lds(int ecap) {
+    return sizeof(uint2) * (2 * kFrontLds + kItemsLds) + (size_t)ecap * 8;
+}
+
+// Steps of four edges a thread in which a workgroup scans its edges: a launch
+// has at least ecap / 16 threads.
+constexpr int kScanSteps = 4;
+
+template <bool UNIT>
+__global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0, int32_t j1,
+                                                          int ecap) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    uint2 *const lf0 = reinterpret_cast<uint2 *>(smem_raw), *const lf1 = lf0 + kFrontLds;
+    uint2 *const li = lf1 + kFrontLds;
+    int32_t *const sup = reinterpret_cast<int32_t *>(li + kItemsLds);
+    uint32_t *const ends = reinterpret_cast<uint32_t *>(sup + ecap);
+    __shared__ int32_t s_job, s_min;
+    __shared__ uint32_t s_nf[2], s_ni[2], s_multi[2];
+    __shared__ u64 s_mask[kLeafBlock / kWave];
+    __shared__ uint32_t s_scan[kLeafBlock / kWave + 1];
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int wv = tid / kWave, nwv = nthr / kWave;
+    u64 *const mask = &s_mask[wv];
+    u64 upd = 0, unb = 0;
+    uint32_t touch = 0, visits = 0;
+    u64 rounds = 0;  // thread 0's
+    int32_t max_level = 0;
+
+    while (true) {
+        __syncthreads();
+        if (tid == 0) s_job = j0 + atomicAdd(A.queue, 1);
+        __syncthreads();
+        const int32_t jb = s_job;
+        if (jb >= j1) break;
+        const LeafJob J = A.jobs[jb];
+        const int32_t ne = J.ne, e0 = J.e0;
+        if (ne <= 0 || ne > ecap) continue;  // the host queues none of these
+        uint2 *const link = A.link + 2 * (int64_t)J.w0;
+        uint2 *const fr0 = A.front[0] + front_base(J, jb), *const fr1 = A.front[1] + front_base(J, jb);
+        uint2 *const items = A.items + items_base(J, jb);
+
+        // Supports and link counts from the wedges: a wedge of a k-bloom
+        // gives each of its edges k - 1 butterflies (Lemma 2) and one link.
+        for (int i = tid; i < ne; i += nthr) {
+            sup[i] = 0;
+            ends[i] = 0;
+        }
+        if (tid == 0) {
+            s_min = INT_MAX;
+            s_nf[0] = s_nf[1] = s_ni[0] = s_ni[1] = s_multi[0] = s_multi[1] = 0;
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < J.nw; i += nthr) {
+            const uint32_t w = J.w0 + i;
+            const int32_t d = A.bk[A.wbl[w]] - 1;
+            const uint32_t a = (uint32_t)A.wea[w], b = (uint32_t)A.web[w];
+            if (!(a & kFixedBit)) {
+                atomicAdd(&sup[a - e0], d);
+                atomicAdd(&ends[a - e0], 1u);
+            }
+            if (!(b & kFixedBit)) {
+                atomicAdd(&sup[b - e0], d);
+                atomicAdd(&ends[b - e0], 1u);
+            }
+        }
+        __syncthreads();
+        {
+            // Exclusive prefix of the link counts, in place; each thread owns
+            // a run of edges.
+            const int per = (ne + nthr - 1) / nthr;
+            const int i0 = min(tid * per, ne), i1 = min(i0 + per, ne);
+            uint32_t mine = 0;
+            for (int i = i0; i < i1; ++i) mine += ends[i];
+            uint32_t total;
+            uint32_t run = block_exclusive_sum<uint32_t>(mine, s_scan, &total);
+            for (int i = i0; i < i1; ++i) {
+                const uint32_t c = ends[i];
+                ends[i] = run;
+                run += c;
+            }
+        }
+        __syncthreads();
+        // The links; ends[e] moves from the start of e's links to their end,
+        // which is where e + 1's begin.
+        for (uint32_t i = tid; i < J.nw; i += nthr) {
+            const uint32_t w = J.w0 + i;
+            const uint32_t bl = (uint32_t)A.wbl[w];
+            const uint32_t a = (uint32_t)A.wea[w], b = (uint32_t)A.web[w];
+            const uint32_t la = a & kFixedBit ? kNoTwin : a - (uint32_t)e0;
+            const uint32_t lb = b & kFixedBit ? kNoTwin : b - (uint32_t)e0;
+            if (la != kNoTwin) link[atomicAdd(&ends[la], 1u)] = make_uint2(bl, lb);
+            if (lb != kNoTwin) link[atomicAdd(&ends[lb], 1u)] = make_uint2(bl, la);
+        }
+        // Edges past the end, up to a multiple of four, are removed ones.
+        if (tid < 4 && ne + tid < ((ne + 3) & ~3)) ends[ne + tid] = kRemoved << kStateShift;
+        __syncthreads();
+
+        // Queues edge t (lanes with pred) for the round of parity q; all 64
+        // lanes call.  An edge without links needs no work item.
+        const auto push_front = [&](bool pred, uint32_t t, int q, int32_t level) {
+            if (!__ballot(pred)) return;
+            uint32_t lo = 0, n = 0;
+            if (pred) {
+                A.phi_out[(int64_t)e0 + t] = level;
+                const uint32_t end = ends[t] & kEndMask;
+                lo = t ? ends[t - 1] & kEndMask : 0u;
+                n = end - lo;
+                ends[t] = end | ((uint32_t)(1 + q) << kStateShift);
+            }
+            if (!__ballot(n != 0)) return;
+            const uint32_t cnt = (n + kWave - 1) / kWave;
+            const uint32_t slot = lds_alloc(cnt, &s_nf[q]);
+            uint2 *const list = q ? fr1 : fr0, *const near = q ? lf1 : lf0;
+            put_pieces(n, lo, cnt, slot, t,
+                       [&](uint32_t s, uint32_t id, uint32_t at, uint32_t len, uint32_t) {
+                           const uint2 v = make_uint2(id | ((len - 1) << 16), at);
+                           if (s < kFrontLds) near[s] = v;
+                           else list[s] = v;
+                       });
+        };
+
+        int32_t levels = 0;
+        int r = 0;
+        while (true) {
+            // The next level: the smallest support among the remaining edges,
+            // which are then taken from the same registers (the scan is bound
+            // by LDS bandwidth).
+            int32_t v[kScanSteps][4];
+            int32_t mn = INT_MAX;
+#pragma unroll
+            for (int k = 0; k < kScanSteps; ++k) {
+                const int i = 4 * (tid + k * nthr);
+                uint4 en = make_uint4(~0u, ~0u, ~0u, ~0u);
+                int4 x = make_int4(0, 0, 0, 0);
+                if (i < ne) {
+                    en = *reinterpret_cast<const uint4 *>(&ends[i]);
+                    x = *reinterpret_cast<const int4 *>(&sup[i]);
+                }
+                v[k][0] = en.x > kEndMask ? INT_MAX : x.x;
+                v[k][1] = en.y > kEndMask ? INT_MAX : x.y;
+                v[k][2] = en.z > kEndMask ? INT_MAX : x.z;
+                v[k][3] = en.w > kEndMask ? INT_MAX : x.w;
+                mn = min(mn, min(min(v[k][0], v[k][1]), min(v[k][2], v[k][3])));
+            }
+            mn = wave_min(mn);
+            if (lane_id() == 0 && mn != INT_MAX) atomicMin(&s_min, mn);
+            __syncthreads();
+            const int32_t level = s_min;
+            if (level == INT_MAX) break;
+            if (mn == level) {  // this wave has some (wave_min gives every lane the minimum)
+#pragma unroll
+                for (int k = 0; k < kScanSteps; ++k)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        push_front(v[k][c] == level, (uint32_t)(4 * (tid + k * nthr) + c), r & 1,
+                                   level);
+            }
+            __syncthreads();
+            if (tid == 0) s_min = INT_MAX;
+            ++levels;
+            if (level > max_level) max_level = level;
+            uint32_t nf = s_nf[r & 1];
+            while (nf > 0) {
+                const int p = r & 1, q = p ^ 1;
+                const uint32_t cur = 1 + p, nxt = 1 + q;
+                const uint2 *const fl = p ? fr1 : fr0, *const fn = p ? lf1 : lf0;
+                const auto front_item = [&](uint32_t i) { return i < kFrontLds ? fn[i] : fl[i]; };
+                // Phase A: the frontier's links.  A wedge whose edges are both
+                // in the frontier is killed by the smaller one.
+                {
+                    const uint32_t per = min((uint32_t)kWave, (nf + nwv - 1) / nwv);
+                    for (uint32_t g0 = wv * per; g0 < nf; g0 += nwv * per) {
+                        const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < nf;
+                        uint2 it = make_uint2(0, 0);
+                        if (ok) it = front_item(g0 + lane_id());
+                        const uint32_t n = ok ? (it.x >> 16) + 1 : 0u;
+                        const uint32_t e = it.x & 0xffffu;
+                        const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
+                        const uint32_t start = inc - n;
+                        const uint32_t total = wave_last(inc);
+                        for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
+                            const int j = item_of(ok, start, t0, mask);
+                            const uint32_t x = t0 + lane_id();
+                            const bool act = x < total;
+                            const uint32_t ej = __shfl(e, j, kWave);
+                            const uint32_t at = __shfl(it.y - start, j, kWave) + x;
+                            uint32_t bl = 0, t = kNoTwin, w0 = 0, w1 = 0, s = kRemaining;
+                            u64 old = 1;
+                            bool alive = false;
+                            if (act) {
+                                const uint2 lk = link[at];
+                                bl = lk.x;
+                                t = lk.y;
+                                if (t != kNoTwin) s = ends[t] >> kStateShift;
+                                alive = s != kRemoved && !(s == cur && t < ej);
+                                w0 = A.bwoff[bl];
+                                w1 = A.bwoff[bl + 1];
+                                if (alive) old = atomicAdd(&A.bs[bl], (u64)1);
+                            }
+                            // The twin, if it stays, loses its k - 1 butterflies.
+                            const int32_t kb = (int32_t)(old >> 32), d = kb - 1;
+                            const bool dec = alive && t != kNoTwin && s != cur && d > 0;
+                            int32_t o = 0;
+                            if (dec) o = atomicSub(&sup[t], d);
+                            push_front(dec && o > level && o - d <= level, t, q, level);
+                            upd += dec ? 1 : 0;
+                            // The bloom's first kill this round queues it.
+                            const bool first = alive && (uint32_t)old == 0 && kb > 1;
+                            if (__ballot(first)) {
+                                const uint32_t len = first ? w1 - w0 : 0u;
+                                const uint32_t cnt = (len + kWave - 1) / kWave;
+                                const uint32_t slot = lds_alloc(cnt, &s_ni[p]);
+                                if (cnt > 1) s_multi[p] = 1;
+                                put_pieces(len, w0 - J.w0, cnt, slot, bl,
+                                           [&](uint32_t sl, uint32_t id, uint32_t pos, uint32_t pn,
+                                               uint32_t pieces) {
+                                               const uint2 v = make_uint2(
+                                                   id | (pieces > 1 ? 0x80000000u : 0u),
+                                                   (pos << 6) | (pn - 1));
+                                               if (sl < kItemsLds) li[sl] = v;
+                                               else items[sl] = v;
+                                           });
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+                const uint32_t ni = s_ni[p];
+                const bool multi = s_multi[p] != 0;
+                if (tid == 0) {
+                    s_nf[p] = 0;
+                    s_ni[q] = 0;
+                    s_multi[q] = 0;
+                    rounds += 1;
+                }
+                for (uint32_t i = tid; i < nf; i += nthr) {
+                    uint32_t *const en = &ends[front_item(i).x & 0xffffu];
+                    *en = (*en & kEndMask) | (kRemoved << kStateShift);
+                }
+                // Phase B: survivors of touched blooms lose their C kills.
+                {
+                    const uint32_t per = min((uint32_t)kWave, (ni + nwv - 1) / nwv);
+                    for (uint32_t g0 = wv * per; g0 < ni; g0 += nwv * per) {
+                        const uint32_t i = g0 + lane_id();
+                        const bool ok = (uint32_t)lane_id() < per && i < ni;
+                        uint2 it = make_uint2(0, 0);
+                        u64 state = 0;
+                        if (ok) {
+                            it = i < kItemsLds ? li[i] : items[i];
+                            state = ld(&A.bs[it.x & kEdgeMask]);  // arrives with the wedges
+                        }
+                        const uint32_t n = ok ? (it.y & 63u) + 1 : 0u;
+                        const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
+                        const uint32_t start = inc - n;
+                        const uint32_t total = wave_last(inc);
+                        for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
+                            const int j = item_of(ok, start, t0, mask);
+                            const uint32_t x = t0 + lane_id();
+                            const bool act = x < total;
+                            const uint32_t w = J.w0 + __shfl((it.y >> 6) - start, j, kWave) + x;
+                            uint32_t a = kFixedBit, b = kFixedBit;
+                            if (act) {
+                                a = (uint32_t)A.wea[w];
+                                b = (uint32_t)A.web[w];
+                            }
+                            const int32_t cj = __shfl((int32_t)(uint32_t)state, j, kWave);
+                            const bool oa = !(a & kFixedBit), ob = !(b & kFixedBit);
+                            const uint32_t la = a - (uint32_t)e0, lb = b - (uint32_t)e0;
+                            const uint32_t sa = oa ? ends[la] >> kStateShift : (uint32_t)kRemaining;
+                            const uint32_t sb = ob ? ends[lb] >> kStateShift : (uint32_t)kRemaining;
+                            const bool live = act && (sa == kRemaining || sa == nxt) &&
+                                              (sb == kRemaining || sb == nxt);
+                            const bool da = live && oa, db = live && ob;
+                            bool f1 = false, f2 = false;
+                            if (UNIT) {
+                                // Without batch bloom processing: one unit per
+                                // kill; the step from level + 1 crosses.
+                                for (int32_t c = 0; c < (live ? cj : 0); ++c) {
+                                    if (da) f1 |= atomicSub(&sup[la], 1) == level + 1;
+                                    if (db) f2 |= atomicSub(&sup[lb], 1) == level + 1;
+                                }
+                                upd += (u64)((da ? cj : 0) + (db ? cj : 0));
+                            } else {
+                                int32_t o1 = 0, o2 = 0;
+                                if (da) o1 = atomicSub(&sup[la], cj);
+                                if (db) o2 = atomicSub(&sup[lb], cj);
+                                f1 = da && o1 > level && o1 - cj <= level;
+                                f2 = db && o2 > level && o2 - cj <= level;
+                                upd += (u64)((da ? 1 : 0) + (db ? 1 : 0));
+                                unb += (u64)((da ? cj - 1 : 0) + (db ? cj - 1 : 0));
+                            }
+                            touch += live ? 1 : 0;
+                            push_front(f1, la, q, level);
+                            push_front(f2, lb, q, level);
+                        }
+                        // A bloom of one piece is settled by its reader.
+                        if (ok && !(it.x & 0x80000000u)) {
+                            st(&A.bs[it.x], settle(state));
+                            visits += 1;
+                        }
+                    }
+                }
+                __syncthreads();
+                if (multi) {
+                    for (uint32_t i = tid; i < ni; i += nthr) {
+                        const uint2 it = i < kItemsLds ? li[i] : items[i];
+                        const uint32_t b = it.x & kEdgeMask;
+                        if (!(it.x & 0x80000000u) || A.bwoff[b] != J.w0 + (it.y >> 6)) continue;
+                        st(&A.bs[b], settle(ld(&A.bs[b])));
+                        visits += 1;
+                    }
+                    __syncthreads();
+                }
+                ++r;
+                nf = s_nf[r & 1];
+            }
+        }
+        if (tid == 0) atomicAdd(&A.glevels[J.graph], levels);
+    }
+    upd = wave_sum(upd);
+    unb = wave_sum(unb);
+    const u64 tt = wave_sum<u64>(touch), vv = wave_sum<u64>(visits);
+    if (lane_id() == 0) {
+        if (upd) atomicAdd(&A.ctl->updates, upd);
+        if (unb) atomicAdd(&A.ctl->unbatched, unb);
+        if (tt) atomicAdd(&A.ctl->touched, tt);
+        if (vv) atomicAdd(&A.ctl->bloom_visits, vv);
+    }
+    if (tid == 0) {
+        if (rounds) atomicAdd(&A.ctl->rounds, rounds);
+        atomicMax(&A.ctl->max_level, max_level);
+    }
+}
+
+// The jobs of a union's small graphs: graph g's edges [off[g], off[g + 1]),
+// its blooms and wedges from its bases to where its cursor stopped.
+__global__ void k_leaf_jobs(const int64_t *off, int32_t ng, const uint64_t *base,
+                            const uint64_t *cursor, LeafJob *jobs, LeafCtl *ctl) {
+    u64 nb = 0, nw = 0;
+    for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < ng; g += gridDim.x * blockDim.x) {
+        LeafJob J;
+        J.e0 = (int32_t)off[g];
+        J.ne = (int32_t)(off[g + 1] - off[g]);
+        J.w0 = (uint32_t)base[g];
+        J.nw = (uint32_t)cursor[g] - J.w0;
+        J.b0 = (uint32_t)(base[g] >> 32);
+        J.nb = (uint32_t)(cursor[g] >> 32) - J.b0;
+        J.graph = g;
+        J.pad = 0;
+        jobs[g] = J;
+        nb += J.nb;
+        nw += J.nw;
+    }
+    nb = wave_sum(nb);
+    nw = wave_sum(nw);
+    if (lane_id() == 0) {
+        if (nb) atomicAdd(&ctl->blooms, nb);
+        if (nw) atomicAdd(&ctl->wedges, nw);
+    }
+}
+
+// Bloom states; slots between the graphs' regions hold leftovers, unused.
+__global__ void k_leaf_state(const int32_t *bk, int64_t n, u64 *bs) {
+    for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < n;
+         b += (int64_t)gridDim.x * blockDim.x)
+        bs[b] = (u64)(uint32_t)bk[b] << 32;
+}
+
+// Workgroups of a launch, by the largest job's edges: small jobs take less
+// LDS and fewer waves, so several share a compute unit.
+struct LeafClass {
+    int ecap, threads;
+};
+constexpr LeafClass kLeafClasses[] = {{(int)kLeafEdges, 1024}, {7168, 512}, {2048, 256}};
+constexpr int kNumLeafClasses = 3;
+
+}  // namespace
+
+int64_t peel_leaf_bytes(int64_t m, int64_t cap_b, int64_t cap_w, int64_t graphs) {
+    const int64_t front = m + cap_w / 32 + graphs + 1, items = cap_b + cap_w / 64 + graphs + 1;
+    const int64_t t = 16 * cap_w + 16 * front + 8 * items + 8 * (cap_b + 1) + 48 * graphs + 4096;
+    return t + t / 8;
+}
+
+void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *doff,
+               int64_t *sup_out, int64_t *phi_out, bool unit_updates, PeelCounters &pc,
+               Workspace &ws, hipStream_t s) {
+    const int32_t ng = (int32_t)off.size() - 1;
+    const int64_t m = off[(size_t)ng];
+    if (m == 0) return;
+    LeafArgs A{};
+    LeafJob *jobs = ws.get<LeafJob>("lf_jobs", ng);
+    LeafCtl *ctl = ws.get<LeafCtl>("lf_ctl", 1);
+    A.jobs = jobs;
+    A.njobs = ng;
+    A.wea = ix.wea;
+    A.web = ix.web;
+    A.wbl = ix.wbl;
+    A.bwoff = ix.bwoff;
+    A.bk = ix.bk;
+    A.bs = ws.get<u64>("lf_bs", ix.cap_b + 1);
+    A.link = ws.get<uint2>("lf_link", 2 * ix.cap_w + 1);
+    A.front[0] = ws.get<uint2>("lf_front0", m + ix.cap_w / 32 + ng + 1);
+    A.front[1] = ws.get<uint2>("lf_front1", m + ix.cap_w / 32 + ng + 1);
+    A.items = ws.get<uint2>("lf_items", ix.cap_b + ix.cap_w / 64 + ng + 1);
+    A.phi_out = phi_out;
+    A.glevels = ws.get<int32_t>("lf_levels", ng);
+    A.ctl = ctl;
+    zero_bytes(ctl, sizeof(LeafCtl), s);
+    zero_bytes(A.glevels, sizeof(int32_t) * ng, s);
+    k_leaf_state<<<grid_for(ix.cap_b + 1, 256, 8192), 256, 0, s>>>(ix.bk, ix.cap_b + 1, A.bs);
+    BT_CHECK_LAUNCH();
+    k_leaf_jobs<<<grid_for(ng, 256, 256), 256, 0, s>>>(doff, ng, ix.base, ix.cursor, jobs, ctl);
+    BT_CHECK_LAUNCH();
+    if (sup_out) supl_to_sup(ix.supl, sup_out, m, s);
+    int dev = 0, cus = 0;
+    BT_HIP(hipGetDevice(&dev));
+    BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    hipEvent_t ev0, ev1;
+    BT_HIP(hipEventCreate(&ev0));
+    BT_HIP(hipEventCreate(&ev1));
+    struct EvFree {
+        hipEvent_t a, b;
+        ~EvFree() {
+            (void)hipEventDestroy(a);
+            (void)hipEventDestroy(b);
+        }
+    } ev_free{ev0, ev1};
+    const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
+    BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)leaf_lds((int)kLeafEdges)));
+    // This peel needs no co-resident workgroups, but it takes its turn like
+    // the others, so that a running peel of a much larger graph gives way.
+    CoopTurn turn(m);
+    BT_HIP(hipEventRecord(ev0, s));
+    // Jobs come in decreasing size: each class is a range of them.  The
+    // classes run beside each other on side streams (one after another they
+    // took the sum of their longest jobs: 24 ms against 14 for 512 graphs of
+    // up to 16,000 edges).
+    int32_t a = 0;
+    hipEvent_t joins[kNumLeafClasses] = {};
+    struct JoinFree {
+        hipEvent_t *e;
+        ~JoinFree() {
+            for (int c = 0; c < kNumLeafClasses; ++c)
+                if (e[c]) (void)hipEventDestroy(e[c]);
+        }
+    } join_free{joins};
+    for (int c = 0; c < kNumLeafClasses; ++c) {
+        const int64_t below = c + 1 < kNumLeafClasses ? kLeafClasses[c + 1].ecap : 0;
+        int32_t b = a;
+        while (b < ng && off[(size_t)b + 1] - off[(size_t)b] > below) ++b;
+        if (b > a) {
+            const LeafClass &K = kLeafClasses[c];
+            int occ = 0;
+            BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, K.threads,
+                                                                leaf_lds(K.ecap)));
+            const int grid = std::min<int>(b - a, cus * std::max(1, occ));
+            const hipStream_t cs = b == ng ? s : ws.side(c);  // the last class stays on s
+            A.queue = &ctl->queue[c];
+            if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
+            kern<<<grid, K.threads, leaf_lds(K.ecap), cs>>>(A, a, b, K.ecap);
+            BT_CHECK_LAUNCH();
+            if (cs != s) {
+                BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
+                BT_HIP(hipEventRecord(joins[c], cs));
+            }
+        }
+        a = b;
+    }
+    for (hipEvent_t e : joins)
+        if (e) BT_HIP(hipStreamWaitEvent(s, e, 0));
+    BT_HIP(hipEventRecord(ev1, s));
+    LeafCtl *hc = reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (ng + 1) / 2)));
+    int32_t *hl = reinterpret_cast<int32_t *>(hc + 1);
+    BT_HIP(hipMemcpyAsync(hc, ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));
+    BT_HIP(hipMemcpyAsync(hl, A.glevels, sizeof(int32_t) * ng, hipMemcpyDeviceToHost, s));
+    BT_HIP(hipStreamSynchronize(s));
+    float t = 0.f;
+    BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
+    pc.kernel_ms += t;
+    pc.launches += 1;
+    pc.rounds = (int64_t)hc->rounds;
+    pc.updates = (int64_t)hc->updates;
+    pc.updates_unbatched = pc.updates + (int64_t)hc->unbatched;
+    pc.bloom_visits = (int64_t)hc->bloom_visits;
+    pc.touched = (int64_t)hc->touched;
+    pc.max_phi = hc->max_level;
+    for (int32_t g = 0; g < ng; ++g) pc.levels = std::max<int64_t>(pc.levels, hl[g]);
+    ix.n_b = (int64_t)hc->blooms;
+    ix.n_w = (int64_t)hc->wedges;
+}
+
+}  // namespace bt

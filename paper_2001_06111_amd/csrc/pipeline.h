@@ -67,6 +67,7 @@ struct RankCSR {
     // Unions only: the first rank of x's graph in x's layer (end vertices of
     // x's wedges lie in [zbase[x], x)); null for a single graph.
     int32_t *zbase = nullptr;
+    int32_t *vgraph = nullptr;  // unions only: the graph of x
 };
 
 // Work items of the wedge sweeps.
@@ -97,6 +98,11 @@ struct IndexArrays {
     int64_t *link_off = nullptr;  // [m + 1]
     uint3 *link = nullptr;        // [2 cap_w] {wedge, bloom of the wedge, twin edge}
     uint64_t *cursor = nullptr;   // device (blooms << 32) | wedges allocated
+    // Small graphs (peel_leaf): each graph's blooms and wedges lie together,
+    // from base[g] (packed as the cursor) to cursor[g]; no links are built,
+    // and n_b, n_w are filled by the peel.
+    int32_t n_graphs = 0;
+    uint64_t *base = nullptr;
     int64_t *butterflies = nullptr;  // device scalar
 };
 
@@ -126,9 +132,11 @@ void count_support(const RankCSR &r, const TaskLists &t, uint64_t *supl, int64_t
                    hipStream_t s);
 
 // Counting plus index emission into `ix` (arrays sized by the caller from
-// r.wedges_po).  Fills supl and cursor; then builds the link lists.
+// r.wedges_po).  Fills supl and cursor; then builds the link lists.  With
+// ix.base (small graphs; comps: the union's graphs) each graph's blooms and
+// wedges lie together and the link lists are left out.
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
-                 hipStream_t s);
+                 hipStream_t s, const Components *comps = nullptr);
 
 // Peel through the index.  sup_out (int64, nullable) receives the initial
 // supports, phi_out (int64) the bitruss numbers.
@@ -174,6 +182,27 @@ void peel(const RankCSR &r, IndexArrays &ix, int64_t *sup_out, int64_t *phi_out,
 // which every graph advances at its own level (one cooperative kernel).
 void peel_multi(const RankCSR &r, IndexArrays &ix, int64_t *sup_out, int64_t *phi_out,
                 const std::vector<int64_t> &off, PeelCounters &pc, Workspace &ws, hipStream_t s);
+
+// Graphs with fewer edges than this peel in one workgroup each (peel_leaf).
+constexpr int64_t kLeafEdges = int64_t(1) << 14;
+struct LeafJob {
+    int32_t e0, ne;       // edges [e0, e0 + ne)
+    uint32_t w0, nw;      // wedges [w0, w0 + nw)
+    uint32_t b0, nb;      // blooms [b0, b0 + nb)
+    int32_t graph, pad;
+};
+struct LeafCtl {
+    int32_t queue[4];  // next job of each launch
+    int32_t max_level, pad;
+    unsigned long long rounds, updates, unbatched, bloom_visits, touched, blooms, wedges;
+};
+// The peel of an index built with per-graph regions (ix.base): one graph, or
+// a union whose graphs [off[g], off[g+1]) (doff: the same on the device) are
+// in decreasing size and all below kLeafEdges.  Fills ix.n_b and ix.n_w.
+void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *doff,
+               int64_t *sup_out, int64_t *phi_out, bool unit_updates, PeelCounters &pc,
+               Workspace &ws, hipStream_t s);
+int64_t peel_leaf_bytes(int64_t m, int64_t cap_b, int64_t cap_w, int64_t graphs);
 
 // Sets the fixed-edge mark in wedge records and link twins (progressive mode).
 void mark_fixed(IndexArrays &ix, const int32_t *fixed, hipStream_t s);

@@ -109,8 +109,17 @@ void device_free(void *p) {
 
 Workspace::~Workspace() { close(); }
 
+hipStream_t Workspace::side(int k) {
+    if (!side_[k]) BT_HIP(hipStreamCreateWithFlags(&side_[k], hipStreamNonBlocking));
+    return side_[k];
+}
+
 void Workspace::close() {
     release();
+    for (hipStream_t &t : side_) {
+        if (t) (void)hipStreamDestroy(t);
+        t = nullptr;
+    }
     if (!stream_) return;
     (void)hipStreamSynchronize(stream_);
     for (int64_t *h : old_host_) (void)hipHostFree(h);

@@ -35,7 +35,8 @@ struct WedgeArgs {
     int64_t *bf;
     int64_t *queue;  // dynamic task counter
     // index mode
-    uint64_t *cursor;
+    uint64_t *cursor;       // of the whole index, or of each graph (vgraph)
+    const int32_t *vgraph;  // nullable: the graph of each start vertex
     uint32_t *bwoff;
     int32_t *bk;
     int32_t *wea;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tas
             if (S.totals[2]) atomicAdd((unsigned long long *)A.bf, (unsigned long long)S.totals[2]);
             S.base = 0;
             if (INDEX && S.totals[0])
-                S.base = atomicAdd((unsigned long long *)A.cursor,
+                S.base = atomicAdd((unsigned long long *)A.cursor + (A.vgraph ? A.vgraph[T.x] : 0),
                                    ((unsigned long long)S.totals[0] << 32) |
                                        (unsigned long long)S.totals[1]);
         }
@@ -314,9 +315,35 @@ __global__ void k_link_scatter(const int32_t *wea, const int32_t *web, const int
     }
 }
 
-__global__ void k_bloom_sentinel(const uint64_t *cursor, uint32_t *bwoff) {
-    const uint64_t c = *cursor;
-    bwoff[c >> 32] = (uint32_t)(c & 0xffffffffu);
+__global__ void k_bloom_sentinel(const uint64_t *cursor, int32_t n, uint32_t *bwoff) {
+    for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n; g += gridDim.x * blockDim.x) {
+        const uint64_t c = cursor[g];
+        bwoff[c >> 32] = (uint32_t)(c & 0xffffffffu);
+    }
+}
+
+// Regions of a union's graphs: graph g has room for its priority-obeyed
+// wedges (those started in its lower and in its upper rank range) and for
+// half as many blooms and a sentinel.  One workgroup.
+__global__ __launch_bounds__(1024) void k_graph_bases(const int64_t *off, const int64_t *wpre,
+                                                      int32_t n_lower, Components cp,
+                                                      uint64_t *base, uint64_t *cursor) {
+    __shared__ uint64_t scr[1024 / kWave + 1];
+    uint64_t carry = 0;
+    for (int32_t g0 = 0; g0 < cp.n; g0 += blockDim.x) {
+        const int32_t g = g0 + threadIdx.x;
+        uint64_t mine = 0;
+        if (g < cp.n) {
+            const int64_t u0 = n_lower + cp.u_off[g], u1 = n_lower + cp.u_off[g + 1];
+            const uint64_t w = (uint64_t)(wpre[off[cp.l_off[g + 1]]] - wpre[off[cp.l_off[g]]] +
+                                          wpre[off[u1]] - wpre[off[u0]]);
+            mine = ((w / 2 + 1) << 32) | w;
+        }
+        uint64_t total;
+        const uint64_t pre = block_exclusive_sum<uint64_t>(mine, scr, &total) + carry;
+        if (g < cp.n) base[g] = cursor[g] = pre;
+        carry += total;
+    }
 }
 
 template <bool DENSE, bool INDEX>
@@ -380,7 +407,7 @@ void count_support(const RankCSR &r, const TaskLists &t, uint64_t *supl, int64_t
 }
 
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
-                 hipStream_t s) {
+                 hipStream_t s, const Components *comps) {
     int64_t *queue = ws.get<int64_t>("wedge_queue", 1);
     WedgeArgs A = make_args(r, ix.supl, ix.butterflies, queue);
     A.cursor = ix.cursor;
@@ -389,10 +416,21 @@ void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspac
     A.wea = ix.wea;
     A.web = ix.web;
     A.wbl = ix.wbl;
+    if (ix.base) {  // small graphs: per-graph regions, no links
+        if (ix.n_graphs > 1) {
+            k_graph_bases<<<1, 1024, 0, s>>>(r.off, r.wpre, r.n_lower, *comps, ix.base, ix.cursor);
+            BT_CHECK_LAUNCH();
+            A.vgraph = r.vgraph;
+        } else {
+            zero_bytes(ix.base, sizeof(uint64_t), s);
+        }
+    }
     launch_wedge<true, true>(A, t.dense, t.n_dense, r.tp.wedge_wg_per_cu, s);
     launch_wedge<false, true>(A, t.hash, t.n_hash, r.tp.wedge_wg_per_cu, s);
-    k_bloom_sentinel<<<1, 1, 0, s>>>(ix.cursor, ix.bwoff);
+    const int32_t nc = ix.base ? ix.n_graphs : 1;
+    k_bloom_sentinel<<<grid_for(nc, 256, 256), 256, 0, s>>>(ix.cursor, nc, ix.bwoff);
     BT_CHECK_LAUNCH();
+    if (ix.base) return;
 
     // Links: per-edge counts -> offsets -> scatter.
     const int64_t m = r.m;

@@ -1,0 +1,50 @@
+"""The workgroup peel of small graphs (below 2^14 edges) at its edges: the
+largest graph it takes and the smallest it does not, the limits of its
+launch sizes (2,048 and 7,168 edges), dense graphs whose blooms and link
+lists span many work items, and batches that mix sizes.  Bit-exact against
+the oracle."""
+import numpy as np
+import pytest
+
+from paper_2001_06111_amd import binding, synth
+from tests import graphs
+from tests.gpu_util import oracle_all, upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _cl(m):
+    return synth.chung_lu(max(20, m // 20), max(30, m // 12), m, 2.2, 2.2, m / 4, m / 4, m)
+
+
+@pytest.mark.parametrize("m", [1, 63, 65, 2047, 2048, 2049, 7168, 7169, 16383, 16384, 16385])
+def test_sizes(m):
+    g = _cl(m) if m > 64 else synth.uniform(20, 30, m, m)
+    osup, obf, ophi = oracle_all(g)
+    sup, phi, st = binding.bt_decompose(upload(g), stats=True)
+    assert np.array_equal(sup.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+    assert st["butterflies"] == obf and st["max_phi"] == int(ophi.max())
+    assert st["levels"] == np.unique(ophi).size
+
+
+@pytest.mark.parametrize("g", [synth.complete(127, 129), synth.complete(2, 8000),
+                               graphs.random_dense(150, 140, 0.7, 5),
+                               graphs.random_dense(1000, 16, 0.9, 6)], ids=lambda g: g.name)
+def test_dense(g):
+    osup, _, ophi = oracle_all(g)
+    for variant in (binding.BT_PEEL_BATCH_BLOOM, binding.BT_PEEL_BATCH_EDGE):
+        sup, phi, _ = binding.bt_decompose_variant(upload(g), variant)
+        assert np.array_equal(sup.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+
+
+def test_batch_of_mixed_sizes():
+    gs = [_cl(m) for m in (70, 16384, 300, 2049, 16383, 7169, 5000, 20000, 2048)]
+    gs += [synth.from_edges(3, 3, []), synth.complete(90, 90), graphs.star(50)]
+    sups, phis, st = binding.bt_decompose_batch([upload(g) for g in gs], stats=True)
+    wedges = 0
+    for g, s, p in zip(gs, sups, phis):
+        osup, _, ophi = oracle_all(g)
+        assert np.array_equal(s.cpu().numpy(), osup) and np.array_equal(p.cpu().numpy(), ophi)
+        if g.m:
+            wedges += binding.bt_decompose(upload(g), stats=True)[2]["bloom_wedges"]
+    assert st["bloom_wedges"] == wedges
