@@ -11,7 +11,7 @@ batched and plain graphs/s come from identical inputs, and every plain
 result is compared with the batched one.
 
 Also reported, each only if the wall-time budget (--budget) still allows
-it: the dominant kernel (k_peel_multi) against the HBM roofline with the
+it: the peel (k_sweep and k_peel_leaf) against the HBM roofline with the
 algorithmic bytes of the method; single graphs (10k-edge uniform, 5M-edge
 Chung-Lu, 20M-edge hub graph by the plain peel and by BiT-PC) with their
 own rooflines; served against plain FIFO latency on a window of Poisson
@@ -36,6 +36,7 @@ sys.path.insert(0, ROOT)
 T_START = time.perf_counter()
 PEAK_HBM_GBS = 8000.0  # MI355X HBM3E, GB/s
 POOL = 4096
+PEEL_SOURCES = ("peel_split.hip", "peel_leaf.hip", "regroup.hip", "peel_common.h", "api.hip")
 
 
 def log(msg):
@@ -235,7 +236,7 @@ def single(name, g, reps, warmup, golden, variant=None, tau=None, traffic=None):
            "counters": {k: st[k] for k in ("butterflies", "wedges_po", "blooms", "bloom_wedges",
                                            "levels", "rounds", "max_phi", "support_updates",
                                            "wedge_visits", "passes")}}
-    out["roofline"] = roofline("k_peel_persistent", st,
+    out["roofline"] = roofline("k_sweep + k_peel_leaf", st,
                                traffic * max(1, st["peel_launches"]) if traffic else None)
     del dg, phi
     torch.cuda.empty_cache()
@@ -411,8 +412,7 @@ def main():
     want = golden.get(f"pool:{POOL}", {}).get("phi_sha256")
     check = "no-oracle-digest" if want is None else ("match" if want == digest else "MISMATCH")
     # api.hip sets the union's edge order, which the traffic depends on.
-    traffic = measured_traffic("peel_multi_pool4096_traffic.md",
-                               ("peel_multi.hip", "peel_common.h", "api.hip"))
+    traffic = measured_traffic("peel_pool4096_traffic.md", PEEL_SOURCES)
     out = {
         "metric": "edges decomposed/s (bit-exact phi_e), batched vs plain; p50/p99 latency",
         "value": m_pool / (ms / 1000.0),
@@ -441,7 +441,7 @@ def main():
         "counters": {k: st[k] for k in ("butterflies", "wedges_po", "blooms", "bloom_wedges",
                                         "levels", "rounds", "support_updates", "bloom_visits",
                                         "wedge_visits", "peel_launches", "index_bytes")},
-        "roofline": roofline("k_peel_multi", st, traffic),
+        "roofline": roofline("k_sweep + k_peel_leaf", st, traffic),
     }
     skipped = {}
 
@@ -475,8 +475,7 @@ def main():
         if key in args.single and key in inputs:
             if left(args.budget) > costs[key][1] + 10:
                 log(f"single {key}")
-                tr = measured_traffic("peel_chunglu5m_traffic.md",
-                                      ("peel.hip", "peel_common.h", "api.hip")) \
+                tr = measured_traffic("peel_chunglu5m_traffic.md", PEEL_SOURCES) \
                     if key == "c1" else None
                 singles[key] = single(key, inputs[key], 5 if key == "c1" else 20, 1, golden,
                                       traffic=tr)

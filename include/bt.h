@@ -79,7 +79,8 @@ typedef struct bt_stats {
     int64_t bloom_wedges;     /* sum of bloom numbers = wedges stored in the index */
     int64_t index_bytes;      /* device bytes of the BE-Index */
     int64_t levels;           /* distinct bitruss levels visited by the peel */
-    int64_t rounds;           /* peel rounds (frontiers processed) */
+    int64_t rounds;           /* peel rounds (frontiers processed; graphs and parts of
+                                 a graph that peel beside each other share theirs) */
     int64_t max_phi;          /* largest bitruss number */
     int64_t support_updates;  /* support decrements issued by the peel */
     int64_t bloom_visits;     /* touched-bloom visits in batch bloom processing */
@@ -88,12 +89,11 @@ typedef struct bt_stats {
     float ms_link;            /* edge-to-wedge links */
     float ms_peel;            /* peel */
     float ms_peel_kernel;     /* device time of the peel kernels alone (HIP events) */
-    int32_t peel_launches;    /* peel kernel (or round-graph) launches */
+    int32_t peel_launches;    /* peels, and their launches after a yield */
     int32_t passes;           /* subgraph passes (1, or BiT-PC's thresholds) */
-    int64_t support_updates_unbatched; /* the plain peel's decrements had each
+    int64_t support_updates_unbatched; /* the same rounds' decrements had each
                                  survivor taken one unit per removed wedge (no
-                                 batch bloom processing, Section V-B); 0 where
-                                 not counted */
+                                 batch bloom processing, Section V-B) */
     int64_t wedge_visits;     /* live wedges of touched blooms visited by batch
                                  bloom processing, summed over rounds: each such
                                  visit lowers the wedge's two edges once */
@@ -242,7 +242,8 @@ typedef struct bt_tune_params {
     int32_t peel_blocks;     /* workgroups of the cooperative peel (0: three per four
                                 compute units; capped at what can be resident);
                                 [0, 65536], 0 */
-    int32_t active_min;      /* smallest active set the peel rebuilds; >= 1, 16384 */
+    int32_t active_min;      /* without effect (the peel rebuilds no active set; kept
+                                for saved files); >= 1, 16384 */
 } bt_tune_params;
 
 enum { BT_TUNE_INDEX = 1, BT_TUNE_PEEL = 2 };
@@ -317,11 +318,9 @@ bt_status bt_bitruss_components(const bt_csr *g, const int64_t *phi, int64_t k,
  * array of n_graphs descriptors (device CSRs); sup_out / phi_out are HOST
  * arrays of n_graphs device pointers (sup_out may be NULL, or hold NULLs;
  * phi_out[i] may be NULL only for a graph without edges).  The graphs are
- * decomposed as disjoint unions of at most 2^26 edges (larger ones alone),
+ * decomposed as disjoint unions of at most 2^24 edges (larger ones alone),
  * cut from the graphs in decreasing edge count; within a union every graph
- * peels at its own level when all of them have at most 2^19 edges, else
- * the union peels with one shared level.  Inside a union each graph's
- * vertices are renumbered by decreasing degree (the support atomics then
+ * peels at its own levels.  Inside a union each graph's vertices are renumbered by decreasing degree (the support atomics then
  * land close together); results are written back in each caller's edge
  * order and equal bt_decompose on each graph.
  * stats (nullable) receives the sums over all graphs; rounds and
@@ -343,7 +342,7 @@ bt_status bt_decompose_batch(const bt_csr *gs, int32_t n_graphs, int64_t *const 
  *   peels of different slots take turns; a second slot counts and builds
  *   the index of the next batch while one slot's batch peels, and when that
  *   batch is of a smaller size class, the running peel ends its launch
- *   between two rounds (within 32 rounds), lets the smaller batch peel,
+ *   between two rounds (within 16 rounds), lets the smaller batch peel,
  *   and resumes where it stopped.  With two or more slots one is kept for
  *   the small class: a slot starts a larger class's batch only while fewer
  *   than slots - 1 others run one.

@@ -172,6 +172,25 @@ void fill_stats(bt_stats *stats, const RankCSR &r, const IndexArrays &ix, const 
 const uint32_t *reorder_union(bt_csr &u, const int64_t *dvoff, int32_t ng, Workspace &ws,
                               hipStream_t s);
 
+bool peel_mode(const char *v) {
+    const char *mv = std::getenv("BT_PEEL_MODE");
+    return mv && std::strcmp(mv, v) == 0;
+}
+
+// Runs a decomposition with the peel that splits; where that does not fit the
+// device's memory, again with the one that needs the least (level by level).
+// BT_PEEL_MODE=plain takes that one at once.
+template <class F> void with_plain_fallback(Workspace &ws, F &&run) {
+    if (peel_mode("plain")) return run(true);
+    try {
+        run(false);
+    } catch (const Error &e) {
+        if (e.status != BT_ENOMEM) throw;
+        ws.release();
+        run(true);
+    }
+}
+
 // Graphs from this many edges up are decomposed in the locality order (see
 // reorder_union); BT_REORDER=0 keeps the caller's numbering.
 constexpr int64_t kReorderMinEdges = int64_t(1) << 20;
@@ -182,10 +201,10 @@ bool reorder_single(int64_t m) {
 }
 
 // Whether a graph of m edges peels in one workgroup (peel_leaf).
-// BT_PEEL_MODE=graph keeps the grid-wide rounds, as replayed kernels.
+// BT_PEEL_MODE=graph (sweeps as replayed kernels) and =plain (level by level)
+// take the sweeps for every graph.
 bool leaf_peel(int64_t m, const Workspace &ws) {
-    const char *mv = std::getenv("BT_PEEL_MODE");
-    return m < kLeafEdges && ws.coop && !(mv && std::strcmp(mv, "graph") == 0);
+    return m < kLeafEdges && ws.coop && !peel_mode("graph") && !peel_mode("plain");
 }
 
 // out[perm[p]] = t[p]: results back to the caller's edge order.
@@ -201,8 +220,9 @@ __global__ void k_unpermute(const uint32_t *perm, int64_t m, const int64_t *sup_
 
 }  // namespace
 
-void decompose_impl(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0, bt_stats *stats,
-                    Workspace &ws, hipStream_t stream, bool unit_updates, bool auto_pc) {
+static void decompose_once(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0,
+                           bt_stats *stats, Workspace &ws, hipStream_t stream, bool unit_updates,
+                           bool auto_pc, bool plain) {
     Events ev(stats != nullptr, stream);
     ev.mark(0);
     // Large graphs peel in the locality order (each layer renumbered by
@@ -242,13 +262,14 @@ void decompose_impl(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0, bt_s
     PeelCounters pc;
     PeelOptions o;
     o.unit_updates = unit_updates;
+    o.plain = plain;
     if (leaf) {
         int64_t *doff = ws.get<int64_t>("lf_off", 2);
         const std::vector<int64_t> off{0, g.m};
         BT_HIP(hipMemcpyAsync(doff, off.data(), 2 * sizeof(int64_t), hipMemcpyHostToDevice, stream));
         peel_leaf(ix, off, doff, sup_out, phi_out, unit_updates, pc, ws, stream);
     } else {
-        peel(r, ix, sup_out, phi_out, pc, ws, stream, &o);
+        peel_split(r, ix, {0, g.m}, sup_out, phi_out, pc, ws, stream, &o);
     }
     if (perm) {
         k_unpermute<<<grid_for(g0.m, 256, 16384), 256, 0, stream>>>(
@@ -260,6 +281,13 @@ void decompose_impl(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out0, bt_s
     BT_HIP(hipMemcpyAsync(hs, ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
     BT_HIP(hipStreamSynchronize(stream));
     if (stats) fill_stats(stats, r, ix, pc, g.m, hs[0], ev);
+}
+
+void decompose_impl(const bt_csr &g, int64_t *sup_out, int64_t *phi_out, bt_stats *stats,
+                    Workspace &ws, hipStream_t stream, bool unit_updates, bool auto_pc) {
+    with_plain_fallback(ws, [&](bool plain) {
+        decompose_once(g, sup_out, phi_out, stats, ws, stream, unit_updates, auto_pc, plain);
+    });
 }
 
 float index_build_ms(const bt_csr &g, Workspace &ws, hipStream_t stream) {
@@ -281,8 +309,8 @@ float index_build_ms(const bt_csr &g, Workspace &ws, hipStream_t stream) {
 // left for later passes) and the levels from eps up fix the numbers of the
 // eps-bitruss.  Algorithm 7's single recount-and-drop of edges below eps is
 // subsumed by that first level, which repeats it to the fixpoint.
-void decompose_pc_impl(const bt_csr &g, double tau, int64_t *sup_out, int64_t *phi_out,
-                       bt_stats *stats, Workspace &ws, hipStream_t s) {
+static void decompose_pc_once(const bt_csr &g, double tau, int64_t *sup_out, int64_t *phi_out,
+                              bt_stats *stats, Workspace &ws, hipStream_t s, bool plain) {
     if (stats) std::memset(stats, 0, sizeof *stats);
     const int64_t m = g.m;
     Events ev(stats != nullptr, s);
@@ -326,8 +354,9 @@ void decompose_pc_impl(const bt_csr &g, double tau, int64_t *sup_out, int64_t *p
             PeelOptions o;
             o.fixed = sg.fixed;
             o.min_level = eps > 0 ? eps - 1 : 0;
+            o.plain = plain;
             PeelCounters pc;
-            peel(rs, ix, nullptr, phi_sub, pc, ws, s, &o);
+            peel_split(rs, ix, {0, sg.g.m}, nullptr, phi_sub, pc, ws, s, &o);
             pc_collect(phi_sub, sg, eps, phi_glob, s);
             tot.levels += pc.levels;
             tot.rounds += pc.rounds;
@@ -373,15 +402,21 @@ void decompose_pc_impl(const bt_csr &g, double tau, int64_t *sup_out, int64_t *p
     }
 }
 
-constexpr int64_t kMultiMaxEdges = int64_t(1) << 19;
+void decompose_pc_impl(const bt_csr &g, double tau, int64_t *sup_out, int64_t *phi_out,
+                       bt_stats *stats, Workspace &ws, hipStream_t s) {
+    with_plain_fallback(ws, [&](bool plain) {
+        decompose_pc_once(g, tau, sup_out, phi_out, stats, ws, s, plain);
+    });
+}
+
 constexpr int64_t kTraceMaxEdges = int64_t(1) << 16;
 
 // A disjoint union of graphs (edge ranges [off[g], off[g+1])): one index
 // build for the union, then one peel in which every graph has its own level.
 void decompose_union_impl(const bt_csr &u, const std::vector<int64_t> &off,
                           const Components &comps, int64_t *sup_out, int64_t *phi_out,
-                          bt_stats *stats, Workspace &ws, hipStream_t s,
-                          const SizedHook *on_sized = nullptr) {
+                          bt_stats *stats, Workspace &ws, hipStream_t s, bool plain,
+                          const SizedHook *on_sized) {
     Events ev(stats != nullptr, s);
     ev.mark(0);
     RankCSR r;
@@ -395,23 +430,26 @@ void decompose_union_impl(const bt_csr &u, const std::vector<int64_t> &off,
     build_all(u, r, ix, false, nullptr, ws, s, &ev, off.size() > 2, &comps);
     ev.mark(3);
     PeelCounters pc;
-    // Per-graph levels pay when there are several graphs, all small: its
-    // gathers rescan a graph's whole edge range, where the shared-level peel
-    // keeps a threshold active set.  BT_BATCH_PEEL=union forces the latter.
-    const bool multi = ws.coop && off.size() > 2 && max_m <= kMultiMaxEdges && !as_union;
-    if (on_sized && *on_sized)
-        (*on_sized)((int64_t)ws.bytes(),
-                    leaf ? peel_leaf_bytes(u.m, ix.cap_b, ix.cap_w, ix.n_graphs)
-                         : peel_state_bytes(u.m, ix.n_b, ix.n_w, (int64_t)off.size() - 1, multi));
+    // BT_BATCH_PEEL=union peels the union as one graph.
+    if (on_sized && *on_sized) {
+        const int64_t ng = (int64_t)off.size() - 1;
+        const int64_t least = leaf ? peel_leaf_bytes(u.m, ix.cap_b, ix.cap_w, ng)
+                                   : peel_split_bytes(u.m, ix.n_b, ix.n_w, ng, true);
+        const int64_t most = leaf ? least : peel_split_bytes(u.m, ix.n_b, ix.n_w, ng, false);
+        if (!(*on_sized)((int64_t)ws.bytes(), least, most)) plain = true;
+    }
+    PeelOptions o;
+    o.plain = plain;
     if (leaf) {
         int64_t *doff = ws.get<int64_t>("lf_off", (int64_t)off.size());
         BT_HIP(hipMemcpyAsync(doff, off.data(), sizeof(int64_t) * off.size(),
                               hipMemcpyHostToDevice, s));
         peel_leaf(ix, off, doff, sup_out, phi_out, false, pc, ws, s);
-    } else if (multi)
-        peel_multi(r, ix, sup_out, phi_out, off, pc, ws, s);
-    else
-        peel(r, ix, sup_out, phi_out, pc, ws, s);
+    } else if (as_union) {
+        peel_split(r, ix, {0, u.m}, sup_out, phi_out, pc, ws, s, &o);
+    } else {
+        peel_split(r, ix, off, sup_out, phi_out, pc, ws, s, &o);
+    }
     ev.mark(4);
     int64_t *hs = ws.host(2);
     BT_HIP(hipMemcpyAsync(hs, ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -638,7 +676,7 @@ void add_stats(bt_stats &t, const bt_stats &s) {
 // Graphs [a, b) as one union; splits the range if the union is too large.
 void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out,
                  int64_t *const *phi_out, bt_stats *stats, Workspace &ws, hipStream_t s,
-                 const SizedHook *on_sized = nullptr) {
+                 bool plain, const SizedHook *on_sized) {
     std::vector<BatchEntry> tab(b - a);
     int64_t nu = 0, nl = 0, m = 0, max_span = 1, max_m = 0;
     for (int32_t i = a; i < b; ++i) {
@@ -662,8 +700,8 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     const bool splittable = b - a > 1;
     if (splittable && (nu + nl >= INT32_MAX || m >= INT32_MAX)) {
         const int32_t mid = a + (b - a) / 2;
-        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s);
-        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s);
+        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain, nullptr);
+        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain, nullptr);
         return;
     }
     BatchEntry *dtab = ws.get<BatchEntry>("batch_tab", b - a);
@@ -711,13 +749,13 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
                                : reorder_union(u, dvoff, b - a, ws, s);
     bt_stats st;
     try {
-        decompose_union_impl(u, off, comps, sup_u, phi_u, stats ? &st : nullptr, ws, s,
+        decompose_union_impl(u, off, comps, sup_u, phi_u, stats ? &st : nullptr, ws, s, plain,
                              on_sized);
     } catch (const Error &e) {
         if (e.status != BT_EOVERFLOW || !splittable) throw;
         const int32_t mid = a + (b - a) / 2;
-        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s);
-        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s);
+        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain, nullptr);
+        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain, nullptr);
         return;
     }
     k_batch_scatter<<<grid, 256, 0, s>>>(dtab, b - a, sup_u, phi_u, perm, flags);
@@ -728,10 +766,11 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     if (stats) add_stats(*stats, st);
 }
 
-// Batches are cut at about kBatchEdges edges so that each union stays well
-// inside the index limits; an oversized union is split in halves.
+// Batches are cut at about kBatchEdges edges, which bounds the memory of a
+// union (about 100 bytes a bloom wedge, 25 to 40 wedges an edge on the pool);
+// an oversized union is split in halves.
 // BT_BATCH_EDGES_LOG2 (16..30) sets another cut, for measurements.
-constexpr int64_t kBatchEdges = int64_t(1) << 26;
+constexpr int64_t kBatchEdges = int64_t(1) << 24;
 int64_t batch_edges() {
     const char *v = std::getenv("BT_BATCH_EDGES_LOG2");
     const int l = v ? std::atoi(v) : 0;
@@ -740,9 +779,9 @@ int64_t batch_edges() {
 
 }  // namespace
 
-void decompose_batch_impl(const bt_csr *gs, int32_t n, int64_t *const *sup_out,
-                          int64_t *const *phi_out, bt_stats *stats, Workspace &ws,
-                          hipStream_t s, const SizedHook *on_sized) {
+static void decompose_batch_once(const bt_csr *gs, int32_t n, int64_t *const *sup_out,
+                                 int64_t *const *phi_out, bt_stats *stats, Workspace &ws,
+                                 hipStream_t s, bool plain, const SizedHook *on_sized) {
     if (stats) std::memset(stats, 0, sizeof *stats);
     // Unions are cut from the graphs in decreasing edge count: a union peels
     // for as many rounds as its slowest graph needs, so the large graphs,
@@ -766,11 +805,22 @@ void decompose_batch_impl(const bt_csr *gs, int32_t n, int64_t *const *sup_out,
         int32_t b = a;
         int64_t m = 0;
         while (b < n && (b == a || m + g2[(size_t)b].m <= cut)) m += g2[(size_t)b++].m;
-        // The size report is exact only when one union holds the whole batch.
+        // The sizes are known only when one union holds the whole batch; a
+        // caller that accounts for them otherwise gets the peel that needs
+        // the least.
+        const bool whole = a == 0 && b == n;
         batch_range(g2.data(), a, b, sup_out ? s2.data() : nullptr, p2.data(), stats, ws, s,
-                    a == 0 && b == n ? on_sized : nullptr);
+                    plain || (on_sized && !whole), whole ? on_sized : nullptr);
         a = b;
     }
+}
+
+void decompose_batch_impl(const bt_csr *gs, int32_t n, int64_t *const *sup_out,
+                          int64_t *const *phi_out, bt_stats *stats, Workspace &ws,
+                          hipStream_t s, const SizedHook *on_sized) {
+    with_plain_fallback(ws, [&](bool plain) {
+        decompose_batch_once(gs, n, sup_out, phi_out, stats, ws, s, plain, on_sized);
+    });
 }
 
 }  // namespace bt
@@ -957,10 +1007,7 @@ bt_status bt_decompose_trace(const bt_csr *g, int64_t *phi_out, int32_t max_roun
                 throw Error{BT_EOVERFLOW, "more rounds than max_rounds"};
             rounds.push_back(t);
         };
-        PeelOptions o;
-        o.trace = &fn;
-        PeelCounters pc;
-        if (m > 0) peel(r, ix, nullptr, phi_out, pc, ws, stream, &o);
+        peel_trace(ix, m, phi_out, fn, ws, stream);
         std::vector<int32_t> wbl((size_t)ix.n_w);
         if (ix.n_w) {
             BT_HIP(hipMemcpy(wedge_ea, ix.wea, sizeof(int32_t) * ix.n_w, hipMemcpyDeviceToHost));

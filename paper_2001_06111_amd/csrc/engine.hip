@@ -54,17 +54,15 @@ struct Done {
     bt_status st;
 };
 
-// Size classes: a batch holds requests of one class.  A batch runs as many
-// peel rounds as its slowest graph needs, so small graphs are not held up
-// by medium ones in their own batch.
+// Size classes: a batch holds requests of one class.  A batch returns when
+// its slowest graph is done, so small graphs are not held up by medium ones
+// in their own batch.
 constexpr int64_t kLargeEdges = int64_t(1) << 19;
 constexpr int64_t kMediumEdges = int64_t(1) << 14;
 constexpr int kClasses = 3;
 inline int size_class_of(int64_t m) { return m >= kLargeEdges ? 2 : m >= kMediumEdges ? 1 : 0; }
-// Large requests share a batch too (one union, one shared level, so their
-// rounds overlap: 2M-edge graphs take 2.18 s alone, 5.00 s four together,
-// 8.27 s eight together), but at most this many, to bound each one's
-// latency.
+// Large requests share a batch too (their rounds overlap), but at most this
+// many, to bound each one's latency.
 constexpr int32_t kLargePerBatch = 8;
 // Batches of the smallest class present go first (they take a fraction of
 // a larger class's time), unless the oldest request of a larger class has
@@ -300,15 +298,20 @@ void bt_engine::run_batch(int slot, const Batch &b, Workspace &ws, hipStream_t s
     }
     // Once the index is built the peel's remaining need replaces what is
     // left of the estimate, so other slots may admit against the
-    // difference.  The slot's commitment never grows past its admission
-    // (held0 + estimate); its real holdings are re-read at the end.
-    const SizedHook on_sized = [&](int64_t held, int64_t peel_bytes) {
+    // difference.  The peel that splits is taken where the budget has room
+    // for it beside the other slots; the one that needs the least always fits
+    // the slot's admission (held0 + estimate).  The real holdings are re-read
+    // at the end.
+    const SizedHook on_sized = [&](int64_t held, int64_t least, int64_t split) {
         std::lock_guard<std::mutex> lk(mu);
         Slot &me = slots[(size_t)slot];
+        const bool room = committed_except(slot) + held + split <= budget;
         me.held = held;
-        me.res = std::max<int64_t>(0, std::min(peel_bytes, b.held0 + b.bytes - held));
+        me.res = room ? split
+                      : std::max<int64_t>(0, std::min(least, b.held0 + b.bytes - held));
         note_peaks();
         cv_work.notify_all();
+        return room;
     };
     std::vector<Done> out;
     bt_stats bst{};
@@ -360,7 +363,7 @@ void bt_engine::worker_loop(int slot) {
     (void)hipSetDevice(device);
     hipStream_t s = nullptr;
     (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-    Workspace ws;  // cooperative peels of different slots take turns (see peel.hip)
+    Workspace ws;  // cooperative peels of different slots take turns (see turn.hip)
     ws.bind_stream(s);
     while (true) {
         Batch b;

@@ -1,7 +1,6 @@
-// peel_common.h - peel state, work items and device helpers shared by the
-// single-graph peel (peel.hip) and the batch peel (peel_multi.hip): coherent
-// loads and stores of shared state, wave-level slot allocation, chunked work
-// items, the two-level grid barrier and the state initialisation kernels.
+// peel_common.h - device helpers of the peels: coherent loads and stores of
+// shared state, wave-level slot allocation, the two-level grid barrier; the
+// turns that peels take on the device.
 #pragma once
 
 #include <algorithm>
@@ -47,8 +46,6 @@ class CoopTurn {
 
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kLinkChunk = kWave;   // links per phase-A work item (one per lane)
 // Progressive mode: edge ids in wedge records and link twins carry this bit
 // when the edge's bitruss number was fixed in an earlier pass; such edges
@@ -56,87 +53,17 @@ constexpr int kLinkChunk = kWave;   // links per phase-A work item (one per lane
 constexpr uint32_t kFixedBit = 0x80000000u;
 constexpr uint32_t kEdgeMask = 0x7fffffffu;
 constexpr int kWedgeChunk = kWave;  // wedges per phase-B work item (one per lane)
-inline int grid_a() {
-    static int g = std::getenv("BT_PEEL_GRID_A") ? std::atoi(std::getenv("BT_PEEL_GRID_A")) : 2048;
-    return g;
-}
-inline int grid_b() {
-    static int g = std::getenv("BT_PEEL_GRID_B") ? std::atoi(std::getenv("BT_PEEL_GRID_B")) : 2048;
-    return g;
-}
-
 typedef unsigned long long u64;
-
-enum : int32_t { kNormal = 0, kGather = 1 };
 
 // A counter alone on its cache line (contended atomics do not share lines).
 struct alignas(128) Counter {
     u64 v;
 };
 
-struct PeelCtl {
-    Counter nf[2];      // frontier work items by round parity
-    Counter ntc[2];     // bloom work items by round parity
-    Counter na[2];      // active-set entries by buffer
-    Counter updates;
-    Counter bloom_visits;
-    Counter unbatched;  // extra decrements if survivors took one per kill (no bloom batching)
-    Counter touched;    // live wedges visited in phase B (survivors of touched blooms)
-    // Round state, indexed by round parity.  Round r's entry is derived
-    // from round r - 1's final counters (every block computes the same
-    // values; block 0 stores them for round r + 1).
-    int32_t mode[2];    // kNormal or kGather
-    int32_t level[2];
-    int32_t cur[2];     // active-set buffer in use
-    int32_t gmin[2];    // gather rounds: minimum support above the level
-    int32_t stall;
-    int32_t thresh;     // active threshold T
-    int32_t max_level;  // largest level at which edges were removed
-    int32_t pad;
-    u64 rounds, levels;
-    u64 prof[6];        // persistent kernel, BT_PEEL_PROFILE=1: block-0 clock ticks
-    // BT_PEEL_PROFILE=1: frontier pushes by twin (phase A) and survivor
-    // (phase B) decrements, by list parity; rounds whose frontier came from
-    // twin decrements alone; log2 histograms of per-round work items.
-    Counter push_twin[2], push_surv[2];
-    u64 twin_only_rounds, twin_pushes, surv_pushes;
-    u64 hist_nf[32], hist_ntc[32];
-    // Block-0 clock ticks of whole rounds by log2 of their frontier items,
-    // and of phase B by log2 of its bloom items.
-    u64 time_nf[32], time_ntc[32];
-};
-
 struct alignas(16) FrontItem {
-    int32_t e;
-    int32_t level;    // level of the round that removes e
+    int32_t e;        // < 0: none
+    int32_t part;
     uint32_t lo, hi;  // link positions of this chunk
-};
-
-struct alignas(16) BloomItem {
-    int32_t b;
-    int32_t nch;    // chunks of this bloom (the last one to finish finalizes)
-    uint32_t lo, hi;  // wedge range of this chunk
-};
-
-struct PeelArgs {
-    PeelCtl *ctl;
-    int32_t *sup;
-    int32_t *phi;
-    uint32_t *alive;
-    int32_t *bc;
-    int32_t *bk;
-    int32_t *bdone;
-    const uint32_t *bwoff;
-    const int32_t *wea;
-    const int32_t *web;
-    const int32_t *wbl;
-    const int64_t *link_off;
-    const uint3 *link;  // {wedge, bloom, twin edge}
-    int32_t prof;       // count profile statistics
-    int32_t unit;       // ablation without batch bloom processing (BiT-BU+)
-    FrontItem *front[2];
-    BloomItem *tc[2];
-    int32_t *act[2];
 };
 
 // Coherent access to state that blocks share within one launch.  The eight
@@ -202,59 +129,18 @@ __device__ __forceinline__ void wave_alloc3(uint32_t c0, u64 *k0, uint32_t c1, u
     for (int k = 0; k < 3; ++k) base[k] = __shfl(r[k], kWave - 1, kWave) + (inc[k] - cnt[k]);
 }
 
-// Frontier work items of an edge: its links in chunks of 64, at least one
-// chunk so that an edge without links still receives its bitruss number.
-__device__ __forceinline__ uint32_t link_chunks(uint32_t lo, uint32_t hi) {
-    return hi - lo <= (uint32_t)kLinkChunk ? 1u : (hi - lo + kLinkChunk - 1) / kLinkChunk;
-}
-
-// The pusher also records the edge's bitruss number: an edge is queued at
-// the level of the round that removes it (a queued frontier keeps the
-// level), and only a gather, which runs once the frontier is empty, reads
-// phi while the peel runs.
-// Writes the cnt 64-element chunks of a lane's range [lo, hi) as items
-// {id, aux, a, min(a + 64, hi)} at slots base, base + 1, ...  A lane writes
-// up to kOwnChunks of its own; the rest of a longer range is written by the
-// whole wave, 64 chunks at a time, so a hub edge or a large bloom does not
-// hold up its wave (and the round) with thousands of serial stores.  All 64
-// lanes must call.
-constexpr uint32_t kOwnChunks = 4;
-template <typename Item>
-__device__ __forceinline__ void put_chunks(Item *list, u64 base, uint32_t cnt, int32_t id,
-                                           int32_t aux, uint32_t lo, uint32_t hi) {
-    const uint32_t own = min(cnt, kOwnChunks);
-    for (uint32_t c = 0; c < own; ++c) {
-        const uint32_t a = lo + c * kWave;
-        st_item(&list[base + c], Item{id, aux, a, min(a + (uint32_t)kWave, hi)});
-    }
-    unsigned long long big = __ballot(cnt > own);
-    while (big) {
-        const int l = __ffsll(big) - 1;
-        big &= big - 1;
-        const uint32_t n = __shfl(cnt, l, kWave);
-        const u64 b = __shfl(base, l, kWave);
-        const int32_t lid = __shfl(id, l, kWave), laux = __shfl(aux, l, kWave);
-        const uint32_t llo = __shfl(lo, l, kWave), lhi = __shfl(hi, l, kWave);
-        for (uint32_t c = kOwnChunks + lane_id(); c < n; c += kWave) {
-            const uint32_t a = llo + c * kWave;
-            st_item(&list[b + c], Item{lid, laux, a, min(a + (uint32_t)kWave, lhi)});
-        }
-    }
-}
-
-__device__ __forceinline__ void put_front(const PeelArgs &P, int q, u64 base, int32_t e,
-                                          uint32_t lo, uint32_t hi, uint32_t k, int32_t level) {
-    if (k) st(&P.phi[e], level);
-    put_chunks(P.front[q], base, k, e, level, lo, hi);  // the item carries the level
-}
-
-enum : int { kSrcTwin = 0, kSrcSurvivor = 1 };
-
-// Profile statistics: frontier pushes by the decrement that caused them.
-__device__ __forceinline__ void count_push(const PeelArgs &P, int q, int src, uint32_t n) {
-    const u64 t = wave_sum<u64>((u64)n);
-    if (lane_id() == 0 && t)
-        atomicAdd(src == kSrcTwin ? &P.ctl->push_twin[q].v : &P.ctl->push_surv[q].v, t);
+// The item of element t0 + lane when the lanes' items start at `start`
+// (increasing over the lanes with ok): the items that start before the
+// window, plus those that start in it at or before this element, less one.
+__device__ __forceinline__ int item_of(bool ok, uint32_t start, uint32_t t0, u64 *mask) {
+    const int before = (int)__popcll(__ballot(ok && start < t0));
+    if (lane_id() == 0) __hip_atomic_store(mask, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (ok && start >= t0 && start < t0 + kWave)
+        __hip_atomic_fetch_or(mask, 1ull << (start - t0), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP);
+    const u64 m = __hip_atomic_load(mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const u64 le = lanemask_lt() | (u64(1) << lane_id());
+    return before + (int)__popcll(m & le) - 1;
 }
 
 // --- cooperative kernels: workgroup size and the grid barrier ------------
@@ -309,37 +195,6 @@ __device__ bool grid_arrive_wait(GridBar *B, u64 &k) {
     }
     drain_memory();
     return ok;
-}
-
-// Edges whose bitruss number is already fixed (progressive mode) start
-// removed-looking (phi >= 0) with an unreachable support, so no gather,
-// refill or crossing ever takes them.
-__global__ void k_init_peel(const uint64_t *supl, int64_t m, const int32_t *fixed, int32_t *sup,
-                            int32_t *phi, int64_t *sup_out) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t s = (int32_t)(supl[e] & 0xffffffffu);
-        const bool fx = fixed && fixed[e];
-        sup[e] = fx ? INT_MAX : s;
-        phi[e] = fx ? INT_MAX : -1;
-        if (sup_out) sup_out[e] = s;
-    }
-}
-
-__global__ void k_init_alive(const uint64_t *cursor, uint32_t *alive) {
-    const int64_t nw = (int64_t)(*cursor & 0xffffffffu);
-    const int64_t words = (nw + 31) / 32;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t rem = nw - i * 32;
-        alive[i] = rem >= 32 ? 0xffffffffu : ((1u << rem) - 1u);
-    }
-}
-
-__global__ void k_phi_out(const int32_t *phi, int64_t *out, int64_t m) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
-         e += (int64_t)gridDim.x * blockDim.x)
-        out[e] = phi[e];
 }
 
 }  // namespace

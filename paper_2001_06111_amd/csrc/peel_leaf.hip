@@ -31,7 +31,7 @@
 #include <algorithm>
 #include <cstdlib>
 
-#include "peel_common.h"
+#include "peel_split.h"
 
 namespace bt {
 
@@ -39,24 +39,23 @@ namespace {
 
 constexpr int kLeafBlock = 1024;
 constexpr uint32_t kNoTwin = 0xffffffffu;  // the twin is not peeled here
-// An edge's state, in the top bits of the word that holds the end of its
-// links: remaining, queued for an even or an odd round (1, 2), removed.
-enum : uint32_t { kRemaining = 0, kRemoved = 3 };
-constexpr int kStateShift = 30;
-constexpr uint32_t kEndMask = (1u << kStateShift) - 1;
+// An edge's state: remaining, queued for an even or an odd round (1, 2), removed.
+enum : uint8_t { kRemaining = 0, kRemoved = 3 };
 
 struct LeafArgs {
     const LeafJob *jobs;
-    int32_t njobs;
+    const int32_t *order;  // jobs in queue order (null: as they are)
     int32_t *queue;
     const int32_t *wea, *web, *wbl;
     const uint32_t *bwoff;
     const int32_t *bk;  // initial bloom numbers
     u64 *bs;            // (live wedges at the round's start << 32) | kills this round
     uint2 *link;        // {bloom, twin}: job's links at [2 w0, 2 (w0 + nw))
+    uint32_t *ends;     // end of each edge's links in its job's
     // Work lists past their part in LDS.
     uint2 *front[2];    // {edge | (links - 1) << 16, first link}
     uint2 *items;       // {bloom | multi << 31, first wedge << 6 | (wedges - 1)}
+    const int32_t *oid;  // where an edge's number goes in phi_out (null: at the edge)
     int64_t *phi_out;
     int32_t *glevels;  // levels per graph
     LeafCtl *ctl;
@@ -114,42 +113,28 @@ __device__ __forceinline__ u64 settle(u64 state) {
     return (u64)((uint32_t)(state >> 32) - (uint32_t)state) << 32;
 }
 
-// The item of element t0 + lane when the lanes' items start at `start`
-// (increasing over the lanes with ok): the items that start before the
-// window, plus those that start in it at or before this element, less one.
-__device__ __forceinline__ int item_of(bool ok, uint32_t start, uint32_t t0, u64 *mask) {
-    const int before = (int)__popcll(__ballot(ok && start < t0));
-    if (lane_id() == 0) __hip_atomic_store(mask, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (ok && start >= t0 && start < t0 + kWave)
-        __hip_atomic_fetch_or(mask, 1ull << (start - t0), __ATOMIC_RELAXED,
-                              __HIP_MEMORY_SCOPE_WORKGROUP);
-    const u64 m = __hip_atomic_load(mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const u64 le = lanemask_lt() | (u64(1) << lane_id());
-    return before + (int)__popcll(m & le) - 1;
-}
-
-// Work lists keep their first entries in LDS (most rounds of a small graph
-// fit) and the rest in global memory at the same index.
-constexpr uint32_t kFrontLds = 512, kItemsLds = 1024;
-
-// LDS of a workgroup for jobs of up to ecap edges (a multiple of 4): the two
-// frontier lists and the bloom items; support and end of links of each edge.
-inline size_t leaf_lds(int ecap) {
-    return sizeof(uint2) * (2 * kFrontLds + kItemsLds) + (size_t)ecap * 8;
-}
-
-// Steps of four edges a thread in which a workgroup scans its edges: a launch
-// has at least ecap / 16 threads.
-constexpr int kScanSteps = 4;
+// A launch: jobs of up to ecap edges (a multiple of 4).  The work lists keep
+// their first entries in LDS and the rest in global memory at the same index.
+// Smaller jobs take less LDS and fewer waves, so that several share a compute
+// unit.
+struct LeafClass {
+    int ecap, threads, front_lds, items_lds;
+    // Frontier lists, bloom items; support and state of each edge.
+    size_t lds() const { return sizeof(uint2) * (2 * front_lds + items_lds) + (size_t)ecap * 5; }
+};
+constexpr LeafClass kLeafClasses[] = {
+    {(int)kLeafCap, 1024, 512, 1024}, {7168, 512, 256, 512}, {2048, 256, 128, 256}};
+constexpr int kNumLeafClasses = 3;
 
 template <bool UNIT>
 __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0, int32_t j1,
-                                                          int ecap) {
+                                                          LeafClass K) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint2 *const lf0 = reinterpret_cast<uint2 *>(smem_raw), *const lf1 = lf0 + kFrontLds;
-    uint2 *const li = lf1 + kFrontLds;
-    int32_t *const sup = reinterpret_cast<int32_t *>(li + kItemsLds);
-    uint32_t *const ends = reinterpret_cast<uint32_t *>(sup + ecap);
+    const uint32_t front_lds = K.front_lds, items_lds = K.items_lds;
+    uint2 *const lf0 = reinterpret_cast<uint2 *>(smem_raw), *const lf1 = lf0 + front_lds;
+    uint2 *const li = lf1 + front_lds;
+    int32_t *const sup = reinterpret_cast<int32_t *>(li + items_lds);
+    uint8_t *const stt = reinterpret_cast<uint8_t *>(sup + K.ecap);
     __shared__ int32_t s_job, s_min;
     __shared__ uint32_t s_nf[2], s_ni[2], s_multi[2];
     __shared__ u64 s_mask[kLeafBlock / kWave];
@@ -157,8 +142,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int wv = tid / kWave, nwv = nthr / kWave;
     u64 *const mask = &s_mask[wv];
-    u64 upd = 0, unb = 0;
-    uint32_t touch = 0, visits = 0;
+    uint32_t upd = 0, unb = 0, touch = 0, visits = 0;  // of this lane
     u64 rounds = 0;  // thread 0's
     int32_t max_level = 0;
 
@@ -166,69 +150,76 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
         __syncthreads();
         if (tid == 0) s_job = j0 + atomicAdd(A.queue, 1);
         __syncthreads();
-        const int32_t jb = s_job;
-        if (jb >= j1) break;
+        if (s_job >= j1) break;
+        const int32_t jb = A.order ? A.order[s_job] : s_job;
         const LeafJob J = A.jobs[jb];
         const int32_t ne = J.ne, e0 = J.e0;
-        if (ne <= 0 || ne > ecap) continue;  // the host queues none of these
+        if (ne <= 0 || ne > K.ecap) continue;  // the host queues none of these
         uint2 *const link = A.link + 2 * (int64_t)J.w0;
         uint2 *const fr0 = A.front[0] + front_base(J, jb), *const fr1 = A.front[1] + front_base(J, jb);
         uint2 *const items = A.items + items_base(J, jb);
 
-        // Supports and link counts from the wedges: a wedge of a k-bloom
-        // gives each of its edges k - 1 butterflies (Lemma 2) and one link.
+        // Links: counts (in LDS, where the supports go later), their prefix
+        // sums, the links, and where each edge's end.
+        uint32_t *const cur_end = reinterpret_cast<uint32_t *>(sup);
+        uint32_t *const ends = A.ends + e0;
         for (int i = tid; i < ne; i += nthr) {
-            sup[i] = 0;
-            ends[i] = 0;
+            cur_end[i] = 0;
+            stt[i] = kRemaining;
         }
+        // Edges past the end, up to a multiple of four, are removed ones.
+        if (tid < 4 && ne + tid < ((ne + 3) & ~3)) stt[ne + tid] = kRemoved;
         if (tid == 0) {
             s_min = INT_MAX;
             s_nf[0] = s_nf[1] = s_ni[0] = s_ni[1] = s_multi[0] = s_multi[1] = 0;
         }
         __syncthreads();
         for (uint32_t i = tid; i < J.nw; i += nthr) {
-            const uint32_t w = J.w0 + i;
-            const int32_t d = A.bk[A.wbl[w]] - 1;
-            const uint32_t a = (uint32_t)A.wea[w], b = (uint32_t)A.web[w];
-            if (!(a & kFixedBit)) {
-                atomicAdd(&sup[a - e0], d);
-                atomicAdd(&ends[a - e0], 1u);
-            }
-            if (!(b & kFixedBit)) {
-                atomicAdd(&sup[b - e0], d);
-                atomicAdd(&ends[b - e0], 1u);
-            }
+            const uint32_t a = (uint32_t)A.wea[J.w0 + i], b = (uint32_t)A.web[J.w0 + i];
+            if (!(a & kFixedBit)) atomicAdd(&cur_end[a - e0], 1u);
+            if (!(b & kFixedBit)) atomicAdd(&cur_end[b - e0], 1u);
         }
         __syncthreads();
         {
-            // Exclusive prefix of the link counts, in place; each thread owns
-            // a run of edges.
+            // Each thread owns a run of edges.
             const int per = (ne + nthr - 1) / nthr;
             const int i0 = min(tid * per, ne), i1 = min(i0 + per, ne);
             uint32_t mine = 0;
-            for (int i = i0; i < i1; ++i) mine += ends[i];
+            for (int i = i0; i < i1; ++i) mine += cur_end[i];
             uint32_t total;
             uint32_t run = block_exclusive_sum<uint32_t>(mine, s_scan, &total);
             for (int i = i0; i < i1; ++i) {
-                const uint32_t c = ends[i];
-                ends[i] = run;
+                const uint32_t c = cur_end[i];
+                cur_end[i] = run;
                 run += c;
             }
         }
         __syncthreads();
-        // The links; ends[e] moves from the start of e's links to their end,
-        // which is where e + 1's begin.
         for (uint32_t i = tid; i < J.nw; i += nthr) {
             const uint32_t w = J.w0 + i;
             const uint32_t bl = (uint32_t)A.wbl[w];
             const uint32_t a = (uint32_t)A.wea[w], b = (uint32_t)A.web[w];
             const uint32_t la = a & kFixedBit ? kNoTwin : a - (uint32_t)e0;
             const uint32_t lb = b & kFixedBit ? kNoTwin : b - (uint32_t)e0;
-            if (la != kNoTwin) link[atomicAdd(&ends[la], 1u)] = make_uint2(bl, lb);
-            if (lb != kNoTwin) link[atomicAdd(&ends[lb], 1u)] = make_uint2(bl, la);
+            if (la != kNoTwin) link[atomicAdd(&cur_end[la], 1u)] = make_uint2(bl, lb);
+            if (lb != kNoTwin) link[atomicAdd(&cur_end[lb], 1u)] = make_uint2(bl, la);
         }
-        // Edges past the end, up to a multiple of four, are removed ones.
-        if (tid < 4 && ne + tid < ((ne + 3) & ~3)) ends[ne + tid] = kRemoved << kStateShift;
+        __syncthreads();
+        for (int i = tid; i < ne; i += nthr) {
+            ends[i] = cur_end[i];
+            sup[i] = 0;
+        }
+        __syncthreads();
+        // Supports: a wedge of a k-bloom gives each of its edges k - 1
+        // butterflies (Lemma 2).
+        for (uint32_t i = tid; i < J.nw; i += nthr) {
+            const uint32_t w = J.w0 + i;
+            const int32_t d = A.bk[A.wbl[w]] - 1;
+            if (d <= 0) continue;  // a part's spent bloom
+            const uint32_t a = (uint32_t)A.wea[w], b = (uint32_t)A.web[w];
+            if (!(a & kFixedBit)) atomicAdd(&sup[a - e0], d);
+            if (!(b & kFixedBit)) atomicAdd(&sup[b - e0], d);
+        }
         __syncthreads();
 
         // Queues edge t (lanes with pred) for the round of parity q; all 64
@@ -237,11 +228,10 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
             if (!__ballot(pred)) return;
             uint32_t lo = 0, n = 0;
             if (pred) {
-                A.phi_out[(int64_t)e0 + t] = level;
-                const uint32_t end = ends[t] & kEndMask;
-                lo = t ? ends[t - 1] & kEndMask : 0u;
-                n = end - lo;
-                ends[t] = end | ((uint32_t)(1 + q) << kStateShift);
+                A.phi_out[A.oid ? A.oid[e0 + t] : e0 + (int32_t)t] = level;
+                stt[t] = (uint8_t)(1 + q);
+                lo = t ? ends[t - 1] : 0u;
+                n = ends[t] - lo;
             }
             if (!__ballot(n != 0)) return;
             const uint32_t cnt = (n + kWave - 1) / kWave;
@@ -250,7 +240,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
             put_pieces(n, lo, cnt, slot, t,
                        [&](uint32_t s, uint32_t id, uint32_t at, uint32_t len, uint32_t) {
                            const uint2 v = make_uint2(id | ((len - 1) << 16), at);
-                           if (s < kFrontLds) near[s] = v;
+                           if (s < front_lds) near[s] = v;
                            else list[s] = v;
                        });
         };
@@ -258,38 +248,37 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
         int32_t levels = 0;
         int r = 0;
         while (true) {
-            // The next level: the smallest support among the remaining edges,
-            // which are then taken from the same registers (the scan is bound
-            // by LDS bandwidth).
-            int32_t v[kScanSteps][4];
-            int32_t mn = INT_MAX;
-#pragma unroll
-            for (int k = 0; k < kScanSteps; ++k) {
-                const int i = 4 * (tid + k * nthr);
-                uint4 en = make_uint4(~0u, ~0u, ~0u, ~0u);
+            // The next level: the smallest support among the remaining edges
+            // (INT_MAX for the others), four edges a thread and step.
+            const auto remaining = [&](int i) {
+                uint32_t s4 = ~0u;
                 int4 x = make_int4(0, 0, 0, 0);
                 if (i < ne) {
-                    en = *reinterpret_cast<const uint4 *>(&ends[i]);
+                    s4 = *reinterpret_cast<const uint32_t *>(&stt[i]);
                     x = *reinterpret_cast<const int4 *>(&sup[i]);
                 }
-                v[k][0] = en.x > kEndMask ? INT_MAX : x.x;
-                v[k][1] = en.y > kEndMask ? INT_MAX : x.y;
-                v[k][2] = en.z > kEndMask ? INT_MAX : x.z;
-                v[k][3] = en.w > kEndMask ? INT_MAX : x.w;
-                mn = min(mn, min(min(v[k][0], v[k][1]), min(v[k][2], v[k][3])));
+                return make_int4(s4 & 0xffu ? INT_MAX : x.x, s4 & 0xff00u ? INT_MAX : x.y,
+                                 s4 & 0xff0000u ? INT_MAX : x.z, s4 & 0xff000000u ? INT_MAX : x.w);
+            };
+            int32_t mn = INT_MAX;
+            for (int i = 4 * tid; i < ne; i += 4 * nthr) {
+                const int4 v = remaining(i);
+                mn = min(mn, min(min(v.x, v.y), min(v.z, v.w)));
             }
             mn = wave_min(mn);
             if (lane_id() == 0 && mn != INT_MAX) atomicMin(&s_min, mn);
             __syncthreads();
             const int32_t level = s_min;
             if (level == INT_MAX) break;
-            if (mn == level) {  // this wave has some (wave_min gives every lane the minimum)
-#pragma unroll
-                for (int k = 0; k < kScanSteps; ++k)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        push_front(v[k][c] == level, (uint32_t)(4 * (tid + k * nthr) + c), r & 1,
-                                   level);
+            if (mn == level) {  // only waves that hold such an edge look again
+                for (int i0 = 0; i0 < ne; i0 += 4 * nthr) {
+                    const int i = i0 + 4 * tid;
+                    const int4 v = remaining(i);
+                    push_front(v.x == level, (uint32_t)i, r & 1, level);
+                    push_front(v.y == level, (uint32_t)i + 1, r & 1, level);
+                    push_front(v.z == level, (uint32_t)i + 2, r & 1, level);
+                    push_front(v.w == level, (uint32_t)i + 3, r & 1, level);
+                }
             }
             __syncthreads();
             if (tid == 0) s_min = INT_MAX;
@@ -298,9 +287,9 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
             uint32_t nf = s_nf[r & 1];
             while (nf > 0) {
                 const int p = r & 1, q = p ^ 1;
-                const uint32_t cur = 1 + p, nxt = 1 + q;
+                const uint8_t cur = (uint8_t)(1 + p), nxt = (uint8_t)(1 + q);
                 const uint2 *const fl = p ? fr1 : fr0, *const fn = p ? lf1 : lf0;
-                const auto front_item = [&](uint32_t i) { return i < kFrontLds ? fn[i] : fl[i]; };
+                const auto front_item = [&](uint32_t i) { return i < front_lds ? fn[i] : fl[i]; };
                 // Phase A: the frontier's links.  A wedge whose edges are both
                 // in the frontier is killed by the smaller one.
                 {
@@ -320,14 +309,15 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                             const bool act = x < total;
                             const uint32_t ej = __shfl(e, j, kWave);
                             const uint32_t at = __shfl(it.y - start, j, kWave) + x;
-                            uint32_t bl = 0, t = kNoTwin, w0 = 0, w1 = 0, s = kRemaining;
+                            uint32_t bl = 0, t = kNoTwin, w0 = 0, w1 = 0;
+                            uint8_t s = kRemaining;
                             u64 old = 1;
                             bool alive = false;
                             if (act) {
                                 const uint2 lk = link[at];
                                 bl = lk.x;
                                 t = lk.y;
-                                if (t != kNoTwin) s = ends[t] >> kStateShift;
+                                if (t != kNoTwin) s = stt[t];
                                 alive = s != kRemoved && !(s == cur && t < ej);
                                 w0 = A.bwoff[bl];
                                 w1 = A.bwoff[bl + 1];
@@ -353,7 +343,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                                                const uint2 v = make_uint2(
                                                    id | (pieces > 1 ? 0x80000000u : 0u),
                                                    (pos << 6) | (pn - 1));
-                                               if (sl < kItemsLds) li[sl] = v;
+                                               if (sl < items_lds) li[sl] = v;
                                                else items[sl] = v;
                                            });
                             }
@@ -369,10 +359,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                     s_multi[q] = 0;
                     rounds += 1;
                 }
-                for (uint32_t i = tid; i < nf; i += nthr) {
-                    uint32_t *const en = &ends[front_item(i).x & 0xffffu];
-                    *en = (*en & kEndMask) | (kRemoved << kStateShift);
-                }
+                for (uint32_t i = tid; i < nf; i += nthr) stt[front_item(i).x & 0xffffu] = kRemoved;
                 // Phase B: survivors of touched blooms lose their C kills.
                 {
                     const uint32_t per = min((uint32_t)kWave, (ni + nwv - 1) / nwv);
@@ -382,7 +369,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                         uint2 it = make_uint2(0, 0);
                         u64 state = 0;
                         if (ok) {
-                            it = i < kItemsLds ? li[i] : items[i];
+                            it = i < items_lds ? li[i] : items[i];
                             state = ld(&A.bs[it.x & kEdgeMask]);  // arrives with the wedges
                         }
                         const uint32_t n = ok ? (it.y & 63u) + 1 : 0u;
@@ -402,8 +389,8 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                             const int32_t cj = __shfl((int32_t)(uint32_t)state, j, kWave);
                             const bool oa = !(a & kFixedBit), ob = !(b & kFixedBit);
                             const uint32_t la = a - (uint32_t)e0, lb = b - (uint32_t)e0;
-                            const uint32_t sa = oa ? ends[la] >> kStateShift : (uint32_t)kRemaining;
-                            const uint32_t sb = ob ? ends[lb] >> kStateShift : (uint32_t)kRemaining;
+                            const uint8_t sa = oa ? stt[la] : (uint8_t)kRemaining;
+                            const uint8_t sb = ob ? stt[lb] : (uint8_t)kRemaining;
                             const bool live = act && (sa == kRemaining || sa == nxt) &&
                                               (sb == kRemaining || sb == nxt);
                             const bool da = live && oa, db = live && ob;
@@ -415,15 +402,15 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                                     if (da) f1 |= atomicSub(&sup[la], 1) == level + 1;
                                     if (db) f2 |= atomicSub(&sup[lb], 1) == level + 1;
                                 }
-                                upd += (u64)((da ? cj : 0) + (db ? cj : 0));
+                                upd += (uint32_t)((da ? cj : 0) + (db ? cj : 0));
                             } else {
                                 int32_t o1 = 0, o2 = 0;
                                 if (da) o1 = atomicSub(&sup[la], cj);
                                 if (db) o2 = atomicSub(&sup[lb], cj);
                                 f1 = da && o1 > level && o1 - cj <= level;
                                 f2 = db && o2 > level && o2 - cj <= level;
-                                upd += (u64)((da ? 1 : 0) + (db ? 1 : 0));
-                                unb += (u64)((da ? cj - 1 : 0) + (db ? cj - 1 : 0));
+                                upd += (da ? 1u : 0u) + (db ? 1u : 0u);
+                                unb += (uint32_t)((da ? cj - 1 : 0) + (db ? cj - 1 : 0));
                             }
                             touch += live ? 1 : 0;
                             push_front(f1, la, q, level);
@@ -439,7 +426,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                 __syncthreads();
                 if (multi) {
                     for (uint32_t i = tid; i < ni; i += nthr) {
-                        const uint2 it = i < kItemsLds ? li[i] : items[i];
+                        const uint2 it = i < items_lds ? li[i] : items[i];
                         const uint32_t b = it.x & kEdgeMask;
                         if (!(it.x & 0x80000000u) || A.bwoff[b] != J.w0 + (it.y >> 6)) continue;
                         st(&A.bs[b], settle(ld(&A.bs[b])));
@@ -453,12 +440,11 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
         }
         if (tid == 0) atomicAdd(&A.glevels[J.graph], levels);
     }
-    upd = wave_sum(upd);
-    unb = wave_sum(unb);
-    const u64 tt = wave_sum<u64>(touch), vv = wave_sum<u64>(visits);
+    const u64 uu = wave_sum<u64>(upd), bb = wave_sum<u64>(unb), tt = wave_sum<u64>(touch),
+              vv = wave_sum<u64>(visits);
     if (lane_id() == 0) {
-        if (upd) atomicAdd(&A.ctl->updates, upd);
-        if (unb) atomicAdd(&A.ctl->unbatched, unb);
+        if (uu) atomicAdd(&A.ctl->updates, uu);
+        if (bb) atomicAdd(&A.ctl->unbatched, bb);
         if (tt) atomicAdd(&A.ctl->touched, tt);
         if (vv) atomicAdd(&A.ctl->bloom_visits, vv);
     }
@@ -502,100 +488,80 @@ __global__ void k_leaf_state(const int32_t *bk, int64_t n, u64 *bs) {
         bs[b] = (u64)(uint32_t)bk[b] << 32;
 }
 
-// Workgroups of a launch, by the largest job's edges: small jobs take less
-// LDS and fewer waves, so several share a compute unit.
-struct LeafClass {
-    int ecap, threads;
-};
-constexpr LeafClass kLeafClasses[] = {{(int)kLeafEdges, 1024}, {7168, 512}, {2048, 256}};
-constexpr int kNumLeafClasses = 3;
-
 }  // namespace
 
 int64_t peel_leaf_bytes(int64_t m, int64_t cap_b, int64_t cap_w, int64_t graphs) {
     const int64_t front = m + cap_w / 32 + graphs + 1, items = cap_b + cap_w / 64 + graphs + 1;
-    const int64_t t = 16 * cap_w + 16 * front + 8 * items + 8 * (cap_b + 1) + 48 * graphs + 4096;
+    const int64_t t = 16 * cap_w + 4 * m + 16 * front + 8 * items + 8 * (cap_b + 1) + 48 * graphs + 4096;
     return t + t / 8;
 }
 
-void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *doff,
-               int64_t *sup_out, int64_t *phi_out, bool unit_updates, PeelCounters &pc,
-               Workspace &ws, hipStream_t s) {
-    const int32_t ng = (int32_t)off.size() - 1;
-    const int64_t m = off[(size_t)ng];
-    if (m == 0) return;
+namespace {
+
+// Buffers of a leaf peel over arrays of m edges, n_b blooms and n_w wedges.
+LeafArgs leaf_args(int64_t m, int64_t n_b, int64_t n_w, int32_t n_jobs, int32_t n_roots,
+                   const int32_t *bk, Workspace &ws, hipStream_t s) {
     LeafArgs A{};
-    LeafJob *jobs = ws.get<LeafJob>("lf_jobs", ng);
-    LeafCtl *ctl = ws.get<LeafCtl>("lf_ctl", 1);
-    A.jobs = jobs;
-    A.njobs = ng;
-    A.wea = ix.wea;
-    A.web = ix.web;
-    A.wbl = ix.wbl;
-    A.bwoff = ix.bwoff;
-    A.bk = ix.bk;
-    A.bs = ws.get<u64>("lf_bs", ix.cap_b + 1);
-    A.link = ws.get<uint2>("lf_link", 2 * ix.cap_w + 1);
-    A.front[0] = ws.get<uint2>("lf_front0", m + ix.cap_w / 32 + ng + 1);
-    A.front[1] = ws.get<uint2>("lf_front1", m + ix.cap_w / 32 + ng + 1);
-    A.items = ws.get<uint2>("lf_items", ix.cap_b + ix.cap_w / 64 + ng + 1);
-    A.phi_out = phi_out;
-    A.glevels = ws.get<int32_t>("lf_levels", ng);
-    A.ctl = ctl;
-    zero_bytes(ctl, sizeof(LeafCtl), s);
-    zero_bytes(A.glevels, sizeof(int32_t) * ng, s);
-    k_leaf_state<<<grid_for(ix.cap_b + 1, 256, 8192), 256, 0, s>>>(ix.bk, ix.cap_b + 1, A.bs);
+    A.bk = bk;
+    A.bs = ws.get<u64>("lf_bs", n_b + 1);
+    A.link = ws.get<uint2>("lf_link", 2 * n_w + 1);
+    A.ends = ws.get<uint32_t>("lf_ends", m);
+    A.front[0] = ws.get<uint2>("lf_front0", m + n_w / 32 + n_jobs + 1);
+    A.front[1] = ws.get<uint2>("lf_front1", m + n_w / 32 + n_jobs + 1);
+    A.items = ws.get<uint2>("lf_items", n_b + n_w / 64 + n_jobs + 1);
+    A.glevels = ws.get<int32_t>("lf_levels", n_roots);
+    A.ctl = ws.get<LeafCtl>("lf_ctl", 1);
+    zero_bytes(A.ctl, sizeof(LeafCtl), s);
+    zero_bytes(A.glevels, sizeof(int32_t) * n_roots, s);
+    k_leaf_state<<<grid_for(n_b + 1, 256, 8192), 256, 0, s>>>(bk, n_b + 1, A.bs);
     BT_CHECK_LAUNCH();
-    k_leaf_jobs<<<grid_for(ng, 256, 256), 256, 0, s>>>(doff, ng, ix.base, ix.cursor, jobs, ctl);
-    BT_CHECK_LAUNCH();
-    if (sup_out) supl_to_sup(ix.supl, sup_out, m, s);
+    return A;
+}
+
+// Runs the jobs, which come by class (size(j): edges of the j-th in queue
+// order), and reads the counters back.
+template <typename Size>
+void run_leaves(LeafArgs A, int32_t n_jobs, Size &&size, bool unit_updates, int32_t n_roots,
+                std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc, LeafCtl &done,
+                Workspace &ws, hipStream_t s) {
     int dev = 0, cus = 0;
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     hipEvent_t ev0, ev1;
     BT_HIP(hipEventCreate(&ev0));
     BT_HIP(hipEventCreate(&ev1));
+    // The classes run beside each other on side streams (one after another
+    // they took the sum of their longest jobs: 24 ms against 14 for 512 graphs
+    // of up to 16,000 edges).
+    hipEvent_t joins[kNumLeafClasses] = {};
     struct EvFree {
-        hipEvent_t a, b;
+        hipEvent_t a, b, *e;
         ~EvFree() {
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
-        }
-    } ev_free{ev0, ev1};
-    const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
-    BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)leaf_lds((int)kLeafEdges)));
-    // This peel needs no co-resident workgroups, but it takes its turn like
-    // the others, so that a running peel of a much larger graph gives way.
-    CoopTurn turn(m);
-    BT_HIP(hipEventRecord(ev0, s));
-    // Jobs come in decreasing size: each class is a range of them.  The
-    // classes run beside each other on side streams (one after another they
-    // took the sum of their longest jobs: 24 ms against 14 for 512 graphs of
-    // up to 16,000 edges).
-    int32_t a = 0;
-    hipEvent_t joins[kNumLeafClasses] = {};
-    struct JoinFree {
-        hipEvent_t *e;
-        ~JoinFree() {
             for (int c = 0; c < kNumLeafClasses; ++c)
                 if (e[c]) (void)hipEventDestroy(e[c]);
         }
-    } join_free{joins};
+    } ev_free{ev0, ev1, joins};
+    const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
+    BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kLeafClasses[0].lds()));
+    BT_HIP(hipEventRecord(ev0, s));
+    int32_t a = 0;
     for (int c = 0; c < kNumLeafClasses; ++c) {
         const int64_t below = c + 1 < kNumLeafClasses ? kLeafClasses[c + 1].ecap : 0;
         int32_t b = a;
-        while (b < ng && off[(size_t)b + 1] - off[(size_t)b] > below) ++b;
+        while (b < n_jobs && size(b) > below) ++b;
         if (b > a) {
             const LeafClass &K = kLeafClasses[c];
             int occ = 0;
             BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, K.threads,
-                                                                leaf_lds(K.ecap)));
+                                                                K.lds()));
             const int grid = std::min<int>(b - a, cus * std::max(1, occ));
-            const hipStream_t cs = b == ng ? s : ws.side(c);  // the last class stays on s
-            A.queue = &ctl->queue[c];
+            const hipStream_t cs = b == n_jobs ? s : ws.side(c);  // the last class stays on s
+            A.queue = &A.ctl->queue[c];
             if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
-            kern<<<grid, K.threads, leaf_lds(K.ecap), cs>>>(A, a, b, K.ecap);
+            kern<<<grid, K.threads, K.lds(), cs>>>(A, a, b, K);
             BT_CHECK_LAUNCH();
             if (cs != s) {
                 BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
@@ -607,24 +573,97 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     for (hipEvent_t e : joins)
         if (e) BT_HIP(hipStreamWaitEvent(s, e, 0));
     BT_HIP(hipEventRecord(ev1, s));
-    LeafCtl *hc = reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (ng + 1) / 2)));
+    LeafCtl *hc =
+        reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (n_roots + 1) / 2)));
     int32_t *hl = reinterpret_cast<int32_t *>(hc + 1);
-    BT_HIP(hipMemcpyAsync(hc, ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));
-    BT_HIP(hipMemcpyAsync(hl, A.glevels, sizeof(int32_t) * ng, hipMemcpyDeviceToHost, s));
+    BT_HIP(hipMemcpyAsync(hc, A.ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));
+    BT_HIP(hipMemcpyAsync(hl, A.glevels, sizeof(int32_t) * n_roots, hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
     float t = 0.f;
     BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
+    if (std::getenv("BT_PEEL_VERBOSE"))
+        std::fprintf(stderr, "[peel] leaves: %d of up to %lld edges: %.2f ms, %llu rounds\n", n_jobs,
+                     (long long)size(0), (double)t, hc->rounds);
     pc.kernel_ms += t;
+    pc.rounds += (int64_t)hc->rounds;
+    pc.updates += (int64_t)hc->updates;
+    pc.updates_unbatched += (int64_t)(hc->updates + hc->unbatched);
+    pc.bloom_visits += (int64_t)hc->bloom_visits;
+    pc.touched += (int64_t)hc->touched;
+    max_level = std::max(max_level, hc->max_level);
+    for (int32_t g = 0; g < n_roots; ++g) levels[(size_t)g] += hl[g];
+    done = *hc;
+}
+
+}  // namespace
+
+void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *doff,
+               int64_t *sup_out, int64_t *phi_out, bool unit_updates, PeelCounters &pc,
+               Workspace &ws, hipStream_t s) {
+    const int32_t ng = (int32_t)off.size() - 1;
+    const int64_t m = off[(size_t)ng];
+    if (m == 0) return;
+    LeafArgs A = leaf_args(m, ix.cap_b, ix.cap_w, ng, ng, ix.bk, ws, s);
+    LeafJob *jobs = ws.get<LeafJob>("lf_jobs", ng);
+    A.jobs = jobs;
+    A.wea = ix.wea;
+    A.web = ix.web;
+    A.wbl = ix.wbl;
+    A.bwoff = ix.bwoff;
+    A.phi_out = phi_out;
+    k_leaf_jobs<<<grid_for(ng, 256, 256), 256, 0, s>>>(doff, ng, ix.base, ix.cursor, jobs, A.ctl);
+    BT_CHECK_LAUNCH();
+    if (sup_out) supl_to_sup(ix.supl, sup_out, m, s);
+    // This peel needs no co-resident workgroups, but it takes its turn like
+    // the others, so that a running peel of a much larger graph gives way.
+    CoopTurn turn(m);
+    std::vector<int32_t> levels((size_t)ng, 0);
+    int32_t max_level = 0;
+    LeafCtl done;
+    run_leaves(A, ng, [&](int32_t j) { return off[(size_t)j + 1] - off[(size_t)j]; }, unit_updates,
+               ng, levels, max_level, pc, done, ws, s);
     pc.launches += 1;
-    pc.rounds = (int64_t)hc->rounds;
-    pc.updates = (int64_t)hc->updates;
-    pc.updates_unbatched = pc.updates + (int64_t)hc->unbatched;
-    pc.bloom_visits = (int64_t)hc->bloom_visits;
-    pc.touched = (int64_t)hc->touched;
-    pc.max_phi = hc->max_level;
-    for (int32_t g = 0; g < ng; ++g) pc.levels = std::max<int64_t>(pc.levels, hl[g]);
-    ix.n_b = (int64_t)hc->blooms;
-    ix.n_w = (int64_t)hc->wedges;
+    pc.max_phi = max_level;
+    for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);
+    ix.n_b = (int64_t)done.blooms;
+    ix.n_w = (int64_t)done.wedges;
+}
+
+void peel_leaf_jobs(const LeafPool &pool, int64_t *phi_out, bool unit_updates,
+                    std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc,
+                    Workspace &ws, hipStream_t s) {
+    const int32_t n = (int32_t)pool.leaves.size(), roots = (int32_t)levels.size();
+    // Queue order: by launch, then the heaviest first.
+    const auto cls = [&](int32_t j) {
+        int c = 0;
+        while (c + 1 < kNumLeafClasses && pool.leaves[(size_t)j].ne <= kLeafClasses[c + 1].ecap) ++c;
+        return c;
+    };
+    std::vector<int32_t> order((size_t)n);
+    for (int32_t j = 0; j < n; ++j) order[(size_t)j] = j;
+    std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        const int cx = cls(x), cy = cls(y);
+        if (cx != cy) return cx < cy;
+        const uint32_t wx = pool.leaves[(size_t)x].work, wy = pool.leaves[(size_t)y].work;
+        return wx != wy ? wx > wy : x < y;
+    });
+    LeafArgs A = leaf_args(pool.m, pool.n_b, pool.n_w, n, roots, pool.bk, ws, s);
+    LeafJob *jobs = ws.get<LeafJob>("lf_jobs", n);
+    int32_t *dorder = ws.get<int32_t>("lf_order", n);
+    BT_HIP(hipMemcpyAsync(jobs, pool.jobs.data(), sizeof(LeafJob) * n, hipMemcpyHostToDevice, s));
+    BT_HIP(hipMemcpyAsync(dorder, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+    A.jobs = jobs;
+    A.order = dorder;
+    A.wea = pool.wea;
+    A.web = pool.web;
+    A.wbl = pool.wbl;
+    A.bwoff = pool.bwoff;
+    A.oid = pool.oid;
+    A.phi_out = phi_out;
+    LeafCtl done;
+    run_leaves(
+        A, n, [&](int32_t j) { return (int64_t)pool.leaves[(size_t)order[(size_t)j]].ne; },
+        unit_updates, roots, levels, max_level, pc, done, ws, s);
 }
 
 }  // namespace bt

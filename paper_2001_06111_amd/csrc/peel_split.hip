@@ -1,0 +1,1390 @@
+// peel_split.hip - the peel of larger graphs: split into ranges of bitruss
+// numbers by grid-wide sweeps, then finish each range by itself.
+//
+// Peeling level by level, as Algorithm 5 does, is a chain of tens of
+// thousands of dependent rounds (75,000 for a 5M-edge power-law graph), and
+// every round touches blooms across the graph.  The two-phase peeling of
+// Lakhotia, Kannan and Prasanna (parallel peeling of bipartite networks)
+// breaks the chain:
+//   1. A sweep works at coarse levels.  It takes every remaining edge with
+//      support at most hi, cascades to the fixpoint as the level-by-level
+//      peel does, and calls the edges removed a part: their bitruss numbers
+//      lie between the smallest support when the part began and hi.  A few
+//      hundred rounds remove everything, and the survivors of a bloom take
+//      one decrement per round for all of a round's kills, so there are
+//      fewer decrements as well.
+//   2. Within a part, edges are peeled level by level against the edges of
+//      this and later parts only, which needs the wedges whose first-removed
+//      edge lies in the part (regroup.hip).  Parts do not wait for each
+//      other.  A part below kLeafEdges edges is peeled by one workgroup
+//      (peel_leaf.hip); a larger one is a job of the next sweep, which
+//      splits all such jobs at once, each at its own levels; a part of a
+//      single level is done.
+// The bitruss numbers are those of Algorithm 5: the edges of later parts
+// outlive a part's levels, so they keep their wedges in its blooms.
+//
+// One sweep is one cooperative kernel.  All jobs advance in each round, each
+// job through: select (a workgroup reads a sample of the job's remaining
+// supports and sets hi so that about a target share of the edges and of the
+// summed support lies below it), gather (the edges at or below hi become the
+// frontier), rounds until no edge falls to hi.
+//
+// Whole calls, level by level and split: 5M-edge Chung-Lu graph (75,000
+// rounds, bound by the 9 us a round's two grid barriers and chains take)
+// 1.107 s and 0.274 s; 200k-edge graph 66.1 and 18.9 ms; 400k-edge hub graph
+// by BiT-PC 439 and 113 ms; 192 pool graphs in one batch 618 and 157 ms.
+// The 5M graph's first sweep is now bound by memory-side requests (about
+// 2e10/s of support atomics and random reads), a small graph's by the 10 to
+// 15 us of a round.  The level-by-level form stays for callers whose memory
+// does not hold the second copy of the index that the split needs.
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <memory>
+
+#include "peel_split.h"
+
+namespace bt {
+
+namespace {
+
+enum : int32_t { kJobActive = 0, kJobDone = 1 };
+constexpr int kGatherPerLane = 8;  // edges per lane of a gather item
+constexpr uint32_t kGatherChunk = kWave * kGatherPerLane;
+// Sweeps of at least this many edges run on every CU by default: they are
+// bound by atomic throughput more than by the latency of their rounds.
+constexpr int64_t kAllCusEdges = int64_t(1) << 24;
+constexpr int32_t kLevelMax = INT_MAX - 1;  // above every support
+
+struct alignas(128) JobState {
+    int32_t state;
+    int32_t level;      // hi of the current part
+    int32_t part;
+    int32_t n_parts;    // parts begun
+    int32_t gmin[2];    // smallest remaining support above the level, by round parity
+    int32_t fr[2];      // frontier items exist for the round of this parity
+    int32_t e0, e1;
+    int64_t gather_round, select_round;  // last scheduled (-1: none)
+    int64_t target_n, target_w;          // edges and summed support a part should take
+    float scale;        // of the targets: cascades add to what a part takes
+    float est_n;        // edges the last select expected to take
+    float rem_n;        // edges it saw remaining
+    int32_t narrow;     // split by levels, not by edges (a job that came back whole)
+    int32_t hi_bound;   // its bitruss numbers are at most this
+};
+
+// A piece of at most 64 wedges of a touched bloom; b < 0: none.
+struct alignas(8) SweepBloomItem {
+    int32_t b;
+    uint32_t chunk;
+};
+
+struct SweepGatherItem {
+    int32_t part, pad;
+    uint32_t lo, hi;  // edges
+};
+
+struct SweepCtl {
+    Counter nf[2], ntc[2], ngth[2], nsel[2];
+    Counter updates, bloom_visits, touched, unbatched;
+    Counter left;      // jobs not done
+    Counter n_parts;   // parts begun
+    u64 rounds;        // rounds run so far (a resumed launch starts at this round)
+    u64 round_b;       // two-kernel rounds: the round of phase B
+    u64 prof[5];       // BT_PEEL_PROFILE=1: block-0 clock ticks (decide, A, bar, B, bar)
+    u64 yield_src;     // address of the host-written yield word (0: none)
+    int32_t yield_req;  // the yield word as the lead last read it
+    int32_t yielded;    // set when the launch ended early to give way
+};
+
+// Every kYieldEvery rounds the lead reads the host's yield word.
+constexpr int64_t kYieldEvery = 16;
+
+// Parts a job may begin in one sweep; the last takes everything left.
+constexpr int32_t kMaxParts = 64;
+constexpr int kSelBins = 256;     // floating bins: 3 mantissa bits
+constexpr int64_t kSelSamples = 4096;  // edges a select looks at
+
+// What the sweep keeps of a bloom: a kill reads it with the atomic that
+// counts in it.
+struct alignas(8) BloomRec {
+    u64 kc;           // (live wedges at the round's start << 32) | kills of this round
+    uint32_t w0, w1;  // its wedges
+    int32_t part;     // the last part that touched it (with P.plain: the last job)
+    int32_t done;     // chunks of it that phase B has finished
+};
+
+struct SweepArgs {
+    SweepCtl *ctl;
+    JobState *js;
+    int32_t n_jobs;
+    SplitPart *parts;
+    int32_t *sup;
+    EdgeMark *mark;
+    uint8_t *dead;      // per wedge
+    BloomRec *bloom;
+    int32_t *wedge_k;
+    const int32_t *wea, *web;
+    const int64_t *link_off;
+    const uint3 *link;
+    uint32_t n_w;
+    int32_t plain;      // level by level, each edge's mark its number
+    int32_t unit;       // one decrement per kill (no batch bloom processing)
+    FrontItem *front[2];  // {edge, part, links [lo, hi)}
+    SweepBloomItem *tc[2];
+    SweepGatherItem *gth[2];
+    int32_t *sel[2];
+};
+
+__device__ __forceinline__ uint32_t chunks_of(uint32_t lo, uint32_t hi) {
+    return (hi - lo + kLinkChunk - 1) / kLinkChunk;
+}
+
+__device__ __forceinline__ void set_front_flag(const SweepArgs &P, int32_t job, int q) {
+    st(&P.js[job].fr[q], 1);
+}
+
+// A wave's reservation of a work list's slots.  All waves of a round append
+// to two lists, and one counter takes an atomic every few nanoseconds: with an
+// atomic per step of a wave those counters bounded large rounds (33 ms of a
+// 5M-edge graph's first sweep in phase A).  In a round of several items a
+// wave, a wave therefore reserves twice its items' number of slots at a time
+// (up to kReserve) and fills what it leaves over with null items, at most half
+// as many as the round had.
+constexpr uint32_t kReserve = 128;
+struct Reserve {
+    uint32_t base = 0, left = 0;  // lists hold fewer than 2^32 items
+};
+// Slots of a step's items 0, 1, ...: the rest of the reservation, then a new one.
+struct Slots {
+    uint32_t old_base, new_base, old_left;
+    __device__ uint32_t operator()(uint32_t i) const {
+        return i < old_left ? old_base + i : new_base + (i - old_left);
+    }
+};
+
+// Slots for n0 items of one list and n1 of another (uniform over the wave);
+// both counters' atomics are issued together.  With grow 0 nothing is left over.
+__device__ __forceinline__ void reserve2(Reserve &R0, uint32_t n0, u64 *k0, Reserve &R1,
+                                         uint32_t n1, u64 *k1, uint32_t grow, Slots &S0,
+                                         Slots &S1) {
+    const uint32_t x0 = n0 > R0.left ? n0 - R0.left : 0u, x1 = n1 > R1.left ? n1 - R1.left : 0u;
+    const uint32_t a0 = x0 ? max(x0, grow) : 0u, a1 = x1 ? max(x1, grow) : 0u;
+    int r = 0;
+    if (a0 | a1) {
+        const uint32_t a = lane_id() == 0 ? a0 : a1;
+        if (lane_id() < 2 && a) r = (int)(uint32_t)atomicAdd(lane_id() == 0 ? k0 : k1, (u64)a);
+    }
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane(r, 0);
+    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane(r, 1);
+    S0 = Slots{R0.base, r0, R0.left};
+    S1 = Slots{R1.base, r1, R1.left};
+    if (x0) {
+        R0.base = r0 + x0;
+        R0.left = a0 - x0;
+    } else {
+        R0.base += n0;
+        R0.left -= n0;
+    }
+    if (x1) {
+        R1.base = r1 + x1;
+        R1.left = a1 - x1;
+    } else {
+        R1.base += n1;
+        R1.left -= n1;
+    }
+}
+
+// Each lane's cnt chunks of bloom b as items at slots S(at), ...: a lane writes its first, the whole wave the others of a longer range.  All
+// 64 lanes call.
+__device__ __forceinline__ void put_blooms(SweepBloomItem *list, const Slots &S, uint32_t cnt,
+                                           uint32_t at, int32_t b) {
+    const auto put = [&](uint32_t slot, int32_t bloom, uint32_t c) {
+        st(reinterpret_cast<u64 *>(&list[slot]), ((u64)c << 32) | (uint32_t)bloom);
+    };
+    if (cnt) put(S(at), b, 0);
+    unsigned long long big = __ballot(cnt > 1);
+    while (big) {
+        const int l = __ffsll(big) - 1;
+        big &= big - 1;
+        const uint32_t n = __shfl(cnt, l, kWave), a = __shfl(at, l, kWave);
+        const int32_t lb = __shfl(b, l, kWave);
+        for (uint32_t c = 1 + lane_id(); c < n; c += kWave) put(S(a + c), lb, c);
+    }
+}
+
+// The same for the links of an edge that joins a part and goes at `round`
+// (lanes with take); an edge without links needs no item.
+__device__ __forceinline__ void put_fronts(const SweepArgs &P, FrontItem *list, const Slots &S,
+                                           bool take, uint32_t cnt, uint32_t at, int32_t e,
+                                           int32_t part, int32_t level, int32_t round,
+                                           uint32_t lo, uint32_t hi) {
+    if (take) st(&P.mark[e].v, edge_mark(P.plain ? level : part, round));
+    if (cnt) st_item(&list[S(at)], FrontItem{e, part, lo, min(lo + (uint32_t)kWave, hi)});
+    unsigned long long big = __ballot(cnt > 1);
+    while (big) {
+        const int l = __ffsll(big) - 1;
+        big &= big - 1;
+        const uint32_t n = __shfl(cnt, l, kWave), a = __shfl(at, l, kWave);
+        const int32_t le = __shfl(e, l, kWave), lp = __shfl(part, l, kWave);
+        const uint32_t llo = __shfl(lo, l, kWave), lhi = __shfl(hi, l, kWave);
+        for (uint32_t c = 1 + lane_id(); c < n; c += kWave) {
+            const uint32_t x = llo + c * kWave;
+            st_item(&list[S(a + c)], FrontItem{le, lp, x, min(x + (uint32_t)kWave, lhi)});
+        }
+    }
+}
+
+// Null items in the slots a wave leaves over at the end of a phase: a bloom
+// item of no bloom (taken as the dead wedge past the last one), a frontier
+// item of no edge.
+__device__ __forceinline__ void fill_blooms(SweepBloomItem *list, const Reserve &R) {
+    for (uint32_t i = lane_id(); i < R.left; i += kWave)
+        st(reinterpret_cast<u64 *>(&list[R.base + i]), (u64)0xffffffffu);
+}
+__device__ __forceinline__ void fill_fronts(FrontItem *list, const Reserve &R) {
+    for (uint32_t i = lane_id(); i < R.left; i += kWave)
+        st_item(&list[R.base + i], FrontItem{-1, 0, 0u, 1u});
+}
+
+// Gather items over edges [e0, e1) for the round of parity q; each lane with
+// n = e1 - e0 > 0 has its own.  All 64 lanes call.
+__device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t part, int32_t e0,
+                                           uint32_t n) {
+    const uint32_t cnt = (n + kGatherChunk - 1) / kGatherChunk;
+    u64 base[3];
+    wave_alloc3(cnt, &P.ctl->ngth[q].v, 0u, nullptr, 0u, nullptr, base);
+    unsigned long long who = __ballot(cnt != 0);
+    while (who) {
+        const int l = __ffsll(who) - 1;
+        who &= who - 1;
+        const uint32_t nc = __shfl(cnt, l, kWave), ln = __shfl(n, l, kWave);
+        const u64 b = __shfl(base[0], l, kWave);
+        const int32_t lp = __shfl(part, l, kWave);
+        const uint32_t le = (uint32_t)__shfl(e0, l, kWave);
+        for (uint32_t c = lane_id(); c < nc; c += kWave) {
+            const uint32_t a = c * kGatherChunk;
+            st_item(&P.gth[q][b + c], SweepGatherItem{lp, 0, le + a, le + min(a + kGatherChunk, ln)});
+        }
+    }
+}
+
+// What each of this thread's jobs does next, decided at the start of round r
+// (parity p) from what the last round left: rounds while there is a
+// frontier; after a gather that took nothing, a gather at the smallest
+// support it saw; else a select for the next part.
+__device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, int64_t nthreads) {
+    const int q = p ^ 1;
+    for (int64_t g0 = tid - lane_id(); g0 < P.n_jobs; g0 += nthreads) {
+        const int64_t g = g0 + lane_id();
+        bool gather = false, select = false;
+        int32_t e0 = 0, e1 = 0, part = 0;
+        if (g < P.n_jobs) {
+            JobState *J = &P.js[g];
+            const int32_t state = ld(&J->state);
+            const int64_t gr = ld(&J->gather_round), sr = ld(&J->select_round);
+            const int32_t fr = ld(&J->fr[p]);
+            const int32_t gm = ld(&J->gmin[q]);
+            const int32_t level = ld(&J->level);
+            part = ld(&J->part);
+            e0 = ld(&J->e0);
+            e1 = ld(&J->e1);
+            if (state != kJobDone) {
+                if (fr) st(&J->fr[p], 0);
+                if (!fr && sr != r && gr != r) {
+                    int32_t next = INT_MAX;
+                    if (gr == r - 1) {
+                        next = gm;
+                        if (gm == INT_MAX) {  // nothing remains
+                            st(&J->state, (int32_t)kJobDone);
+                            atomicAdd(&P.ctl->left.v, ~0ull);
+                        }
+                    } else if (level >= kLevelMax) {
+                        // the part took everything
+                        st(&J->state, (int32_t)kJobDone);
+                        atomicAdd(&P.ctl->left.v, ~0ull);
+                    } else if (P.plain) {
+                        next = level + 1;
+                        atomicAdd(&J->n_parts, 1);
+                    } else {
+                        select = true;
+                        st(&J->select_round, r + 1);
+                    }
+                    if (next != INT_MAX) {
+                        gather = true;
+                        st(&J->level, next);
+                        st(&P.parts[part].hi, next);
+                        st(&J->gather_round, r + 1);
+                        st(&J->gmin[q], (int32_t)INT_MAX);
+                    }
+                }
+            }
+        }
+        put_gather(P, q, part, e0, gather ? (uint32_t)(e1 - e0) : 0u);
+        const u64 slot = wave_alloc(select ? 1u : 0u, &P.ctl->nsel[q].v);
+        if (select) st(&P.sel[q][slot], (int32_t)g);
+    }
+}
+
+// Floating bins of d >= 1 with three mantissa bits, and the smallest value
+// past a bin.
+__device__ __forceinline__ int sel_bin(uint32_t d) {
+    const int l = 31 - __clz((int)d);
+    return l <= 3 ? (int)d : (int)((l - 3) * 8 + (int)(d >> (l - 3)));
+}
+__device__ __forceinline__ int64_t sel_end(int b) {
+    if (b < 16) return (int64_t)b + 1;
+    const int sh = b / 8 - 1;
+    return (int64_t)(b % 8 + 8 + 1) << sh;
+}
+
+// Begins a job's next part: from a sample of its remaining supports, the
+// largest level below which no more than the targets lie (at least the
+// smallest support sampled), and the gather at it for round r + 1.  A job
+// that came back whole from the last sweep (some range's cascade took all of
+// it) is cut into sixteenths of its range of levels instead, down to single
+// levels.  One workgroup; all its threads call.
+__device__ void sweep_select(const SweepArgs &P, int32_t g, int64_t r, int q) {
+    __shared__ uint32_t s_n[kSelBins];
+    __shared__ int32_t s_mn, s_mx;
+    JobState *J = &P.js[g];
+    const int32_t e0 = ld(&J->e0), e1 = ld(&J->e1);
+    const int64_t n = e1 - e0;
+    const int64_t samples = n < kSelSamples ? n : kSelSamples;
+    const u64 step = samples ? ((u64)n << 31) / (u64)samples : 0;  // 31-bit fraction
+    for (int i = threadIdx.x; i < kSelBins; i += blockDim.x) s_n[i] = 0;
+    if (threadIdx.x == 0) {
+        s_mn = INT_MAX;
+        s_mx = -1;
+    }
+    __syncthreads();
+    // Four samples' supports at a time, INT_MAX where the edge is gone.
+    const auto sample4 = [&](int64_t i0, int32_t (&v)[4]) {
+        int32_t ph[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + (int64_t)k * blockDim.x;
+            ph[k] = 0;
+            v[k] = INT_MAX;
+            if (i < samples) {
+                const int64_t e = e0 + (int64_t)(((u64)i * step) >> 31);
+                ph[k] = mark_part(ld(&P.mark[e].v));
+                v[k] = ld(&P.sup[e]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = ph[k] < 0 ? v[k] : INT_MAX;
+    };
+    int32_t mn = INT_MAX, mx = -1;
+    for (int64_t i = threadIdx.x; i < samples; i += 4 * (int64_t)blockDim.x) {
+        int32_t v[4];
+        sample4(i, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            mn = min(mn, v[k]);
+            mx = max(mx, v[k] == INT_MAX ? -1 : v[k]);
+        }
+    }
+    mn = wave_min(mn);
+    mx = -wave_min(-mx);
+    if (lane_id() == 0) {
+        atomicMin(&s_mn, mn);
+        atomicMax(&s_mx, mx);
+    }
+    __syncthreads();
+    mn = s_mn;
+    mx = s_mx;
+    for (int64_t i = threadIdx.x; i < samples; i += 4 * (int64_t)blockDim.x) {
+        int32_t v[4];
+        sample4(i, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (v[k] != INT_MAX) atomicAdd(&s_n[sel_bin((uint32_t)(v[k] - mn) + 1u)], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        // One wave: four bins a lane, their prefix sums, and the first bin
+        // past a target.
+        const int b0 = 4 * lane_id();
+        uint32_t cn[4];
+        float cw[4], lw = 0.f;  // summed support of a bin, from its middle
+        uint32_t ln = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int b = b0 + k;
+            cn[k] = s_n[b];
+            cw[k] = cn[k] ? (float)cn[k] * ((float)mn + 0.5f * (float)(sel_end(b - 1) + sel_end(b)) - 1.f)
+                          : 0.f;
+            ln += cn[k];
+            lw += cw[k];
+        }
+        const uint32_t in = wave_inclusive_sum<uint32_t>(ln);
+        const float iw = wave_inclusive_sum<float>(lw);
+        const float up = samples ? (float)n / (float)samples : 1.f;
+        const float rem = (float)wave_last(in) * up;
+        const float all = __shfl(iw, kWave - 1, kWave);
+        const int32_t np = ld(&J->n_parts), level = ld(&J->level);
+        const int64_t tn0 = ld(&J->target_n);
+        int64_t tw = ld(&J->target_w);
+        float scale = ld(&J->scale);
+        if (np == 0) {  // the job's whole support, from the sample
+            tw = (int64_t)(all * up * ((float)tn0 / (float)(n > 0 ? n : 1)));
+        } else {
+            // The last part took rem(then) - rem(now) edges; what it was
+            // expected to take, over that, tells how far to aim below.
+            const float took = ld(&J->rem_n) - rem, est = ld(&J->est_n);
+            if (took > 0.f && est > 0.f)
+                scale = fminf(1.f, fmaxf(0.05f, 0.5f * scale + 0.5f * est / took));
+        }
+        const float tn = (float)tn0 * scale, tws = (float)tw * scale;
+        int cut = kSelBins;  // this lane's first bin past a target
+        float an = (float)(in - ln) * up, aw = (iw - lw) * up;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float bn = (float)cn[k] * up, bw = cw[k] * up;
+            if (cut == kSelBins && cn[k] && an > 0.f && (an + bn > tn || aw + bw > tws))
+                cut = b0 + k;
+            an += bn;
+            aw += bw;
+        }
+        cut = wave_min(cut);
+        int last = -1;  // the last bin taken
+        uint32_t taken = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (b0 + k < cut && cn[k]) {
+                last = b0 + k;
+                taken += cn[k];
+            }
+        last = -wave_min(-last);
+        taken = wave_sum(taken);
+        if (lane_id() == 0) {
+            int64_t end = (int64_t)kLevelMax + 1;  // of the supports taken
+            if (np + 1 < kMaxParts && mn != INT_MAX) {
+                if (ld(&J->narrow)) {
+                    const int64_t top = min(ld(&J->hi_bound), mx);
+                    const int64_t width = (top - mn + 1) / 16;
+                    // Of single levels the gather finds the exact minimum: a
+                    // part at the old level takes nothing and jumps to it.
+                    end = width > 1 ? (int64_t)mn + width : (int64_t)level + 1;
+                } else if (cut < kSelBins) {
+                    end = (int64_t)mn + sel_end(last) - 1;
+                }
+            }
+            const int32_t hi = (int32_t)(end - 1 < kLevelMax ? end - 1 : kLevelMax);
+            const int32_t part = (int32_t)atomicAdd(&P.ctl->n_parts.v, 1ull);
+            st(&P.parts[part].hi, hi);
+            st(&P.parts[part].lo, (int32_t)INT_MAX);
+            st(&P.parts[part].job, g);
+            st(&P.parts[part].pad, 0);
+            st(&J->target_w, tw);
+            st(&J->scale, scale);
+            st(&J->est_n, (float)taken * up);
+            st(&J->rem_n, rem);
+            st(&J->n_parts, np + 1);
+            st(&J->level, hi);
+            st(&J->part, part);
+            st(&J->gather_round, r + 1);
+            st(&J->gmin[q], (int32_t)INT_MAX);
+            s_mn = part;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave)  // one wave writes the gather's items
+        put_gather(P, q, s_mn, e0, threadIdx.x == 0 ? (uint32_t)n : 0u);
+    __syncthreads();
+}
+
+// A gather item: remaining edges at or below the part's level become the next
+// frontier; the smallest support above it is kept for a jump, the smallest
+// taken as the part's lower bound.
+__device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int p,
+                                             const SweepGatherItem it) {
+    SweepCtl *C = P.ctl;
+    const int q = p ^ 1;
+    const int32_t level = ld(&P.parts[it.part].hi), job = ld(&P.parts[it.part].job);
+    int32_t ph[kGatherPerLane], sv[kGatherPerLane];
+#pragma unroll
+    for (int k = 0; k < kGatherPerLane; ++k) {
+        const uint32_t e = it.lo + k * kWave + lane_id();
+        ph[k] = 0;
+        sv[k] = INT_MAX;
+        if (e < it.hi) {
+            ph[k] = mark_part(ld(&P.mark[e].v));
+            sv[k] = ld(&P.sup[e]);
+        }
+    }
+    int32_t mn = INT_MAX, lowest = INT_MAX;
+    uint32_t take = 0;
+#pragma unroll
+    for (int k = 0; k < kGatherPerLane; ++k)
+        if (ph[k] < 0) {
+            if (sv[k] <= level) {
+                take |= 1u << k;
+                lowest = min(lowest, sv[k]);
+            } else {
+                mn = min(mn, sv[k]);
+            }
+        }
+    if (__ballot(take != 0)) {
+        uint32_t lo[kGatherPerLane], hi[kGatherPerLane], tot = 0;
+#pragma unroll
+        for (int k = 0; k < kGatherPerLane; ++k) {
+            const uint32_t e = it.lo + k * kWave + lane_id();
+            lo[k] = hi[k] = 0;
+            if ((take >> k) & 1u) {
+                lo[k] = (uint32_t)P.link_off[e];
+                hi[k] = (uint32_t)P.link_off[(int64_t)e + 1];
+            }
+            tot += chunks_of(lo[k], hi[k]);
+        }
+        u64 base[3];
+        wave_alloc3(tot, &C->nf[q].v, 0u, nullptr, 0u, nullptr, base);
+        const Slots S{0, 0, 0xffffffffu};
+        uint32_t at = (uint32_t)base[0];
+#pragma unroll
+        for (int k = 0; k < kGatherPerLane; ++k) {
+            const uint32_t cnt = chunks_of(lo[k], hi[k]);
+            put_fronts(P, P.front[q], S, (take >> k) & 1u, cnt, at,
+                       (int32_t)(it.lo + k * kWave + lane_id()), it.part, level, (int32_t)(r + 1), lo[k],
+                       hi[k]);
+            at += cnt;
+        }
+        lowest = wave_min(lowest);
+        if (lane_id() == 0) {
+            set_front_flag(P, job, q);
+            atomicMin(&P.parts[it.part].lo, lowest);
+        }
+    }
+    mn = wave_min(mn);
+    if (lane_id() == 0 && mn != INT_MAX) atomicMin(&P.js[job].gmin[p], mn);
+}
+
+// Work items of a phase per wave and step: one while there are fewer items
+// than waves, so that a small round spreads over the chip; up to 64, one a
+// lane, when there are more (most items hold a few links or wedges, which
+// the wave then spreads over its lanes).
+__device__ __forceinline__ uint32_t items_per_step(u64 n, int64_t nwaves) {
+    const u64 per = n / (u64)(4 * nwaves);
+    return per < 1 ? 1u : per > kWave ? (uint32_t)kWave : (uint32_t)per;
+}
+
+// Phase A: the frontier's wedges are killed; each kill counts in its bloom,
+// and the twin edge loses all of its butterflies in the bloom.  A wedge is
+// alive unless its twin was removed in an earlier round; where both edges are
+// in the frontier the smaller one kills it.  (A wedge that outlived its bloom
+// is killed for nothing: the bloom has no butterfly left to take.)  Bound by
+// random accesses: a link reads its twin's mark; a kill adds two atomics and
+// a byte, a bloom's first kill one read of its record.
+__device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int p, u64 nf,
+                                              u64 ngth, int64_t wid, int64_t nwaves, u64 *mask,
+                                              uint32_t &upd) {
+    SweepCtl *C = P.ctl;
+    const int q = p ^ 1;
+    const int32_t now = (int32_t)r;
+    const uint32_t per = items_per_step(nf, nwaves);
+    const uint32_t grow = per > 1 ? 2 * per : 0u;
+    Reserve rb, rf;
+    for (int64_t g0 = wid * per; g0 < (int64_t)nf; g0 += nwaves * per) {
+        const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)nf;
+        FrontItem it{0, 0, 0, 0};
+        int32_t level_l = 0;
+        if (ok) {
+            it = ld_item(&P.front[p][g0 + lane_id()]);
+            level_l = ld(&P.parts[it.part].hi);
+        }
+        const uint32_t n = ok ? it.hi - it.lo : 0u;
+        const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
+        const uint32_t start = inc - n;
+        const uint32_t total = wave_last(inc);
+        for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
+            const int src = per == 1 ? 0 : item_of(ok, start, t0, mask);
+            const uint32_t x = t0 + lane_id();
+            const bool has = x < total;
+            const uint32_t j = __shfl(it.lo - start, src, kWave) + x;
+            const int32_t e = __shfl(it.e, src, kWave), part = __shfl(it.part, src, kWave);
+            const int32_t level = __shfl(level_l, src, kWave);
+            uint3 lk = make_uint3(0, 0, kFixedBit);
+            int32_t tround = INT_MAX;
+            if (has) {
+                lk = P.link[j];
+                if (!(lk.z & kFixedBit)) tround = mark_round(ld(&P.mark[lk.z].v));
+            }
+            const bool tfix = (lk.z & kFixedBit) != 0;
+            const int32_t twin = (int32_t)(lk.z & kEdgeMask);
+            const bool kill = has && e >= 0 && tround >= now && !(tround == now && twin < e);
+            BloomRec *const B = &P.bloom[lk.y];
+            u64 old = 1;
+            if (kill) {
+                old = atomicAdd(&B->kc, (u64)1);
+                st(&P.dead[lk.x], (uint8_t)1);
+            }
+            const int32_t kb = (int32_t)(old >> 32), d = kb - 1;
+            const bool dec = kill && d > 0 && !tfix && tround != now;
+            // The first kill of the round queues the bloom; the first of the
+            // part records the bloom's number as the part finds it.
+            const bool first = kill && d > 0 && (uint32_t)old == 0;
+            int32_t otw = 0;
+            uint2 w01 = make_uint2(0, 0);
+            if (dec) otw = atomicSub(&P.sup[twin], d);
+            if (first) {
+                w01 = *reinterpret_cast<const uint2 *>(&B->w0);
+                if (ld(&B->part) != part) {
+                    st(&B->part, part);
+                    if (!P.plain) P.wedge_k[lk.x] = kb;
+                }
+            }
+            const bool tf = dec && otw > level && otw - d <= level;
+            if (__ballot(first || tf)) {
+                uint32_t tlo = 0, thi = 0;
+                if (tf) {
+                    tlo = (uint32_t)P.link_off[twin];
+                    thi = (uint32_t)P.link_off[(int64_t)twin + 1];
+                }
+                const uint32_t nch = (w01.y - w01.x + kWedgeChunk - 1) / kWedgeChunk;
+                const uint32_t tk = chunks_of(tlo, thi);
+                const uint32_t ib = wave_inclusive_sum<uint32_t>(nch);
+                const uint32_t jf = wave_inclusive_sum<uint32_t>(tk);
+                Slots sb, sf;
+                reserve2(rb, wave_last(ib), &C->ntc[p].v, rf, wave_last(jf), &C->nf[q].v, grow, sb,
+                         sf);
+                put_blooms(P.tc[p], sb, nch, ib - nch, (int32_t)lk.y);
+                put_fronts(P, P.front[q], sf, tf, tk, jf - tk, twin, part, level, now + 1, tlo, thi);
+                if (tf) set_front_flag(P, ld(&P.parts[part].job), q);
+            }
+            upd += dec ? 1 : 0;
+        }
+    }
+    fill_blooms(P.tc[p], rb);
+    fill_fronts(P.front[q], rf);
+    for (int64_t i = wid; i < (int64_t)ngth; i += nwaves)
+        sweep_gather(P, r, p, ld_item(&P.gth[p][i]));
+}
+
+// Phase B: the survivors of every touched bloom lose its kills; the last
+// chunk of a bloom to finish settles it.
+__device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int p, u64 ntc, int64_t wid,
+                                              int64_t nwaves, u64 *mask, uint32_t &upd,
+                                              uint32_t &visits, uint32_t &touch, uint32_t &unb) {
+    SweepCtl *C = P.ctl;
+    const int q = p ^ 1;
+    const uint32_t per = items_per_step(ntc, nwaves);
+    const uint32_t grow = per > 1 ? 2 * per : 0u;
+    Reserve rf;
+    for (int64_t g0 = wid * per; g0 < (int64_t)ntc; g0 += nwaves * per) {
+        const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)ntc;
+        int32_t b_l = -1, level_l = 0, part_l = 0, c_l = 0, k_l = 0;
+        uint32_t lo_l = P.n_w, n = ok ? 1u : 0u, nch = 0;
+        if (ok) {
+            const u64 item = ld(reinterpret_cast<const u64 *>(&P.tc[p][g0 + lane_id()]));
+            b_l = (int32_t)(uint32_t)item;
+            if (b_l >= 0) {
+                const BloomRec *B = &P.bloom[b_l];
+                const u64 kc = ld(&B->kc);
+                const uint2 w01 = *reinterpret_cast<const uint2 *>(&B->w0);
+                part_l = ld(&B->part);
+                c_l = (int32_t)(uint32_t)kc;
+                k_l = (int32_t)(kc >> 32);
+                lo_l = w01.x + (uint32_t)(item >> 32) * kWedgeChunk;
+                n = min(w01.y - lo_l, (uint32_t)kWedgeChunk);
+                nch = (w01.y - w01.x + kWedgeChunk - 1) / kWedgeChunk;
+                level_l = ld(&P.parts[part_l].hi);
+            }
+        }
+        const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
+        const uint32_t start = inc - n;
+        const uint32_t total = wave_last(inc);
+        for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
+            const int src = per == 1 ? 0 : item_of(ok, start, t0, mask);
+            const uint32_t x = t0 + lane_id();
+            const bool inr = x < total;
+            const uint32_t w = __shfl(lo_l - start, src, kWave) + x;
+            uint32_t ra = kFixedBit, rb = kFixedBit;
+            uint8_t gone = 1;
+            if (inr) {
+                ra = (uint32_t)P.wea[w];
+                rb = (uint32_t)P.web[w];
+                gone = ld(&P.dead[w]);
+            }
+            const int32_t part = __shfl(part_l, src, kWave);
+            const int32_t level = __shfl(level_l, src, kWave);
+            const int32_t c = __shfl(c_l, src, kWave), kn = __shfl(k_l, src, kWave) - c;
+            const bool live = kn > 0 && !gone;
+            const bool da = live && !(ra & kFixedBit), db = live && !(rb & kFixedBit);
+            const int32_t ea = (int32_t)(ra & kEdgeMask), eb = (int32_t)(rb & kEdgeMask);
+            bool f1 = false, f2 = false;
+            if (P.unit) {
+                // Ablation: one unit per kill; the step from level + 1 crosses.
+                for (int32_t t = 0; t < (live ? c : 0); ++t) {
+                    if (da) f1 |= atomicSub(&P.sup[ea], 1) == level + 1;
+                    if (db) f2 |= atomicSub(&P.sup[eb], 1) == level + 1;
+                }
+            } else {
+                int32_t o1 = 0, o2 = 0;
+                if (da) o1 = atomicSub(&P.sup[ea], c);
+                if (db) o2 = atomicSub(&P.sup[eb], c);
+                f1 = da && o1 > level && o1 - c <= level;
+                f2 = db && o2 > level && o2 - c <= level;
+            }
+            if (__ballot(f1 || f2)) {
+                uint32_t lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
+                if (f1) {
+                    lo1 = (uint32_t)P.link_off[ea];
+                    hi1 = (uint32_t)P.link_off[(int64_t)ea + 1];
+                }
+                if (f2) {
+                    lo2 = (uint32_t)P.link_off[eb];
+                    hi2 = (uint32_t)P.link_off[(int64_t)eb + 1];
+                }
+                const uint32_t k1 = chunks_of(lo1, hi1), k2 = chunks_of(lo2, hi2);
+                const uint32_t i1 = wave_inclusive_sum<uint32_t>(k1 + k2);
+                Slots sf, none;
+                Reserve no;
+                reserve2(rf, wave_last(i1), &C->nf[q].v, no, 0u, nullptr, grow, sf, none);
+                put_fronts(P, P.front[q], sf, f1, k1, i1 - k1 - k2, ea, part, level, (int32_t)(r + 1),
+                           lo1, hi1);
+                put_fronts(P, P.front[q], sf, f2, k2, i1 - k2, eb, part, level, (int32_t)(r + 1), lo2,
+                           hi2);
+                if (f1 || f2) set_front_flag(P, ld(&P.parts[part].job), q);
+            }
+            const int32_t each = P.unit ? c : 1;
+            upd += (uint32_t)((da ? each : 0) + (db ? each : 0));
+            if (!P.unit) unb += (uint32_t)((da ? c - 1 : 0) + (db ? c - 1 : 0));
+            touch += live ? 1 : 0;
+        }
+        // A chunk counts itself done once its reads of the bloom's counts
+        // have returned (they are used above), so the last one's update of
+        // both cannot overtake them.
+        if (b_l >= 0) {
+            const int32_t kn = k_l - c_l;
+            BloomRec *B = &P.bloom[b_l];
+            if (kn != INT_MIN && (nch == 1 || atomicAdd(&B->done, 1) == (int32_t)nch - 1)) {
+                st(&B->kc, (u64)(uint32_t)kn << 32);
+                if (nch > 1) st(&B->done, 0);
+                visits += 1;
+            }
+        }
+    }
+    fill_fronts(P.front[q], rf);
+}
+
+// Adds the lanes' statistics to the control block and clears them.
+__device__ __forceinline__ void sweep_flush(SweepCtl *C, uint32_t &upd, uint32_t &visits,
+                                            uint32_t &touch, uint32_t &unb) {
+    const u64 a = wave_sum<u64>(upd), b = wave_sum<u64>(visits), c = wave_sum<u64>(touch),
+              d = wave_sum<u64>(unb);
+    if (lane_id() == 0) {
+        if (a) atomicAdd(&C->updates.v, a);
+        if (b) atomicAdd(&C->bloom_visits.v, b);
+        if (c) atomicAdd(&C->touched.v, c);
+        if (d) atomicAdd(&C->unbatched.v, d);
+    }
+    upd = visits = touch = unb = 0;
+}
+
+__global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int64_t max_rounds,
+                                                   int prof) {
+    SweepCtl *C = P.ctl;
+    __shared__ u64 s_nf, s_ngth, s_nsel, s_ntc, s_left, s_r0;
+    __shared__ int s_ok, s_y;
+    __shared__ u64 s_mask[kPBlock / kWave];
+    __shared__ const int32_t *s_ys;
+    u64 gen_local = 0;
+    // Wave ids run across blocks first: a small round spreads over many CUs.
+    const int64_t wid = (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x;
+    const int64_t nwaves = (int64_t)gridDim.x * (kPBlock / kWave);
+    const int64_t tid = wid * kWave + lane_id();
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    uint32_t upd = 0, visits = 0, touch = 0, unb = 0;
+    if (threadIdx.x == 0) {
+        // A launch resumes at the round where the previous one yielded.
+        s_r0 = ld(&C->rounds);
+        s_left = ld(&C->left.v);
+        s_nf = ld(&C->nf[s_r0 & 1].v);
+        s_ngth = ld(&C->ngth[s_r0 & 1].v);
+        s_nsel = ld(&C->nsel[s_r0 & 1].v);
+        s_ys = reinterpret_cast<const int32_t *>(ld(&C->yield_src));
+        s_ok = 1;
+        s_y = 0;
+    }
+    if (lead) st(&C->yielded, 0);
+    __syncthreads();
+    int64_t r = (int64_t)s_r0;
+    for (; r < max_rounds && s_left > 0 && s_ok; ++r) {
+        const int p = (int)(r & 1), q = p ^ 1;
+        const u64 nf = s_nf, ngth = s_ngth, nsel = s_nsel;
+        u64 t0 = 0, t1 = 0, t2 = 0, t3 = 0, t4 = 0;
+        if (prof && lead) t0 = wall_clock64();
+        if (lead) st(&C->ntc[q].v, (u64)0);
+        sweep_decide(P, r, p, tid, nwaves * kWave);
+        // Selects take their blocks out of phase A (they are chains of waits
+        // behind its traffic), unless there are too many.
+        const u64 busy = nsel <= gridDim.x / 2 ? nsel : 0;
+        for (u64 i = blockIdx.x; i < nsel; i += gridDim.x)
+            sweep_select(P, ld(&P.sel[p][i]), r, q);
+        if (prof && lead) t1 = wall_clock64();
+        if (blockIdx.x >= busy)
+            sweep_phase_a(P, r, p, nf, ngth,
+                          (int64_t)(threadIdx.x / kWave) * (gridDim.x - busy) + blockIdx.x - busy,
+                          (int64_t)(gridDim.x - busy) * (kPBlock / kWave),
+                          &s_mask[threadIdx.x / kWave], upd);
+        if (prof && lead) t2 = wall_clock64();
+        drain_memory();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            s_ok = grid_arrive_wait(B, gen_local);
+            s_ntc = ld(&C->ntc[p].v);
+        }
+        __syncthreads();
+        if (!s_ok) break;
+        if (prof && lead) t3 = wall_clock64();
+        if (lead) {
+            st(&C->nf[p].v, (u64)0);
+            st(&C->ngth[p].v, (u64)0);
+            st(&C->nsel[p].v, (u64)0);
+        }
+        sweep_phase_b(P, r, p, s_ntc, wid, nwaves, &s_mask[threadIdx.x / kWave], upd, visits, touch,
+                      unb);
+        drain_memory();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            // Every kYieldEvery rounds the lead publishes the host's yield
+            // word before the barrier and every block reads it after, so all
+            // blocks stop after the same round.
+            const bool chk = s_ys && ((r + 1) % kYieldEvery) == 0;
+            if (chk && lead) {
+                st(&C->yield_req, __hip_atomic_load(s_ys, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_SYSTEM));
+                drain_memory();
+            }
+            s_ok = grid_arrive_wait(B, gen_local);
+            s_left = ld(&C->left.v);
+            s_nf = ld(&C->nf[q].v);
+            s_ngth = ld(&C->ngth[q].v);
+            s_nsel = ld(&C->nsel[q].v);
+            s_y = s_ok && chk && ld(&C->yield_req) != 0;
+        }
+        __syncthreads();
+        if (prof && lead) {
+            t4 = wall_clock64();
+            C->prof[0] += t1 - t0;
+            C->prof[1] += t2 - t1;
+            C->prof[2] += t3 - t2;
+            C->prof[4] += t4 - t3;
+        }
+        if ((r & 1023) == 1023) sweep_flush(C, upd, visits, touch, unb);  // 32-bit per lane
+        if (s_y) {
+            ++r;
+            if (lead && s_left > 0) st(&C->yielded, 1);
+            break;
+        }
+    }
+    sweep_flush(C, upd, visits, touch, unb);
+    if (lead) st(&C->rounds, (u64)r);
+}
+
+// The same rounds as two kernels each, replayed from a captured HIP graph or
+// launched directly (a job list that is done makes them empty).
+__global__ __launch_bounds__(kPBlock) void k_sweep_a(SweepArgs P, int p) {
+    SweepCtl *C = P.ctl;
+    __shared__ u64 s_r, s_nf, s_ngth, s_nsel, s_mask[kPBlock / kWave];
+    if (threadIdx.x == 0) {
+        s_r = ld(&C->rounds);
+        s_nf = ld(&C->nf[p].v);
+        s_ngth = ld(&C->ngth[p].v);
+        s_nsel = ld(&C->nsel[p].v);
+    }
+    __syncthreads();
+    const int q = p ^ 1;
+    const int64_t wid = (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x;
+    const int64_t nwaves = (int64_t)gridDim.x * (kPBlock / kWave);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st(&C->ntc[q].v, (u64)0);
+        st(&C->round_b, s_r);
+    }
+    sweep_decide(P, (int64_t)s_r, p, wid * kWave + lane_id(), nwaves * kWave);
+    for (u64 i = blockIdx.x; i < s_nsel; i += gridDim.x)
+        sweep_select(P, ld(&P.sel[p][i]), (int64_t)s_r, q);
+    uint32_t upd = 0, none = 0;
+    sweep_phase_a(P, (int64_t)s_r, p, s_nf, s_ngth, wid, nwaves, &s_mask[threadIdx.x / kWave], upd);
+    sweep_flush(C, upd, none, none, none);
+}
+
+__global__ __launch_bounds__(kPBlock) void k_sweep_b(SweepArgs P, int p) {
+    SweepCtl *C = P.ctl;
+    __shared__ u64 s_ntc, s_r, s_mask[kPBlock / kWave];
+    if (threadIdx.x == 0) {
+        s_ntc = ld(&C->ntc[p].v);
+        s_r = ld(&C->round_b);
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st(&C->nf[p].v, (u64)0);
+        st(&C->ngth[p].v, (u64)0);
+        st(&C->nsel[p].v, (u64)0);
+        // Phase B reads round_b, phase A rounds: each is set where the other
+        // kernel runs.
+        if (ld(&C->left.v) > 0) st(&C->rounds, s_r + 1);
+    }
+    uint32_t upd = 0, visits = 0, touch = 0, unb = 0;
+    sweep_phase_b(P, (int64_t)s_r, p, s_ntc, (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x,
+                  (int64_t)gridDim.x * (kPBlock / kWave), &s_mask[threadIdx.x / kWave], upd, visits,
+                  touch, unb);
+    sweep_flush(C, upd, visits, touch, unb);
+}
+
+// Edge and bloom state at a sweep's start.  Edges fixed by earlier passes
+// (progressive mode) are in no part and never taken: their support is out of
+// reach.
+__global__ void k_sweep_edges(const uint64_t *supl, int64_t m, const int32_t *fixed, int32_t *sup,
+                              EdgeMark *mark, int64_t *sup_out) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t v = (int32_t)(supl[e] & 0xffffffffu);
+        const bool fx = fixed && fixed[e];
+        sup[e] = fx ? INT_MAX : v;
+        mark[e].v = edge_mark(fx ? INT_MAX : -1, INT_MAX);
+        if (sup_out) sup_out[e] = v;
+    }
+}
+
+__global__ void k_put_byte(uint8_t *p, uint8_t v) { *p = v; }
+
+__global__ void k_sweep_blooms(const uint32_t *bwoff, const int32_t *bk, int64_t n, BloomRec *rec) {
+    for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < n;
+         b += (int64_t)gridDim.x * blockDim.x)
+        rec[b] = BloomRec{(u64)(uint32_t)bk[b] << 32, bwoff[b], bwoff[b + 1], -1, 0};
+}
+
+// Captured chunks of rounds, cached in the workspace by argument bytes.
+template <typename F>
+hipGraphExec_t chunk_graph(const void *args, size_t bytes, int rounds, Workspace &ws, F &&launch) {
+    const unsigned char *a = static_cast<const unsigned char *>(args);
+    std::vector<unsigned char> key(a, a + bytes);
+    auto &cache = ws.graphs;
+    for (auto &g : cache)
+        if (g.rounds == rounds && g.key == key) return g.exec;
+    if (cache.size() >= 16) {
+        (void)hipGraphExecDestroy(cache.front().exec);
+        cache.erase(cache.begin());
+    }
+    hipStream_t cs;
+    BT_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+    hipGraph_t g;
+    BT_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+    launch(cs);
+    BT_HIP(hipStreamEndCapture(cs, &g));
+    hipGraphExec_t ex;
+    BT_HIP(hipGraphInstantiate(&ex, g, nullptr, nullptr, 0));
+    (void)hipGraphDestroy(g);
+    (void)hipStreamDestroy(cs);
+    cache.push_back(Workspace::GraphEntry{key, rounds, ex});
+    return ex;
+}
+
+// Parts each job of n edges aims at in a sweep.
+int64_t parts_for(int64_t n, int64_t work, int64_t total) {
+    const int64_t cap = total >= (int64_t(1) << 20) ? 16 : 32;
+    return std::max<int64_t>(4, std::min<int64_t>(cap, std::max<int64_t>(n / 2048, work / 32768)));
+}
+
+// What a sweep is asked: supl holds the jobs' supports; progressive passes
+// carry fixed edges and a first level.
+struct SweepAsk {
+    const uint64_t *supl = nullptr;
+    const int32_t *fixed = nullptr;
+    int32_t min_level = 0;
+    bool unit = false, plain = false;
+    int64_t *sup_out = nullptr;
+};
+
+// State of a sweep over the jobs of a depth, ready for its first round by
+// `pblocks` workgroups.
+SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const SweepAsk &ask,
+                      int pblocks, const int32_t *yield_word, Workspace &ws, hipStream_t s) {
+    const int64_t m = ix.m;
+    const int32_t nj = (int32_t)jobs.size();
+    if (2 * ix.n_w >= (int64_t)UINT32_MAX)
+        throw Error{BT_EOVERFLOW, "edge-to-wedge links must be below 2^32"};
+    const int64_t nb = ix.n_b > 0 ? ix.n_b : 1;
+    // A phase's waves leave at most kReserve slots each; a round's frontier
+    // list takes those of two phases.
+    const int64_t spare = (int64_t)pblocks * (kPBlock / kWave) * kReserve;
+    const int64_t max_tc = nb + ix.n_w / kWedgeChunk + 1 + spare;
+    const int64_t max_front = m + 2 * ix.n_w / kLinkChunk + 1 + 2 * spare;
+    const int64_t max_gth = m / kGatherChunk + nj + 1;
+    const int64_t max_parts = ask.plain ? nj : (int64_t)nj * (kMaxParts + 1) + 1;
+    SweepArgs P{};
+    P.ctl = ws.get<SweepCtl>("sw_ctl", 1);
+    P.js = ws.get<JobState>("sw_jobs", nj);
+    P.n_jobs = nj;
+    P.parts = ws.get<SplitPart>("sw_parts", max_parts);
+    P.sup = ws.get<int32_t>("peel_sup", m);
+    P.mark = ws.get<EdgeMark>("sw_mark", m);
+    const int64_t dead_bytes = (ix.n_w + 4) & ~int64_t(3);
+    P.dead = ws.get<uint8_t>("sw_dead", dead_bytes);
+    P.bloom = ws.get<BloomRec>("sw_bloom", nb);
+    P.wedge_k = ask.plain ? nullptr : ws.get<int32_t>("sw_wedge_k", ix.n_w);
+    P.plain = ask.plain ? 1 : 0;
+    P.wea = ix.wea;
+    P.web = ix.web;
+    P.link_off = ix.link_off;
+    P.link = ix.link;
+    P.n_w = (uint32_t)ix.n_w;
+    P.unit = ask.unit ? 1 : 0;
+    P.front[0] = ws.get<FrontItem>("peel_front0", max_front);
+    P.front[1] = ws.get<FrontItem>("peel_front1", max_front);
+    P.tc[0] = ws.get<SweepBloomItem>("peel_tc0", max_tc);
+    P.tc[1] = ws.get<SweepBloomItem>("peel_tc1", max_tc);
+    P.gth[0] = ws.get<SweepGatherItem>("sw_gth0", max_gth);
+    P.gth[1] = ws.get<SweepGatherItem>("sw_gth1", max_gth);
+    P.sel[0] = ws.get<int32_t>("sw_sel0", nj);
+    P.sel[1] = ws.get<int32_t>("sw_sel1", nj);
+
+    k_sweep_edges<<<grid_for(m, 256, 16384), 256, 0, s>>>(ask.supl, m, ask.fixed, P.sup, P.mark,
+                                                         ask.sup_out);
+    BT_CHECK_LAUNCH();
+    if (ix.n_b > 0) {
+        k_sweep_blooms<<<grid_for(ix.n_b, 256, 16384), 256, 0, s>>>(ix.bwoff, ix.bk, ix.n_b, P.bloom);
+        BT_CHECK_LAUNCH();
+    }
+    zero_bytes(P.dead, (size_t)dead_bytes, s);
+    k_put_byte<<<1, 1, 0, s>>>(P.dead + ix.n_w, 1);  // the null items' wedge
+    BT_CHECK_LAUNCH();
+    if (ix.n_w && !ask.plain) zero_bytes(P.wedge_k, sizeof(int32_t) * ix.n_w, s);
+
+    std::vector<JobState> js((size_t)nj);
+    std::vector<SplitPart> first((size_t)nj);
+    // Progressive passes begin with a part at min_level: the edges outside the
+    // pass's bitruss, which need no numbers.
+    const bool preset = ask.min_level > 0 || ask.plain;
+    for (int32_t j = 0; j < nj; ++j) {
+        JobState &J = js[(size_t)j];
+        std::memset(&J, 0, sizeof J);
+        J.state = kJobActive;
+        J.e0 = jobs[(size_t)j].e0;
+        J.e1 = J.e0 + jobs[(size_t)j].ne;
+        J.gmin[0] = INT_MAX;
+        J.gmin[1] = preset ? ask.min_level : INT_MAX;
+        J.gather_round = preset ? -1 : -8;
+        J.select_round = -8;
+        J.level = -1;
+        J.part = j;
+        J.scale = 1.f;
+        J.narrow = jobs[(size_t)j].stuck ? 1 : 0;
+        J.hi_bound = jobs[(size_t)j].hi;
+        const int64_t n = jobs[(size_t)j].ne;
+        J.target_n = std::max<int64_t>(512, n / parts_for(n, jobs[(size_t)j].work, m));
+        first[(size_t)j] = SplitPart{ask.min_level, ask.min_level, j, 1};
+    }
+    BT_HIP(hipMemcpyAsync(P.js, js.data(), sizeof(JobState) * nj, hipMemcpyHostToDevice, s));
+    if (preset)
+        BT_HIP(hipMemcpyAsync(P.parts, first.data(), sizeof(SplitPart) * nj, hipMemcpyHostToDevice,
+                              s));
+    SweepCtl init{};
+    init.left.v = (u64)nj;
+    init.n_parts.v = preset ? (u64)nj : 0;
+    init.yield_src = reinterpret_cast<u64>(yield_word);
+    BT_HIP(hipMemcpyAsync(P.ctl, &init, sizeof init, hipMemcpyHostToDevice, s));
+    BT_HIP(hipStreamSynchronize(s));  // the host arrays are read until here
+    return P;
+}
+
+// One sweep over the jobs of a depth; `turn` is held.
+SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const SweepAsk &ask,
+                  const TuneParams &tp, CoopTurn *turn, PeelCounters &pc, Workspace &ws,
+                  hipStream_t s) {
+    const int64_t m = ix.m;
+    const int32_t nj = (int32_t)jobs.size();
+    int dev = 0, cus = 0, occ = 0;
+    BT_HIP(hipGetDevice(&dev));
+    BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_sweep, kPBlock, 0));
+    const int pblocks = !turn ? cus
+                        : tp.peel_blocks == 0 && m >= kAllCusEdges
+                            ? std::max(1, std::min(cus, occ * cus))
+                            : peel_grid(tp, cus, occ * cus);
+    // BT_PEEL_YIELD=1 makes every launch stop at its first check (a test of
+    // the resume path).
+    const char *yv = std::getenv("BT_PEEL_YIELD");
+    SweepArgs P = sweep_setup(ix, jobs, ask, pblocks,
+                              turn ? turn->yield_word(yv && std::atoi(yv) == 1) : nullptr, ws, s);
+    hipEvent_t ev0, ev1;
+    BT_HIP(hipEventCreate(&ev0));
+    BT_HIP(hipEventCreate(&ev1));
+    struct EvFree {
+        hipEvent_t a, b;
+        ~EvFree() {
+            (void)hipEventDestroy(a);
+            (void)hipEventDestroy(b);
+        }
+    } ev_free{ev0, ev1};
+    SweepCtl hc{};
+    const int64_t max_rounds = 8 * m + 1024;
+    const int prof = std::getenv("BT_PEEL_PROFILE") ? 1 : 0;
+    const bool verbose = std::getenv("BT_PEEL_VERBOSE") != nullptr;
+    float ms = 0.f;
+    if (turn) {
+        GridBar *bar = ws.get<GridBar>("peel_bar", 1);
+        void *args[] = {&P, &bar, (void *)&max_rounds, (void *)&prof};
+        for (;;) {
+            zero_bytes(bar, sizeof(GridBar), s);
+            BT_HIP(hipEventRecord(ev0, s));
+            BT_HIP(hipLaunchCooperativeKernel((const void *)k_sweep, dim3(pblocks), dim3(kPBlock),
+                                              args, 0, s));
+            BT_HIP(hipEventRecord(ev1, s));
+            int32_t fail = 0;
+            BT_HIP(hipMemcpyAsync(&hc, P.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
+            BT_HIP(hipMemcpyAsync(&fail, &bar->fail, sizeof fail, hipMemcpyDeviceToHost, s));
+            BT_HIP(hipStreamSynchronize(s));
+            float t = 0.f;
+            BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
+            ms += t;
+            if (fail) throw Error{BT_EDEVICE, "peel grid barrier timed out"};
+            if (hc.left.v == 0) break;
+            if (!hc.yielded) throw Error{BT_EDEVICE, "peel stopped early"};
+            // Each launch that yields has run at least one round.
+            if ((int64_t)hc.rounds >= max_rounds) throw Error{BT_EDEVICE, "peel made no progress"};
+            pc.yields += 1;
+            turn->requeue();
+        }
+    } else {
+        const char *gv = std::getenv("BT_PEEL_GRAPH");
+        const bool use_graph = !(gv && std::atoi(gv) == 0);
+        constexpr int kChunk = 32;
+        const auto rounds = [&](hipStream_t t) {
+            for (int k = 0; k < kChunk; ++k) {
+                k_sweep_a<<<cus, kPBlock, 0, t>>>(P, k & 1);
+                k_sweep_b<<<cus, kPBlock, 0, t>>>(P, k & 1);
+            }
+        };
+        hipGraphExec_t ex = nullptr;
+        if (use_graph) ex = chunk_graph(&P, sizeof P, kChunk, ws, rounds);
+        do {
+            BT_HIP(hipEventRecord(ev0, s));
+            if (use_graph) {
+                BT_HIP(hipGraphLaunch(ex, s));
+            } else {
+                rounds(s);
+                BT_CHECK_LAUNCH();
+            }
+            BT_HIP(hipEventRecord(ev1, s));
+            BT_HIP(hipMemcpyAsync(&hc, P.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
+            BT_HIP(hipStreamSynchronize(s));
+            float t = 0.f;
+            BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
+            ms += t;
+            if ((int64_t)hc.rounds >= max_rounds) throw Error{BT_EDEVICE, "peel made no progress"};
+        } while (hc.left.v != 0);
+    }
+    pc.kernel_ms += ms;
+    pc.rounds += (int64_t)hc.rounds;
+    pc.updates += (int64_t)hc.updates.v;
+    pc.updates_unbatched += (int64_t)(hc.updates.v + hc.unbatched.v);
+    pc.bloom_visits += (int64_t)hc.bloom_visits.v;
+    pc.touched += (int64_t)hc.touched.v;
+    if (verbose)
+        std::fprintf(stderr,
+                     "[peel] sweep: %d jobs, %lld edges, %lld blooms, %lld wedges: %.2f ms, %llu rounds, %llu parts, %.3g updates\n",
+                     nj, (long long)m, (long long)ix.n_b, (long long)ix.n_w, (double)ms, hc.rounds,
+                     hc.n_parts.v, (double)hc.updates.v);
+    if (prof)
+        std::fprintf(stderr, "[peel] block0 us: decide %.0f phaseA %.0f bar1 %.0f phaseB+bar2 %.0f\n",
+                     hc.prof[0] / 100.0, hc.prof[1] / 100.0, hc.prof[2] / 100.0, hc.prof[4] / 100.0);
+    return SweepResult{P.mark, P.wedge_k, P.parts, (int32_t)hc.n_parts.v};
+}
+
+__global__ void k_marks_out(const EdgeMark *mark, int64_t m, int64_t *out) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x)
+        out[e] = mark_part(mark[e].v);
+}
+
+__global__ void k_max_mark(const EdgeMark *mark, int64_t m, unsigned long long *out) {
+    unsigned long long v = 0;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = mark_part(mark[e].v);
+        if (p != INT_MAX) v = max(v, (unsigned long long)max(p, 0));  // not the fixed ones
+    }
+    for (int d = kWave / 2; d > 0; d >>= 1) v = max(v, (unsigned long long)__shfl_xor(v, d, kWave));
+    if (lane_id() == 0) atomicMax(out, v);
+}
+
+SplitIndex view_of(const IndexArrays &ix, int64_t m) {
+    SplitIndex v;
+    v.m = m;
+    v.n_b = ix.n_b;
+    v.n_w = ix.n_w;
+    v.bwoff = ix.bwoff;
+    v.bk = ix.bk;
+    v.wea = ix.wea;
+    v.web = ix.web;
+    v.wbl = ix.wbl;
+    v.link_off = ix.link_off;
+    v.link = ix.link;
+    return v;
+}
+
+__global__ void k_blooms_live(const BloomRec *rec, int64_t n, int32_t *out) {
+    for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < n;
+         b += (int64_t)gridDim.x * blockDim.x)
+        out[b] = (int32_t)(rec[b].kc >> 32);
+}
+
+}  // namespace
+
+// The peel level by level, one round at a time from the host: after each
+// round, the edges whose marks name it, the supports and the blooms' live
+// wedges.
+void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn &trace,
+                Workspace &ws, hipStream_t s) {
+    if (m == 0) return;
+    const std::vector<SplitJob> jobs{SplitJob{0, 0, (int32_t)m, 0, kLevelMax, 0, false}};
+    SweepAsk ask;
+    ask.supl = ix.supl;
+    ask.plain = true;
+    const int blocks = 64;
+    const SweepArgs P = sweep_setup(view_of(ix, m), jobs, ask, blocks, nullptr, ws, s);
+    int32_t *live = ws.get<int32_t>("trace_live", ix.n_b);
+    SweepCtl hc{};
+    std::vector<EdgeMark> mark((size_t)m);
+    for (int64_t r = 0;; ++r) {
+        if (r > 8 * m + 1024) throw Error{BT_EDEVICE, "peel made no progress"};
+        k_sweep_a<<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
+        k_sweep_b<<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
+        BT_CHECK_LAUNCH();
+        if (ix.n_b) k_blooms_live<<<grid_for(ix.n_b, 256, 4096), 256, 0, s>>>(P.bloom, ix.n_b, live);
+        BT_CHECK_LAUNCH();
+        BT_HIP(hipMemcpyAsync(&hc, P.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
+        BT_HIP(hipMemcpyAsync(mark.data(), P.mark, sizeof(EdgeMark) * m, hipMemcpyDeviceToHost, s));
+        BT_HIP(hipStreamSynchronize(s));
+        PeelTraceRound t;
+        for (int64_t e = 0; e < m; ++e)
+            if ((int32_t)(uint32_t)mark[(size_t)e].v == (int32_t)r) {
+                t.level = (int32_t)(mark[(size_t)e].v >> 32);
+                t.removed.push_back((int32_t)e);
+            }
+        if (!t.removed.empty()) {
+            t.sup.resize((size_t)m);
+            t.bloom_k.resize((size_t)ix.n_b);
+            BT_HIP(hipMemcpy(t.sup.data(), P.sup, sizeof(int32_t) * m, hipMemcpyDeviceToHost));
+            if (ix.n_b)
+                BT_HIP(hipMemcpy(t.bloom_k.data(), live, sizeof(int32_t) * ix.n_b,
+                                 hipMemcpyDeviceToHost));
+            trace(t);
+        }
+        if (hc.left.v == 0) break;
+    }
+    k_marks_out<<<grid_for(m, 256, 16384), 256, 0, s>>>(P.mark, m, phi_out);
+    BT_CHECK_LAUNCH();
+}
+
+int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bool plain) {
+    const int64_t spare = 256 * 16 * (int64_t)kReserve;  // one wave's, on a card of 256 CUs
+    // Sweep: edges, blooms, wedges, work lists.  The deeper sweeps' blooms
+    // are parts of the first's, at most one a wedge.
+    const int64_t nb = plain ? n_b : std::max(n_b, n_w);
+    int64_t t = 12 * m + 24 * nb + n_w + 32 * (m + n_w / 32 + 2 * spare) +
+                16 * (nb + n_w / 64 + spare) + 32 * (m / kGatherChunk + graphs) +
+                (128 + 8 + 16 * (plain ? 1 : kMaxParts + 1)) * graphs;
+    if (!plain) {
+        t += 4 * n_w;                                  // wedge_k
+        t += 44 * m + 4 * n_w + 12 * n_w;              // regroup: edges, parts, sort scratch
+        t += 2 * (12 * n_w + 8 * nb) + 24 * n_w + 24 * m;  // next depths, their links
+        t += 16 * n_w + 8 * nb + 16 * (m + n_w / 32) + 8 * (nb + n_w / 64) + 8 * m;  // leaves
+    }
+    t += 64 * 256 + 4096;
+    return t + t / 8;
+}
+
+void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
+                int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,
+                const PeelOptions *opt) {
+    const int32_t ng = (int32_t)off.size() - 1;
+    const int64_t m = off[(size_t)ng];
+    if (m == 0) return;
+    const bool unit = opt && opt->unit_updates;
+    const char *mv = std::getenv("BT_PEEL_MODE");
+    const bool coop = ws.coop && !(mv && std::strcmp(mv, "graph") == 0);
+    const bool verbose = std::getenv("BT_PEEL_VERBOSE") != nullptr;
+    std::vector<SplitJob> jobs;
+    for (int32_t g = 0; g < ng; ++g)
+        if (off[(size_t)g + 1] > off[(size_t)g])
+            jobs.push_back(SplitJob{0, (int32_t)off[(size_t)g],
+                                    (int32_t)(off[(size_t)g + 1] - off[(size_t)g]), g, kLevelMax,
+                                    (uint32_t)(ix.n_w * (off[(size_t)g + 1] - off[(size_t)g]) / m), false});
+    std::vector<int32_t> levels((size_t)ng, 0);
+    int32_t max_level = 0;
+    std::unique_ptr<CoopTurn> turn;
+    if (coop) turn.reset(new CoopTurn(m));
+    SplitIndex cur = view_of(ix, m);
+    SweepAsk ask;
+    ask.supl = ix.supl;
+    ask.fixed = opt ? opt->fixed : nullptr;
+    ask.min_level = opt ? opt->min_level : 0;
+    ask.unit = unit;
+    ask.plain = opt && opt->plain;
+    ask.sup_out = sup_out;
+    if (ask.plain) {
+        // Level by level, with the memory of the index alone.
+        const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);
+        k_marks_out<<<grid_for(m, 256, 16384), 256, 0, s>>>(sw.mark, m, phi_out);
+        BT_CHECK_LAUNCH();
+        unsigned long long *mx = ws.get<unsigned long long>("sp_max", 1);
+        zero_bytes(mx, sizeof *mx, s);
+        k_max_mark<<<grid_for(m, 256, 4096), 256, 0, s>>>(sw.mark, m, mx);
+        BT_CHECK_LAUNCH();
+        unsigned long long hmx = 0;
+        std::vector<JobState> js(jobs.size());
+        BT_HIP(hipMemcpyAsync(&hmx, mx, sizeof hmx, hipMemcpyDeviceToHost, s));
+        BT_HIP(hipMemcpyAsync(js.data(), ws.get<JobState>("sw_jobs", (int64_t)jobs.size()),
+                              sizeof(JobState) * js.size(), hipMemcpyDeviceToHost, s));
+        BT_HIP(hipStreamSynchronize(s));
+        pc.launches += 1 + pc.yields;
+        pc.max_phi = (int64_t)hmx;
+        for (const JobState &J : js) pc.levels = std::max<int64_t>(pc.levels, J.n_parts);
+        return;
+    }
+    LeafPool pool;
+    for (int depth = 0; !jobs.empty(); ++depth) {
+        const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);
+        // The links are not needed after the first sweep; their memory (24
+        // bytes a wedge) takes the leaves' wedges and blooms (20).
+        if (depth == 0) pool.place(ix.link, ix.n_w, m, ws);
+        Regrouped g;
+        regroup(cur, sw, jobs, depth, phi_out, levels, max_level, g, pool, ws, s);
+        if (verbose)
+            std::fprintf(stderr, "[peel] regrouped: %zu jobs (%lld edges, %lld wedges); %zu leaves (%lld edges, %lld wedges) in all\n",
+                         g.jobs.size(), (long long)g.m, (long long)g.n_w, pool.leaves.size(),
+                         (long long)pool.m, (long long)pool.n_w);
+        jobs = g.jobs;
+        if (jobs.empty()) break;
+        uint64_t *supl2 = ws.get<uint64_t>("sp_supl", g.m + 1);
+        int64_t *loff2 = ws.get<int64_t>("sp_loff", g.m + 1);
+        uint3 *link2 = ws.get<uint3>("sp_link", 2 * g.n_w + 1);
+        regroup_links(g, supl2, loff2, link2, ws, s);
+        cur.m = g.m;
+        cur.n_b = g.n_b;
+        cur.n_w = g.n_w;
+        cur.bwoff = g.bwoff;
+        cur.bk = g.bk;
+        cur.wea = g.wea;
+        cur.web = g.web;
+        cur.wbl = g.wbl;
+        cur.link_off = loff2;
+        cur.link = link2;
+        cur.oid = g.oid;
+        ask.supl = supl2;
+        ask.fixed = nullptr;
+        ask.min_level = 0;
+        ask.sup_out = nullptr;
+    }
+    // All leaves at the end, side by side.
+    if (!pool.leaves.empty()) peel_leaf_jobs(pool, phi_out, unit, levels, max_level, pc, ws, s);
+    pc.launches += 1 + pc.yields;
+    pc.max_phi = max_level;
+    for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);
+}
+
+}  // namespace bt

@@ -28,7 +28,7 @@ struct TuneParams {
     int32_t dense_chunk = 6144;    // counter range of a dense task (hub start vertices)
     int32_t wedge_wg_per_cu = 2;   // wedge-sweep workgroups per CU
     int32_t peel_blocks = 0;       // persistent peel workgroups (0: three per four CUs)
-    int32_t active_min = 16384;    // smallest active set the peel rebuilds
+    int32_t active_min = 16384;    // without effect; kept for saved files
 };
 constexpr int32_t kHashMaxWorkLimit = 2048;  // hash tables hold at most 4096 slots
 constexpr int32_t kDenseChunkLimit = 6144;   // dense counters per workgroup in LDS
@@ -138,8 +138,7 @@ void count_support(const RankCSR &r, const TaskLists &t, uint64_t *supl, int64_t
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
                  hipStream_t s, const Components *comps = nullptr);
 
-// Peel through the index.  sup_out (int64, nullable) receives the initial
-// supports, phi_out (int64) the bitruss numbers.
+// Counters of a peel.
 struct PeelCounters {
     int64_t levels = 0, rounds = 0, max_phi = 0, updates = 0, bloom_visits = 0;
     int64_t updates_unbatched = 0;  // the same peel without batch bloom processing
@@ -157,11 +156,6 @@ struct PeelTraceRound {
     std::vector<int32_t> bloom_k;
 };
 using PeelTraceFn = std::function<void(const PeelTraceRound &)>;
-// Progressive mode (Section V-C): `fixed` (per edge, nullable) marks edges
-// whose bitruss numbers an earlier pass fixed; the index must carry their
-// marks (mark_fixed).  The first level is at least `min_level`.
-// `trace` (nullable): run the rounds one at a time from the host and report
-// each (small graphs; for inspection and tests).
 // The weight of this thread's later turns on the device for cooperative
 // peels (w < 0: each peel's edge count).  A waiting peel that weighs under
 // 1/8 of the running one makes it yield between two rounds.  The serving
@@ -169,22 +163,33 @@ using PeelTraceFn = std::function<void(const PeelTraceRound &)>;
 // always takes the device from a running one of a larger class.
 void set_turn_weight(int64_t w);
 
+// Progressive mode (Section V-C): `fixed` (per edge, nullable) marks edges
+// whose bitruss numbers an earlier pass fixed; the index must carry their
+// marks (mark_fixed).  The first level is at least `min_level`.
 struct PeelOptions {
     const int32_t *fixed = nullptr;
     int32_t min_level = 0;
     bool unit_updates = false;  // ablation: no batch bloom processing
-    const PeelTraceFn *trace = nullptr;
+    bool plain = false;  // level by level, without the memory that splitting takes
 };
-void peel(const RankCSR &r, IndexArrays &ix, int64_t *sup_out, int64_t *phi_out,
-          PeelCounters &pc, Workspace &ws, hipStream_t s, const PeelOptions *opt = nullptr);
+// The peel level by level, each round that removes edges reported (small
+// graphs; for inspection and tests).
+void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn &trace,
+                Workspace &ws, hipStream_t s);
 
-// Peel of a disjoint union of graphs (edge ranges [off[g], off[g+1])) in
-// which every graph advances at its own level (one cooperative kernel).
-void peel_multi(const RankCSR &r, IndexArrays &ix, int64_t *sup_out, int64_t *phi_out,
-                const std::vector<int64_t> &off, PeelCounters &pc, Workspace &ws, hipStream_t s);
+// The peel of one graph or of a union of graphs (edge ranges [off[g],
+// off[g+1])): split into ranges of bitruss numbers by grid-wide sweeps, the
+// ranges then finished by themselves.
+// Device bytes it allocates, an upper bound with the workspace's growth slack.
+int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bool plain);
+void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
+                int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,
+                const PeelOptions *opt = nullptr);
 
 // Graphs with fewer edges than this peel in one workgroup each (peel_leaf).
 constexpr int64_t kLeafEdges = int64_t(1) << 14;
+// A part of a larger graph may have up to this many (what fits LDS).
+constexpr int64_t kLeafCap = 28672;
 struct LeafJob {
     int32_t e0, ne;       // edges [e0, e0 + ne)
     uint32_t w0, nw;      // wedges [w0, w0 + nw)
@@ -222,16 +227,13 @@ TuneParams autotune(const bt_csr *gs, int32_t n, uint32_t what, Workspace &ws, h
 // Device time of the index build alone (priority order, sweeps, links).
 float index_build_ms(const bt_csr &g, Workspace &ws, hipStream_t stream);
 // Called when a batch that forms a single union has its index built: the
-// bytes the workspace holds now, and at most how many the peel still adds.
-using SizedHook = std::function<void(int64_t held, int64_t peel_bytes)>;
+// bytes the workspace holds now, and at most how many the peel still adds, in
+// the form that needs the least and in the form that splits.  Returns whether
+// the latter may be used.
+using SizedHook = std::function<bool(int64_t held, int64_t least, int64_t split)>;
 void decompose_batch_impl(const bt_csr *gs, int32_t n, int64_t *const *sup_out,
                           int64_t *const *phi_out, bt_stats *stats, Workspace &ws,
                           hipStream_t s, const SizedHook *on_sized = nullptr);
-// Device bytes of peel state for a graph (or union of `graphs` graphs) with
-// m edges and an index of n_b blooms and n_w wedges, for the per-graph-level
-// peel (multi) or the shared-level one; an upper bound, workspace growth
-// slack included.
-int64_t peel_state_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bool multi);
 // BiT-PC steps (pc.hip).  A pass's subgraph G_{>=eps}: the edges of g with
 // support >= eps in g, in g's order; orig maps them back, fixed marks those
 // whose bitruss numbers earlier passes fixed, open counts the others.

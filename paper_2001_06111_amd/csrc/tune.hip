@@ -263,16 +263,14 @@ TuneParams autotune(const bt_csr *gs, int32_t n, uint32_t what, Workspace &ws, h
     }
     if (what & BT_TUNE_PEEL) {
         knobs.push_back({&TuneParams::peel_blocks, {cus / 2, 0, cus}, true});
-        knobs.push_back({&TuneParams::active_min, {4096, 16384, 65536}, true});
     }
     static const char *const names[] = {"hash_max_work", "dense_chunk", "wedge_wg_per_cu",
-                                        "peel_blocks", "active_min"};
+                                        "peel_blocks"};
     auto name_of = [&](int32_t TuneParams::*f) {
         if (f == &TuneParams::hash_max_work) return names[0];
         if (f == &TuneParams::dense_chunk) return names[1];
         if (f == &TuneParams::wedge_wg_per_cu) return names[2];
-        if (f == &TuneParams::peel_blocks) return names[3];
-        return names[4];
+        return names[3];
     };
     const bool verbose = std::getenv("BT_TUNE_VERBOSE") != nullptr;
     TuneParams cur = tune_params(batch, mt);

@@ -1,0 +1,68 @@
+"""The peel that splits graphs of 2^14 edges and more into ranges of bitruss
+numbers, at its edges: graphs around the sizes that one workgroup takes
+(2^14 edges whole, 28,672 as a part), dense cores that no level splits,
+unions whose graphs differ in size and in depth, the level-by-level form and
+the two-kernel rounds.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2001_06111_amd import binding, synth
+from tests import graphs
+from tests.gpu_util import oracle_all, upload
+
+pytestmark = pytest.mark.gpu
+MODES = [None, "plain", "graph"]
+
+
+def _cl(m, seed=0):
+    return synth.chung_lu(max(20, m // 20), max(30, m // 12), m, 2.2, 2.2, m / 4, m / 4, m + seed)
+
+
+def _set(monkeypatch, mode):
+    if mode:
+        monkeypatch.setenv("BT_PEEL_MODE", mode)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("m", [1, 65, 16384, 28671, 28672, 28673, 60000, 150001])
+def test_sizes(m, mode, monkeypatch):
+    g = _cl(m) if m > 65 else synth.uniform(20, 30, m, m)
+    osup, obf, ophi = oracle_all(g)
+    _set(monkeypatch, mode)
+    sup, phi, st = binding.bt_decompose(upload(g), stats=True)
+    assert np.array_equal(sup.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+    assert st["butterflies"] == obf and st["max_phi"] == int(ophi.max())
+    assert st["levels"] == np.unique(ophi).size
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("g", [synth.complete(160, 180), synth.complete(2, 20000),
+                               synth.complete(128, 129),
+                               graphs.random_dense(220, 210, 0.8, 5),
+                               graphs.random_dense(3000, 12, 0.9, 6),
+                               graphs.disjoint_union(_cl(30000), synth.complete(170, 170))],
+                         ids=lambda g: g.name)
+def test_dense(g, mode, monkeypatch):
+    osup, _, ophi = oracle_all(g)
+    _set(monkeypatch, mode)
+    for variant in (binding.BT_PEEL_BATCH_BLOOM, binding.BT_PEEL_BATCH_EDGE):
+        sup, phi, _ = binding.bt_decompose_variant(upload(g), variant)
+        assert np.array_equal(sup.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+    _, phi, _ = binding.bt_decompose_pc(upload(g), tau=0.3)
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("union", ["0", "1"])
+def test_union_of_mixed_sizes(mode, union, monkeypatch):
+    gs = [_cl(m, i) for i, m in enumerate((90000, 16384, 28672, 28673, 17000, 50000))]
+    gs += [graphs.random_dense(220, 210, 0.8, 5), graphs.star(20000), synth.complete(3, 9000)]
+    if mode:  # the sweeps then take small graphs as well
+        gs += [synth.from_edges(3, 3, []), synth.uniform(20, 30, 64, 1), _cl(300)]
+    _set(monkeypatch, mode)
+    if union == "1":
+        monkeypatch.setenv("BT_BATCH_PEEL", "union")
+    sups, phis, _ = binding.bt_decompose_batch([upload(g) for g in gs])
+    for g, s, p in zip(gs, sups, phis):
+        osup, _, ophi = oracle_all(g)
+        assert np.array_equal(s.cpu().numpy(), osup) and np.array_equal(p.cpu().numpy(), ophi)
