@@ -316,15 +316,13 @@ static void decompose_pc_once(const bt_csr &g, double tau, int64_t *sup_out, int
     Events ev(stats != nullptr, s);
     ev.mark(0);
     RankCSR r;
-    prepare(g, r, ws, s);
-    TaskLists t;
-    make_tasks(r, t, ws, s);
+    prepare(g, r, ws, s, nullptr, true);
     ev.mark(1);
     uint64_t *supl = ws.get<uint64_t>("pc_supl", m + 1);
     int64_t *bf = ws.get<int64_t>("pc_bf", 2);
     zero_bytes(supl, sizeof(uint64_t) * (m + 1), s);
     zero_bytes(bf, sizeof(int64_t) * 2, s);
-    count_support(r, t, supl, bf, s);
+    r.wedges_po = count_support(r, supl, bf, ws, s);
     check_butterfly_total(supl, m, bf, ws, s);
     if (sup_out && m) supl_to_sup(supl, sup_out, m, s);
     int32_t *sup0 = ws.get<int32_t>("pc_sup0", m);
@@ -877,14 +875,12 @@ bt_status bt_support(const bt_csr *g, int64_t *sup_out, int64_t *butterflies_out
         std::lock_guard<std::mutex> lk(lib().mu);
         Workspace &ws = lib().ws;
         RankCSR r;
-        prepare(*g, r, ws, stream);
-        TaskLists t;
-        make_tasks(r, t, ws, stream);
+        prepare(*g, r, ws, stream, nullptr, true);
         uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 1);
         int64_t *bf = ws.get<int64_t>("sup_bf", 2);
         zero_bytes(supl, sizeof(uint64_t) * (g->m + 1), stream);
         zero_bytes(bf, sizeof(int64_t) * 2, stream);
-        count_support(r, t, supl, bf, stream);
+        count_support(r, supl, bf, ws, stream);
         check_butterfly_total(supl, g->m, bf, ws, stream);
         supl_to_sup(supl, sup_out, g->m, stream);
         int64_t *hs = ws.host(2);

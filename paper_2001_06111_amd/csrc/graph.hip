@@ -161,15 +161,23 @@ __global__ void k_low(const int64_t *off, const int32_t *adj, const int32_t *deg
     }
 }
 
-// rev for prefix entries (x -> y): position of x in row y.
+// rev for prefix entries (x -> y): position of x in row y.  zlen (nullable)
+// for all entries: the entries of row y above both x and y, and rst.
 __global__ void k_rev(const uint64_t *keys, int64_t n2, int nb, const int64_t *off,
-                      const int32_t *adj, const int32_t *low, int32_t *rev) {
+                      const int32_t *adj, const int32_t *low, int32_t *rev, int32_t *zlen,
+                      uint32_t *rst) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n2;
          j += (int64_t)gridDim.x * blockDim.x) {
         const int32_t x = (int32_t)(keys[j] >> nb);
         int32_t r = 0;
-        if (j - off[x] < low[x]) {
-            const int32_t y = adj[j];
+        const int32_t y = adj[j];
+        const bool down = j - off[x] < low[x];
+        if (!down) {
+            if (zlen) {
+                zlen[j] = (int32_t)(off[y + 1] - off[y]) - low[y];
+                rst[j] = (uint32_t)off[y] + low[y];
+            }
+        } else {
             int64_t lo = off[y], hi = off[y + 1];
             while (lo < hi) {
                 const int64_t mid = lo + (hi - lo) / 2;
@@ -177,6 +185,10 @@ __global__ void k_rev(const uint64_t *keys, int64_t n2, int nb, const int64_t *o
                 else hi = mid;
             }
             r = (int32_t)(lo - off[y]);
+            if (zlen) {
+                zlen[j] = (int32_t)(off[y + 1] - lo) - 1;
+                rst[j] = (uint32_t)off[y];
+            }
         }
         rev[j] = r;
     }
@@ -206,7 +218,7 @@ void validate_graph(const bt_csr &g, Workspace &ws, hipStream_t s) {
 }
 
 void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
-             const Components *comps) {
+             const Components *comps, bool up) {
     const int32_t nu = g.n_upper, nl = g.n_lower;
     const int64_t m = g.m;
     const int64_t n = (int64_t)nu + nl;
@@ -272,6 +284,9 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     r.rev = ws.get<int32_t>("rank_rev", n2);
     r.low = ws.get<int32_t>("rank_low", n);
     r.wpre = ws.get<int64_t>("rank_wpre", n2 + 1);
+    r.zlen = up ? ws.get<int32_t>("rank_zlen", n2) : nullptr;
+    r.rst = up ? ws.get<uint32_t>("rank_rst", n2) : nullptr;
+    r.zpre = up ? ws.get<int64_t>("rank_zpre", n2 + 1) : nullptr;
     if (m > 0) {
         k_entries<<<grid_for((int64_t)nu * kWave, kBlock, 16384), kBlock, 0, s>>>(
             g.row_ptr, g.col, nu, nl, old2new, nb, ekeys, evals);
@@ -288,10 +303,11 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     }
     if (m > 0) {
         k_rev<<<grid_for(n2, 256, 16384), 256, 0, s>>>(ekeys, n2, nb, r.off, r.adj, r.low,
-                                                       r.rev);
+                                                       r.rev, r.zlen, r.rst);
         BT_CHECK_LAUNCH();
     }
     scan_exclusive_i32_to_i64(r.rev, r.wpre, n2, ws, s);
+    if (up) scan_exclusive_i32_to_i64(r.zlen, r.zpre, n2, ws, s);
 }
 
 // ------------------------------------------------------------- tasks

@@ -65,14 +65,12 @@ extern "C" bt_status bt_support_noalloc(const bt_csr *g, int64_t *sup_out,
         Workspace &ws = D.ws;
         ws.use_arena(D.ptr, kScratchBytes, D.host, kHostWords);
         RankCSR r;
-        prepare(*g, r, ws, stream);
-        TaskLists t;
-        make_tasks(r, t, ws, stream);
+        prepare(*g, r, ws, stream, nullptr, true);
         uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 1);
         int64_t *bf = ws.get<int64_t>("sup_bf", 2);
         zero_bytes(supl, sizeof(uint64_t) * (g->m + 1), stream);
         zero_bytes(bf, sizeof(int64_t) * 2, stream);
-        count_support(r, t, supl, bf, stream);
+        count_support(r, supl, bf, ws, stream);
         check_butterfly_total(supl, g->m, bf, ws, stream);
         supl_to_sup(supl, sup_out, g->m, stream);
         int64_t *hs = ws.host(2);

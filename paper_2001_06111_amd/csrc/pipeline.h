@@ -62,6 +62,13 @@ struct RankCSR {
     int32_t *rev = nullptr;   // [2m] z-prefix length for prefix entries, else 0
     int32_t *low = nullptr;   // [n]
     int64_t *wpre = nullptr;  // [2m + 1] exclusive prefix of rev: wedge work
+    // Support counting alone, by entry (s -> y): how many entries of row y are
+    // above both s and y (a suffix of the row), their prefix, and in the
+    // adjacency the start of row y (y below s: the suffix then starts rev + 1
+    // later) or of that suffix (y above s).
+    int32_t *zlen = nullptr;  // [2m]
+    uint32_t *rst = nullptr;  // [2m]
+    int64_t *zpre = nullptr;  // [2m + 1]
     int64_t wedges_po = 0;    // priority-obeyed wedges (host copy)
     int32_t max_deg = 0;
     // Unions only: the first rank of x's graph in x's layer (end vertices of
@@ -119,17 +126,18 @@ int64_t bitruss_components(const bt_csr &g, const int64_t *phi, int64_t k, int32
 // Throws Error{BT_EINVAL} for malformed input.
 // `comps` (nullable): g is a disjoint union of these graphs; the rank order
 // then puts each graph's vertices together within a layer (the order
-// restricted to a graph is unchanged).
+// restricted to a graph is unchanged).  `up`: fills zlen, zpre and rst.
 void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
-             const Components *comps = nullptr);
+             const Components *comps = nullptr, bool up = false);
 
 // Splits start vertices into wedge tasks (sync point: reads counts).
 void make_tasks(const RankCSR &r, TaskLists &t, Workspace &ws, hipStream_t s);
 
-// Support only: sup_out[e] (int64, may be null) and the butterfly total
-// (device scalar *bf, must be zeroed by the caller).
-void count_support(const RankCSR &r, const TaskLists &t, uint64_t *supl, int64_t *bf,
-                   hipStream_t s);
+// Support only (support.hip; r prepared with `up`): supl[e] and the butterfly
+// total *bf, device memory that the caller has zeroed; the number of
+// priority-obeyed wedges.
+int64_t count_support(const RankCSR &r, uint64_t *supl, int64_t *bf, Workspace &ws,
+                      hipStream_t s);
 
 // Counting plus index emission into `ix` (arrays sized by the caller from
 // r.wedges_po).  Fills supl and cursor; then builds the link lists.  With

@@ -1,5 +1,5 @@
-// wedge.hip - priority-obeyed wedge sweeps: support counting and BE-Index
-// emission (Algorithm 3; Lemmas 1-3 and 7).
+// wedge.hip - priority-obeyed wedge sweeps that emit the BE-Index, supports
+// included (Algorithm 3; Lemmas 1-3 and 7).
 //
 // A task is a start vertex x (or, for heavy x, one range of end vertices z).
 // Its workgroup walks every wedge (x, y, z) with p(y), p(z) < p(x) twice:
@@ -8,8 +8,8 @@
 //          priority-obeyed bloom anchored by x and z when c[z] >= 2;
 //   emit:  each wedge of a bloom (c >= 2) is one twin pair {(x,y), (y,z)};
 //          both edges lie in c - 1 butterflies of that bloom (Lemma 2), so
-//          their supports grow by c - 1 (exact by Lemma 3), and in index
-//          mode the pair is written as a wedge record of the bloom.
+//          their supports grow by c - 1 (exact by Lemma 3), and the pair is
+//          written as a wedge record of the bloom.
 // Supports and link counts share one 64-bit word per edge,
 // (links << 32) | support, so one atomic adds both; a support is below
 // m < 2^31, so the halves never carry into each other.
@@ -34,7 +34,6 @@ struct WedgeArgs {
     uint64_t *supl;
     int64_t *bf;
     int64_t *queue;  // dynamic task counter
-    // index mode
     uint64_t *cursor;       // of the whole index, or of each graph (vgraph)
     const int32_t *vgraph;  // nullable: the graph of each start vertex
     uint32_t *bwoff;
@@ -115,7 +114,7 @@ __device__ __forceinline__ int slot_find(int32_t z, const int32_t *keys, int32_t
 }
 
 // One pass over the task's wedges.  PASS 0 counts, PASS 1 emits.
-template <bool DENSE, bool INDEX, int PASS>
+template <bool DENSE, int PASS>
 __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *v0,
                            uint32_t *v1, int32_t mask, int32_t x, int32_t zlo, int32_t zhi,
                            uint32_t wbase) {
@@ -155,22 +154,16 @@ __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *
             } else {
                 const int sl = slot_find<DENSE>(z, keys, mask, zlo);
                 const int32_t b = v0[sl];
-                if (INDEX) {
-                    if (b >= 0) {
-                        const uint32_t pos = atomicAdd(&v1[sl], 1u);
-                        const int64_t w = (int64_t)wbase + pos;
-                        const int32_t c = A.bk[b];
-                        const int32_t ezy = A.eid[t];
-                        A.wea[w] = S.exy[jj];
-                        A.web[w] = ezy;
-                        A.wbl[w] = b;
-                        const uint64_t add = (uint64_t(1) << 32) | (uint32_t)(c - 1);
-                        atomicAdd((unsigned long long *)&A.supl[ezy], (unsigned long long)add);
-                        atomicAdd((unsigned long long *)&S.acc[jj], (unsigned long long)add);
-                    }
-                } else if (b >= 2) {
-                    const uint64_t add = (uint32_t)(b - 1);
-                    atomicAdd((unsigned long long *)&A.supl[A.eid[t]], (unsigned long long)add);
+                if (b >= 0) {
+                    const uint32_t pos = atomicAdd(&v1[sl], 1u);
+                    const int64_t w = (int64_t)wbase + pos;
+                    const int32_t c = A.bk[b];
+                    const int32_t ezy = A.eid[t];
+                    A.wea[w] = S.exy[jj];
+                    A.web[w] = ezy;
+                    A.wbl[w] = b;
+                    const uint64_t add = (uint64_t(1) << 32) | (uint32_t)(c - 1);
+                    atomicAdd((unsigned long long *)&A.supl[ezy], (unsigned long long)add);
                     atomicAdd((unsigned long long *)&S.acc[jj], (unsigned long long)add);
                 }
             }
@@ -182,7 +175,7 @@ __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *
     }
 }
 
-template <bool DENSE, bool INDEX>
+template <bool DENSE>
 __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tasks,
                                                int64_t ntasks) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -206,7 +199,7 @@ __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tas
         }
         __syncthreads();
 
-        wedge_pass<DENSE, INDEX, 0>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, 0);
+        wedge_pass<DENSE, 0>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, 0);
 
         // Sweep 1: blooms, their wedges and butterflies in this task.
         int64_t nb = 0, nw = 0, bfl = 0;
@@ -232,7 +225,7 @@ __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tas
         if (tid == 0) {
             if (S.totals[2]) atomicAdd((unsigned long long *)A.bf, (unsigned long long)S.totals[2]);
             S.base = 0;
-            if (INDEX && S.totals[0])
+            if (S.totals[0])
                 S.base = atomicAdd((unsigned long long *)A.cursor + (A.vgraph ? A.vgraph[T.x] : 0),
                                    ((unsigned long long)S.totals[0] << 32) |
                                        (unsigned long long)S.totals[1]);
@@ -242,35 +235,33 @@ __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tas
         const uint32_t bbase = (uint32_t)(S.base >> 32);
         const uint32_t wbase = (uint32_t)(S.base & 0xffffffffu);
 
-        if (INDEX) {
-            // Sweep 2: number blooms and lay out their wedge ranges in slot
-            // order; blooms and wedges share one allocation order, so bloom
-            // b's range ends where bloom b + 1's begins.
-            uint64_t carry = 0;
-            for (int s0 = 0; s0 < cap; s0 += kWG) {
-                const int s = s0 + tid;
-                const bool valid = s < cap && (DENSE || keys[s] != kEmpty);
-                const int32_t c = valid ? v0[s] : 0;
-                const bool isb = c >= 2;
-                const uint64_t mine = isb ? ((uint64_t(1) << 32) | (uint32_t)c) : 0;
-                uint64_t tot;
-                const uint64_t pre = block_exclusive_sum<uint64_t>(mine, S.scr2, &tot) + carry;
-                if (isb) {
-                    const int32_t b = (int32_t)(bbase + (uint32_t)(pre >> 32));
-                    const uint32_t lw = (uint32_t)(pre & 0xffffffffu);
-                    A.bk[b] = c;
-                    A.bwoff[b] = wbase + lw;
-                    v0[s] = b;
-                    v1[s] = lw;
-                } else if (valid) {
-                    v0[s] = kEmpty;
-                }
-                carry += tot;
+        // Sweep 2: number blooms and lay out their wedge ranges in slot
+        // order; blooms and wedges share one allocation order, so bloom
+        // b's range ends where bloom b + 1's begins.
+        uint64_t carry = 0;
+        for (int s0 = 0; s0 < cap; s0 += kWG) {
+            const int s = s0 + tid;
+            const bool valid = s < cap && (DENSE || keys[s] != kEmpty);
+            const int32_t c = valid ? v0[s] : 0;
+            const bool isb = c >= 2;
+            const uint64_t mine = isb ? ((uint64_t(1) << 32) | (uint32_t)c) : 0;
+            uint64_t tot;
+            const uint64_t pre = block_exclusive_sum<uint64_t>(mine, S.scr2, &tot) + carry;
+            if (isb) {
+                const int32_t b = (int32_t)(bbase + (uint32_t)(pre >> 32));
+                const uint32_t lw = (uint32_t)(pre & 0xffffffffu);
+                A.bk[b] = c;
+                A.bwoff[b] = wbase + lw;
+                v0[s] = b;
+                v1[s] = lw;
+            } else if (valid) {
+                v0[s] = kEmpty;
             }
-            __syncthreads();
+            carry += tot;
         }
+        __syncthreads();
 
-        wedge_pass<DENSE, INDEX, 1>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, wbase);
+        wedge_pass<DENSE, 1>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, wbase);
     }
 }
 
@@ -346,7 +337,7 @@ __global__ __launch_bounds__(1024) void k_graph_bases(const int64_t *off, const 
     }
 }
 
-template <bool DENSE, bool INDEX>
+template <bool DENSE>
 void launch_wedge(const WedgeArgs &A, const WedgeTask *tasks, int64_t n, int wg_per_cu,
                   hipStream_t s) {
     if (n <= 0) return;
@@ -355,7 +346,7 @@ void launch_wedge(const WedgeArgs &A, const WedgeTask *tasks, int64_t n, int wg_
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int64_t grid = std::min<int64_t>(n, (int64_t)cus * wg_per_cu);
-    k_wedge<DENSE, INDEX><<<(unsigned)grid, kWG, kSmemBytes, s>>>(A, tasks, n);
+    k_wedge<DENSE><<<(unsigned)grid, kWG, kSmemBytes, s>>>(A, tasks, n);
     BT_CHECK_LAUNCH();
 }
 
@@ -397,17 +388,9 @@ void check_butterfly_total(const uint64_t *supl, int64_t m, const int64_t *butte
                                     std::to_string(h[1])};
 }
 
-void count_support(const RankCSR &r, const TaskLists &t, uint64_t *supl, int64_t *bf,
-                   hipStream_t s) {
-    static_assert(kSmemBytes <= 65536, "LDS budget");
-    int64_t *queue = reinterpret_cast<int64_t *>(bf) + 1;  // caller gives 2 scalars
-    WedgeArgs A = make_args(r, supl, bf, queue);
-    launch_wedge<true, false>(A, t.dense, t.n_dense, r.tp.wedge_wg_per_cu, s);
-    launch_wedge<false, false>(A, t.hash, t.n_hash, r.tp.wedge_wg_per_cu, s);
-}
-
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
                  hipStream_t s, const Components *comps) {
+    static_assert(kSmemBytes <= 65536, "LDS budget");
     int64_t *queue = ws.get<int64_t>("wedge_queue", 1);
     WedgeArgs A = make_args(r, ix.supl, ix.butterflies, queue);
     A.cursor = ix.cursor;
@@ -425,8 +408,8 @@ void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspac
             zero_bytes(ix.base, sizeof(uint64_t), s);
         }
     }
-    launch_wedge<true, true>(A, t.dense, t.n_dense, r.tp.wedge_wg_per_cu, s);
-    launch_wedge<false, true>(A, t.hash, t.n_hash, r.tp.wedge_wg_per_cu, s);
+    launch_wedge<true>(A, t.dense, t.n_dense, r.tp.wedge_wg_per_cu, s);
+    launch_wedge<false>(A, t.hash, t.n_hash, r.tp.wedge_wg_per_cu, s);
     const int32_t nc = ix.base ? ix.n_graphs : 1;
     k_bloom_sentinel<<<grid_for(nc, 256, 256), 256, 0, s>>>(ix.cursor, nc, ix.bwoff);
     BT_CHECK_LAUNCH();

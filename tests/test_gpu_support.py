@@ -1,0 +1,76 @@
+"""Support counting at the edges of its walks: starts of each tier (a wave,
+256, 512 and 1,024 threads; cut into parts above 2^18 wedges), hash and dense
+tables, windows of ids, rows longer than a workgroup's step, and counts above
+8 and 16 bits.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2001_06111_amd import binding, synth
+from tests import graphs
+from tests.gpu_util import upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _skewed(n_light, n_mid, deg_mid, n_x, name):
+    """A start whose wedges all lie in one share of the degrees.  Lower ids:
+    x, n_x vertices that share two middles with it, n_light of degree one,
+    and n_mid of degree deg_mid that hold most of the degrees."""
+    xs = 0
+    z = 1 + np.arange(n_x)
+    light = 1 + n_x + np.arange(n_light)
+    mid = 1 + n_x + n_light + np.arange(n_mid)
+    nl = 1 + n_x + n_light + n_mid
+    own = n_x + 10  # middles of x alone, so that its priority is the highest
+    u, l = [], []
+
+    def add(uu, ll):
+        uu, ll = np.broadcast_arrays(uu, ll)
+        u.append(uu.ravel())
+        l.append(ll.ravel())
+
+    for y in (0, 1):
+        add(y, z)
+        add(y, xs)
+    add(2 + np.arange(own), xs)
+    far = 2 + own
+    add(far + np.arange(n_light) // 100, light)
+    blk = far + (n_light + 99) // 100
+    add(blk + np.arange(deg_mid)[:, None], mid[None, :])
+    nu = blk + deg_mid
+    keys = np.sort(np.concatenate(u).astype(np.int64) * nl + np.concatenate(l))
+    return synth._csr_from_keys(nu, nl, keys, name)
+
+
+CASES = [
+    synth.uniform(3, 5, 9, 0),
+    synth.complete(2, 2),
+    synth.complete(16, 17),       # starts of up to 256 wedges
+    synth.complete(16, 129),
+    synth.complete(45, 46),       # 2,048
+    synth.complete(128, 129),     # 16,384
+    synth.complete(500, 530),     # above 2^18: parts
+    synth.complete(2, 70001),     # more rows than a 16-bit count holds
+    synth.complete(3, 65536),
+    synth.complete(255, 300),     # counts of a byte, and above
+    synth.complete(256, 300),
+    synth.complete(257, 300),
+    synth.chung_lu(3000, 200000, 400000, 1.9, 2.2, 20000, 20000, 11),
+    synth.chung_lu(90000, 150000, 500000, 2.1, 2.3, 30000, 30000, 12),
+    synth.chung_lu(300000, 400, 600000, 2.0, 2.0, 400, 30000, 13),
+    graphs.star(5000),
+]
+
+
+@pytest.mark.parametrize("g", CASES, ids=lambda g: g.name)
+def test_support(g):
+    osup, obf, _ = oracle.support(g.n_upper, g.n_lower, g.row_ptr, g.col)
+    sup, bf = binding.bt_support(upload(g))
+    assert np.array_equal(sup.cpu().numpy(), osup) and bf == obf
+
+
+@pytest.mark.parametrize("shape", [(200000, 400, 1000, 2500), (1000000, 400, 3000, 6000),
+                                   (40000, 100, 500, 1000)])
+def test_wedges_in_one_share_of_the_degrees(shape):
+    test_support(_skewed(*shape, "skewed"))
