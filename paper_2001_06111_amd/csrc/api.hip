@@ -96,17 +96,20 @@ void alloc_index(const RankCSR &r, IndexArrays &ix, bool owned, Workspace &ws,
     ix.wea = (int32_t *)get("ix_wea", sizeof(int32_t) * (ix.cap_w + 1));
     ix.web = (int32_t *)get("ix_web", sizeof(int32_t) * (ix.cap_w + 1));
     ix.wbl = (int32_t *)get("ix_wbl", sizeof(int32_t) * (ix.cap_w + 1));
-    ix.supl = (uint64_t *)get("ix_supl", sizeof(uint64_t) * (m + 1));
+    // All that starts at zero, in one piece: supports, then queues, sums,
+    // cursors and bases.
+    const int64_t nc = std::max(1, ix.n_graphs);
+    ix.zeroed = m + 1 + 4 + 2 * nc;
+    ix.supl = (uint64_t *)get("ix_supl", sizeof(uint64_t) * ix.zeroed);
+    ix.queue = (int64_t *)(ix.supl + m + 1);
+    ix.sums = ix.queue + 2;
+    ix.cursor = (uint64_t *)(ix.sums + 2);
     if (ix.n_graphs > 0) {
-        ix.butterflies = (int64_t *)get("ix_small", sizeof(uint64_t) * (1 + 2 * (size_t)ix.n_graphs));
-        ix.cursor = (uint64_t *)(ix.butterflies + 1);
-        ix.base = ix.cursor + ix.n_graphs;
+        ix.base = ix.cursor + nc;
         return;
     }
     ix.link_off = (int64_t *)get("ix_link_off", sizeof(int64_t) * (m + 1));
     ix.link = (uint3 *)get("ix_link", sizeof(uint3) * (2 * ix.cap_w + 1));
-    ix.cursor = (uint64_t *)get("ix_cursor", sizeof(uint64_t) * 2);
-    ix.butterflies = (int64_t *)(ix.cursor + 1);
 }
 
 int64_t index_bytes(const IndexArrays &ix, int64_t m) {
@@ -126,17 +129,12 @@ void build_all(const bt_csr &g, RankCSR &r, IndexArrays &ix, bool owned,
     make_tasks(r, t, ws, s);
     if (ev) ev->mark(1);
     alloc_index(r, ix, owned, ws, own);
-    zero_bytes(ix.supl, sizeof(uint64_t) * (r.m + 1), s);
-    if (ix.n_graphs > 0) zero_bytes(ix.butterflies, sizeof(uint64_t) * (1 + ix.n_graphs), s);
-    else zero_bytes(ix.cursor, sizeof(uint64_t) * 2, s);
+    zero_bytes(ix.supl, sizeof(uint64_t) * ix.zeroed, s);
     build_index(r, t, ix, ws, s, comps);
     if (ev) ev->mark(2);
-    check_butterfly_total(ix.supl, r.m, ix.butterflies, ws, s);
+    uint64_t c;
+    ix.butterflies = check_butterfly_total(ix.supl, r.m, ix.sums, nullptr, ws, s, &c);
     if (ix.n_graphs > 0) return;  // the peel reads the sizes
-    int64_t *hs = ws.host(4);
-    BT_HIP(hipMemcpyAsync(hs, ix.cursor, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    BT_HIP(hipStreamSynchronize(s));
-    const uint64_t c = (uint64_t)hs[0];
     ix.n_b = (int64_t)(c >> 32);
     ix.n_w = (int64_t)(c & 0xffffffffu);
 }
@@ -251,10 +249,7 @@ static void decompose_once(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out
     if (auto_pc && g.m > 0) {
         // Where support updates, not rounds, bound the peel (hub-heavy
         // graphs), BiT-PC's smaller updates pay for its extra passes.
-        int64_t *hb = ws.host(2);
-        BT_HIP(hipMemcpyAsync(hb, ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-        BT_HIP(hipStreamSynchronize(stream));
-        if (hb[0] / g.m >= kAutoPcButterfliesPerEdge) {
+        if (ix.butterflies / g.m >= kAutoPcButterfliesPerEdge) {
             decompose_pc_impl(g0, kAutoPcTau, sup_out0, phi_out0, stats, ws, stream);
             return;
         }
@@ -277,10 +272,8 @@ static void decompose_once(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out
         BT_CHECK_LAUNCH();
     }
     ev.mark(4);
-    int64_t *hs = ws.host(2);
-    BT_HIP(hipMemcpyAsync(hs, ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
     BT_HIP(hipStreamSynchronize(stream));
-    if (stats) fill_stats(stats, r, ix, pc, g.m, hs[0], ev);
+    if (stats) fill_stats(stats, r, ix, pc, g.m, ix.butterflies, ev);
 }
 
 void decompose_impl(const bt_csr &g, int64_t *sup_out, int64_t *phi_out, bt_stats *stats,
@@ -318,20 +311,14 @@ static void decompose_pc_once(const bt_csr &g, double tau, int64_t *sup_out, int
     RankCSR r;
     prepare(g, r, ws, s, nullptr, true);
     ev.mark(1);
-    uint64_t *supl = ws.get<uint64_t>("pc_supl", m + 1);
-    int64_t *bf = ws.get<int64_t>("pc_bf", 2);
-    zero_bytes(supl, sizeof(uint64_t) * (m + 1), s);
-    zero_bytes(bf, sizeof(int64_t) * 2, s);
+    uint64_t *supl = ws.get<uint64_t>("pc_supl", m + 3);  // and the sums
+    int64_t *bf = reinterpret_cast<int64_t *>(supl + m + 1);
+    zero_bytes(supl, sizeof(uint64_t) * (m + 3), s);
     r.wedges_po = count_support(r, supl, bf, ws, s);
-    check_butterfly_total(supl, m, bf, ws, s);
-    if (sup_out && m) supl_to_sup(supl, sup_out, m, s);
+    const int64_t butterflies = check_butterfly_total(supl, m, bf, sup_out, ws, s);
     int32_t *sup0 = ws.get<int32_t>("pc_sup0", m);
     const int32_t kmax = pc_kmax(supl, m, sup0, ws, s);
     ev.mark(2);
-    int64_t *hs = ws.host(2);
-    BT_HIP(hipMemcpyAsync(hs, bf, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    BT_HIP(hipStreamSynchronize(s));
-    const int64_t butterflies = hs[0];
     const int64_t wedges_po = r.wedges_po;
     int32_t *phi_glob = ws.get<int32_t>("pc_phi", m);
     int64_t *phi_sub = ws.get<int64_t>("pc_phisub", m);
@@ -449,10 +436,8 @@ void decompose_union_impl(const bt_csr &u, const std::vector<int64_t> &off,
         peel_split(r, ix, off, sup_out, phi_out, pc, ws, s, &o);
     }
     ev.mark(4);
-    int64_t *hs = ws.host(2);
-    BT_HIP(hipMemcpyAsync(hs, ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
-    if (stats) fill_stats(stats, r, ix, pc, u.m, hs[0], ev);
+    if (stats) fill_stats(stats, r, ix, pc, u.m, ix.butterflies, ev);
 }
 
 namespace {
@@ -548,12 +533,12 @@ __device__ __forceinline__ int32_t block_of(const int64_t *off, int32_t ng, int6
 // Keys (graph, decreasing degree) of one layer's vertices; the stable sort
 // keeps id order among equal degrees.
 __global__ void k_reo_vertex_keys(const int64_t *row_ptr, const int32_t *deg, int32_t n,
-                                  const int64_t *boff, int32_t ng, uint64_t *keys,
+                                  const int64_t *boff, int32_t ng, int dbits, uint64_t *keys,
                                   uint32_t *vals) {
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n;
          x += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t d = row_ptr ? (uint32_t)(row_ptr[x + 1] - row_ptr[x]) : (uint32_t)deg[x];
-        keys[x] = ((uint64_t)block_of(boff, ng, x) << 32) | (uint64_t)(~d);
+        keys[x] = ((uint64_t)block_of(boff, ng, x) << dbits) | (((uint64_t(1) << dbits) - 1) - d);
         vals[x] = (uint32_t)x;
     }
 }
@@ -576,26 +561,30 @@ __global__ void k_reo_newid(const uint32_t *order, int32_t n, const int64_t *row
     }
 }
 
-// One wave per row: key (new upper, new lower) and the union position of
-// each edge.
-__global__ void k_reo_edge_keys(const int64_t *row_ptr, const int32_t *col, int32_t nu,
-                                const int32_t *new_u, const int32_t *new_l, uint64_t *keys,
-                                uint32_t *vals) {
+// Key (new upper, new lower) and the union position of each edge; a wave
+// takes runs of edges, whatever their rows.
+constexpr int kReoRun = 1024;
+__global__ void k_reo_edge_keys(const int64_t *row_ptr, const int32_t *col, int64_t m, int32_t nu,
+                                const int32_t *new_u, const int32_t *new_l, int nbl,
+                                uint64_t *keys, uint32_t *vals) {
     const int64_t nw = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t x = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; x < nu;
-         x += nw) {
-        const uint64_t hi = (uint64_t)(uint32_t)new_u[x] << 32;
-        for (int64_t e = row_ptr[x] + lane_id(); e < row_ptr[x + 1]; e += kWave) {
-            keys[e] = hi | (uint64_t)(uint32_t)new_l[col[e]];
+    for (int64_t run = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+         run * kReoRun < m; run += nw) {
+        const int64_t e0 = run * kReoRun, e1 = min(e0 + kReoRun, m);
+        const int32_t first = block_of(row_ptr, nu, e0);
+        const int32_t n = block_of(row_ptr, nu, e1 - 1) - first + 1;
+        for (int64_t e = e0 + lane_id(); e < e1; e += kWave) {
+            const int32_t x = first + block_of(row_ptr + first, n, e);
+            keys[e] = ((uint64_t)(uint32_t)new_u[x] << nbl) | (uint64_t)(uint32_t)new_l[col[e]];
             vals[e] = (uint32_t)e;
         }
     }
 }
 
-__global__ void k_reo_col(const uint64_t *keys, int64_t m, int32_t *col) {
+__global__ void k_reo_col(const uint64_t *keys, int64_t m, int nbl, int32_t *col) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m;
          i += (int64_t)gridDim.x * blockDim.x)
-        col[i] = (int32_t)(uint32_t)keys[i];
+        col[i] = (int32_t)(keys[i] & ((uint64_t(1) << nbl) - 1));
 }
 
 // The union u rebuilt in the locality order; returns perm (union position
@@ -605,7 +594,9 @@ const uint32_t *reorder_union(bt_csr &u, const int64_t *dvoff, int32_t ng, Works
     const int32_t nu = u.n_upper, nl = u.n_lower;
     const int64_t m = u.m;
     if (m == 0 || nu == 0 || nl == 0) return nullptr;
-    const int cbits = bits_for((uint64_t)(ng > 1 ? ng - 1 : 1));
+    const int cbits = bits_for((uint64_t)(ng - 1));
+    const int dbits = bits_for((uint64_t)std::max(nu, nl));  // of a degree
+    const int nbl = bits_for((uint64_t)(nl - 1)), nbu = bits_for((uint64_t)(nu - 1));
     const int64_t nv = std::max<int64_t>(nu, nl);
     uint64_t *vkeys = ws.get<uint64_t>("reo_vkeys", nv);
     uint32_t *vvals = ws.get<uint32_t>("reo_vvals", nv);
@@ -617,31 +608,31 @@ const uint32_t *reorder_union(bt_csr &u, const int64_t *dvoff, int32_t ng, Works
     zero_bytes(dl, sizeof(int32_t) * nl, s);
     k_reo_count<<<grid_for(m, 256, 16384), 256, 0, s>>>(u.col, m, dl);
     BT_CHECK_LAUNCH();
-    k_reo_vertex_keys<<<grid_for(nl, 256, 8192), 256, 0, s>>>(nullptr, dl, nl, dvoff, ng, vkeys,
-                                                             vvals);
+    k_reo_vertex_keys<<<grid_for(nl, 256, 8192), 256, 0, s>>>(nullptr, dl, nl, dvoff, ng, dbits,
+                                                             vkeys, vvals);
     BT_CHECK_LAUNCH();
-    radix_sort_u64_u32(vkeys, vvals, nl, 32 + cbits, ws, s);
+    radix_sort_u64_u32(vkeys, vvals, nl, dbits + cbits, ws, s);
     k_reo_newid<<<grid_for(nl, 256, 8192), 256, 0, s>>>(vvals, nl, nullptr, new_l, nullptr);
     BT_CHECK_LAUNCH();
     // Upper layer.
     k_reo_vertex_keys<<<grid_for(nu, 256, 8192), 256, 0, s>>>(u.row_ptr, nullptr, nu,
-                                                             dvoff + (ng + 1), ng, vkeys, vvals);
+                                                             dvoff + (ng + 1), ng, dbits, vkeys,
+                                                             vvals);
     BT_CHECK_LAUNCH();
-    radix_sort_u64_u32(vkeys, vvals, nu, 32 + cbits, ws, s);
+    radix_sort_u64_u32(vkeys, vvals, nu, dbits + cbits, ws, s);
     k_reo_newid<<<grid_for(nu, 256, 8192), 256, 0, s>>>(vvals, nu, u.row_ptr, new_u, deg_new);
     BT_CHECK_LAUNCH();
     // Edges sorted by (new upper, new lower).
     uint64_t *ekeys = ws.get<uint64_t>("reo_ekeys", m);
     uint32_t *perm = ws.get<uint32_t>("reo_perm", m);
-    k_reo_edge_keys<<<grid_for((int64_t)nu * kWave, 256, 16384), 256, 0, s>>>(
-        u.row_ptr, u.col, nu, new_u, new_l, ekeys, perm);
+    k_reo_edge_keys<<<grid_for(ceil_div(m, kReoRun) * kWave, 256, 8192), 256, 0, s>>>(
+        u.row_ptr, u.col, m, nu, new_u, new_l, nbl, ekeys, perm);
     BT_CHECK_LAUNCH();
-    radix_sort_u64_u32(ekeys, perm, m, 32 + bits_for((uint64_t)(nu - 1 > 0 ? nu - 1 : 1)), ws,
-                       s);
+    radix_sort_u64_u32(ekeys, perm, m, nbl + nbu, ws, s);
     int64_t *row_ptr = ws.get<int64_t>("reo_rowptr", (int64_t)nu + 1);
     int32_t *col = ws.get<int32_t>("reo_col", m);
     scan_exclusive_i32_to_i64(deg_new, row_ptr, nu, ws, s);
-    k_reo_col<<<grid_for(m, 256, 16384), 256, 0, s>>>(ekeys, m, col);
+    k_reo_col<<<grid_for(m, 256, 16384), 256, 0, s>>>(ekeys, m, nbl, col);
     BT_CHECK_LAUNCH();
     u.row_ptr = row_ptr;
     u.col = col;
@@ -876,17 +867,12 @@ bt_status bt_support(const bt_csr *g, int64_t *sup_out, int64_t *butterflies_out
         Workspace &ws = lib().ws;
         RankCSR r;
         prepare(*g, r, ws, stream, nullptr, true);
-        uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 1);
-        int64_t *bf = ws.get<int64_t>("sup_bf", 2);
-        zero_bytes(supl, sizeof(uint64_t) * (g->m + 1), stream);
-        zero_bytes(bf, sizeof(int64_t) * 2, stream);
+        uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 3);  // and the sums
+        int64_t *bf = reinterpret_cast<int64_t *>(supl + g->m + 1);
+        zero_bytes(supl, sizeof(uint64_t) * (g->m + 3), stream);
         count_support(r, supl, bf, ws, stream);
-        check_butterfly_total(supl, g->m, bf, ws, stream);
-        supl_to_sup(supl, sup_out, g->m, stream);
-        int64_t *hs = ws.host(2);
-        BT_HIP(hipMemcpyAsync(hs, bf, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-        BT_HIP(hipStreamSynchronize(stream));
-        if (butterflies_out) *butterflies_out = hs[0];
+        const int64_t total = check_butterfly_total(supl, g->m, bf, sup_out, ws, stream);
+        if (butterflies_out) *butterflies_out = total;
     });
 }
 
@@ -901,11 +887,8 @@ bt_status bt_index_build(const bt_csr *g, bt_index **out, hipStream_t stream) {
         try {
             RankCSR r;
             build_all(*g, r, h->ix, true, &h->owned, ws, stream, nullptr);
-            int64_t *hs = ws.host(2);
-            BT_HIP(hipMemcpyAsync(hs, h->ix.butterflies, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                  stream));
             BT_HIP(hipStreamSynchronize(stream));
-            h->butterflies = hs[0];
+            h->butterflies = h->ix.butterflies;
             h->m = g->m;
             h->wedges_po = r.wedges_po;
         } catch (...) {

@@ -1,6 +1,8 @@
 // graph.hip - input validation, vertex priority order and the rank-space
 // adjacency (priority of Definition 6; the "p(v) < p(u)" filters of
 // Algorithm 3's sweeps become row prefixes).
+#include <algorithm>
+
 #include "pipeline.h"
 
 namespace bt {
@@ -9,6 +11,17 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Largest row r in [lo, hi] with row_ptr[r] <= e (lo if there is none).
+__device__ __forceinline__ int32_t upper_row_of(const int64_t *row_ptr, int32_t lo, int32_t hi,
+                                                int64_t e) {
+    while (lo < hi) {
+        const int32_t mid = lo + (hi - lo + 1) / 2;
+        if (row_ptr[mid] <= e) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 // Validation flags.
 enum : int32_t {
     kBadRowPtr = 1,   // row_ptr not a partition of [0, m)
@@ -16,37 +29,40 @@ enum : int32_t {
     kUnsorted = 4,    // lower ids not strictly increasing in a row (or duplicate)
 };
 
-// One wave per row.  Reads col only inside a row whose bounds were checked.
+// One thread a row, then one an edge (a wave a row takes 2 ms where one of
+// 20M edges' rows holds 165,000).  Where lower ids do not increase a row has
+// to begin, which is looked up; with bad row bounds the answer is arbitrary
+// but the search stays inside row_ptr, and the bounds are reported first.
 __global__ __launch_bounds__(kBlock) void k_validate(const int64_t *row_ptr, const int32_t *col,
                                                      int32_t n_upper, int32_t n_lower,
                                                      int64_t m, int32_t *flags) {
-    const int64_t waves = (int64_t)gridDim.x * (kBlock / kWave);
+    const int64_t t0 = blockIdx.x * (int64_t)kBlock + threadIdx.x, nt = (int64_t)gridDim.x * kBlock;
     int32_t bad = 0;
-    for (int64_t i = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; i < n_upper;
-         i += waves) {
+    for (int64_t i = t0; i < n_upper; i += nt) {
         const int64_t a = row_ptr[i], b = row_ptr[i + 1];
         if (i == 0 && a != 0) bad |= kBadRowPtr;
         if (i == n_upper - 1 && b != m) bad |= kBadRowPtr;
-        if (a < 0 || b < a || b > m) {
-            bad |= kBadRowPtr;
-            continue;
-        }
-        for (int64_t k = a + lane_id(); k < b; k += kWave) {
-            const int32_t c = col[k];
-            if (c < 0 || c >= n_lower) bad |= kBadCol;
-            if (k + 1 < b && col[k + 1] <= c) bad |= kUnsorted;
-        }
+        if (a < 0 || b < a || b > m) bad |= kBadRowPtr;
+    }
+    for (int64_t k = t0; k < m; k += nt) {
+        const int32_t c = col[k];
+        if (c < 0 || c >= n_lower) bad |= kBadCol;
+        if (k + 1 < m && col[k + 1] <= c &&
+            row_ptr[upper_row_of(row_ptr, 0, n_upper - 1, k + 1)] != k + 1)
+            bad |= kUnsorted;
     }
     bad = wave_or(bad);
     if (lane_id() == 0 && bad) atomicOr(flags, bad);
 }
 
-// deg[gid]: lower j -> j, upper i -> n_lower + i.
-__global__ void k_upper_degree(const int64_t *row_ptr, int32_t n_upper, int32_t n_lower,
-                               int32_t *deg) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_upper;
-         i += (int64_t)gridDim.x * blockDim.x)
+// deg[gid]: lower j -> j, upper i -> n_lower + i.  Lower degrees start at zero.
+__global__ void k_degrees(const int64_t *row_ptr, const int32_t *col, int64_t m, int32_t n_upper,
+                          int32_t n_lower, int32_t *deg) {
+    const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t nt = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t0; i < n_upper; i += nt)
         deg[n_lower + i] = (int32_t)(row_ptr[i + 1] - row_ptr[i]);
+    for (int64_t e = t0; e < m; e += nt) atomicAdd(&deg[col[e]], 1);
 }
 
 __global__ void k_lower_degree(const int32_t *col, int64_t m, int32_t *deg) {
@@ -56,11 +72,11 @@ __global__ void k_lower_degree(const int32_t *col, int64_t m, int32_t *deg) {
 }
 
 // Sort key: layer above degree; the stable sort keeps id order on ties.
-__global__ void k_rank_keys(const int32_t *deg, int32_t n_lower, int32_t n, uint64_t *keys,
-                            uint32_t *vals) {
+__global__ void k_rank_keys(const int32_t *deg, int32_t n_lower, int32_t n, int dbits,
+                            uint64_t *keys, uint32_t *vals) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x) {
-        keys[v] = ((uint64_t)(v >= n_lower) << 31) | (uint64_t)deg[v];
+        keys[v] = ((uint64_t)(v >= n_lower) << dbits) | (uint64_t)deg[v];
         vals[v] = (uint32_t)v;
     }
 }
@@ -78,12 +94,12 @@ __device__ __forceinline__ int32_t comp_of(const int64_t *off, int32_t n, int64_
 
 // Union: layer above graph above degree; the stable sort keeps id order.
 __global__ void k_rank_keys_comp(const int32_t *deg, int32_t n_lower, int32_t n, Components cp,
-                                 int cbits, uint64_t *keys, uint32_t *vals) {
+                                 int cbits, int dbits, uint64_t *keys, uint32_t *vals) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x) {
         const bool up = v >= n_lower;
         const int32_t c = up ? comp_of(cp.u_off, cp.n, v - n_lower) : comp_of(cp.l_off, cp.n, v);
-        keys[v] = ((uint64_t)up << (31 + cbits)) | ((uint64_t)c << 31) | (uint64_t)deg[v];
+        keys[v] = ((uint64_t)up << (dbits + cbits)) | ((uint64_t)c << dbits) | (uint64_t)deg[v];
         vals[v] = (uint32_t)v;
     }
 }
@@ -112,30 +128,39 @@ __global__ void k_rank_apply(const uint32_t *order, const int32_t *deg, int32_t 
     }
 }
 
-// Two adjacency entries per edge; one wave per upper row.
+// The edges in upper rank order: key (upper rank in its layer << nbl | lower
+// rank), value the edge.  A wave takes runs of edges, whatever their rows.
 __global__ __launch_bounds__(kBlock) void k_entries(const int64_t *row_ptr, const int32_t *col,
-                                                    int32_t n_upper, int32_t n_lower,
-                                                    const int32_t *old2new, int nb,
-                                                    uint64_t *keys, uint32_t *vals) {
+                                                    int64_t m, int32_t n_upper, int32_t n_lower,
+                                                    const int32_t *old2new, const int64_t *off,
+                                                    int nbl, int run_len, uint64_t *keys, uint32_t *vals) {
     const int64_t waves = (int64_t)gridDim.x * (kBlock / kWave);
-    for (int64_t i = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; i < n_upper;
-         i += waves) {
-        const uint64_t ru = (uint64_t)old2new[n_lower + i];
-        for (int64_t e = row_ptr[i] + lane_id(); e < row_ptr[i + 1]; e += kWave) {
+    for (int64_t run = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; run * run_len < m;
+         run += waves) {
+        const int64_t e0 = run * run_len, e1 = min(e0 + run_len, m);
+        const int32_t first = upper_row_of(row_ptr, 0, n_upper - 1, e0);
+        const int32_t last = upper_row_of(row_ptr, first, n_upper - 1, e1 - 1);
+        for (int64_t e = e0 + lane_id(); e < e1; e += kWave) {
+            const int32_t i = upper_row_of(row_ptr, first, last, e);
+            const int32_t ru = old2new[n_lower + i];
             const uint64_t rl = (uint64_t)old2new[col[e]];
-            keys[2 * e] = (ru << nb) | rl;
-            vals[2 * e] = (uint32_t)e;
-            keys[2 * e + 1] = (rl << nb) | ru;
-            vals[2 * e + 1] = (uint32_t)e;
+            const int64_t at = off[ru] - m + (e - row_ptr[i]);
+            keys[at] = ((uint64_t)(ru - n_lower) << nbl) | rl;
+            vals[at] = (uint32_t)e;
         }
     }
 }
 
-__global__ void k_entries_apply(const uint64_t *keys, const uint32_t *vals, int64_t n2,
-                                uint64_t mask, int32_t *adj, int32_t *eid) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n2;
+// Rows of one layer from the sorted edges: adj and eid, and the row's vertex.
+__global__ void k_entries_apply(const uint64_t *keys, const uint32_t *vals, int64_t m, int nbl,
+                                int32_t n_lower, bool upper, int32_t *adj, int32_t *eid,
+                                int32_t *src) {
+    const uint64_t mask = (uint64_t(1) << nbl) - 1;
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < m;
          j += (int64_t)gridDim.x * blockDim.x) {
-        adj[j] = (int32_t)(keys[j] & mask);
+        const int32_t rl = (int32_t)(keys[j] & mask), ru = n_lower + (int32_t)(keys[j] >> nbl);
+        adj[j] = upper ? rl : ru;
+        src[j] = upper ? ru : rl;
         eid[j] = (int32_t)vals[j];
     }
 }
@@ -163,12 +188,12 @@ __global__ void k_low(const int64_t *off, const int32_t *adj, const int32_t *deg
 
 // rev for prefix entries (x -> y): position of x in row y.  zlen (nullable)
 // for all entries: the entries of row y above both x and y, and rst.
-__global__ void k_rev(const uint64_t *keys, int64_t n2, int nb, const int64_t *off,
-                      const int32_t *adj, const int32_t *low, int32_t *rev, int32_t *zlen,
+__global__ void k_rev(const int32_t *src, int64_t n2, const int64_t *off, const int32_t *adj,
+                      const int32_t *low, int32_t *rev, int32_t *zlen,
                       uint32_t *rst) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n2;
          j += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t x = (int32_t)(keys[j] >> nb);
+        const int32_t x = src[j];
         int32_t r = 0;
         const int32_t y = adj[j];
         const bool down = j - off[x] < low[x];
@@ -203,7 +228,7 @@ void validate_graph(const bt_csr &g, Workspace &ws, hipStream_t s) {
     int32_t *flags = ws.get<int32_t>("prep_flags", 4);
     zero_bytes(flags, 4 * sizeof(int32_t), s);
     if (nu > 0) {
-        k_validate<<<grid_for((int64_t)nu * kWave, kBlock, 16384), kBlock, 0, s>>>(
+        k_validate<<<grid_for(std::max<int64_t>(nu, m), kBlock, 4096), kBlock, 0, s>>>(
             g.row_ptr, g.col, nu, nl, m, flags);
         BT_CHECK_LAUNCH();
     }
@@ -231,13 +256,10 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
 
     // Degrees and the priority order.
     int32_t *deg = ws.get<int32_t>("prep_deg", n);
-    zero_bytes(deg, sizeof(int32_t) * (n > 0 ? n : 1), s);
-    if (nu > 0) {
-        k_upper_degree<<<grid_for(nu, 256, 8192), 256, 0, s>>>(g.row_ptr, nu, nl, deg);
-        BT_CHECK_LAUNCH();
-    }
-    if (m > 0) {
-        k_lower_degree<<<grid_for(m, 256, 16384), 256, 0, s>>>(g.col, m, deg);
+    zero_bytes(deg, sizeof(int32_t) * (nl > 0 ? nl : 1), s);
+    if (n > 0) {
+        k_degrees<<<grid_for(std::max<int64_t>(nu, m), 256, 16384), 256, 0, s>>>(
+            g.row_ptr, g.col, m, nu, nl, deg);
         BT_CHECK_LAUNCH();
     }
     uint64_t *vkeys = ws.get<uint64_t>("prep_vkeys", n);
@@ -247,18 +269,20 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     int32_t *deg_new = ws.get<int32_t>("prep_degnew", n);
     const bool uni = comps && comps->n > 1;
     r.zbase = r.vgraph = nullptr;
+    // No degree exceeds the size of the other layer.
+    const int dbits = bits_for((uint64_t)std::max(nu, nl));
     if (n > 0) {
         if (uni) {
             const int cbits = bits_for((uint64_t)(comps->n - 1));
             k_rank_keys_comp<<<grid_for(n, 256, 8192), 256, 0, s>>>(deg, nl, (int32_t)n, *comps,
-                                                                   cbits, vkeys, vorder);
+                                                                   cbits, dbits, vkeys, vorder);
             BT_CHECK_LAUNCH();
-            radix_sort_u64_u32(vkeys, vorder, n, 32 + cbits, ws, s);
+            radix_sort_u64_u32(vkeys, vorder, n, dbits + cbits + 1, ws, s);
         } else {
-            k_rank_keys<<<grid_for(n, 256, 8192), 256, 0, s>>>(deg, nl, (int32_t)n, vkeys,
+            k_rank_keys<<<grid_for(n, 256, 8192), 256, 0, s>>>(deg, nl, (int32_t)n, dbits, vkeys,
                                                               vorder);
             BT_CHECK_LAUNCH();
-            radix_sort_u64_u32(vkeys, vorder, n, 32, ws, s);
+            radix_sort_u64_u32(vkeys, vorder, n, dbits + 1, ws, s);
         }
         k_rank_apply<<<grid_for(n, 256, 8192), 256, 0, s>>>(vorder, deg, (int32_t)n, old2new,
                                                             new2old, deg_new);
@@ -274,11 +298,14 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     r.off = ws.get<int64_t>("rank_off", n + 1);
     scan_exclusive_i32_to_i64(deg_new, r.off, n, ws, s);
 
-    // Rank-space rows sorted by neighbour priority.
+    // Rank-space rows sorted by neighbour priority: the edges in upper rank
+    // order, sorted (stably) by lower rank, are the lower rows; those, sorted
+    // by upper rank, are the upper rows.
     const int64_t n2 = 2 * m;
-    const int nb = bits_for((uint64_t)(n > 0 ? n - 1 : 0)) > 0 ? bits_for((uint64_t)(n - 1)) : 1;
-    uint64_t *ekeys = ws.get<uint64_t>("prep_ekeys", n2);
-    uint32_t *evals = ws.get<uint32_t>("prep_evals", n2);
+    const int nbl = bits_for((uint64_t)std::max(nl - 1, 0)), nbu = bits_for((uint64_t)std::max(nu - 1, 0));
+    uint64_t *ekeys = ws.get<uint64_t>("prep_ekeys", m);
+    uint32_t *evals = ws.get<uint32_t>("prep_evals", m);
+    int32_t *src = ws.get<int32_t>("prep_src", n2);
     r.adj = ws.get<int32_t>("rank_adj", n2);
     r.eid = ws.get<int32_t>("rank_eid", n2);
     r.rev = ws.get<int32_t>("rank_rev", n2);
@@ -288,13 +315,18 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     r.rst = up ? ws.get<uint32_t>("rank_rst", n2) : nullptr;
     r.zpre = up ? ws.get<int64_t>("rank_zpre", n2 + 1) : nullptr;
     if (m > 0) {
-        k_entries<<<grid_for((int64_t)nu * kWave, kBlock, 16384), kBlock, 0, s>>>(
-            g.row_ptr, g.col, nu, nl, old2new, nb, ekeys, evals);
+        // Short runs where there are too few to fill the chip.
+        const int run = m < (int64_t(1) << 20) ? kWave : 8 * kWave;
+        k_entries<<<grid_for(ceil_div(m, run) * kWave, kBlock, 8192), kBlock, 0, s>>>(
+            g.row_ptr, g.col, m, nu, nl, old2new, r.off, nbl, run, ekeys, evals);
         BT_CHECK_LAUNCH();
-        radix_sort_u64_u32(ekeys, evals, n2, 2 * nb, ws, s);
-        k_entries_apply<<<grid_for(n2, 256, 16384), 256, 0, s>>>(
-            ekeys, evals, n2, (uint64_t(1) << nb) - 1, r.adj, r.eid);
-        BT_CHECK_LAUNCH();
+        for (const bool upper : {false, true}) {
+            radix_sort_u64_u32(ekeys, evals, m, upper ? nbu : nbl, ws, s, upper ? nbl : 0);
+            k_entries_apply<<<grid_for(m, 256, 16384), 256, 0, s>>>(
+                ekeys, evals, m, nbl, nl, upper, r.adj + (upper ? m : 0), r.eid + (upper ? m : 0),
+                src + (upper ? m : 0));
+            BT_CHECK_LAUNCH();
+        }
     }
     if (n > 0) {
         k_low<<<grid_for(n, 256, 8192), 256, 0, s>>>(r.off, r.adj, deg_new, new2old,
@@ -302,7 +334,7 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
         BT_CHECK_LAUNCH();
     }
     if (m > 0) {
-        k_rev<<<grid_for(n2, 256, 16384), 256, 0, s>>>(ekeys, n2, nb, r.off, r.adj, r.low,
+        k_rev<<<grid_for(n2, 256, 16384), 256, 0, s>>>(src, n2, r.off, r.adj, r.low,
                                                        r.rev, r.zlen, r.rst);
         BT_CHECK_LAUNCH();
     }
@@ -448,7 +480,7 @@ int64_t footprint_bytes(const bt_csr &g, Workspace &ws, hipStream_t s) {
     unsigned long long *sum = ws.get<unsigned long long>("fp_sum", 1);
     zero_bytes(flags, 4 * sizeof(int32_t), s);
     if (nu > 0) {
-        k_validate<<<grid_for((int64_t)nu * kWave, kBlock, 16384), kBlock, 0, s>>>(
+        k_validate<<<grid_for(std::max<int64_t>(nu, m), kBlock, 4096), kBlock, 0, s>>>(
             g.row_ptr, g.col, nu, nl, m, flags);
         BT_CHECK_LAUNCH();
     }

@@ -66,17 +66,12 @@ extern "C" bt_status bt_support_noalloc(const bt_csr *g, int64_t *sup_out,
         ws.use_arena(D.ptr, kScratchBytes, D.host, kHostWords);
         RankCSR r;
         prepare(*g, r, ws, stream, nullptr, true);
-        uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 1);
-        int64_t *bf = ws.get<int64_t>("sup_bf", 2);
-        zero_bytes(supl, sizeof(uint64_t) * (g->m + 1), stream);
-        zero_bytes(bf, sizeof(int64_t) * 2, stream);
+        uint64_t *supl = ws.get<uint64_t>("sup_supl", g->m + 3);  // and the sums
+        int64_t *bf = reinterpret_cast<int64_t *>(supl + g->m + 1);
+        zero_bytes(supl, sizeof(uint64_t) * (g->m + 3), stream);
         count_support(r, supl, bf, ws, stream);
-        check_butterfly_total(supl, g->m, bf, ws, stream);
-        supl_to_sup(supl, sup_out, g->m, stream);
-        int64_t *hs = ws.host(2);
-        BT_HIP(hipMemcpyAsync(hs, bf, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-        BT_HIP(hipStreamSynchronize(stream));
-        if (butterflies_out) *butterflies_out = hs[0];
+        const int64_t total = check_butterfly_total(supl, g->m, bf, sup_out, ws, stream);
+        if (butterflies_out) *butterflies_out = total;
         return BT_OK;
     } catch (const Error &e) {
         set_error(e.msg);

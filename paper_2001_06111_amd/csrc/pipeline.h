@@ -110,7 +110,10 @@ struct IndexArrays {
     // and n_b, n_w are filled by the peel.
     int32_t n_graphs = 0;
     uint64_t *base = nullptr;
-    int64_t *butterflies = nullptr;  // device scalar
+    int64_t *queue = nullptr;  // task cursors of the two wedge sweeps
+    int64_t *sums = nullptr;   // butterflies, and the sum of the supports; then cursor
+    int64_t zeroed = 0;        // words from supl on that start at zero
+    int64_t butterflies = 0;   // host copy after build
 };
 
 // Checks the CSR on the device (BT_EINVAL with the reason if malformed).
@@ -272,8 +275,10 @@ int64_t footprint_bytes(const bt_csr &g, Workspace &ws, hipStream_t s);
 void supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m, hipStream_t s);
 // The butterfly total two ways (Lemma 1: every butterfly has four edges;
 // Lemma 8: a k-bloom holds C(k, 2)): the supports must sum to four times the
-// blooms' total, else BT_EDEVICE.
-void check_butterfly_total(const uint64_t *supl, int64_t m, const int64_t *butterflies,
-                           Workspace &ws, hipStream_t s);
+// blooms' total, else BT_EDEVICE.  Returns it, and writes the supports to
+// `sup` unless that is null.  `sums`: the blooms' total and a cleared word;
+// `next` (nullable) receives the word after them.
+int64_t check_butterfly_total(const uint64_t *supl, int64_t m, int64_t *sums, int64_t *sup,
+                              Workspace &ws, hipStream_t s, uint64_t *next = nullptr);
 
 }  // namespace bt

@@ -310,13 +310,45 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_tile(const Tin *in, int64_t
     }
     int64_t total;
     int64_t run = block_exclusive_sum(sum, scratch, &total);
-    if (boff) run += boff[blockIdx.x];
+    run += boff[blockIdx.x];
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         int64_t idx = base + i;
         if (idx < n) out[idx] = run;
         run += v[i];
         if (idx == n - 1) out[n] = run;
+    }
+}
+
+// Up to kScanOne elements: each workgroup sums what precedes its tile by
+// itself, one launch instead of three (a launch costs 3 to 4 us, the sums of
+// the last workgroup under 3 us).
+constexpr int64_t kScanOne = 16 * kScanTile;
+
+template <typename Tin>
+__global__ __launch_bounds__(kScanBlock) void k_scan_one(const Tin *in, int64_t *out, int64_t n) {
+    __shared__ int64_t scratch[kScanBlock / kWave + 1];
+    const int64_t tile = (int64_t)blockIdx.x * kScanTile;
+    int64_t before = 0;
+#pragma unroll 8
+    for (int64_t i = threadIdx.x; i < tile; i += kScanBlock) before += (int64_t)in[i];
+    int64_t off;
+    (void)block_exclusive_sum(before, scratch, &off);
+    const int64_t base = tile + (int64_t)threadIdx.x * kScanItems;
+    int64_t v[kScanItems];
+    int64_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        v[i] = base + i < n ? (int64_t)in[base + i] : 0;
+        sum += v[i];
+    }
+    int64_t total;
+    int64_t run = block_exclusive_sum(sum, scratch, &total) + off;
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        if (base + i < n) out[base + i] = run;
+        run += v[i];
+        if (base + i == n - 1) out[n] = run;
     }
 }
 
@@ -328,8 +360,8 @@ static void scan_impl(const Tin *in, int64_t *out, int64_t n, Workspace &ws, hip
         return;
     }
     int64_t nb = ceil_div(n, kScanTile);
-    if (nb == 1) {
-        k_scan_tile<Tin><<<1, kScanBlock, 0, s>>>(in, out, n, nullptr);
+    if (n <= kScanOne) {
+        k_scan_one<Tin><<<(unsigned)nb, kScanBlock, 0, s>>>(in, out, n);
         BT_CHECK_LAUNCH();
         return;
     }
@@ -356,101 +388,180 @@ void scan_exclusive_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Works
 }
 
 // ------------------------------------------------------- radix sort
-// Stable LSD radix sort, 8-bit digits.  Pass: per-tile digit histograms
-// (digit-major), one exclusive scan over them, then a stable scatter in
-// which each wave ranks equal digits with eight ballots and waves are
-// ordered through LDS counters, one row of kRsBlock elements at a time.
+// Stable LSD radix sort.  A pass: per-tile digit histograms, one exclusive
+// scan over them, a stable scatter.
+//
+// The scatter's workgroup loads its whole tile at once and each wave owns a
+// run of it: the waves' digit counts give every wave its own output
+// positions, so ranking the 64 elements of a row (one ballot a digit bit)
+// needs no barrier.  With a tile loaded row by row and three barriers a row a
+// pass of 10M elements took 86 us in the scatter, and one of 20,000 15 us;
+// now one of 5M takes 38 us and one of 10,000 8 us.  Few tiles (kRsDirect)
+// are scanned by the scatter itself, each workgroup for its own, which saves a
+// pass its scan launches.
+//
+// Digits: up to 11 bits up to kRsSmall elements, where a pass costs its two
+// launches whatever it moves; up to 8 above, where wide digits write short
+// runs (5M-edge graph, six or nine passes: 408 and 340 us in the scatter).
 
+template <int ITEMS> constexpr int kRsDigit = ITEMS == 4 ? 11 : 8;
 constexpr int kRsBlock = 256;
-constexpr int kRsItems = 16;
-constexpr int kRsTile = kRsBlock * kRsItems;
 constexpr int kRsWaves = kRsBlock / kWave;
+constexpr int64_t kRsSmall = int64_t(1) << 16;  // up to here: tiles of 1,024, else of 4,096
+constexpr int64_t kRsDirect = 64;
 
-__global__ __launch_bounds__(kRsBlock) void k_rs_hist(const uint64_t *keys, int64_t n,
-                                                      int shift, int32_t *hist, int64_t nb) {
-    __shared__ int32_t h[256];
-    h[threadIdx.x] = 0;
+template <int ITEMS>
+__global__ __launch_bounds__(kRsBlock) void k_rs_hist(const uint64_t *keys, int64_t n, int shift,
+                                                      int bins, bool direct, int32_t *hist,
+                                                      int64_t nb) {
+    extern __shared__ int32_t h[];
+    for (int d = threadIdx.x; d < bins; d += kRsBlock) h[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int i = threadIdx.x; i < kRsTile; i += kRsBlock) {
-        int64_t idx = base + i;
-        if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & 255], 1);
+    const int64_t base = (int64_t)blockIdx.x * (ITEMS * kRsBlock);
+    uint64_t k[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t idx = base + i * kRsBlock + threadIdx.x;
+        k[i] = idx < n ? keys[idx] : 0;
     }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (base + i * kRsBlock + threadIdx.x < n)
+            atomicAdd(&h[(int)(k[i] >> shift) & (bins - 1)], 1);
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+    for (int d = threadIdx.x; d < bins; d += kRsBlock)
+        hist[direct ? (int64_t)blockIdx.x * bins + d : (int64_t)d * nb + blockIdx.x] = h[d];
 }
 
-__global__ __launch_bounds__(kRsBlock) void k_rs_scatter(const uint64_t *kin,
-                                                         const uint32_t *vin, uint64_t *kout,
-                                                         uint32_t *vout, int64_t n, int shift,
+// offs: the scanned histograms (digit by digit), or null for few tiles, whose
+// histograms (tile by tile) are summed here.
+template <int ITEMS>
+__global__ __launch_bounds__(kRsBlock) void k_rs_scatter(const uint64_t *kin, const uint32_t *vin,
+                                                         uint64_t *kout, uint32_t *vout, int64_t n,
+                                                         int shift, int bits, const int32_t *hist,
                                                          const int64_t *offs, int64_t nb) {
-    __shared__ int64_t run[256];
-    __shared__ int32_t wc[kRsWaves][256];
+    extern __shared__ uint32_t wc[];  // [wave][digit]: counts, then output positions
+    __shared__ uint32_t scr[kRsWaves + 1];
+    const int bins = 1 << bits;
     const int w = threadIdx.x / kWave;
-    run[threadIdx.x] = offs[(int64_t)threadIdx.x * nb + blockIdx.x];
-    for (int i = 0; i < kRsWaves; ++i) wc[i][threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int r = 0; r < kRsItems; ++r) {
-        const int64_t idx = base + (int64_t)r * kRsBlock + threadIdx.x;
-        const bool valid = idx < n;
-        uint64_t key = valid ? kin[idx] : 0;
-        uint32_t val = valid ? vin[idx] : 0;
-        const int d = (int)((key >> shift) & 255);
-        const uint64_t vmask = __ballot(valid);
-        uint64_t peers = vmask;
+    uint32_t *mine = wc + w * bins;
+    const int64_t base = (int64_t)blockIdx.x * (ITEMS * kRsBlock) + w * (ITEMS * kWave);
+    uint64_t k[ITEMS];
+    uint32_t v[ITEMS];
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t idx = base + i * kWave + lane_id();
+        k[i] = idx < n ? kin[idx] : 0;
+        v[i] = idx < n ? vin[idx] : 0;
+    }
+    for (int d = threadIdx.x; d < kRsWaves * bins; d += kRsBlock) wc[d] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (base + i * kWave + lane_id() < n) atomicAdd(&mine[(int)(k[i] >> shift) & (bins - 1)], 1u);
+    __syncthreads();
+    uint32_t *first = wc + kRsWaves * bins;  // few tiles: each digit's first position
+    uint32_t before[(1 << kRsDigit<ITEMS>) / kRsBlock];
+    if (!offs) {
+#pragma unroll
+        for (int i = 0; i < (1 << kRsDigit<ITEMS>) / kRsBlock; ++i) {
+            const int d = i * kRsBlock + (int)threadIdx.x;
+            before[i] = 0;
+            if (d >= bins) continue;
+            uint32_t total = 0;
+#pragma unroll 8
+            for (int t = 0; t < (int)nb; ++t) {
+                const uint32_t c = (uint32_t)hist[t * bins + d];
+                before[i] += t < (int)blockIdx.x ? c : 0;
+                total += c;
+            }
+            first[d] = total;
+        }
+        __syncthreads();
+        const int per = (bins + kRsBlock - 1) / kRsBlock;
+        const int d0 = (int)threadIdx.x * per, d1 = min(d0 + per, bins);
+        uint32_t sum = 0, all;
+        for (int d = d0; d < d1; ++d) sum += first[d];
+        uint32_t run = block_exclusive_sum<uint32_t>(sum, scr, &all);
+        for (int d = d0; d < d1; ++d) {
+            const uint32_t c = first[d];
+            first[d] = run;
+            run += c;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < (1 << kRsDigit<ITEMS>) / kRsBlock; ++i) {
+        const int d = i * kRsBlock + (int)threadIdx.x;
+        if (d >= bins) continue;
+        uint32_t pos =
+            offs ? (uint32_t)offs[(int64_t)d * nb + blockIdx.x] : first[d] + before[i];
+        for (int j = 0; j < kRsWaves; ++j) {
+            const uint32_t c = wc[j * bins + d];
+            wc[j * bins + d] = pos;
+            pos += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool valid = base + i * kWave + lane_id() < n;
+        const int d = (int)(k[i] >> shift) & (bins - 1);
+        uint64_t peers = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
             const bool bit = (d >> b) & 1;
-            const uint64_t bal = __ballot(valid && bit);
+            const uint64_t bal = __ballot(bit);
             peers &= bit ? bal : ~bal;
         }
-        peers &= vmask;
-        const int rank = (int)__popcll(peers & lanemask_lt());
-        if (valid && rank == 0) wc[w][d] = (int)__popcll(peers);
-        __syncthreads();
+        const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
         if (valid) {
-            int64_t pos = run[d] + rank;
-            for (int i = 0; i < w; ++i) pos += wc[i][d];
-            kout[pos] = key;
-            vout[pos] = val;
+            const uint32_t pos = mine[d] + rank;
+            kout[pos] = k[i];
+            vout[pos] = v[i];
+            if (rank == 0) mine[d] += (uint32_t)__popcll(peers);
         }
-        __syncthreads();
-        int64_t add = 0;
-        for (int i = 0; i < kRsWaves; ++i) {
-            add += wc[i][threadIdx.x];
-            wc[i][threadIdx.x] = 0;
-        }
-        run[threadIdx.x] += add;
-        __syncthreads();
     }
 }
 
-void radix_sort_u64_u32(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits,
-                        Workspace &ws, hipStream_t s) {
-    if (n <= 1 || key_bits <= 0) return;
-    const int64_t nb = ceil_div(n, kRsTile);
+template <int ITEMS>
+static void radix_passes(uint64_t *keys, uint32_t *vals, int64_t n, int begin, int key_bits,
+                         Workspace &ws, hipStream_t s) {
+    const int64_t nb = ceil_div(n, ITEMS * kRsBlock);
+    const int passes = (key_bits + kRsDigit<ITEMS> - 1) / kRsDigit<ITEMS>;
+    const int widest = (key_bits + passes - 1) / passes;
+    const bool direct = nb <= kRsDirect;
     uint64_t *k2 = ws.get<uint64_t>("rs_keys", n);
     uint32_t *v2 = ws.get<uint32_t>("rs_vals", n);
-    int32_t *hist = ws.get<int32_t>("rs_hist", 256 * nb);
-    int64_t *offs = ws.get<int64_t>("rs_offs", 256 * nb + 1);
+    int32_t *hist = ws.get<int32_t>("rs_hist", nb << widest);
+    int64_t *offs = direct ? nullptr : ws.get<int64_t>("rs_offs", (nb << widest) + 1);
     uint64_t *ka = keys, *kb = k2;
     uint32_t *va = vals, *vb = v2;
-    const int passes = (key_bits + 7) / 8;
-    for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
-        k_rs_hist<<<(unsigned)nb, kRsBlock, 0, s>>>(ka, n, shift, hist, nb);
+    for (int p = 0, done = 0; p < passes; ++p) {
+        const int bits = (key_bits - done + passes - p - 1) / (passes - p);
+        const int shift = begin + done, bins = 1 << bits;
+        k_rs_hist<ITEMS><<<(unsigned)nb, kRsBlock, sizeof(int32_t) * bins, s>>>(
+            ka, n, shift, bins, direct, hist, nb);
         BT_CHECK_LAUNCH();
-        scan_exclusive_i32_to_i64(hist, offs, 256 * nb, ws, s);
-        k_rs_scatter<<<(unsigned)nb, kRsBlock, 0, s>>>(ka, va, kb, vb, n, shift, offs, nb);
+        if (!direct) scan_exclusive_i32_to_i64(hist, offs, nb << bits, ws, s);
+        k_rs_scatter<ITEMS><<<(unsigned)nb, kRsBlock, sizeof(int32_t) * (kRsWaves + 1) * bins, s>>>(
+            ka, va, kb, vb, n, shift, bits, hist, offs, nb);
         BT_CHECK_LAUNCH();
         std::swap(ka, kb);
         std::swap(va, vb);
+        done += bits;
     }
     if (ka != keys) {
         BT_HIP(hipMemcpyAsync(keys, ka, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
         BT_HIP(hipMemcpyAsync(vals, va, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
     }
+}
+
+void radix_sort_u64_u32(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, Workspace &ws,
+                        hipStream_t s, int begin) {
+    if (n <= 1 || key_bits <= 0) return;
+    if (n >> 32) throw Error{BT_EOVERFLOW, "too many elements to sort"};
+    if (n <= kRsSmall) radix_passes<4>(keys, vals, n, begin, key_bits, ws, s);
+    else radix_passes<16>(keys, vals, n, begin, key_bits, ws, s);
 }
 
 }  // namespace bt

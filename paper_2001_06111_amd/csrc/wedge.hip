@@ -271,14 +271,28 @@ __global__ void k_supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m) {
         sup[e] = (int64_t)(supl[e] & 0xffffffffu);
 }
 
-// Sum of the supports (low halves of the packed words).
-__global__ void k_support_total(const uint64_t *supl, int64_t m, unsigned long long *out) {
+// Sum of the supports (low halves of the packed words), and the supports if
+// asked for.  One atomic a workgroup and few workgroups: an atomic a wave, on
+// one address, took 200 us at 16,384 waves.
+constexpr int kTotalBlock = 512;
+__global__ __launch_bounds__(kTotalBlock) void k_support_total(const uint64_t *supl, int64_t m,
+                                                               int64_t *sup,
+                                                               unsigned long long *out) {
+    __shared__ unsigned long long part[kTotalBlock / kWave];
     unsigned long long acc = 0;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
-         e += (int64_t)gridDim.x * blockDim.x)
-        acc += supl[e] & 0xffffffffu;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t v = supl[e] & 0xffffffffu;
+        if (sup) sup[e] = (int64_t)v;
+        acc += v;
+    }
     acc = wave_sum(acc);
-    if (lane_id() == 0 && acc) atomicAdd(out, acc);
+    if (lane_id() == 0) part[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kTotalBlock / kWave; ++w) acc += part[w];
+        if (acc) atomicAdd(out, acc);
+    }
 }
 
 __global__ void k_link_counts(const uint64_t *supl, int64_t m, int32_t *cnt) {
@@ -341,7 +355,6 @@ template <bool DENSE>
 void launch_wedge(const WedgeArgs &A, const WedgeTask *tasks, int64_t n, int wg_per_cu,
                   hipStream_t s) {
     if (n <= 0) return;
-    zero_bytes(A.queue, sizeof(int64_t), s);
     int dev = 0, cus = 0;
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -371,28 +384,28 @@ void supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m, hipStream_t s) {
     BT_CHECK_LAUNCH();
 }
 
-void check_butterfly_total(const uint64_t *supl, int64_t m, const int64_t *butterflies,
-                           Workspace &ws, hipStream_t s) {
-    if (m <= 0) return;
-    unsigned long long *tot = ws.get<unsigned long long>("bf_check", 1);
-    zero_bytes(tot, sizeof *tot, s);
-    k_support_total<<<grid_for(m, 256, 4096), 256, 0, s>>>(supl, m, tot);
-    BT_CHECK_LAUNCH();
-    int64_t *h = ws.host(2);
-    BT_HIP(hipMemcpyAsync(h, tot, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    BT_HIP(hipMemcpyAsync(h + 1, butterflies, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+int64_t check_butterfly_total(const uint64_t *supl, int64_t m, int64_t *sums, int64_t *sup,
+                              Workspace &ws, hipStream_t s, uint64_t *next) {
+    int64_t *h = ws.host(3);
+    if (m > 0) {
+        k_support_total<<<grid_for(m, kTotalBlock, 1024), kTotalBlock, 0, s>>>(
+            supl, m, sup, reinterpret_cast<unsigned long long *>(sums + 1));
+        BT_CHECK_LAUNCH();
+    }
+    BT_HIP(hipMemcpyAsync(h, sums, (next ? 3 : 2) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
-    if (h[0] != 4 * h[1])
+    if (h[1] != 4 * h[0])
         throw Error{BT_EDEVICE, "butterfly totals disagree: supports sum to " +
-                                    std::to_string(h[0]) + ", blooms give 4 x " +
-                                    std::to_string(h[1])};
+                                    std::to_string(h[1]) + ", blooms give 4 x " +
+                                    std::to_string(h[0])};
+    if (next) *next = (uint64_t)h[2];
+    return h[0];
 }
 
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
                  hipStream_t s, const Components *comps) {
     static_assert(kSmemBytes <= 65536, "LDS budget");
-    int64_t *queue = ws.get<int64_t>("wedge_queue", 1);
-    WedgeArgs A = make_args(r, ix.supl, ix.butterflies, queue);
+    WedgeArgs A = make_args(r, ix.supl, ix.sums, ix.queue);
     A.cursor = ix.cursor;
     A.bwoff = ix.bwoff;
     A.bk = ix.bk;
@@ -404,11 +417,10 @@ void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspac
             k_graph_bases<<<1, 1024, 0, s>>>(r.off, r.wpre, r.n_lower, *comps, ix.base, ix.cursor);
             BT_CHECK_LAUNCH();
             A.vgraph = r.vgraph;
-        } else {
-            zero_bytes(ix.base, sizeof(uint64_t), s);
         }
     }
     launch_wedge<true>(A, t.dense, t.n_dense, r.tp.wedge_wg_per_cu, s);
+    A.queue += 1;
     launch_wedge<false>(A, t.hash, t.n_hash, r.tp.wedge_wg_per_cu, s);
     const int32_t nc = ix.base ? ix.n_graphs : 1;
     k_bloom_sentinel<<<grid_for(nc, 256, 256), 256, 0, s>>>(ix.cursor, nc, ix.bwoff);

@@ -74,3 +74,28 @@ def test_support(g):
                                    (40000, 100, 500, 1000)])
 def test_wedges_in_one_share_of_the_degrees(shape):
     test_support(_skewed(*shape, "skewed"))
+
+
+@pytest.mark.parametrize("m", [1, 1023, 1024, 1025, 65536, 65537, 262143, 262145])
+def test_sizes_of_the_sorts(m):
+    f = max(1, m // 10)
+    test_support(synth.chung_lu(max(3, f // 2), max(3, f), m, 2.1, 2.4, f, f, m)
+                 if m > 1 else synth.uniform(3, 4, 1, 0))
+
+
+@pytest.mark.parametrize("where", [0, 1, 4999, 9997, 9998])
+def test_order_inside_and_between_rows(where):
+    """Lower ids may start over at a row's beginning only, empty rows or not."""
+    row_ptr = np.array([0, 0, 5000, 5000, 5000, 10000, 10000])
+    col = np.concatenate([np.arange(5000), np.arange(5000)]).astype(np.int32)
+    g = synth.Graph(6, 5000, row_ptr, col, "two rows")
+    test_support(g)
+    bad = col.copy()
+    bad[where + 1 if where != 4999 else 5001] = bad[where if where != 4999 else 5000]
+    with pytest.raises(binding.BtError) as ei:
+        binding.bt_support(upload(synth.Graph(6, 5000, row_ptr, bad, "bad")))
+    assert ei.value.status == binding.BT_EINVAL
+    for r in (row_ptr + 1, row_ptr[::-1].copy(), np.array([0, 0, 5000, 4000, 5000, 10000, 9999])):
+        with pytest.raises(binding.BtError) as ei:
+            binding.bt_support(upload(synth.Graph(6, 5000, r, col, "bad rows")))
+        assert ei.value.status == binding.BT_EINVAL
