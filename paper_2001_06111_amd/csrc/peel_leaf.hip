@@ -17,7 +17,10 @@
 // item, link, bloom state (a returning memory atomic) in phase A and work
 // item, bloom state, wedge records in phase B, at 4 cycles an instruction.
 // Counting the kills in an LDS hash table instead of memory did not shorten
-// it.  512 graphs of 200 to 16,000 edges in one batch: 63.3 ms grid-wide,
+// it, nor did the links' ends in LDS by more than 3%.  An edge that crosses
+// the level waits in LDS for the end of its wave's phase, as queueing it takes
+// another wait for memory, and phase B has four elements a lane in flight:
+// 192 pool graphs' leaves 40 ms without either, 35 ms so.  512 graphs of 200 to 16,000 edges in one batch: 63.3 ms grid-wide,
 // 19.8 ms so; the 10k-edge uniform graph 0.67 ms and 0.46 ms.
 //
 // The workgroup makes its own link lists (twin and bloom of each wedge of an
@@ -38,6 +41,8 @@ namespace bt {
 namespace {
 
 constexpr int kLeafBlock = 1024;
+constexpr int kAhead = 4;   // elements per lane in flight in phase B
+constexpr int kCross = 96;  // edges a wave holds back until they are queued (at least 64)
 constexpr uint32_t kNoTwin = 0xffffffffu;  // the twin is not peeled here
 // An edge's state: remaining, queued for an even or an odd round (1, 2), removed.
 enum : uint8_t { kRemaining = 0, kRemoved = 3 };
@@ -108,6 +113,24 @@ __device__ __forceinline__ void put_pieces(uint32_t n, uint32_t lo, uint32_t cnt
     }
 }
 
+// The lanes' items of elements t0 + lane, t0 + 64 + lane, ... (see item_of).
+template <int U>
+__device__ __forceinline__ void items_of(bool ok, uint32_t start, uint32_t t0, u64 *mask, int (&j)[U]) {
+    int before = (int)__popcll(__ballot(ok && start < t0));
+    if (lane_id() < U)
+        __hip_atomic_store(&mask[lane_id()], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (ok && start >= t0 && start < t0 + U * kWave)
+        __hip_atomic_fetch_or(&mask[(start - t0) / kWave], 1ull << ((start - t0) % kWave),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const u64 le = lanemask_lt() | (u64(1) << lane_id());
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const u64 m = __hip_atomic_load(&mask[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        j[u] = before + (int)__popcll(m & le) - 1;
+        before += (int)__popcll(m);
+    }
+}
+
 // A bloom's state for the next round: its kills leave it.
 __device__ __forceinline__ u64 settle(u64 state) {
     return (u64)((uint32_t)(state >> 32) - (uint32_t)state) << 32;
@@ -137,11 +160,13 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
     uint8_t *const stt = reinterpret_cast<uint8_t *>(sup + K.ecap);
     __shared__ int32_t s_job, s_min;
     __shared__ uint32_t s_nf[2], s_ni[2], s_multi[2];
-    __shared__ u64 s_mask[kLeafBlock / kWave];
+    __shared__ u64 s_mask[kLeafBlock / kWave][kAhead];
+    __shared__ uint16_t s_cross[kLeafBlock / kWave][kCross];
     __shared__ uint32_t s_scan[kLeafBlock / kWave + 1];
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int wv = tid / kWave, nwv = nthr / kWave;
-    u64 *const mask = &s_mask[wv];
+    u64 *const mask = s_mask[wv];
+    uint16_t *const cross = s_cross[wv];
     uint32_t upd = 0, unb = 0, touch = 0, visits = 0;  // of this lane
     u64 rounds = 0;  // thread 0's
     int32_t max_level = 0;
@@ -245,6 +270,25 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                        });
         };
 
+        // An edge that crosses the level is noted (in LDS) and queued with
+        // others at the end of its wave's phase: queueing waits for memory.
+        uint32_t n_cross = 0;
+        const auto queue_crossed = [&](int q, int32_t level) {
+            for (uint32_t i = 0; i < n_cross; i += kWave) {
+                const bool has = i + lane_id() < n_cross;
+                push_front(has, has ? cross[i + lane_id()] : 0u, q, level);
+            }
+            n_cross = 0;
+        };
+        const auto crossed = [&](bool pred, uint32_t t, int q, int32_t level) {
+            const u64 who = __ballot(pred);
+            if (!who) return;
+            const uint32_t n = (uint32_t)__popcll(who);
+            if (n_cross + n > kCross) queue_crossed(q, level);
+            if (pred) cross[n_cross + (uint32_t)__popcll(who & lanemask_lt())] = (uint16_t)t;
+            n_cross += n;
+        };
+
         int32_t levels = 0;
         int r = 0;
         while (true) {
@@ -328,7 +372,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                             const bool dec = alive && t != kNoTwin && s != cur && d > 0;
                             int32_t o = 0;
                             if (dec) o = atomicSub(&sup[t], d);
-                            push_front(dec && o > level && o - d <= level, t, q, level);
+                            crossed(dec && o > level && o - d <= level, t, q, level);
                             upd += dec ? 1 : 0;
                             // The bloom's first kill this round queues it.
                             const bool first = alive && (uint32_t)old == 0 && kb > 1;
@@ -349,6 +393,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                             }
                         }
                     }
+                    queue_crossed(q, level);
                 }
                 __syncthreads();
                 const uint32_t ni = s_ni[p];
@@ -376,45 +421,56 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                         const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
                         const uint32_t start = inc - n;
                         const uint32_t total = wave_last(inc);
-                        for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
-                            const int j = item_of(ok, start, t0, mask);
-                            const uint32_t x = t0 + lane_id();
-                            const bool act = x < total;
-                            const uint32_t w = J.w0 + __shfl((it.y >> 6) - start, j, kWave) + x;
-                            uint32_t a = kFixedBit, b = kFixedBit;
-                            if (act) {
-                                a = (uint32_t)A.wea[w];
-                                b = (uint32_t)A.web[w];
-                            }
-                            const int32_t cj = __shfl((int32_t)(uint32_t)state, j, kWave);
-                            const bool oa = !(a & kFixedBit), ob = !(b & kFixedBit);
-                            const uint32_t la = a - (uint32_t)e0, lb = b - (uint32_t)e0;
-                            const uint8_t sa = oa ? stt[la] : (uint8_t)kRemaining;
-                            const uint8_t sb = ob ? stt[lb] : (uint8_t)kRemaining;
-                            const bool live = act && (sa == kRemaining || sa == nxt) &&
-                                              (sb == kRemaining || sb == nxt);
-                            const bool da = live && oa, db = live && ob;
-                            bool f1 = false, f2 = false;
-                            if (UNIT) {
-                                // Without batch bloom processing: one unit per
-                                // kill; the step from level + 1 crosses.
-                                for (int32_t c = 0; c < (live ? cj : 0); ++c) {
-                                    if (da) f1 |= atomicSub(&sup[la], 1) == level + 1;
-                                    if (db) f2 |= atomicSub(&sup[lb], 1) == level + 1;
+                        for (uint32_t t0 = 0; t0 < total; t0 += kAhead * kWave) {
+                            int j[kAhead];
+                            uint32_t a[kAhead], b[kAhead];
+                            items_of(ok, start, t0, mask, j);
+#pragma unroll
+                            for (int u = 0; u < kAhead; ++u) {
+                                const uint32_t x = t0 + u * kWave + lane_id();
+                                a[u] = b[u] = kFixedBit;
+                                if (t0 + u * kWave >= total) continue;
+                                const uint32_t w =
+                                    J.w0 + __shfl((it.y >> 6) - start, j[u], kWave) + x;
+                                if (x < total) {
+                                    a[u] = (uint32_t)A.wea[w];
+                                    b[u] = (uint32_t)A.web[w];
                                 }
-                                upd += (uint32_t)((da ? cj : 0) + (db ? cj : 0));
-                            } else {
-                                int32_t o1 = 0, o2 = 0;
-                                if (da) o1 = atomicSub(&sup[la], cj);
-                                if (db) o2 = atomicSub(&sup[lb], cj);
-                                f1 = da && o1 > level && o1 - cj <= level;
-                                f2 = db && o2 > level && o2 - cj <= level;
-                                upd += (da ? 1u : 0u) + (db ? 1u : 0u);
-                                unb += (uint32_t)((da ? cj - 1 : 0) + (db ? cj - 1 : 0));
                             }
-                            touch += live ? 1 : 0;
-                            push_front(f1, la, q, level);
-                            push_front(f2, lb, q, level);
+#pragma unroll
+                            for (int u = 0; u < kAhead; ++u) {
+                                if (t0 + u * kWave >= total) break;
+                                const bool act = t0 + u * kWave + lane_id() < total;
+                                const int32_t cj = __shfl((int32_t)(uint32_t)state, j[u], kWave);
+                                const bool oa = !(a[u] & kFixedBit), ob = !(b[u] & kFixedBit);
+                                const uint32_t la = a[u] - (uint32_t)e0, lb = b[u] - (uint32_t)e0;
+                                const uint8_t sa = oa ? stt[la] : (uint8_t)kRemaining;
+                                const uint8_t sb = ob ? stt[lb] : (uint8_t)kRemaining;
+                                const bool live = act && (sa == kRemaining || sa == nxt) &&
+                                                  (sb == kRemaining || sb == nxt);
+                                const bool da = live && oa, db = live && ob;
+                                bool f1 = false, f2 = false;
+                                if (UNIT) {
+                                    // Without batch bloom processing: one unit per
+                                    // kill; the step from level + 1 crosses.
+                                    for (int32_t c = 0; c < (live ? cj : 0); ++c) {
+                                        if (da) f1 |= atomicSub(&sup[la], 1) == level + 1;
+                                        if (db) f2 |= atomicSub(&sup[lb], 1) == level + 1;
+                                    }
+                                    upd += (uint32_t)((da ? cj : 0) + (db ? cj : 0));
+                                } else {
+                                    int32_t o1 = 0, o2 = 0;
+                                    if (da) o1 = atomicSub(&sup[la], cj);
+                                    if (db) o2 = atomicSub(&sup[lb], cj);
+                                    f1 = da && o1 > level && o1 - cj <= level;
+                                    f2 = db && o2 > level && o2 - cj <= level;
+                                    upd += (da ? 1u : 0u) + (db ? 1u : 0u);
+                                    unb += (uint32_t)((da ? cj - 1 : 0) + (db ? cj - 1 : 0));
+                                }
+                                touch += live ? 1 : 0;
+                                crossed(f1, la, q, level);
+                                crossed(f2, lb, q, level);
+                            }
                         }
                         // A bloom of one piece is settled by its reader.
                         if (ok && !(it.x & 0x80000000u)) {
@@ -422,6 +478,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
                             visits += 1;
                         }
                     }
+                    queue_crossed(q, level);
                 }
                 __syncthreads();
                 if (multi) {
