@@ -67,7 +67,7 @@ public:
     int64_t *host(int n);  // pinned, at least n int64; valid until a larger request
     void release();
     size_t bytes() const;
-    // Side stream k (0 or 1), made on first use and kept: for launches that
+    // Side stream k (0 to 2), made on first use and kept: for launches that
     // may run beside each other.  Work on it is ordered after and before the
     // caller's stream by events, so nothing outlives a call on it.
     hipStream_t side(int k);
@@ -96,7 +96,7 @@ private:
     int64_t *host_ = nullptr;
     int host_cap_ = 0;
     hipStream_t stream_ = nullptr;
-    hipStream_t side_[2] = {};
+    hipStream_t side_[3] = {};
     std::vector<int64_t *> old_host_;  // outgrown host scratch of a bound workspace
     char *arena_ = nullptr;
     size_t arena_cap_ = 0, arena_top_ = 0;

@@ -47,10 +47,17 @@ constexpr uint32_t kNoTwin = 0xffffffffu;  // the twin is not peeled here
 // An edge's state: remaining, queued for an even or an odd round (1, 2), removed.
 enum : uint8_t { kRemaining = 0, kRemoved = 3 };
 
-struct LeafArgs {
+// Jobs [j0, j1) of a list, handed out through `queue`.
+struct LeafList {
     const LeafJob *jobs;
     const int32_t *order;  // jobs in queue order (null: as they are)
     int32_t *queue;
+    int32_t j0, j1;
+};
+
+struct LeafArgs {
+    LeafList list[kLeafLists];  // taken in turn
+    int32_t n_lists;
     const int32_t *wea, *web, *wbl;
     const uint32_t *bwoff;
     const int32_t *bk;  // initial bloom numbers
@@ -68,11 +75,11 @@ struct LeafArgs {
 
 // First slots of the job's regions of the work lists: an edge has at most
 // one item more than its links / 64, a bloom one more than its wedges / 64.
-__device__ __forceinline__ int64_t front_base(const LeafJob &J, int32_t j) {
-    return (int64_t)J.e0 + J.w0 / 32 + j;
+__device__ __forceinline__ int64_t front_base(const LeafJob &J) {
+    return (int64_t)J.e0 + J.w0 / 32 + J.id;
 }
-__device__ __forceinline__ int64_t items_base(const LeafJob &J, int32_t j) {
-    return (int64_t)J.b0 + J.w0 / 64 + j;
+__device__ __forceinline__ int64_t items_base(const LeafJob &J) {
+    return (int64_t)J.b0 + J.w0 / 64 + J.id;
 }
 
 // Each lane asks for cnt consecutive slots of a counter in LDS.  Must be
@@ -147,18 +154,24 @@ struct LeafClass {
 };
 constexpr LeafClass kLeafClasses[] = {
     {(int)kLeafCap, 1024, 512, 1024}, {7168, 512, 256, 512}, {2048, 256, 128, 256}};
-constexpr int kNumLeafClasses = 3;
+static_assert(sizeof kLeafClasses / sizeof *kLeafClasses == kNumLeafClasses, "a queue each");
+
+int leaf_class(int64_t edges) {
+    int c = 0;
+    while (c + 1 < kNumLeafClasses && edges <= kLeafClasses[c + 1].ecap) ++c;
+    return c;
+}
 
 template <bool UNIT>
-__global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0, int32_t j1,
-                                                          LeafClass K) {
+__global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass K) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const uint32_t front_lds = K.front_lds, items_lds = K.items_lds;
     uint2 *const lf0 = reinterpret_cast<uint2 *>(smem_raw), *const lf1 = lf0 + front_lds;
     uint2 *const li = lf1 + front_lds;
     int32_t *const sup = reinterpret_cast<int32_t *>(li + items_lds);
     uint8_t *const stt = reinterpret_cast<uint8_t *>(sup + K.ecap);
-    __shared__ int32_t s_job, s_min;
+    __shared__ LeafJob s_job;
+    __shared__ int32_t s_min;
     __shared__ uint32_t s_nf[2], s_ni[2], s_multi[2];
     __shared__ u64 s_mask[kLeafBlock / kWave][kAhead];
     __shared__ uint16_t s_cross[kLeafBlock / kWave][kCross];
@@ -170,19 +183,28 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, int32_t j0
     uint32_t upd = 0, unb = 0, touch = 0, visits = 0;  // of this lane
     u64 rounds = 0;  // thread 0's
     int32_t max_level = 0;
+    int32_t list = 0;  // thread 0's
 
     while (true) {
         __syncthreads();
-        if (tid == 0) s_job = j0 + atomicAdd(A.queue, 1);
+        if (tid == 0) {
+            s_job.ne = -1;
+            for (; list < A.n_lists; ++list) {
+                const LeafList &L = A.list[list];
+                const int32_t i = L.j0 + atomicAdd(L.queue, 1);
+                if (i >= L.j1) continue;
+                s_job = L.jobs[L.order ? L.order[i] : i];
+                break;
+            }
+        }
         __syncthreads();
-        if (s_job >= j1) break;
-        const int32_t jb = A.order ? A.order[s_job] : s_job;
-        const LeafJob J = A.jobs[jb];
+        const LeafJob J = s_job;
+        if (J.ne < 0) break;
         const int32_t ne = J.ne, e0 = J.e0;
         if (ne <= 0 || ne > K.ecap) continue;  // the host queues none of these
         uint2 *const link = A.link + 2 * (int64_t)J.w0;
-        uint2 *const fr0 = A.front[0] + front_base(J, jb), *const fr1 = A.front[1] + front_base(J, jb);
-        uint2 *const items = A.items + items_base(J, jb);
+        uint2 *const fr0 = A.front[0] + front_base(J), *const fr1 = A.front[1] + front_base(J);
+        uint2 *const items = A.items + items_base(J);
 
         // Links: counts (in LDS, where the supports go later), their prefix
         // sums, the links, and where each edge's end.
@@ -525,7 +547,7 @@ __global__ void k_leaf_jobs(const int64_t *off, int32_t ng, const uint64_t *base
         J.b0 = (uint32_t)(base[g] >> 32);
         J.nb = (uint32_t)(cursor[g] >> 32) - J.b0;
         J.graph = g;
-        J.pad = 0;
+        J.id = g;
         jobs[g] = J;
         nb += J.nb;
         nw += J.nw;
@@ -556,10 +578,9 @@ int64_t peel_leaf_bytes(int64_t m, int64_t cap_b, int64_t cap_w, int64_t graphs)
 namespace {
 
 // Buffers of a leaf peel over arrays of m edges, n_b blooms and n_w wedges.
-LeafArgs leaf_args(int64_t m, int64_t n_b, int64_t n_w, int32_t n_jobs, int32_t n_roots,
-                   const int32_t *bk, Workspace &ws, hipStream_t s) {
+LeafArgs leaf_args(int64_t m, int64_t n_b, int64_t n_w, int64_t n_jobs, int32_t n_roots,
+                   Workspace &ws, hipStream_t s) {
     LeafArgs A{};
-    A.bk = bk;
     A.bs = ws.get<u64>("lf_bs", n_b + 1);
     A.link = ws.get<uint2>("lf_link", 2 * n_w + 1);
     A.ends = ws.get<uint32_t>("lf_ends", m);
@@ -570,20 +591,38 @@ LeafArgs leaf_args(int64_t m, int64_t n_b, int64_t n_w, int32_t n_jobs, int32_t 
     A.ctl = ws.get<LeafCtl>("lf_ctl", 1);
     zero_bytes(A.ctl, sizeof(LeafCtl), s);
     zero_bytes(A.glevels, sizeof(int32_t) * n_roots, s);
-    k_leaf_state<<<grid_for(n_b + 1, 256, 8192), 256, 0, s>>>(bk, n_b + 1, A.bs);
-    BT_CHECK_LAUNCH();
     return A;
 }
 
-// Runs the jobs, which come by class (size(j): edges of the j-th in queue
-// order), and reads the counters back.
-template <typename Size>
-void run_leaves(LeafArgs A, int32_t n_jobs, Size &&size, bool unit_updates, int32_t n_roots,
-                std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc, LeafCtl &done,
-                Workspace &ws, hipStream_t s) {
-    int dev = 0, cus = 0;
+void leaf_state(const LeafArgs &A, int64_t b0, int64_t n, hipStream_t s) {
+    k_leaf_state<<<grid_for(n, 256, 8192), 256, 0, s>>>(A.bk + b0, n, A.bs + b0);
+    BT_CHECK_LAUNCH();
+}
+
+// Launches class c over A's lists by at most `most` workgroups.
+void launch_leaves(const LeafArgs &A, int c, bool unit_updates, int most, hipStream_t s) {
+    const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
+    const LeafClass &K = kLeafClasses[c];
+    int dev = 0, cus = 0, occ = 0;
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kLeafClasses[0].lds()));
+    BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, K.threads, K.lds()));
+    int64_t n = 0;
+    for (int l = 0; l < A.n_lists; ++l) n += A.list[l].j1 - A.list[l].j0;
+    const int64_t grid = std::min<int64_t>({n, (int64_t)cus * std::max(1, occ), most});
+    if (grid <= 0) return;
+    kern<<<(unsigned)grid, K.threads, K.lds(), s>>>(A, K);
+    BT_CHECK_LAUNCH();
+}
+
+// Runs lists of jobs (lists[l][c]: list l's jobs of class c) to their end and
+// reads the counters back.  `early` (nullable): the end of a launch that has
+// taken from them already.
+void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hipEvent_t early,
+                bool unit_updates, int32_t n_roots, std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc,
+                LeafCtl &done, Workspace &ws, hipStream_t s) {
     hipEvent_t ev0, ev1;
     BT_HIP(hipEventCreate(&ev0));
     BT_HIP(hipEventCreate(&ev1));
@@ -600,35 +639,34 @@ void run_leaves(LeafArgs A, int32_t n_jobs, Size &&size, bool unit_updates, int3
                 if (e[c]) (void)hipEventDestroy(e[c]);
         }
     } ev_free{ev0, ev1, joins};
-    const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
-    BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)kLeafClasses[0].lds()));
     BT_HIP(hipEventRecord(ev0, s));
-    int32_t a = 0;
+    int last = -1;
+    int64_t n_jobs = 0;
+    const auto jobs_of = [&](int c) {
+        int64_t n = 0;
+        for (const auto &l : lists) n += l[(size_t)c].j1 - l[(size_t)c].j0;
+        return n;
+    };
     for (int c = 0; c < kNumLeafClasses; ++c) {
-        const int64_t below = c + 1 < kNumLeafClasses ? kLeafClasses[c + 1].ecap : 0;
-        int32_t b = a;
-        while (b < n_jobs && size(b) > below) ++b;
-        if (b > a) {
-            const LeafClass &K = kLeafClasses[c];
-            int occ = 0;
-            BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, K.threads,
-                                                                K.lds()));
-            const int grid = std::min<int>(b - a, cus * std::max(1, occ));
-            const hipStream_t cs = b == n_jobs ? s : ws.side(c);  // the last class stays on s
-            A.queue = &A.ctl->queue[c];
-            if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
-            kern<<<grid, K.threads, K.lds(), cs>>>(A, a, b, K);
-            BT_CHECK_LAUNCH();
-            if (cs != s) {
-                BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
-                BT_HIP(hipEventRecord(joins[c], cs));
-            }
+        if (jobs_of(c)) last = c;
+        n_jobs += jobs_of(c);
+    }
+    for (int c = 0; c < kNumLeafClasses; ++c) {
+        if (!jobs_of(c)) continue;
+        A.n_lists = 0;
+        for (const auto &l : lists)
+            if (l[(size_t)c].j1 > l[(size_t)c].j0) A.list[A.n_lists++] = l[(size_t)c];
+        const hipStream_t cs = c == last ? s : ws.side(c);  // the last class stays on s
+        if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
+        launch_leaves(A, c, unit_updates, INT_MAX, cs);
+        if (cs != s) {
+            BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
+            BT_HIP(hipEventRecord(joins[c], cs));
         }
-        a = b;
     }
     for (hipEvent_t e : joins)
         if (e) BT_HIP(hipStreamWaitEvent(s, e, 0));
+    if (early) BT_HIP(hipStreamWaitEvent(s, early, 0));
     BT_HIP(hipEventRecord(ev1, s));
     LeafCtl *hc =
         reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (n_roots + 1) / 2)));
@@ -639,8 +677,8 @@ void run_leaves(LeafArgs A, int32_t n_jobs, Size &&size, bool unit_updates, int3
     float t = 0.f;
     BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
     if (std::getenv("BT_PEEL_VERBOSE"))
-        std::fprintf(stderr, "[peel] leaves: %d of up to %lld edges: %.2f ms, %llu rounds\n", n_jobs,
-                     (long long)size(0), (double)t, hc->rounds);
+        std::fprintf(stderr, "[peel] leaves: %lld: %.2f ms, %llu rounds\n", (long long)n_jobs,
+                     (double)t, hc->rounds);
     pc.kernel_ms += t;
     pc.rounds += (int64_t)hc->rounds;
     pc.updates += (int64_t)hc->updates;
@@ -660,9 +698,10 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     const int32_t ng = (int32_t)off.size() - 1;
     const int64_t m = off[(size_t)ng];
     if (m == 0) return;
-    LeafArgs A = leaf_args(m, ix.cap_b, ix.cap_w, ng, ng, ix.bk, ws, s);
+    LeafArgs A = leaf_args(m, ix.cap_b, ix.cap_w, ng, ng, ws, s);
     LeafJob *jobs = ws.get<LeafJob>("lf_jobs", ng);
-    A.jobs = jobs;
+    A.bk = ix.bk;
+    leaf_state(A, 0, ix.cap_b + 1, s);
     A.wea = ix.wea;
     A.web = ix.web;
     A.wbl = ix.wbl;
@@ -677,8 +716,15 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     std::vector<int32_t> levels((size_t)ng, 0);
     int32_t max_level = 0;
     LeafCtl done;
-    run_leaves(A, ng, [&](int32_t j) { return off[(size_t)j + 1] - off[(size_t)j]; }, unit_updates,
-               ng, levels, max_level, pc, done, ws, s);
+    // The graphs come in decreasing size, so by class.
+    std::vector<std::vector<LeafList>> lists(1);
+    for (int32_t c = 0, a = 0; c < kNumLeafClasses; ++c) {
+        int32_t b = a;
+        while (b < ng && leaf_class(off[(size_t)b + 1] - off[(size_t)b]) == c) ++b;
+        lists[0].push_back(LeafList{jobs, nullptr, &A.ctl->queue[0][c], a, b});
+        a = b;
+    }
+    run_leaves(A, lists, nullptr, unit_updates, ng, levels, max_level, pc, done, ws, s);
     pc.launches += 1;
     pc.max_phi = max_level;
     for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);
@@ -686,41 +732,104 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     ix.n_w = (int64_t)done.wedges;
 }
 
-void peel_leaf_jobs(const LeafPool &pool, int64_t *phi_out, bool unit_updates,
-                    std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc,
-                    Workspace &ws, hipStream_t s) {
-    const int32_t n = (int32_t)pool.leaves.size(), roots = (int32_t)levels.size();
-    // Queue order: by launch, then the heaviest first.
-    const auto cls = [&](int32_t j) {
-        int c = 0;
-        while (c + 1 < kNumLeafClasses && pool.leaves[(size_t)j].ne <= kLeafClasses[c + 1].ecap) ++c;
-        return c;
-    };
-    std::vector<int32_t> order((size_t)n);
-    for (int32_t j = 0; j < n; ++j) order[(size_t)j] = j;
-    std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        const int cx = cls(x), cy = cls(y);
-        if (cx != cy) return cx < cy;
-        const uint32_t wx = pool.leaves[(size_t)x].work, wy = pool.leaves[(size_t)y].work;
-        return wx != wy ? wx > wy : x < y;
-    });
-    LeafArgs A = leaf_args(pool.m, pool.n_b, pool.n_w, n, roots, pool.bk, ws, s);
-    LeafJob *jobs = ws.get<LeafJob>("lf_jobs", n);
-    int32_t *dorder = ws.get<int32_t>("lf_order", n);
-    BT_HIP(hipMemcpyAsync(jobs, pool.jobs.data(), sizeof(LeafJob) * n, hipMemcpyHostToDevice, s));
-    BT_HIP(hipMemcpyAsync(dorder, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-    A.jobs = jobs;
-    A.order = dorder;
+// State of a pool's leaves while they are run in lists.
+struct LeafRun::State {
+    LeafArgs A;
+    std::vector<std::vector<LeafList>> lists;
+    size_t taken = 0;       // leaves in lists
+    int64_t b_taken = 0;    // blooms of theirs
+    hipEvent_t early = nullptr;  // the end of an early launch
+    hipStream_t stream = nullptr;
+};
+
+LeafRun::LeafRun(const LeafPool &pool, int64_t m, int64_t n_w, int64_t *phi_out, bool unit_updates,
+                 int32_t n_roots, Workspace &ws, hipStream_t s)
+    : pool_(pool), unit_(unit_updates), roots_(n_roots), ws_(ws), s_(s), st_(new State()) {
+    LeafArgs &A = st_->A;
+    // A leaf holds an edge or more, a bloom a wedge or more; a depth's blooms
+    // have a slot more than there are.
+    A = leaf_args(m, n_w + 64, n_w, m, n_roots, ws, s);
+    A.bk = pool.bk;
     A.wea = pool.wea;
     A.web = pool.web;
     A.wbl = pool.wbl;
     A.bwoff = pool.bwoff;
     A.oid = pool.oid;
     A.phi_out = phi_out;
+}
+
+LeafRun::~LeafRun() {
+    if (st_->early) {
+        (void)hipStreamSynchronize(st_->stream);  // its buffers go with the workspace
+        (void)hipEventDestroy(st_->early);
+    }
+}
+
+// The leaves that are in no list yet, as a list: by class, then the heaviest first.
+void LeafRun::take() {
+    State &S = *st_;
+    const int l = (int)S.lists.size();
+    const size_t n = pool_.leaves.size() - S.taken;
+    std::vector<int32_t> order(n);
+    for (size_t j = 0; j < n; ++j) order[j] = (int32_t)j;
+    const auto leaf = [&](int32_t j) -> const SplitJob & { return pool_.leaves[S.taken + (size_t)j]; };
+    std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        const int cx = leaf_class(leaf(x).ne), cy = leaf_class(leaf(y).ne);
+        if (cx != cy) return cx < cy;
+        return leaf(x).work != leaf(y).work ? leaf(x).work > leaf(y).work : x < y;
+    });
+    const char *const names[kLeafLists][2] = {
+        {"lf_jobs", "lf_order"}, {"lf_jobs1", "lf_order1"}, {"lf_jobs2", "lf_order2"}};
+    LeafJob *jobs = ws_.get<LeafJob>(names[l][0], (int64_t)n);
+    int32_t *dorder = ws_.get<int32_t>(names[l][1], (int64_t)n);
+    BT_HIP(hipMemcpyAsync(jobs, pool_.jobs.data() + S.taken, sizeof(LeafJob) * n,
+                          hipMemcpyHostToDevice, s_));
+    BT_HIP(hipMemcpyAsync(dorder, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s_));
+    BT_HIP(hipStreamSynchronize(s_));  // the host arrays are read until here
+    if (pool_.n_b > S.b_taken) leaf_state(S.A, S.b_taken, pool_.n_b - S.b_taken, s_);
+    std::vector<LeafList> list;
+    for (int32_t c = 0, a = 0; c < kNumLeafClasses; ++c) {
+        int32_t b = a;
+        while (b < (int32_t)n && leaf_class(leaf(order[(size_t)b]).ne) == c) ++b;
+        list.push_back(LeafList{jobs, dorder, &S.A.ctl->queue[l][c], a, b});
+        a = b;
+    }
+    S.lists.push_back(std::move(list));
+    S.taken = pool_.leaves.size();
+    S.b_taken = pool_.n_b;
+}
+
+void LeafRun::start(int groups) {
+    State &S = *st_;
+    if (pool_.leaves.size() == S.taken || groups <= 0 || (int)S.lists.size() + 1 >= kLeafLists) return;
+    if (S.early) {
+        if (hipEventQuery(S.early) != hipSuccess) {  // the last ones still run
+            (void)hipGetLastError();
+            return;
+        }
+    } else {
+        BT_HIP(hipEventCreateWithFlags(&S.early, hipEventDisableTiming));
+        S.stream = ws_.side(2);  // the others run classes at the end
+    }
+    take();
+    hipEvent_t ready;
+    BT_HIP(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
+    BT_HIP(hipEventRecord(ready, s_));
+    BT_HIP(hipStreamWaitEvent(S.stream, ready, 0));
+    BT_HIP(hipEventDestroy(ready));
+    LeafArgs A = S.A;
+    A.n_lists = 1;
+    A.list[0] = S.lists.back()[0];
+    launch_leaves(A, 0, unit_, groups, S.stream);
+    BT_HIP(hipEventRecord(S.early, S.stream));
+}
+
+void LeafRun::finish(std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc) {
+    State &S = *st_;
+    if (pool_.leaves.size() > S.taken) take();
+    if (S.lists.empty()) return;
     LeafCtl done;
-    run_leaves(
-        A, n, [&](int32_t j) { return (int64_t)pool.leaves[(size_t)order[(size_t)j]].ne; },
-        unit_updates, roots, levels, max_level, pc, done, ws, s);
+    run_leaves(S.A, S.lists, S.early, unit_, roots_, levels, max_level, pc, done, ws_, s_);
 }
 
 }  // namespace bt

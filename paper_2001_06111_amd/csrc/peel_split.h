@@ -3,6 +3,8 @@
 // regrouping of their results (regroup.hip).
 #pragma once
 
+#include <memory>
+
 #include "peel_common.h"
 
 namespace bt {
@@ -87,10 +89,33 @@ void regroup(const SplitIndex &ix, const SweepResult &sw, const std::vector<Spli
              int depth, int64_t *phi_out, std::vector<int32_t> &levels, int32_t &max_level,
              Regrouped &out, LeafPool &pool, Workspace &ws, hipStream_t s);
 
-// Peels the pool's leaves (peel_leaf.hip); levels[root] grows by each leaf's.
-void peel_leaf_jobs(const LeafPool &pool, int64_t *phi_out, bool unit_updates,
-                    std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc,
-                    Workspace &ws, hipStream_t s);
+// Peels the pool's leaves (peel_leaf.hip).  A leaf does not wait for other
+// parts, so leaves that a depth finds may start beside the deeper sweeps.
+class LeafRun {
+  public:
+    // For a pool of up to m edges and n_w wedges.
+    LeafRun(const LeafPool &pool, int64_t m, int64_t n_w, int64_t *phi_out, bool unit_updates,
+            int32_t n_roots, Workspace &ws, hipStream_t s);
+    ~LeafRun();  // waits for what was started
+    LeafRun(const LeafRun &) = delete;
+    LeafRun &operator=(const LeafRun &) = delete;
+    // Starts the large ones of the leaves found so far, on a stream of their
+    // own and by at most so many workgroups (a compute unit each), unless
+    // earlier ones still run.
+    void start(int groups);
+    // Peels what is left to its end; levels[root] grows by each leaf's.
+    void finish(std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc);
+
+  private:
+    struct State;
+    void take();
+    const LeafPool &pool_;
+    bool unit_;
+    int32_t roots_;
+    Workspace &ws_;
+    hipStream_t s_;
+    std::unique_ptr<State> st_;
+};
 
 // Supports, link counts and links of a regrouped depth's jobs.
 void regroup_links(const Regrouped &g, uint64_t *supl, int64_t *link_off, uint3 *link,

@@ -1292,7 +1292,7 @@ int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bo
         t += 4 * n_w;                                  // wedge_k
         t += 44 * m + 4 * n_w + 12 * n_w;              // regroup: edges, parts, sort scratch
         t += 2 * (12 * n_w + 8 * nb) + 24 * n_w + 24 * m;  // next depths, their links
-        t += 16 * n_w + 8 * nb + 16 * (m + n_w / 32) + 8 * (nb + n_w / 64) + 8 * m;  // leaves
+        t += 16 * n_w + 8 * nb + 16 * (2 * m + n_w / 32) + 8 * (nb + n_w / 64 + m) + 8 * m;  // leaves
     }
     t += 64 * 256 + 4096;
     return t + t / 8;
@@ -1347,6 +1347,10 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         return;
     }
     LeafPool pool;
+    std::unique_ptr<LeafRun> leaves;
+    int dev = 0, cus = 0;
+    BT_HIP(hipGetDevice(&dev));
+    BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     for (int depth = 0; !jobs.empty(); ++depth) {
         const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);
         // The links are not needed after the first sweep; their memory (24
@@ -1359,7 +1363,14 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
                          g.jobs.size(), (long long)g.m, (long long)g.n_w, pool.leaves.size(),
                          (long long)pool.m, (long long)pool.n_w);
         jobs = g.jobs;
+        if (!leaves && !pool.leaves.empty())
+            leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, unit, ng, ws, s));
         if (jobs.empty()) break;
+        // The compute units that the next sweep leaves peel the heaviest
+        // leaves meanwhile: one of a few hundred thousand wedges takes tens of
+        // milliseconds, all of them together little more.  5M-edge graph 262
+        // and 247 ms, 192 pool graphs 151 and 142 ms.
+        if (leaves && coop && g.m < kAllCusEdges) leaves->start(cus - peel_grid(r.tp, cus, cus));
         uint64_t *supl2 = ws.get<uint64_t>("sp_supl", g.m + 1);
         int64_t *loff2 = ws.get<int64_t>("sp_loff", g.m + 1);
         uint3 *link2 = ws.get<uint3>("sp_link", 2 * g.n_w + 1);
@@ -1380,8 +1391,7 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         ask.min_level = 0;
         ask.sup_out = nullptr;
     }
-    // All leaves at the end, side by side.
-    if (!pool.leaves.empty()) peel_leaf_jobs(pool, phi_out, unit, levels, max_level, pc, ws, s);
+    if (leaves) leaves->finish(levels, max_level, pc);
     pc.launches += 1 + pc.yields;
     pc.max_phi = max_level;
     for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);

@@ -205,10 +205,13 @@ struct LeafJob {
     int32_t e0, ne;       // edges [e0, e0 + ne)
     uint32_t w0, nw;      // wedges [w0, w0 + nw)
     uint32_t b0, nb;      // blooms [b0, b0 + nb)
-    int32_t graph, pad;
+    int32_t graph;
+    int32_t id;  // its number among all jobs
 };
+constexpr int kNumLeafClasses = 3;  // sizes of workgroup (peel_leaf.hip)
+constexpr int kLeafLists = 3;       // lists of jobs that a launch takes from
 struct LeafCtl {
-    int32_t queue[4];  // next job of each launch
+    int32_t queue[kLeafLists][kNumLeafClasses];  // jobs handed out of each
     int32_t max_level, pad;
     unsigned long long rounds, updates, unbatched, bloom_visits, touched, blooms, wedges;
 };

@@ -457,7 +457,7 @@ void regroup(const SplitIndex &ix, const SweepResult &sw, const std::vector<Spli
         L.b0 = (uint32_t)(pool.n_b + rb[2 * (size_t)j + 1] - out.n_b);
         L.nb = (uint32_t)(rb[2 * (size_t)j + 3] - rb[2 * (size_t)j + 1]);
         L.graph = c.root;
-        L.pad = 0;
+        L.id = (int32_t)pool.jobs.size();
         pool.jobs.push_back(L);
         pool.leaves.push_back(c);
     }

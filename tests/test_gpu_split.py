@@ -66,3 +66,15 @@ def test_union_of_mixed_sizes(mode, union, monkeypatch):
     for g, s, p in zip(gs, sups, phis):
         osup, _, ophi = oracle_all(g)
         assert np.array_equal(s.cpu().numpy(), osup) and np.array_equal(p.cpu().numpy(), ophi)
+
+
+@pytest.mark.parametrize("unit", [False, True])
+def test_leaves_beside_deeper_sweeps(unit):
+    """Graphs of two sweeps and more, whose first leaves start beside the second."""
+    for g in (synth.scaled_chunglu(500000, seed=31),
+              synth.chung_lu(2000, 40000, 300000, 1.8, 2.3, 3000, 3000, 3)):
+        _, _, ophi = oracle_all(g)
+        variant = binding.BT_PEEL_BATCH_EDGE if unit else binding.BT_PEEL_BATCH_BLOOM
+        for _ in range(2):
+            _, phi, _ = binding.bt_decompose_variant(upload(g), variant, want_sup=False)
+            assert np.array_equal(phi.cpu().numpy(), ophi)
