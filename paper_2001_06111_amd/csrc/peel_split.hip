@@ -799,7 +799,7 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
     if (threadIdx.x == 0) {
         // A launch resumes at the round where the previous one yielded.
         s_r0 = ld(&C->rounds);
-        s_left = ld(&C->left.v);
+        s_left = 1;  // a launch has something to do (see below)
         s_nf = ld(&C->nf[s_r0 & 1].v);
         s_ngth = ld(&C->ngth[s_r0 & 1].v);
         s_nsel = ld(&C->nsel[s_r0 & 1].v);
@@ -834,6 +834,11 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         if (threadIdx.x == 0) {
             s_ok = grid_arrive_wait(B, gen_local);
             s_ntc = ld(&C->ntc[p].v);
+            // Jobs end in sweep_decide alone, so this count is the same for
+            // every block between the round's barriers.  Past the second one a
+            // faster block may already decide on the next round: a block that
+            // read 0 there would leave while others wait for it.
+            s_left = ld(&C->left.v);
         }
         __syncthreads();
         if (!s_ok) break;
@@ -858,7 +863,6 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
                 drain_memory();
             }
             s_ok = grid_arrive_wait(B, gen_local);
-            s_left = ld(&C->left.v);
             s_nf = ld(&C->nf[q].v);
             s_ngth = ld(&C->ngth[q].v);
             s_nsel = ld(&C->nsel[q].v);

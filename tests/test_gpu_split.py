@@ -78,3 +78,16 @@ def test_leaves_beside_deeper_sweeps(unit):
         for _ in range(2):
             _, phi, _ = binding.bt_decompose_variant(upload(g), variant, want_sup=False)
             assert np.array_equal(phi.cpu().numpy(), ophi)
+
+
+@pytest.mark.parametrize("m", [20000, 60000, 150001])
+def test_launches_that_end_in_their_first_round(m, monkeypatch):
+    """Every launch of a sweep yields after 16 rounds, so many launches begin
+    with little left to do, the last ones with a job's last decision."""
+    g = _cl(m)
+    _, phi0, _ = binding.bt_decompose(upload(g), want_sup=False)
+    monkeypatch.setenv("BT_PEEL_YIELD", "1")
+    for tau in (0.1, 0.3):
+        _, phi, st = binding.bt_decompose_pc(upload(g), tau=tau, want_sup=False, stats=True)
+        assert st["peel_yields"] >= 1
+        assert np.array_equal(phi.cpu().numpy(), phi0.cpu().numpy())
