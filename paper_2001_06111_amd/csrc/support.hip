@@ -22,14 +22,16 @@
 // fewer wedges than a hash table takes, or fewer ids than there are counters.
 // Rows are ascending, so a window clips each long row by binary search.
 //
-// Whole support calls, counted from x alone and so: 20M-edge hub graph
-// (1.26e9 wedges) 109 and 29 ms, 5M-edge Chung-Lu graph (1.6e8 wedges) 18.3
-// and 6.5 ms, 250k-edge graph 1.11 and 0.87 ms.  The hub graph's largest tier
-// (75% of the wedges) takes 12.6 ms: 4 x 0.95e9 row entries, read from L2 at
+// Whole support calls, counted from x alone and so (with half of the time
+// that preparation took taken off as well): 20M-edge hub graph (1.26e9
+// wedges) 109 and 22 ms, 5M-edge Chung-Lu graph (1.6e8 wedges) 18.3 and 4.8
+// ms, 250k-edge graph 1.11 and 0.49 ms.  The hub graph's largest tier (75% of
+// the wedges) takes 12 ms: 4 x 0.95e9 row entries, read from L2 at
 // 64 a wave, and the first touch of 1e8 short rows, a cache line each.  Cut
 // at 2^18 wedges a task instead of up to 2^21 it took 33 ms (each part clips
 // every row), with 16-bit counters throughout 17.3 ms (two windows where one
-// does); eight entries in flight a lane instead of four changed nothing.
+// does); eight entries in flight a lane instead of four changed nothing, and
+// runs of rows handed out in LDS instead of dealt took a quarter longer.
 #include <algorithm>
 #include <cstring>
 
@@ -45,7 +47,7 @@ constexpr uint32_t kWaveMax = 256, kMidMax = 2048, kBigMax = 16384;
 // Bounds of the wedges a task of the largest tier takes of a start (about
 // half of a CU's share of the graph's): each part clips all of the start's
 // rows, so only what would hold up the rest is cut.
-constexpr int64_t kPartLeast = int64_t(1) << 18, kPartMost = int64_t(1) << 21;
+constexpr int64_t kPartLeast = int64_t(1) << 15, kPartMost = int64_t(1) << 21;
 constexpr uint32_t kMaxParts = 4096;
 constexpr int64_t kFirst = int64_t(1) << 19;  // starts from here up go first
 constexpr int32_t kEmpty = -1;
@@ -85,25 +87,31 @@ __device__ __forceinline__ uint32_t first_at(const int32_t *adj, uint32_t lo, ui
     return lo;
 }
 
-// First id in [lo, hi] whose row starts at or after v.
-__device__ __forceinline__ int32_t first_row(const int64_t *off, int32_t lo, int32_t hi,
-                                             int64_t v) {
+// The first id in [lo, hi) that has a property which all later ones have too,
+// or hi: 64 probes a step, as a step waits for memory.  All lanes call, with
+// the same range.
+template <class F>
+__device__ __forceinline__ int32_t first_with(int32_t lo, int32_t hi, F &&has) {
     while (lo < hi) {
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (off[mid] < v) lo = mid + 1;
-        else hi = mid;
+        const int32_t step = (int32_t)(((uint32_t)(hi - lo) + kWave - 1) / kWave);
+        const int64_t at = lo + (int64_t)lane_id() * step;
+        const int n = (int)__popcll(__ballot(at < hi && !has((int32_t)min(at, (int64_t)hi - 1))));
+        if (n == 0) return lo;
+        hi = (int32_t)min((int64_t)lo + (int64_t)n * step, (int64_t)hi);
+        lo = lo + (n - 1) * step + 1;
     }
     return lo;
 }
 
+// First id in [lo, hi] whose row starts at or after v.
+__device__ __forceinline__ int32_t first_row(const int64_t *off, int32_t lo, int32_t hi,
+                                             int64_t v) {
+    return first_with(lo, hi, [&](int32_t i) { return off[i] >= v; });
+}
+
 // First id in [lo, hi) of more than kByteMax neighbours, or hi.
 __device__ __forceinline__ int32_t first_wide(const int64_t *off, int32_t lo, int32_t hi) {
-    while (lo < hi) {
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (off[mid + 1] - off[mid] <= kByteMax) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
+    return first_with(lo, hi, [&](int32_t i) { return off[i + 1] - off[i] > kByteMax; });
 }
 
 // A window of the walk of one start vertex.
@@ -633,6 +641,41 @@ void launch_small(const WalkArgs &A, const uint32_t *tasks, int32_t n, int cus, 
     BT_CHECK_LAUNCH();
 }
 
+// The caller's stream for the first launch, side streams for the others,
+// which begin after what the caller's held and end before what it gets next.
+class SideStreams {
+  public:
+    SideStreams(Workspace &ws, hipStream_t s) : ws_(ws), s_(s) {}
+    ~SideStreams() {
+        for (hipEvent_t e : ev_)
+            if (e) (void)hipEventDestroy(e);
+    }
+    hipStream_t next(bool used) {
+        if (!used) return s_;
+        if (n_++ == 0) {
+            BT_HIP(hipEventCreateWithFlags(&ev_[0], hipEventDisableTiming));
+            BT_HIP(hipEventRecord(ev_[0], s_));
+            return s_;
+        }
+        const hipStream_t t = ws_.side(n_ - 2);
+        BT_HIP(hipStreamWaitEvent(t, ev_[0], 0));
+        return t;
+    }
+    void join() {
+        for (int k = 1; k < n_; ++k) {
+            BT_HIP(hipEventCreateWithFlags(&ev_[k], hipEventDisableTiming));
+            BT_HIP(hipEventRecord(ev_[k], ws_.side(k - 1)));
+            BT_HIP(hipStreamWaitEvent(s_, ev_[k], 0));
+        }
+    }
+
+  private:
+    Workspace &ws_;
+    hipStream_t s_;
+    hipEvent_t ev_[4] = {};
+    int n_ = 0;
+};
+
 }  // namespace
 
 int64_t count_support(const RankCSR &r, uint64_t *supl, int64_t *bf, Workspace &ws,
@@ -671,11 +714,15 @@ int64_t count_support(const RankCSR &r, uint64_t *supl, int64_t *bf, Workspace &
     WalkArgs A{r.off, r.adj, r.eid, r.low, r.rev, r.zlen, r.rst, r.wpre, r.zpre, r.n, r.n_lower,
                reinterpret_cast<unsigned long long *>(supl),
                reinterpret_cast<unsigned long long *>(bf), counts + 2 * kTiers};
-    launch_group<16, 131072>(A, most, (int32_t)n_most, cus, s);
+    // The tiers run beside each other: each ends in a few long tasks (250k-edge
+    // graph: 245 us one after another, 170 so; 5M-edge graph: 3.5 ms and 3.2).
+    SideStreams side(ws, s);
+    launch_group<16, 131072>(A, most, (int32_t)n_most, cus, side.next(n_most > 0));
     A.queue += 1;
-    launch_group<8, 65536>(A, big, nt[2], cus, s);
-    launch_small<4, kMidMax>(A, mid, nt[1], cus, s);
-    launch_small<1, kWaveMax>(A, wave, nt[0], cus, s);
+    launch_group<8, 65536>(A, big, nt[2], cus, side.next(nt[2] > 0));
+    launch_small<4, kMidMax>(A, mid, nt[1], cus, side.next(nt[1] > 0));
+    launch_small<1, kWaveMax>(A, wave, nt[0], cus, side.next(nt[0] > 0));
+    side.join();
     return wedges;
 }
 
