@@ -74,7 +74,7 @@ constexpr double kLargeWaitS = 10.0;
 // graphs submitted at once: 93 ms where the last of nine medium ones just
 // missed its batch and ran alone after it, 70 ms so); the oldest waits kGatherMostS
 // at most.  Small batches, of a millisecond or little more, start at once.
-constexpr double kGatherS = 0.0005, kGatherMostS = 0.005;
+constexpr double kGatherS = 0.001, kGatherMostS = 0.010;
 constexpr int kDefaultSlots = 2;
 // Weights of a batch's turns on the device, by size class (each class's
 // bound on its graphs' edges; the large one well above 8x the medium): a
