@@ -167,6 +167,28 @@ template <typename T> __device__ __forceinline__ T wave_min(T v) {
     return v;
 }
 
+// The first id in [lo, hi) that has a property which all later ones have too,
+// or hi: 64 probes a step, as a step waits for memory.  All lanes call, with
+// the same range.
+template <class F>
+__device__ __forceinline__ int32_t first_with(int32_t lo, int32_t hi, F &&has) {
+    while (lo < hi) {
+        const int32_t step = (int32_t)(((uint32_t)(hi - lo) + kWave - 1) / kWave);
+        const int64_t at = lo + (int64_t)lane_id() * step;
+        const int n = (int)__popcll(__ballot(at < hi && !has((int32_t)min(at, (int64_t)hi - 1))));
+        if (n == 0) return lo;
+        hi = (int32_t)min((int64_t)lo + (int64_t)n * step, (int64_t)hi);
+        lo = lo + (n - 1) * step + 1;
+    }
+    return lo;
+}
+
+// First id in [lo, hi] whose row starts at or after v.
+__device__ __forceinline__ int32_t first_row(const int64_t *off, int32_t lo, int32_t hi,
+                                             int64_t v) {
+    return first_with(lo, hi, [&](int32_t i) { return off[i] >= v; });
+}
+
 // Block-wide exclusive sum; `scratch` holds one T per wave.  Returns the
 // thread's exclusive prefix and writes the block total to *total.
 template <typename T>

@@ -82,7 +82,8 @@ struct WedgeTask {
     int32_t x;     // start vertex (new id)
     int32_t zlo;   // dense mode: counter range [zlo, zhi); hash mode: unused
     int32_t zhi;
-    int32_t cap;   // hash mode: table slots (power of two); dense: zhi - zlo
+    int32_t cap;   // hash mode: table slots (power of two); dense: zhi - zlo;
+                   // -1: share zlo of zhi of the degrees below x
 };
 
 struct TaskLists {

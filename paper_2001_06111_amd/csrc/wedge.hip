@@ -1,7 +1,9 @@
 // wedge.hip - priority-obeyed wedge sweeps that emit the BE-Index, supports
 // included (Algorithm 3; Lemmas 1-3 and 7).
 //
-// A task is a start vertex x (or, for heavy x, one range of end vertices z).
+// A task is a start vertex x (or, for heavy x, one range of end vertices z:
+// as many as there are dense counters, or a share of the degrees below x whose
+// wedges a hash table takes).
 // Its workgroup walks every wedge (x, y, z) with p(y), p(z) < p(x) twice:
 //   count: c[z] += 1 for each wedge, in an LDS table (hash or dense range);
 //          then c[z] = |M(x, z)| is the bloom number of the maximal
@@ -34,6 +36,9 @@ struct WedgeArgs {
     uint64_t *supl;
     int64_t *bf;
     int64_t *queue;  // dynamic task counter
+    const int32_t *zbase;  // first rank of x's end vertices (null: of its layer)
+    int32_t n_lower;
+    int32_t chunk, hash_max;
     uint64_t *cursor;       // of the whole index, or of each graph (vgraph)
     const int32_t *vgraph;  // nullable: the graph of each start vertex
     uint32_t *bwoff;
@@ -114,7 +119,7 @@ __device__ __forceinline__ int slot_find(int32_t z, const int32_t *keys, int32_t
 }
 
 // One pass over the task's wedges.  PASS 0 counts, PASS 1 emits.
-template <bool DENSE, int PASS>
+template <bool DENSE, bool CLIP, int PASS>
 __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *v0,
                            uint32_t *v1, int32_t mask, int32_t x, int32_t zlo, int32_t zhi,
                            uint32_t wbase) {
@@ -129,7 +134,7 @@ __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *
             const int32_t y = A.adj[p];
             st = A.off[y];
             len = A.rev[p];
-            if (DENSE) {
+            if (CLIP) {
                 const int64_t lo = lower_bound(A.adj, st, st + len, zlo);
                 const int64_t hi = lower_bound(A.adj, lo, st + len, zhi);
                 st = lo;
@@ -175,93 +180,142 @@ __device__ void wedge_pass(const WedgeArgs &A, Smem &S, int32_t *keys, int32_t *
     }
 }
 
-template <bool DENSE>
+// Blooms of start x whose end vertices lie in [zlo, zhi) (CLIP; else all of
+// them), counted in `cap` slots.
+template <bool DENSE, bool CLIP>
+__device__ void wedge_task(const WedgeArgs &A, Smem &S, unsigned char *table, int32_t x, int32_t zlo,
+                           int32_t zhi, int32_t cap) {
+    const int tid = threadIdx.x;
+    int32_t *keys = reinterpret_cast<int32_t *>(table);
+    int32_t *v0 = DENSE ? keys : keys + cap;
+    uint32_t *v1 = reinterpret_cast<uint32_t *>(v0 + cap);
+    for (int s = tid; s < cap; s += kWG) {
+        if (!DENSE) keys[s] = kEmpty;
+        v0[s] = 0;
+    }
+    __syncthreads();
+
+    wedge_pass<DENSE, CLIP, 0>(A, S, keys, v0, v1, cap - 1, x, zlo, zhi, 0);
+
+    // Sweep 1: blooms, their wedges and butterflies in this task.
+    int64_t nb = 0, nw = 0, bfl = 0;
+    for (int s = tid; s < cap; s += kWG) {
+        const int32_t c = (DENSE || keys[s] != kEmpty) ? v0[s] : 0;
+        if (c >= 2) {
+            ++nb;
+            nw += c;
+            bfl += (int64_t)c * (c - 1) / 2;
+        }
+    }
+    nb = wave_sum(nb);
+    nw = wave_sum(nw);
+    bfl = wave_sum(bfl);
+    if (tid == 0) S.totals[0] = S.totals[1] = S.totals[2] = 0;
+    __syncthreads();
+    if (lane_id() == 0) {
+        atomicAdd((unsigned long long *)&S.totals[0], (unsigned long long)nb);
+        atomicAdd((unsigned long long *)&S.totals[1], (unsigned long long)nw);
+        atomicAdd((unsigned long long *)&S.totals[2], (unsigned long long)bfl);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        if (S.totals[2]) atomicAdd((unsigned long long *)A.bf, (unsigned long long)S.totals[2]);
+        S.base = 0;
+        if (S.totals[0])
+            S.base = atomicAdd((unsigned long long *)A.cursor + (A.vgraph ? A.vgraph[x] : 0),
+                               ((unsigned long long)S.totals[0] << 32) |
+                                   (unsigned long long)S.totals[1]);
+    }
+    __syncthreads();
+    if (S.totals[0] == 0) return;  // no bloom anchored here
+    const uint32_t bbase = (uint32_t)(S.base >> 32);
+    const uint32_t wbase = (uint32_t)(S.base & 0xffffffffu);
+
+    // Sweep 2: number blooms and lay out their wedge ranges in slot
+    // order; blooms and wedges share one allocation order, so bloom
+    // b's range ends where bloom b + 1's begins.
+    uint64_t carry = 0;
+    for (int s0 = 0; s0 < cap; s0 += kWG) {
+        const int s = s0 + tid;
+        const bool valid = s < cap && (DENSE || keys[s] != kEmpty);
+        const int32_t c = valid ? v0[s] : 0;
+        const bool isb = c >= 2;
+        const uint64_t mine = isb ? ((uint64_t(1) << 32) | (uint32_t)c) : 0;
+        uint64_t tot;
+        const uint64_t pre = block_exclusive_sum<uint64_t>(mine, S.scr2, &tot) + carry;
+        if (isb) {
+            const int32_t b = (int32_t)(bbase + (uint32_t)(pre >> 32));
+            const uint32_t lw = (uint32_t)(pre & 0xffffffffu);
+            A.bk[b] = c;
+            A.bwoff[b] = wbase + lw;
+            v0[s] = b;
+            v1[s] = lw;
+        } else if (valid) {
+            v0[s] = kEmpty;
+        }
+        carry += tot;
+    }
+    __syncthreads();
+
+    wedge_pass<DENSE, CLIP, 1>(A, S, keys, v0, v1, cap - 1, x, zlo, zhi, wbase);
+}
+
+// Wedges of start x that end in [zlo, zhi).
+__device__ int64_t wedges_in(const WedgeArgs &A, Smem &S, int32_t x, int32_t zlo, int32_t zhi) {
+    const int64_t ox = A.off[x];
+    const int32_t lx = A.low[x];
+    int64_t t = 0;
+    for (int32_t j = threadIdx.x; j < lx; j += kWG) {
+        const int64_t st = A.off[A.adj[ox + j]], en = st + A.rev[ox + j];
+        const int64_t lo = lower_bound(A.adj, st, en, zlo);
+        t += lower_bound(A.adj, lo, en, zhi) - lo;
+    }
+    int64_t total;
+    (void)block_exclusive_sum<int64_t>(t, S.scr, &total);
+    return total;
+}
+
+// HEAVY: tasks are ranges of end vertices (see heavy_tasks in graph.hip), else
+// whole starts.
+template <bool HEAVY>
 __global__ __launch_bounds__(kWG) void k_wedge(WedgeArgs A, const WedgeTask *tasks,
                                                int64_t ntasks) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem &S = *reinterpret_cast<Smem *>(smem_raw);
     unsigned char *table = smem_raw + sizeof(Smem);
-    const int tid = threadIdx.x;
     while (true) {
-        if (tid == 0) S.task = atomicAdd((unsigned long long *)A.queue, 1ull);
+        __syncthreads();  // the last task's shared state is read no more
+        if (threadIdx.x == 0) S.task = atomicAdd((unsigned long long *)A.queue, 1ull);
         __syncthreads();
         const int64_t ti = S.task;
-        __syncthreads();
         if (ti >= ntasks) break;
         const WedgeTask T = tasks[ti];
-        const int32_t cap = T.cap;
-        int32_t *keys = reinterpret_cast<int32_t *>(table);
-        int32_t *v0 = DENSE ? keys : keys + cap;
-        uint32_t *v1 = reinterpret_cast<uint32_t *>(v0 + cap);
-        for (int s = tid; s < cap; s += kWG) {
-            if (!DENSE) keys[s] = kEmpty;
-            v0[s] = 0;
+        if (!HEAVY) {
+            wedge_task<false, false>(A, S, table, T.x, 0, 0, T.cap);
+            continue;
         }
-        __syncthreads();
-
-        wedge_pass<DENSE, 0>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, 0);
-
-        // Sweep 1: blooms, their wedges and butterflies in this task.
-        int64_t nb = 0, nw = 0, bfl = 0;
-        for (int s = tid; s < cap; s += kWG) {
-            const int32_t c = (DENSE || keys[s] != kEmpty) ? v0[s] : 0;
-            if (c >= 2) {
-                ++nb;
-                nw += c;
-                bfl += (int64_t)c * (c - 1) / 2;
+        if (T.cap >= 0) {
+            wedge_task<true, true>(A, S, table, T.x, T.zlo, T.zhi, T.cap);
+            continue;
+        }
+        const int32_t base = A.zbase ? A.zbase[T.x] : (T.x >= A.n_lower ? A.n_lower : 0);
+        const int64_t o0 = A.off[base], d = A.off[T.x] - o0;
+        const int32_t zlo = T.zlo ? first_row(A.off, base, T.x, o0 + d * T.zlo / T.zhi) : base;
+        const int32_t zhi =
+            T.zlo + 1 < T.zhi ? first_row(A.off, base, T.x, o0 + d * (T.zlo + 1) / T.zhi) : T.x;
+        if (zlo >= zhi) continue;
+        const int64_t w = zhi - zlo <= A.chunk ? INT64_MAX : wedges_in(A, S, T.x, zlo, zhi);
+        if (w <= A.hash_max) {
+            int32_t cap = 128;
+            while (cap < 2 * w) cap <<= 1;
+            if (w > 0) wedge_task<false, true>(A, S, table, T.x, zlo, zhi, cap);
+        } else {
+            for (int32_t c = zlo; c < zhi; c += A.chunk) {
+                __syncthreads();
+                const int32_t e = min(c + A.chunk, zhi);
+                wedge_task<true, true>(A, S, table, T.x, c, e, e - c);
             }
         }
-        nb = wave_sum(nb);
-        nw = wave_sum(nw);
-        bfl = wave_sum(bfl);
-        if (tid == 0) S.totals[0] = S.totals[1] = S.totals[2] = 0;
-        __syncthreads();
-        if (lane_id() == 0) {
-            atomicAdd((unsigned long long *)&S.totals[0], (unsigned long long)nb);
-            atomicAdd((unsigned long long *)&S.totals[1], (unsigned long long)nw);
-            atomicAdd((unsigned long long *)&S.totals[2], (unsigned long long)bfl);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            if (S.totals[2]) atomicAdd((unsigned long long *)A.bf, (unsigned long long)S.totals[2]);
-            S.base = 0;
-            if (S.totals[0])
-                S.base = atomicAdd((unsigned long long *)A.cursor + (A.vgraph ? A.vgraph[T.x] : 0),
-                                   ((unsigned long long)S.totals[0] << 32) |
-                                       (unsigned long long)S.totals[1]);
-        }
-        __syncthreads();
-        if (S.totals[0] == 0) continue;  // no bloom anchored here
-        const uint32_t bbase = (uint32_t)(S.base >> 32);
-        const uint32_t wbase = (uint32_t)(S.base & 0xffffffffu);
-
-        // Sweep 2: number blooms and lay out their wedge ranges in slot
-        // order; blooms and wedges share one allocation order, so bloom
-        // b's range ends where bloom b + 1's begins.
-        uint64_t carry = 0;
-        for (int s0 = 0; s0 < cap; s0 += kWG) {
-            const int s = s0 + tid;
-            const bool valid = s < cap && (DENSE || keys[s] != kEmpty);
-            const int32_t c = valid ? v0[s] : 0;
-            const bool isb = c >= 2;
-            const uint64_t mine = isb ? ((uint64_t(1) << 32) | (uint32_t)c) : 0;
-            uint64_t tot;
-            const uint64_t pre = block_exclusive_sum<uint64_t>(mine, S.scr2, &tot) + carry;
-            if (isb) {
-                const int32_t b = (int32_t)(bbase + (uint32_t)(pre >> 32));
-                const uint32_t lw = (uint32_t)(pre & 0xffffffffu);
-                A.bk[b] = c;
-                A.bwoff[b] = wbase + lw;
-                v0[s] = b;
-                v1[s] = lw;
-            } else if (valid) {
-                v0[s] = kEmpty;
-            }
-            carry += tot;
-        }
-        __syncthreads();
-
-        wedge_pass<DENSE, 1>(A, S, keys, v0, v1, cap - 1, T.x, T.zlo, T.zhi, wbase);
     }
 }
 
@@ -351,7 +405,7 @@ __global__ __launch_bounds__(1024) void k_graph_bases(const int64_t *off, const 
     }
 }
 
-template <bool DENSE>
+template <bool HEAVY>
 void launch_wedge(const WedgeArgs &A, const WedgeTask *tasks, int64_t n, int wg_per_cu,
                   hipStream_t s) {
     if (n <= 0) return;
@@ -359,7 +413,7 @@ void launch_wedge(const WedgeArgs &A, const WedgeTask *tasks, int64_t n, int wg_
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int64_t grid = std::min<int64_t>(n, (int64_t)cus * wg_per_cu);
-    k_wedge<DENSE><<<(unsigned)grid, kWG, kSmemBytes, s>>>(A, tasks, n);
+    k_wedge<HEAVY><<<(unsigned)grid, kWG, kSmemBytes, s>>>(A, tasks, n);
     BT_CHECK_LAUNCH();
 }
 
@@ -373,6 +427,10 @@ WedgeArgs make_args(const RankCSR &r, uint64_t *supl, int64_t *bf, int64_t *queu
     A.supl = supl;
     A.bf = bf;
     A.queue = queue;
+    A.zbase = r.zbase;
+    A.n_lower = r.n_lower;
+    A.chunk = r.tp.dense_chunk;
+    A.hash_max = r.tp.hash_max_work;
     return A;
 }
 

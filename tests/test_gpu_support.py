@@ -99,3 +99,15 @@ def test_order_inside_and_between_rows(where):
         with pytest.raises(binding.BtError) as ei:
             binding.bt_support(upload(synth.Graph(6, 5000, r, col, "bad rows")))
         assert ei.value.status == binding.BT_EINVAL
+
+
+@pytest.mark.parametrize("shape", [(200000, 100, 500, 2500), (60000, 60, 300, 1500)])
+def test_index_of_wedges_in_one_share_of_the_degrees(shape):
+    """The index's sweep over shares of the degrees: one share holds more
+    wedges than its hash table, the others next to none."""
+    g = _skewed(*shape, "skewed")
+    osup, obf, _ = oracle.support(g.n_upper, g.n_lower, g.row_ptr, g.col)
+    ophi, _ = oracle.bitruss(g.n_upper, g.n_lower, g.row_ptr, g.col, sup=osup)
+    sup, phi, st = binding.bt_decompose(upload(g), stats=True)
+    assert np.array_equal(sup.cpu().numpy(), osup) and st["butterflies"] == obf
+    assert np.array_equal(phi.cpu().numpy(), ophi)
