@@ -62,8 +62,11 @@ constexpr int64_t kMediumEdges = int64_t(1) << 14;
 constexpr int kClasses = 3;
 inline int size_class_of(int64_t m) { return m >= kLargeEdges ? 2 : m >= kMediumEdges ? 1 : 0; }
 // Large requests share a batch too (their rounds overlap), but at most this
-// many, to bound each one's latency.
-constexpr int32_t kLargePerBatch = 8;
+// many: 2M-edge graphs take 0.54 s alone, 0.92 s two together, 1.53 s four and
+// 2.79 s eight, and what the peel that splits needs for four or more in each of
+// two slots no longer fits half of the device's memory.  Eight at a time, level
+// by level for that reason, took 11.6 s.
+constexpr int32_t kLargePerBatch = 2;
 // Batches of the smallest class present go first (they take a fraction of
 // a larger class's time), unless the oldest request of a larger class has
 // waited this long (so a steady stream of small requests cannot starve

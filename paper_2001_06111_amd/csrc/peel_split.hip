@@ -71,7 +71,20 @@ struct alignas(128) JobState {
     float rem_n;        // edges it saw remaining
     int32_t narrow;     // split by levels, not by edges (a job that came back whole)
     int32_t hi_bound;   // its bitruss numbers are at most this
+    // P.plain: the list of remaining edges that gathers scan.
+    int32_t n_list;     // its length; -1: the job's range of edges
+    int32_t which;      // of the two halves of P.list
+    int32_t packing;    // the scheduled gather writes the next list
+    int32_t gathers;    // so far
+    u64 n_next;         // edges the next list has so far
 };
+
+// With P.plain every kPackEvery-th gather of a job also lists the edges that
+// remain, and later ones scan that list: most edges go at the lowest of a
+// graph's thousands of levels (5M-edge graph level by level: 1851 -> 1542 ms).
+// Short lists are not listed anew: their scan costs a round as it is.
+constexpr int32_t kPackEvery = 32;
+constexpr uint32_t kPackLeast = 1u << 17;
 
 // A piece of at most 64 wedges of a touched bloom; b < 0: none.
 struct alignas(8) SweepBloomItem {
@@ -80,9 +93,12 @@ struct alignas(8) SweepBloomItem {
 };
 
 struct SweepGatherItem {
-    int32_t part, pad;
-    uint32_t lo, hi;  // edges
+    int32_t part;
+    int32_t how;      // kGatherList, kGatherPack
+    uint32_t lo, hi;  // edges, or places of P.list
 };
+constexpr int32_t kGatherList = 1;  // scans places of P.list
+constexpr int32_t kGatherPack = 2;  // lists the edges it leaves
 
 struct SweepCtl {
     Counter nf[2], ntc[2], ngth[2], nsel[2];
@@ -129,6 +145,8 @@ struct SweepArgs {
     const uint3 *link;
     uint32_t n_w;
     int32_t plain;      // level by level, each edge's mark its number
+    int32_t *list;      // with plain: two lists of remaining edges, 2 * m places
+    uint32_t m;
     int32_t unit;       // one decrement per kill (no batch bloom processing)
     FrontItem *front[2];  // {edge, part, links [lo, hi)}
     SweepBloomItem *tc[2];
@@ -247,10 +265,10 @@ __device__ __forceinline__ void fill_fronts(FrontItem *list, const Reserve &R) {
         st_item(&list[R.base + i], FrontItem{-1, 0, 0u, 1u});
 }
 
-// Gather items over edges [e0, e1) for the round of parity q; each lane with
-// n = e1 - e0 > 0 has its own.  All 64 lanes call.
-__device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t part, int32_t e0,
-                                           uint32_t n) {
+// Gather items over edges (or places) [e0, e0 + n) for the round of parity q;
+// each lane with n > 0 has its own.  All 64 lanes call.
+__device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t part, uint32_t e0,
+                                           uint32_t n, int32_t how) {
     const uint32_t cnt = (n + kGatherChunk - 1) / kGatherChunk;
     u64 base[3];
     wave_alloc3(cnt, &P.ctl->ngth[q].v, 0u, nullptr, 0u, nullptr, base);
@@ -261,10 +279,11 @@ __device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t pa
         const uint32_t nc = __shfl(cnt, l, kWave), ln = __shfl(n, l, kWave);
         const u64 b = __shfl(base[0], l, kWave);
         const int32_t lp = __shfl(part, l, kWave);
-        const uint32_t le = (uint32_t)__shfl(e0, l, kWave);
+        const uint32_t le = __shfl(e0, l, kWave);
+        const int32_t lh = __shfl(how, l, kWave);
         for (uint32_t c = lane_id(); c < nc; c += kWave) {
             const uint32_t a = c * kGatherChunk;
-            st_item(&P.gth[q][b + c], SweepGatherItem{lp, 0, le + a, le + min(a + kGatherChunk, ln)});
+            st_item(&P.gth[q][b + c], SweepGatherItem{lp, lh, le + a, le + min(a + kGatherChunk, ln)});
         }
     }
 }
@@ -278,7 +297,8 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
     for (int64_t g0 = tid - lane_id(); g0 < P.n_jobs; g0 += nthreads) {
         const int64_t g = g0 + lane_id();
         bool gather = false, select = false;
-        int32_t e0 = 0, e1 = 0, part = 0;
+        uint32_t e0 = 0, n = 0;
+        int32_t part = 0, how = 0;
         if (g < P.n_jobs) {
             JobState *J = &P.js[g];
             const int32_t state = ld(&J->state);
@@ -287,8 +307,8 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
             const int32_t gm = ld(&J->gmin[q]);
             const int32_t level = ld(&J->level);
             part = ld(&J->part);
-            e0 = ld(&J->e0);
-            e1 = ld(&J->e1);
+            e0 = (uint32_t)ld(&J->e0);
+            n = (uint32_t)ld(&J->e1) - e0;
             if (state != kJobDone) {
                 if (fr) st(&J->fr[p], 0);
                 if (!fr && sr != r && gr != r) {
@@ -316,11 +336,33 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
                         st(&P.parts[part].hi, next);
                         st(&J->gather_round, r + 1);
                         st(&J->gmin[q], (int32_t)INT_MAX);
+                        if (P.plain) {
+                            const int32_t ng = ld(&J->gathers);
+                            int32_t which = ld(&J->which);
+                            int32_t nl = ld(&J->n_list);
+                            if (ld(&J->packing)) {  // the last gather wrote the next list
+                                which ^= 1;
+                                nl = (int32_t)ld(&J->n_next);
+                                st(&J->which, which);
+                                st(&J->n_list, nl);
+                            }
+                            const bool pack = ng % kPackEvery == kPackEvery - 1 &&
+                                              (nl >= 0 ? (uint32_t)nl : n) >= kPackLeast;
+                            if (pack) st(&J->n_next, (u64)0);
+                            st(&J->packing, pack ? 1 : 0);
+                            st(&J->gathers, ng + 1);
+                            how = (nl >= 0 ? kGatherList : 0) | (pack ? kGatherPack : 0);
+                            if (nl >= 0) {
+                                e0 += which ? P.m : 0u;
+                                n = (uint32_t)nl;
+                            }
+                        }
                     }
                 }
             }
         }
-        put_gather(P, q, part, e0, gather ? (uint32_t)(e1 - e0) : 0u);
+        if (!__any(gather || select)) continue;
+        put_gather(P, q, part, e0, gather ? n : 0u, how);
         const u64 slot = wave_alloc(select ? 1u : 0u, &P.ctl->nsel[q].v);
         if (select) st(&P.sel[q][slot], (int32_t)g);
     }
@@ -491,25 +533,41 @@ __device__ void sweep_select(const SweepArgs &P, int32_t g, int64_t r, int q) {
     }
     __syncthreads();
     if (threadIdx.x < kWave)  // one wave writes the gather's items
-        put_gather(P, q, s_mn, e0, threadIdx.x == 0 ? (uint32_t)n : 0u);
+        put_gather(P, q, s_mn, (uint32_t)e0, threadIdx.x == 0 ? (uint32_t)n : 0u, 0);
     __syncthreads();
+}
+
+// The smallest support a wave's gather items saw; most waves find a smaller
+// one there already.
+__device__ __forceinline__ void flush_min(const SweepArgs &P, int p, int32_t job, int32_t mn) {
+    if (lane_id() == 0 && mn != INT_MAX && mn < ld(&P.js[job].gmin[p]))
+        atomicMin(&P.js[job].gmin[p], mn);
 }
 
 // A gather item: remaining edges at or below the part's level become the next
 // frontier; the smallest support above it is kept for a jump, the smallest
-// taken as the part's lower bound.
+// taken as the part's lower bound.  The smallest is kept by the wave until its
+// items' job changes: one counter takes an atomic every few nanoseconds.
 __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int p,
-                                             const SweepGatherItem it) {
+                                             const SweepGatherItem it, int32_t &mn_job,
+                                             int32_t &mn_all) {
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
     const int32_t level = ld(&P.parts[it.part].hi), job = ld(&P.parts[it.part].job);
     int32_t ph[kGatherPerLane], sv[kGatherPerLane];
+    uint32_t ed[kGatherPerLane];
 #pragma unroll
     for (int k = 0; k < kGatherPerLane; ++k) {
-        const uint32_t e = it.lo + k * kWave + lane_id();
+        const uint32_t i = it.lo + k * kWave + lane_id();
+        ed[k] = i;
+        if ((it.how & kGatherList) && i < it.hi) ed[k] = (uint32_t)ld(&P.list[i]);
+    }
+#pragma unroll
+    for (int k = 0; k < kGatherPerLane; ++k) {
+        const uint32_t e = ed[k];
         ph[k] = 0;
         sv[k] = INT_MAX;
-        if (e < it.hi) {
+        if (it.lo + k * kWave + lane_id() < it.hi) {
             ph[k] = mark_part(ld(&P.mark[e].v));
             sv[k] = ld(&P.sup[e]);
         }
@@ -530,7 +588,7 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
         uint32_t lo[kGatherPerLane], hi[kGatherPerLane], tot = 0;
 #pragma unroll
         for (int k = 0; k < kGatherPerLane; ++k) {
-            const uint32_t e = it.lo + k * kWave + lane_id();
+            const uint32_t e = ed[k];
             lo[k] = hi[k] = 0;
             if ((take >> k) & 1u) {
                 lo[k] = (uint32_t)P.link_off[e];
@@ -546,8 +604,7 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
         for (int k = 0; k < kGatherPerLane; ++k) {
             const uint32_t cnt = chunks_of(lo[k], hi[k]);
             put_fronts(P, P.front[q], S, (take >> k) & 1u, cnt, at,
-                       (int32_t)(it.lo + k * kWave + lane_id()), it.part, level, (int32_t)(r + 1), lo[k],
-                       hi[k]);
+                       (int32_t)ed[k], it.part, level, (int32_t)(r + 1), lo[k], hi[k]);
             at += cnt;
         }
         lowest = wave_min(lowest);
@@ -556,9 +613,26 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
             atomicMin(&P.parts[it.part].lo, lowest);
         }
     }
+    if (it.how & kGatherPack) {
+        uint32_t keep = 0;
+#pragma unroll
+        for (int k = 0; k < kGatherPerLane; ++k) keep += ph[k] < 0 && sv[k] > level ? 1u : 0u;
+        u64 at = wave_alloc(keep, &P.js[job].n_next);
+        // The half of P.list that the job's current list is not in.
+        at += (uint64_t)(uint32_t)ld(&P.js[job].e0) + (ld(&P.js[job].which) ? 0u : P.m);
+#pragma unroll
+        for (int k = 0; k < kGatherPerLane; ++k)
+            if (ph[k] < 0 && sv[k] > level) st(&P.list[at++], (int32_t)ed[k]);
+    }
     mn = wave_min(mn);
-    if (lane_id() == 0 && mn != INT_MAX) atomicMin(&P.js[job].gmin[p], mn);
+    if (job != mn_job) {
+        flush_min(P, p, mn_job, mn_all);
+        mn_job = job;
+        mn_all = INT_MAX;
+    }
+    mn_all = min(mn_all, mn);
 }
+
 
 // Work items of a phase per wave and step: one while there are fewer items
 // than waves, so that a small round spreads over the chip; up to 64, one a
@@ -657,8 +731,10 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
     }
     fill_blooms(P.tc[p], rb);
     fill_fronts(P.front[q], rf);
+    int32_t mn_job = -1, mn_all = INT_MAX;
     for (int64_t i = wid; i < (int64_t)ngth; i += nwaves)
-        sweep_gather(P, r, p, ld_item(&P.gth[p][i]));
+        sweep_gather(P, r, p, ld_item(&P.gth[p][i]), mn_job, mn_all);
+    flush_min(P, p, mn_job, mn_all);
 }
 
 // Phase B: the survivors of every touched bloom lose its kills; the last
@@ -986,9 +1062,13 @@ hipGraphExec_t chunk_graph(const void *args, size_t bytes, int rounds, Workspace
     return ex;
 }
 
-// Parts each job of n edges aims at in a sweep.
+// Parts each job of n edges aims at in a sweep: fewer parts touch each bloom
+// less often, more leave less to deeper sweeps.  Of caps of 4, 8, 12, 16, 24,
+// 32, 48 and 64 the 5M-edge graph took 316, 262, 258, 245, 240, 238, 260 and
+// 286 ms, 1,024 pool graphs 1541, 1324, 1237, 1205, 1162, 1211, 1287 and 1347
+// ms; a 200k-edge graph, bound by its leaves' rounds, takes 32 best.
 int64_t parts_for(int64_t n, int64_t work, int64_t total) {
-    const int64_t cap = total >= (int64_t(1) << 20) ? 16 : 32;
+    const int64_t cap = total >= (int64_t(1) << 20) ? 24 : 32;
     return std::max<int64_t>(4, std::min<int64_t>(cap, std::max<int64_t>(n / 2048, work / 32768)));
 }
 
@@ -1000,6 +1080,7 @@ struct SweepAsk {
     int32_t min_level = 0;
     bool unit = false, plain = false;
     int64_t *sup_out = nullptr;
+    int64_t *scratch = nullptr;  // plain: m places that the caller writes afterwards
 };
 
 // State of a sweep over the jobs of a depth, ready for its first round by
@@ -1030,6 +1111,8 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     P.bloom = ws.get<BloomRec>("sw_bloom", nb);
     P.wedge_k = ask.plain ? nullptr : ws.get<int32_t>("sw_wedge_k", ix.n_w);
     P.plain = ask.plain ? 1 : 0;
+    P.list = reinterpret_cast<int32_t *>(ask.scratch);
+    P.m = (uint32_t)m;
     P.wea = ix.wea;
     P.web = ix.web;
     P.link_off = ix.link_off;
@@ -1074,6 +1157,7 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
         J.select_round = -8;
         J.level = -1;
         J.part = j;
+        J.n_list = -1;
         J.scale = 1.f;
         J.narrow = jobs[(size_t)j].stuck ? 1 : 0;
         J.hi_bound = jobs[(size_t)j].hi;
@@ -1248,6 +1332,7 @@ void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn 
     SweepAsk ask;
     ask.supl = ix.supl;
     ask.plain = true;
+    ask.scratch = phi_out;
     const int blocks = 64;
     const SweepArgs P = sweep_setup(view_of(ix, m), jobs, ask, blocks, nullptr, ws, s);
     int32_t *live = ws.get<int32_t>("trace_live", ix.n_b);
@@ -1330,6 +1415,7 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
     ask.unit = unit;
     ask.plain = opt && opt->plain;
     ask.sup_out = sup_out;
+    ask.scratch = phi_out;
     if (ask.plain) {
         // Level by level, with the memory of the index alone.
         const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);

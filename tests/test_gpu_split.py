@@ -91,3 +91,14 @@ def test_launches_that_end_in_their_first_round(m, monkeypatch):
         _, phi, st = binding.bt_decompose_pc(upload(g), tau=tau, want_sup=False, stats=True)
         assert st["peel_yields"] >= 1
         assert np.array_equal(phi.cpu().numpy(), phi0.cpu().numpy())
+
+
+@pytest.mark.parametrize("mode", ["plain", "graph"])
+def test_listed_gathers(mode, monkeypatch):
+    """Ranges long enough that level-by-level gathers list what remains."""
+    gs = [_cl(140000, 1), _cl(200000, 2), _cl(3000, 3)]
+    want = [oracle_all(g)[2] for g in gs]
+    monkeypatch.setenv("BT_PEEL_MODE", mode)
+    phis = binding.bt_decompose_batch([upload(g) for g in gs])[1]
+    for w, phi in zip(want, phis):
+        assert np.array_equal(phi.cpu().numpy(), w)
