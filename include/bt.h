@@ -205,11 +205,12 @@ typedef enum bt_peel_variant {
      * per round. */
     BT_PEEL_BATCH_EDGE = 1,
     /* BiT-BU++, or BiT-PC (bt_decompose_pc, tau = 0.05) when the graph has at
-     * least 16,384 butterflies per edge: there the peel is bound by support
-     * updates, which BiT-PC cuts (20M-edge hub graph, 43k per edge: 40.6 s
-     * against 67.4 s), while below it the rounds bound it and BiT-PC's extra
-     * passes cost more (5M-edge Chung-Lu graph, 930 per edge; 2M-edge
-     * request graph, 5.9k per edge: equal).  Decided after the index build. */
+     * least 131,072 butterflies per edge: there most of a bloom's wedges lie
+     * among edges of one bitruss, which BiT-PC peels without the others (the
+     * complete 1,000 x 1,000 graph, 250k per edge: 109 against 176 ms), while
+     * below it BiT-PC's extra passes cost more than they save (20M-edge hub
+     * graph, 43k per edge: 5.99 against 2.87 s; 2M-edge hub graph, 5.5k per
+     * edge: 531 against 204 ms).  Decided after the index build. */
     BT_PEEL_AUTO = 2
 } bt_peel_variant;
 

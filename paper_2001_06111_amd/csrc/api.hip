@@ -247,8 +247,8 @@ static void decompose_once(const bt_csr &g0, int64_t *sup_out0, int64_t *phi_out
     build_all(g, r, ix, false, nullptr, ws, stream, &ev);
     ev.mark(3);
     if (auto_pc && g.m > 0) {
-        // Where support updates, not rounds, bound the peel (hub-heavy
-        // graphs), BiT-PC's smaller updates pay for its extra passes.
+        // Only near-complete graphs save more updates by BiT-PC than its
+        // extra passes cost (figures at BT_PEEL_AUTO).
         if (ix.butterflies / g.m >= kAutoPcButterfliesPerEdge) {
             decompose_pc_impl(g0, kAutoPcTau, sup_out0, phi_out0, stats, ws, stream);
             return;

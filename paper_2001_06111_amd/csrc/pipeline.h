@@ -234,7 +234,7 @@ void mark_fixed(IndexArrays &ix, const int32_t *fixed, hipStream_t s);
 void decompose_impl(const bt_csr &g, int64_t *sup_out, int64_t *phi_out, bt_stats *stats,
                     Workspace &ws, hipStream_t stream, bool unit_updates = false,
                     bool auto_pc = false);
-constexpr int64_t kAutoPcButterfliesPerEdge = 16384;
+constexpr int64_t kAutoPcButterfliesPerEdge = 131072;
 constexpr double kAutoPcTau = 0.05;
 // Measures candidate launch parameters on these graphs (one graph, or a
 // batch) and stores the best for their kind and size class (tune.hip).
