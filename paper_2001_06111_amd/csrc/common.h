@@ -232,12 +232,19 @@ void scan_exclusive_i64(const int64_t *in, int64_t *out, int64_t n, Workspace &w
                         hipStream_t s);
 void scan_exclusive_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Workspace &ws,
                                hipStream_t s);
+// Two of them over as many elements each.
+void scan_two_i32_to_i64(const int32_t *in0, int64_t *out0, const int32_t *in1, int64_t *out1,
+                         int64_t n, Workspace &ws, hipStream_t s);
 
 // Stable LSD radix sort of (key, value) pairs on `key_bits` bits from bit
 // `begin` up (n < 2^32).  Sorted data ends in keys/vals (buffers are
 // ping-ponged with ws scratch).
 void radix_sort_u64_u32(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits,
                         Workspace &ws, hipStream_t s, int begin = 0);
+// The same between the caller's two pairs of buffers; keys and vals name the
+// sorted pair afterwards, keys2 and vals2 the other.
+void radix_sort_swap(uint64_t *&keys, uint32_t *&vals, uint64_t *&keys2, uint32_t *&vals2,
+                     int64_t n, int key_bits, Workspace &ws, hipStream_t s, int begin = 0);
 
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 void fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);

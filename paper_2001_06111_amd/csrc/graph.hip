@@ -242,6 +242,96 @@ void validate_graph(const bt_csr &g, Workspace &ws, hipStream_t s) {
         throw Error{BT_EINVAL, "lower ids not strictly increasing within a row (duplicate edge?)"};
 }
 
+// The priority order of up to kRankSmall vertices of one graph by one
+// workgroup: what k_rank_keys, the sort, k_rank_apply and the scan of the
+// degrees do in seven launches, each of which costs more than its work (2,500
+// vertices: 12 us, before about 45 with the gaps between them; with two scans
+// in one launch and sorts that leave their result where the last pass wrote it,
+// the 10,000-edge graph's support count 190 -> 157 us).  LDS holds (layer, degree, id) in one word; two stable
+// counting passes over layer and degree, in which each wave ranks its own run
+// of rows by ballots.
+constexpr int kRankBlock = 1024;
+constexpr int32_t kRankSmall = 1 << 13;
+constexpr int kRankIdBits = 13, kRankDigit = 8;
+
+__global__ __launch_bounds__(kRankBlock) void k_rank_small(const int32_t *deg, int32_t n_lower,
+                                                           int32_t n, int dbits, int32_t *old2new,
+                                                           int32_t *new2old, int32_t *deg_new,
+                                                           int64_t *off) {
+    constexpr int kWaves = kRankBlock / kWave;
+    __shared__ uint32_t s_key[2][kRankSmall];
+    __shared__ uint32_t s_cnt[kWaves << kRankDigit];  // [wave][digit]
+    __shared__ uint32_t s_scr[kWaves + 1];
+    __shared__ int64_t s_scr64[kWaves + 1];
+    const int w = threadIdx.x / kWave;
+    const int32_t rows = (n + kRankBlock - 1) / kRankBlock;  // of a wave
+    for (int32_t v = threadIdx.x; v < n; v += kRankBlock)
+        s_key[0][v] = ((((uint32_t)(v >= n_lower) << dbits) | (uint32_t)deg[v]) << kRankIdBits) |
+                      (uint32_t)v;
+    uint32_t *const mine = s_cnt + (w << kRankDigit);
+    for (int pass = 0, done = 0; pass < 2; ++pass) {
+        const uint32_t *in = s_key[pass];
+        uint32_t *out = s_key[pass ^ 1];
+        const int bits = pass == 0 ? (dbits + 2) / 2 : dbits + 1 - done;
+        const int shift = kRankIdBits + done, bins = 1 << bits;
+        for (int i = threadIdx.x; i < kWaves << kRankDigit; i += kRankBlock) s_cnt[i] = 0;
+        __syncthreads();
+        for (int32_t i = 0; i < rows; ++i) {
+            const int32_t x = (w * rows + i) * kWave + lane_id();
+            if (x < n) atomicAdd(&mine[(in[x] >> shift) & (uint32_t)(bins - 1)], 1u);
+        }
+        __syncthreads();
+        uint32_t sum = 0, all;
+        if ((int)threadIdx.x < bins)
+            for (int j = 0; j < kWaves; ++j) sum += s_cnt[(j << kRankDigit) + threadIdx.x];
+        uint32_t pos = block_exclusive_sum<uint32_t>(sum, s_scr, &all);
+        if ((int)threadIdx.x < bins)
+            for (int j = 0; j < kWaves; ++j) {
+                const uint32_t c = s_cnt[(j << kRankDigit) + threadIdx.x];
+                s_cnt[(j << kRankDigit) + threadIdx.x] = pos;
+                pos += c;
+            }
+        __syncthreads();
+        for (int32_t i = 0; i < rows; ++i) {
+            const int32_t x = (w * rows + i) * kWave + lane_id();
+            const bool ok = x < n;
+            const uint32_t k = ok ? in[x] : 0u;
+            const uint32_t d = (k >> shift) & (uint32_t)(bins - 1);
+            uint64_t peers = __ballot(ok);
+            for (int b = 0; b < bits; ++b) {
+                const bool bit = (d >> b) & 1;
+                const uint64_t bal = __ballot(bit);
+                peers &= bit ? bal : ~bal;
+            }
+            const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
+            if (ok) {
+                out[mine[d] + rank] = k;
+                if (rank == 0) mine[d] += (uint32_t)__popcll(peers);
+            }
+        }
+        __syncthreads();
+        done += bits;
+    }
+    // Back in s_key[0].  Each thread takes a run of ranks.
+    const int32_t p0 = (int32_t)threadIdx.x * rows;
+    int64_t sum = 0, all;
+    const uint32_t dmask = (1u << dbits) - 1;
+    for (int32_t p = p0; p < min(p0 + rows, n); ++p) sum += (s_key[0][p] >> kRankIdBits) & dmask;
+    int64_t run = block_exclusive_sum<int64_t>(sum, s_scr64, &all);
+    for (int32_t p = p0; p < min(p0 + rows, n); ++p) {
+        off[p] = run;
+        run += (s_key[0][p] >> kRankIdBits) & dmask;
+    }
+    if (threadIdx.x == 0) off[n] = all;
+    for (int32_t p = threadIdx.x; p < n; p += kRankBlock) {
+        const uint32_t k = s_key[0][p];
+        const int32_t v = (int32_t)(k & ((1u << kRankIdBits) - 1));
+        old2new[v] = p;
+        new2old[p] = v;
+        deg_new[p] = (int32_t)((k >> kRankIdBits) & dmask);
+    }
+}
+
 void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
              const Components *comps, bool up) {
     const int32_t nu = g.n_upper, nl = g.n_lower;
@@ -262,8 +352,6 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
             g.row_ptr, g.col, m, nu, nl, deg);
         BT_CHECK_LAUNCH();
     }
-    uint64_t *vkeys = ws.get<uint64_t>("prep_vkeys", n);
-    uint32_t *vorder = ws.get<uint32_t>("prep_vorder", n);
     int32_t *old2new = ws.get<int32_t>("prep_old2new", n);
     int32_t *new2old = ws.get<int32_t>("prep_new2old", n);
     int32_t *deg_new = ws.get<int32_t>("prep_degnew", n);
@@ -271,7 +359,15 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
     r.zbase = r.vgraph = nullptr;
     // No degree exceeds the size of the other layer.
     const int dbits = bits_for((uint64_t)std::max(nu, nl));
-    if (n > 0) {
+    r.off = ws.get<int64_t>("rank_off", n + 1);
+    const bool small = !uni && n > 0 && n <= kRankSmall;
+    if (small) {
+        k_rank_small<<<1, kRankBlock, 0, s>>>(deg, nl, (int32_t)n, dbits, old2new, new2old, deg_new,
+                                              r.off);
+        BT_CHECK_LAUNCH();
+    } else if (n > 0) {
+        uint64_t *vkeys = ws.get<uint64_t>("prep_vkeys", n);
+        uint32_t *vorder = ws.get<uint32_t>("prep_vorder", n);
         if (uni) {
             const int cbits = bits_for((uint64_t)(comps->n - 1));
             k_rank_keys_comp<<<grid_for(n, 256, 8192), 256, 0, s>>>(deg, nl, (int32_t)n, *comps,
@@ -295,8 +391,7 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
             BT_CHECK_LAUNCH();
         }
     }
-    r.off = ws.get<int64_t>("rank_off", n + 1);
-    scan_exclusive_i32_to_i64(deg_new, r.off, n, ws, s);
+    if (!small) scan_exclusive_i32_to_i64(deg_new, r.off, n, ws, s);
 
     // Rank-space rows sorted by neighbour priority: the edges in upper rank
     // order, sorted (stably) by lower rank, are the lower rows; those, sorted
@@ -320,8 +415,11 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
         k_entries<<<grid_for(ceil_div(m, run) * kWave, kBlock, 8192), kBlock, 0, s>>>(
             g.row_ptr, g.col, m, nu, nl, old2new, r.off, nbl, run, ekeys, evals);
         BT_CHECK_LAUNCH();
+        uint64_t *ekeys2 = ws.get<uint64_t>("rs_keys", m);
+        uint32_t *evals2 = ws.get<uint32_t>("rs_vals", m);
         for (const bool upper : {false, true}) {
-            radix_sort_u64_u32(ekeys, evals, m, upper ? nbu : nbl, ws, s, upper ? nbl : 0);
+            radix_sort_swap(ekeys, evals, ekeys2, evals2, m, upper ? nbu : nbl, ws, s,
+                            upper ? nbl : 0);
             k_entries_apply<<<grid_for(m, 256, 16384), 256, 0, s>>>(
                 ekeys, evals, m, nbl, nl, upper, r.adj + (upper ? m : 0), r.eid + (upper ? m : 0),
                 src + (upper ? m : 0));
@@ -338,8 +436,8 @@ void prepare(const bt_csr &g, RankCSR &r, Workspace &ws, hipStream_t s,
                                                        r.rev, r.zlen, r.rst);
         BT_CHECK_LAUNCH();
     }
-    scan_exclusive_i32_to_i64(r.rev, r.wpre, n2, ws, s);
-    if (up) scan_exclusive_i32_to_i64(r.zlen, r.zpre, n2, ws, s);
+    if (up) scan_two_i32_to_i64(r.rev, r.wpre, r.zlen, r.zpre, n2, ws, s);
+    else scan_exclusive_i32_to_i64(r.rev, r.wpre, n2, ws, s);
 }
 
 // ------------------------------------------------------------- tasks

@@ -325,8 +325,12 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_tile(const Tin *in, int64_t
 // the last workgroup under 3 us).
 constexpr int64_t kScanOne = 16 * kScanTile;
 
+// A second row of workgroups scans in1.
 template <typename Tin>
-__global__ __launch_bounds__(kScanBlock) void k_scan_one(const Tin *in, int64_t *out, int64_t n) {
+__global__ __launch_bounds__(kScanBlock) void k_scan_one(const Tin *in0, int64_t *out0,
+                                                         const Tin *in1, int64_t *out1, int64_t n) {
+    const Tin *const in = blockIdx.y ? in1 : in0;
+    int64_t *const out = blockIdx.y ? out1 : out0;
     __shared__ int64_t scratch[kScanBlock / kWave + 1];
     const int64_t tile = (int64_t)blockIdx.x * kScanTile;
     int64_t before = 0;
@@ -361,7 +365,7 @@ static void scan_impl(const Tin *in, int64_t *out, int64_t n, Workspace &ws, hip
     }
     int64_t nb = ceil_div(n, kScanTile);
     if (n <= kScanOne) {
-        k_scan_one<Tin><<<(unsigned)nb, kScanBlock, 0, s>>>(in, out, n);
+        k_scan_one<Tin><<<(unsigned)nb, kScanBlock, 0, s>>>(in, out, nullptr, nullptr, n);
         BT_CHECK_LAUNCH();
         return;
     }
@@ -385,6 +389,18 @@ void scan_exclusive_i64(const int64_t *in, int64_t *out, int64_t n, Workspace &w
 void scan_exclusive_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Workspace &ws,
                                hipStream_t s) {
     scan_impl<int32_t>(in, out, n, ws, s, 0);
+}
+
+void scan_two_i32_to_i64(const int32_t *in0, int64_t *out0, const int32_t *in1, int64_t *out1,
+                         int64_t n, Workspace &ws, hipStream_t s) {
+    if (n > 0 && n <= kScanOne) {
+        k_scan_one<int32_t><<<dim3((unsigned)ceil_div(n, kScanTile), 2), kScanBlock, 0, s>>>(
+            in0, out0, in1, out1, n);
+        BT_CHECK_LAUNCH();
+        return;
+    }
+    scan_exclusive_i32_to_i64(in0, out0, n, ws, s);
+    scan_exclusive_i32_to_i64(in1, out1, n, ws, s);
 }
 
 // ------------------------------------------------------- radix sort
@@ -524,18 +540,14 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_scatter(const uint64_t *kin, co
 }
 
 template <int ITEMS>
-static void radix_passes(uint64_t *keys, uint32_t *vals, int64_t n, int begin, int key_bits,
-                         Workspace &ws, hipStream_t s) {
+static void radix_passes(uint64_t *&ka, uint32_t *&va, uint64_t *&kb, uint32_t *&vb, int64_t n,
+                         int begin, int key_bits, Workspace &ws, hipStream_t s) {
     const int64_t nb = ceil_div(n, ITEMS * kRsBlock);
     const int passes = (key_bits + kRsDigit<ITEMS> - 1) / kRsDigit<ITEMS>;
     const int widest = (key_bits + passes - 1) / passes;
     const bool direct = nb <= kRsDirect;
-    uint64_t *k2 = ws.get<uint64_t>("rs_keys", n);
-    uint32_t *v2 = ws.get<uint32_t>("rs_vals", n);
     int32_t *hist = ws.get<int32_t>("rs_hist", nb << widest);
     int64_t *offs = direct ? nullptr : ws.get<int64_t>("rs_offs", (nb << widest) + 1);
-    uint64_t *ka = keys, *kb = k2;
-    uint32_t *va = vals, *vb = v2;
     for (int p = 0, done = 0; p < passes; ++p) {
         const int bits = (key_bits - done + passes - p - 1) / (passes - p);
         const int shift = begin + done, bins = 1 << bits;
@@ -550,18 +562,26 @@ static void radix_passes(uint64_t *keys, uint32_t *vals, int64_t n, int begin, i
         std::swap(va, vb);
         done += bits;
     }
-    if (ka != keys) {
-        BT_HIP(hipMemcpyAsync(keys, ka, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
-        BT_HIP(hipMemcpyAsync(vals, va, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
-    }
+}
+
+void radix_sort_swap(uint64_t *&keys, uint32_t *&vals, uint64_t *&keys2, uint32_t *&vals2,
+                     int64_t n, int key_bits, Workspace &ws, hipStream_t s, int begin) {
+    if (n <= 1 || key_bits <= 0) return;
+    if (n >> 32) throw Error{BT_EOVERFLOW, "too many elements to sort"};
+    if (n <= kRsSmall) radix_passes<4>(keys, vals, keys2, vals2, n, begin, key_bits, ws, s);
+    else radix_passes<16>(keys, vals, keys2, vals2, n, begin, key_bits, ws, s);
 }
 
 void radix_sort_u64_u32(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, Workspace &ws,
                         hipStream_t s, int begin) {
     if (n <= 1 || key_bits <= 0) return;
-    if (n >> 32) throw Error{BT_EOVERFLOW, "too many elements to sort"};
-    if (n <= kRsSmall) radix_passes<4>(keys, vals, n, begin, key_bits, ws, s);
-    else radix_passes<16>(keys, vals, n, begin, key_bits, ws, s);
+    uint64_t *ka = keys, *kb = ws.get<uint64_t>("rs_keys", n);
+    uint32_t *va = vals, *vb = ws.get<uint32_t>("rs_vals", n);
+    radix_sort_swap(ka, va, kb, vb, n, key_bits, ws, s, begin);
+    if (ka != keys) {
+        BT_HIP(hipMemcpyAsync(keys, ka, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
+        BT_HIP(hipMemcpyAsync(vals, va, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
+    }
 }
 
 }  // namespace bt

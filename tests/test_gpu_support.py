@@ -8,7 +8,7 @@ import pytest
 import oracle
 from paper_2001_06111_amd import binding, synth
 from tests import graphs
-from tests.gpu_util import upload
+from tests.gpu_util import oracle_all, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -111,3 +111,17 @@ def test_index_of_wedges_in_one_share_of_the_degrees(shape):
     sup, phi, st = binding.bt_decompose(upload(g), stats=True)
     assert np.array_equal(sup.cpu().numpy(), osup) and st["butterflies"] == obf
     assert np.array_equal(phi.cpu().numpy(), ophi)
+
+
+@pytest.mark.parametrize("nu,nl", [(1, 1), (1, 2), (2, 1022), (500, 524), (500, 525), (1, 8191),
+                                   (8191, 1), (4096, 4096), (3000, 5192), (3000, 5193), (1, 8192)])
+def test_orders_by_one_workgroup(nu, nl):
+    """Vertex counts around a wave's rows, one block's and the most that one
+    workgroup ranks (8,192); degrees up to the whole other layer."""
+    m = min(nu * nl, max(nl, 6 * (nu + nl)))
+    g = synth.complete(nu, nl) if m == nu * nl else synth.uniform(nu, nl, m, nu + nl)
+    osup, obf, ophi = oracle_all(g)
+    got, phi, st = binding.bt_decompose(upload(g), stats=True)
+    assert np.array_equal(got.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+    assert st["butterflies"] == obf
+    assert np.array_equal(binding.bt_support(upload(g))[0].cpu().numpy(), osup)
