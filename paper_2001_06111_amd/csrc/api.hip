@@ -99,11 +99,11 @@ void alloc_index(const RankCSR &r, IndexArrays &ix, bool owned, Workspace &ws,
     // All that starts at zero, in one piece: supports, then queues, sums,
     // cursors and bases.
     const int64_t nc = std::max(1, ix.n_graphs);
-    ix.zeroed = m + 1 + 4 + 2 * nc;
+    ix.zeroed = m + 1 + 5 + 2 * nc;
     ix.supl = (uint64_t *)get("ix_supl", sizeof(uint64_t) * ix.zeroed);
     ix.queue = (int64_t *)(ix.supl + m + 1);
     ix.sums = ix.queue + 2;
-    ix.cursor = (uint64_t *)(ix.sums + 2);
+    ix.cursor = (uint64_t *)(ix.sums + 3);
     if (ix.n_graphs > 0) {
         ix.base = ix.cursor + nc;
         return;
@@ -133,7 +133,7 @@ void build_all(const bt_csr &g, RankCSR &r, IndexArrays &ix, bool owned,
     build_index(r, t, ix, ws, s, comps);
     if (ev) ev->mark(2);
     uint64_t c;
-    ix.butterflies = check_butterfly_total(ix.supl, r.m, ix.sums, nullptr, ws, s, &c);
+    ix.butterflies = check_butterfly_total(ix.supl, r.m, ix.sums, nullptr, ws, s, &ix.max_sup, &c);
     if (ix.n_graphs > 0) return;  // the peel reads the sizes
     ix.n_b = (int64_t)(c >> 32);
     ix.n_w = (int64_t)(c & 0xffffffffu);
@@ -339,6 +339,7 @@ static void decompose_pc_once(const bt_csr &g, double tau, int64_t *sup_out, int
             PeelOptions o;
             o.fixed = sg.fixed;
             o.min_level = eps > 0 ? eps - 1 : 0;
+            o.levels = (int64_t)alpha + 1;  // from eps - 1 to the last pass's
             o.plain = plain;
             PeelCounters pc;
             peel_split(rs, ix, {0, sg.g.m}, nullptr, phi_sub, pc, ws, s, &o);

@@ -148,6 +148,7 @@ struct SweepArgs {
     int32_t *list;      // with plain: two lists of remaining edges, 2 * m places
     uint32_t m;
     int32_t unit;       // one decrement per kill (no batch bloom processing)
+    int32_t short_a, short_b;  // items that fill a wave in phases A, B; 0: most are long
     FrontItem *front[2];  // {edge, part, links [lo, hi)}
     SweepBloomItem *tc[2];
     SweepGatherItem *gth[2];
@@ -160,6 +161,22 @@ __device__ __forceinline__ uint32_t chunks_of(uint32_t lo, uint32_t hi) {
 
 __device__ __forceinline__ void set_front_flag(const SweepArgs &P, int32_t job, int q) {
     st(&P.js[job].fr[q], 1);
+}
+
+// The same for the jobs of the lanes with `on`; `last` is the job (uniform over
+// the wave) whose flag the wave set last in this phase.  Stores to one
+// address queue at the memory side, so a wave sets a job's flag once (a
+// uniform graph of 4M edges, whose every step takes edges: 152 -> 93 ms).
+// All 64 lanes call.
+__device__ __forceinline__ void set_front_flags(const SweepArgs &P, bool on, int32_t part, int q,
+                                                int32_t &last) {
+    const int32_t job = on ? ld(&P.parts[part].job) : -1;
+    unsigned long long who = __ballot(on && job != last);
+    while (who) {
+        last = __shfl(job, __ffsll(who) - 1, kWave);
+        if (lane_id() == 0) set_front_flag(P, last, q);
+        who &= ~__ballot(job == last);
+    }
 }
 
 // A wave's reservation of a work list's slots.  All waves of a round append
@@ -550,7 +567,7 @@ __device__ __forceinline__ void flush_min(const SweepArgs &P, int p, int32_t job
 // items' job changes: one counter takes an atomic every few nanoseconds.
 __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int p,
                                              const SweepGatherItem it, int32_t &mn_job,
-                                             int32_t &mn_all) {
+                                             int32_t &mn_all, int32_t &flagged) {
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
     const int32_t level = ld(&P.parts[it.part].hi), job = ld(&P.parts[it.part].job);
@@ -609,9 +626,10 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
         }
         lowest = wave_min(lowest);
         if (lane_id() == 0) {
-            set_front_flag(P, job, q);
-            atomicMin(&P.parts[it.part].lo, lowest);
+            if (job != flagged) set_front_flag(P, job, q);
+            if (!P.plain) atomicMin(&P.parts[it.part].lo, lowest);
         }
+        flagged = job;
     }
     if (it.how & kGatherPack) {
         uint32_t keep = 0;
@@ -634,12 +652,17 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
 }
 
 
-// Work items of a phase per wave and step: one while there are fewer items
-// than waves, so that a small round spreads over the chip; up to 64, one a
-// lane, when there are more (most items hold a few links or wedges, which
-// the wave then spreads over its lanes).
-__device__ __forceinline__ uint32_t items_per_step(u64 n, int64_t nwaves) {
-    const u64 per = n / (u64)(4 * nwaves);
+// Work items of a phase per wave and step: one while there are few items, so
+// that a small round spreads over the chip; up to 64, one a lane, when there
+// are more (most items hold a few links or wedges, which the wave then spreads
+// over its lanes).  Items are few while a wave has fewer than four of them, as
+// the longest bound the phase; where most are short (`least` > 0), a wave takes
+// its share in one step and at least as many as fill its lanes, since each
+// step also takes slots from counters that all waves share (a uniform graph of
+// 117,248 edges, items of two to five: 89 -> 44 us a round).
+__device__ __forceinline__ uint32_t items_per_step(u64 n, int64_t nwaves, int32_t least) {
+    const u64 per = least > 0 ? max((n + (u64)nwaves - 1) / (u64)nwaves, (u64)least)
+                              : n / (u64)(4 * nwaves);
     return per < 1 ? 1u : per > kWave ? (uint32_t)kWave : (uint32_t)per;
 }
 
@@ -656,9 +679,10 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
     const int32_t now = (int32_t)r;
-    const uint32_t per = items_per_step(nf, nwaves);
+    const uint32_t per = items_per_step(nf, nwaves, P.short_a);
     const uint32_t grow = per > 1 ? 2 * per : 0u;
     Reserve rb, rf;
+    int32_t flagged = -1;
     for (int64_t g0 = wid * per; g0 < (int64_t)nf; g0 += nwaves * per) {
         const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)nf;
         FrontItem it{0, 0, 0, 0};
@@ -724,7 +748,7 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
                          sf);
                 put_blooms(P.tc[p], sb, nch, ib - nch, (int32_t)lk.y);
                 put_fronts(P, P.front[q], sf, tf, tk, jf - tk, twin, part, level, now + 1, tlo, thi);
-                if (tf) set_front_flag(P, ld(&P.parts[part].job), q);
+                set_front_flags(P, tf, part, q, flagged);
             }
             upd += dec ? 1 : 0;
         }
@@ -733,7 +757,7 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
     fill_fronts(P.front[q], rf);
     int32_t mn_job = -1, mn_all = INT_MAX;
     for (int64_t i = wid; i < (int64_t)ngth; i += nwaves)
-        sweep_gather(P, r, p, ld_item(&P.gth[p][i]), mn_job, mn_all);
+        sweep_gather(P, r, p, ld_item(&P.gth[p][i]), mn_job, mn_all, flagged);
     flush_min(P, p, mn_job, mn_all);
 }
 
@@ -744,9 +768,10 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
                                               uint32_t &visits, uint32_t &touch, uint32_t &unb) {
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
-    const uint32_t per = items_per_step(ntc, nwaves);
+    const uint32_t per = items_per_step(ntc, nwaves, P.short_b);
     const uint32_t grow = per > 1 ? 2 * per : 0u;
     Reserve rf;
+    int32_t flagged = -1;
     for (int64_t g0 = wid * per; g0 < (int64_t)ntc; g0 += nwaves * per) {
         const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)ntc;
         int32_t b_l = -1, level_l = 0, part_l = 0, c_l = 0, k_l = 0;
@@ -821,7 +846,7 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
                            lo1, hi1);
                 put_fronts(P, P.front[q], sf, f2, k2, i1 - k2, eb, part, level, (int32_t)(r + 1), lo2,
                            hi2);
-                if (f1 || f2) set_front_flag(P, ld(&P.parts[part].job), q);
+                set_front_flags(P, f1 || f2, part, q, flagged);
             }
             const int32_t each = P.unit ? c : 1;
             upd += (uint32_t)((da ? each : 0) + (db ? each : 0));
@@ -1111,6 +1136,10 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     P.bloom = ws.get<BloomRec>("sw_bloom", nb);
     P.wedge_k = ask.plain ? nullptr : ws.get<int32_t>("sw_wedge_k", ix.n_w);
     P.plain = ask.plain ? 1 : 0;
+    // Links of an edge, wedges of a bloom, on average.
+    const int64_t links = 2 * ix.n_w / m + 1, wedges = ix.n_w / nb + 1;
+    P.short_a = links <= 16 ? (int32_t)(kWave / links) : 0;
+    P.short_b = wedges <= 3 ? (int32_t)(kWave / wedges) : 0;
     P.list = reinterpret_cast<int32_t *>(ask.scratch);
     P.m = (uint32_t)m;
     P.wea = ix.wea;
@@ -1387,6 +1416,20 @@ int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bo
     return t + t / 8;
 }
 
+// Whether a peel of at most so many levels goes level by level.  A level costs
+// some 30 us in rounds of its own; a split costs 0.2 ms and more in launches,
+// and 0.5 ns a wedge for the first sweep (which a graph of few levels falls
+// to as a whole) and the regrouping.  Uniform graphs of 17,000, 117,248,
+// 400,000, 1.5M and 4M edges (largest supports 8, 22, 58, about 150 and 350)
+// take 0.79, 2.8, 9.8, 41.9 and 190 ms split and 0.57, 2.5, 5.3, 22.9 and 92 ms
+// level by level; a Chung-Lu graph of 20,000 edges (thousands) 4.1 and 13.9 ms.
+// BT_PEEL_MODE=split splits whatever the levels.
+bool few_levels(int64_t levels, int64_t n_w) {
+    const char *mv = std::getenv("BT_PEEL_MODE");
+    if (mv && std::strcmp(mv, "split") == 0) return false;
+    return levels <= 24 + n_w / 65536;
+}
+
 void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
                 int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,
                 const PeelOptions *opt) {
@@ -1413,7 +1456,9 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
     ask.fixed = opt ? opt->fixed : nullptr;
     ask.min_level = opt ? opt->min_level : 0;
     ask.unit = unit;
-    ask.plain = opt && opt->plain;
+    // Few levels: level by level as well, as splitting passes over the graph
+    // once more.
+    ask.plain = opt && (opt->plain || few_levels(std::min(ix.max_sup, opt->levels), ix.n_w));
     ask.sup_out = sup_out;
     ask.scratch = phi_out;
     if (ask.plain) {

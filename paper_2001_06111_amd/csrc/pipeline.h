@@ -112,9 +112,10 @@ struct IndexArrays {
     int32_t n_graphs = 0;
     uint64_t *base = nullptr;
     int64_t *queue = nullptr;  // task cursors of the two wedge sweeps
-    int64_t *sums = nullptr;   // butterflies, and the sum of the supports; then cursor
+    int64_t *sums = nullptr;   // butterflies, sum of the supports, their largest; then cursor
     int64_t zeroed = 0;        // words from supl on that start at zero
-    int64_t butterflies = 0;   // host copy after build
+    int64_t butterflies = 0;   // host copies after build
+    int64_t max_sup = 0;
 };
 
 // Checks the CSR on the device (BT_EINVAL with the reason if malformed).
@@ -183,6 +184,8 @@ struct PeelOptions {
     int32_t min_level = 0;
     bool unit_updates = false;  // ablation: no batch bloom processing
     bool plain = false;  // level by level, without the memory that splitting takes
+    // The levels at which edges can go are at most so many.
+    int64_t levels = INT64_MAX;
 };
 // The peel level by level, each round that removes edges reported (small
 // graphs; for inspection and tests).
@@ -281,8 +284,10 @@ void supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m, hipStream_t s);
 // Lemma 8: a k-bloom holds C(k, 2)): the supports must sum to four times the
 // blooms' total, else BT_EDEVICE.  Returns it, and writes the supports to
 // `sup` unless that is null.  `sums`: the blooms' total and a cleared word;
-// `next` (nullable) receives the word after them.
+// with `next`, another cleared word, which takes the largest support (to
+// `most`), and one that `next` receives.
 int64_t check_butterfly_total(const uint64_t *supl, int64_t m, int64_t *sums, int64_t *sup,
-                              Workspace &ws, hipStream_t s, uint64_t *next = nullptr);
+                              Workspace &ws, hipStream_t s, int64_t *most = nullptr,
+                              uint64_t *next = nullptr);
 
 }  // namespace bt

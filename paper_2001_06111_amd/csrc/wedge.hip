@@ -325,27 +325,41 @@ __global__ void k_supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m) {
         sup[e] = (int64_t)(supl[e] & 0xffffffffu);
 }
 
-// Sum of the supports (low halves of the packed words), and the supports if
-// asked for.  One atomic a workgroup and few workgroups: an atomic a wave, on
+// Sum of the supports (low halves of the packed words), and the largest and
+// the supports themselves if asked for.  One atomic a workgroup and few workgroups: an atomic a wave, on
 // one address, took 200 us at 16,384 waves.
 constexpr int kTotalBlock = 512;
 __global__ __launch_bounds__(kTotalBlock) void k_support_total(const uint64_t *supl, int64_t m,
                                                                int64_t *sup,
-                                                               unsigned long long *out) {
+                                                               unsigned long long *out,
+                                                               unsigned long long *most) {
     __shared__ unsigned long long part[kTotalBlock / kWave];
-    unsigned long long acc = 0;
+    __shared__ unsigned long long top[kTotalBlock / kWave];
+    unsigned long long acc = 0, mx = 0;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
          e += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t v = supl[e] & 0xffffffffu;
         if (sup) sup[e] = (int64_t)v;
         acc += v;
+        mx = v > mx ? v : mx;
     }
     acc = wave_sum(acc);
-    if (lane_id() == 0) part[threadIdx.x / kWave] = acc;
+    for (int d = kWave / 2; most && d > 0; d >>= 1) {
+        const unsigned long long o = __shfl_xor(mx, d, kWave);
+        mx = o > mx ? o : mx;
+    }
+    if (lane_id() == 0) {
+        part[threadIdx.x / kWave] = acc;
+        top[threadIdx.x / kWave] = mx;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kTotalBlock / kWave; ++w) acc += part[w];
+        for (int w = 1; w < kTotalBlock / kWave; ++w) {
+            acc += part[w];
+            mx = top[w] > mx ? top[w] : mx;
+        }
         if (acc) atomicAdd(out, acc);
+        if (most && mx) atomicMax(most, mx);
     }
 }
 
@@ -443,20 +457,24 @@ void supl_to_sup(const uint64_t *supl, int64_t *sup, int64_t m, hipStream_t s) {
 }
 
 int64_t check_butterfly_total(const uint64_t *supl, int64_t m, int64_t *sums, int64_t *sup,
-                              Workspace &ws, hipStream_t s, uint64_t *next) {
-    int64_t *h = ws.host(3);
+                              Workspace &ws, hipStream_t s, int64_t *most, uint64_t *next) {
+    int64_t *h = ws.host(4);
     if (m > 0) {
         k_support_total<<<grid_for(m, kTotalBlock, 1024), kTotalBlock, 0, s>>>(
-            supl, m, sup, reinterpret_cast<unsigned long long *>(sums + 1));
+            supl, m, sup, reinterpret_cast<unsigned long long *>(sums + 1),
+            next ? reinterpret_cast<unsigned long long *>(sums + 2) : nullptr);
         BT_CHECK_LAUNCH();
     }
-    BT_HIP(hipMemcpyAsync(h, sums, (next ? 3 : 2) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    BT_HIP(hipMemcpyAsync(h, sums, (next ? 4 : 2) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
     if (h[1] != 4 * h[0])
         throw Error{BT_EDEVICE, "butterfly totals disagree: supports sum to " +
                                     std::to_string(h[1]) + ", blooms give 4 x " +
                                     std::to_string(h[0])};
-    if (next) *next = (uint64_t)h[2];
+    if (next) {
+        *most = h[2];
+        *next = (uint64_t)h[3];
+    }
     return h[0];
 }
 

@@ -102,3 +102,18 @@ def test_listed_gathers(mode, monkeypatch):
     phis = binding.bt_decompose_batch([upload(g) for g in gs])[1]
     for w, phi in zip(want, phis):
         assert np.array_equal(phi.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("mode", [None, "split", "graph"])
+@pytest.mark.parametrize("m", [16400, 117248, 300000])
+def test_few_levels(m, mode, monkeypatch):
+    """Uniform graphs, whose few levels are peeled one by one (or split)."""
+    f = (m / 10000) ** 0.5
+    g = synth.uniform(round(1000 * f), round(1500 * f), m, m)
+    osup, _, ophi = oracle_all(g)
+    _set(monkeypatch, mode)
+    sup, phi, st = binding.bt_decompose(upload(g), stats=True)
+    assert np.array_equal(sup.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
+    assert st["max_phi"] == int(ophi.max()) and st["levels"] == np.unique(ophi).size
+    _, phi, _ = binding.bt_decompose_pc(upload(g), 0.05)
+    assert np.array_equal(phi.cpu().numpy(), ophi)
