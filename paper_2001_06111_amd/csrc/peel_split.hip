@@ -1108,6 +1108,21 @@ struct SweepAsk {
     int64_t *scratch = nullptr;  // plain: m places that the caller writes afterwards
 };
 
+// The state of a sweep over one job.
+__global__ void k_sweep_init(SweepArgs P, JobState job, SplitPart first, int32_t n_parts,
+                             u64 yield_src) {
+    u64 *c = reinterpret_cast<u64 *>(P.ctl);
+    for (uint32_t i = threadIdx.x; i < sizeof(SweepCtl) / sizeof(u64); i += blockDim.x) c[i] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        P.ctl->left.v = 1;
+        P.ctl->n_parts.v = (u64)n_parts;
+        P.ctl->yield_src = yield_src;
+        P.js[0] = job;
+        if (n_parts) P.parts[0] = first;
+    }
+}
+
 // State of a sweep over the jobs of a depth, ready for its first round by
 // `pblocks` workgroups.
 SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const SweepAsk &ask,
@@ -1194,6 +1209,14 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
         J.target_n = std::max<int64_t>(512, n / parts_for(n, jobs[(size_t)j].work, m));
         first[(size_t)j] = SplitPart{ask.min_level, ask.min_level, j, 1};
     }
+    if (nj == 1) {
+        // By value: copies from the host's arrays and the wait for them took 50
+        // us of each of BiT-PC's passes.
+        k_sweep_init<<<1, 256, 0, s>>>(P, js[0], first[0], preset ? 1 : 0,
+                                       reinterpret_cast<u64>(yield_word));
+        BT_CHECK_LAUNCH();
+        return P;
+    }
     BT_HIP(hipMemcpyAsync(P.js, js.data(), sizeof(JobState) * nj, hipMemcpyHostToDevice, s));
     if (preset)
         BT_HIP(hipMemcpyAsync(P.parts, first.data(), sizeof(SplitPart) * nj, hipMemcpyHostToDevice,
@@ -1251,9 +1274,12 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
                                               args, 0, s));
             BT_HIP(hipEventRecord(ev1, s));
             int32_t fail = 0;
-            BT_HIP(hipMemcpyAsync(&hc, P.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
-            BT_HIP(hipMemcpyAsync(&fail, &bar->fail, sizeof fail, hipMemcpyDeviceToHost, s));
+            char *h = reinterpret_cast<char *>(ws.host((int)(sizeof hc / sizeof(int64_t)) + 1));
+            BT_HIP(hipMemcpyAsync(h, P.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
+            BT_HIP(hipMemcpyAsync(h + sizeof hc, &bar->fail, sizeof fail, hipMemcpyDeviceToHost, s));
             BT_HIP(hipStreamSynchronize(s));
+            std::memcpy(&hc, h, sizeof hc);
+            std::memcpy(&fail, h + sizeof hc, sizeof fail);
             float t = 0.f;
             BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
             ms += t;
@@ -1470,15 +1496,17 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         zero_bytes(mx, sizeof *mx, s);
         k_max_mark<<<grid_for(m, 256, 4096), 256, 0, s>>>(sw.mark, m, mx);
         BT_CHECK_LAUNCH();
-        unsigned long long hmx = 0;
-        std::vector<JobState> js(jobs.size());
-        BT_HIP(hipMemcpyAsync(&hmx, mx, sizeof hmx, hipMemcpyDeviceToHost, s));
-        BT_HIP(hipMemcpyAsync(js.data(), ws.get<JobState>("sw_jobs", (int64_t)jobs.size()),
-                              sizeof(JobState) * js.size(), hipMemcpyDeviceToHost, s));
+        static_assert(sizeof(JobState) % sizeof(int64_t) == 0, "copied as words");
+        int64_t *h = ws.host(1 + (int)(jobs.size() * (sizeof(JobState) / sizeof(int64_t))));
+        BT_HIP(hipMemcpyAsync(h, mx, sizeof *mx, hipMemcpyDeviceToHost, s));
+        BT_HIP(hipMemcpyAsync(h + 1, ws.get<JobState>("sw_jobs", (int64_t)jobs.size()),
+                              sizeof(JobState) * jobs.size(), hipMemcpyDeviceToHost, s));
         BT_HIP(hipStreamSynchronize(s));
         pc.launches += 1 + pc.yields;
-        pc.max_phi = (int64_t)hmx;
-        for (const JobState &J : js) pc.levels = std::max<int64_t>(pc.levels, J.n_parts);
+        pc.max_phi = h[0];
+        const JobState *js = reinterpret_cast<const JobState *>(h + 1);
+        for (size_t j = 0; j < jobs.size(); ++j)
+            pc.levels = std::max<int64_t>(pc.levels, js[j].n_parts);
         return;
     }
     LeafPool pool;
