@@ -28,7 +28,9 @@ class CoopTurn {
   public:
     // Blocks until this turn comes.  The turn weighs `weight` (the peel's
     // edges) unless the calling thread set another weight for its turns.
-    explicit CoopTurn(int64_t weight);
+    // With barriers false the peel launches no cooperative kernel: it also
+    // goes beside a holder that has said leaves_only().
+    explicit CoopTurn(int64_t weight, bool barriers = true);
     ~CoopTurn();
     CoopTurn(const CoopTurn &) = delete;
     CoopTurn &operator=(const CoopTurn &) = delete;
@@ -38,10 +40,13 @@ class CoopTurn {
     // Gives the device up, queues behind every current waiter and returns
     // when the turn comes again.
     void requeue();
+    // The holder launches no cooperative kernel any more.
+    void leaves_only();
 
   private:
     uint64_t ticket_ = 0;
     int64_t weight_ = 0;
+    bool held_ = true;  // false: beside another holder
 };
 
 namespace {

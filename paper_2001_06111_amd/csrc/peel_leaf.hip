@@ -20,8 +20,9 @@
 // it, nor did the links' ends in LDS by more than 3%.  An edge that crosses
 // the level waits in LDS for the end of its wave's phase, as queueing it takes
 // another wait for memory, and phase B has four elements a lane in flight:
-// 192 pool graphs' leaves 40 ms without either, 35 ms so.  512 graphs of 200 to 16,000 edges in one batch: 63.3 ms grid-wide,
-// 19.8 ms so; the 10k-edge uniform graph 0.67 ms and 0.46 ms.
+// 192 pool graphs' leaves 40 ms without either, 35 ms so.  512 graphs of 200 to
+// 16,000 edges in one batch: 63.3 ms grid-wide, 18.8 ms so; the 10k-edge uniform
+// graph 0.67 ms and 0.29 ms.
 //
 // The workgroup makes its own link lists (twin and bloom of each wedge of an
 // edge) from the wedge records by counting in LDS, so the index build of
@@ -58,6 +59,7 @@ struct LeafList {
 struct LeafArgs {
     LeafList list[kLeafLists];  // taken in turn
     int32_t n_lists;
+    int32_t once;  // a workgroup takes one job
     const int32_t *wea, *web, *wbl;
     const uint32_t *bwoff;
     const int32_t *bk;  // initial bloom numbers
@@ -185,7 +187,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
     int32_t max_level = 0;
     int32_t list = 0;  // thread 0's
 
-    while (true) {
+    for (bool more = true; more; more = !A.once) {
         __syncthreads();
         if (tid == 0) {
             s_job.ne = -1;
@@ -600,18 +602,19 @@ void leaf_state(const LeafArgs &A, int64_t b0, int64_t n, hipStream_t s) {
 }
 
 // Launches class c over A's lists by at most `most` workgroups.
-void launch_leaves(const LeafArgs &A, int c, bool unit_updates, int most, hipStream_t s) {
+void launch_leaves(LeafArgs A, int c, bool unit_updates, int most, hipStream_t s) {
     const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
     const LeafClass &K = kLeafClasses[c];
-    int dev = 0, cus = 0, occ = 0;
-    BT_HIP(hipGetDevice(&dev));
-    BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kLeafClasses[0].lds()));
-    BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, K.threads, K.lds()));
     int64_t n = 0;
     for (int l = 0; l < A.n_lists; ++l) n += A.list[l].j1 - A.list[l].j0;
-    const int64_t grid = std::min<int64_t>({n, (int64_t)cus * std::max(1, occ), most});
+    // Without a limit each job has a workgroup: one that took job after job
+    // would hold its CU, and small requests' peels on other streams would wait
+    // for the last of a large graph's leaves (small requests served beside
+    // 2M-edge graphs: 30 ms in the middle, 12 ms so).
+    const int64_t grid = std::min<int64_t>(n, most);
+    A.once = grid == n ? 1 : 0;
     if (grid <= 0) return;
     kern<<<(unsigned)grid, K.threads, K.lds(), s>>>(A, K);
     BT_CHECK_LAUNCH();
@@ -711,8 +714,9 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     BT_CHECK_LAUNCH();
     if (sup_out) supl_to_sup(ix.supl, sup_out, m, s);
     // This peel needs no co-resident workgroups, but it takes its turn like
-    // the others, so that a running peel of a much larger graph gives way.
-    CoopTurn turn(m);
+    // the others, so that a running sweep of a much larger graph gives way;
+    // it runs beside another peel's leaves.
+    CoopTurn turn(m, false);
     std::vector<int32_t> levels((size_t)ng, 0);
     int32_t max_level = 0;
     LeafCtl done;

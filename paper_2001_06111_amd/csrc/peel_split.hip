@@ -31,12 +31,14 @@
 //
 // Whole calls, level by level and split: 5M-edge Chung-Lu graph (75,000
 // rounds, bound by the 9 us a round's two grid barriers and chains take)
-// 1.107 s and 0.274 s; 200k-edge graph 66.1 and 18.9 ms; 400k-edge hub graph
-// by BiT-PC 439 and 113 ms; 192 pool graphs in one batch 618 and 157 ms.
+// 1.115 s and 0.239 s; 200k-edge graph 66.4 and 17.5 ms; 400k-edge hub graph
+// by BiT-PC 436 and 99 ms; 192 pool graphs in one batch 620 and 143 ms.
 // The 5M graph's first sweep is now bound by memory-side requests (about
 // 2e10/s of support atomics and random reads), a small graph's by the 10 to
-// 15 us of a round.  The level-by-level form stays for callers whose memory
-// does not hold the second copy of the index that the split needs.
+// 15 us of a round.  The level-by-level form (the same kernel, its parts single
+// levels) stays for graphs of few levels (few_levels below) and for callers
+// whose memory does not hold the second copy of the index that the split
+// needs.
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -1091,9 +1093,10 @@ hipGraphExec_t chunk_graph(const void *args, size_t bytes, int rounds, Workspace
 // less often, more leave less to deeper sweeps.  Of caps of 4, 8, 12, 16, 24,
 // 32, 48 and 64 the 5M-edge graph took 316, 262, 258, 245, 240, 238, 260 and
 // 286 ms, 1,024 pool graphs 1541, 1324, 1237, 1205, 1162, 1211, 1287 and 1347
-// ms; a 200k-edge graph, bound by its leaves' rounds, takes 32 best.
-int64_t parts_for(int64_t n, int64_t work, int64_t total) {
-    const int64_t cap = total >= (int64_t(1) << 20) ? 24 : 32;
+// ms; a 200k-edge graph, bound by its leaves' rounds, takes 32 best.  Unit
+// updates pay for each touch: 1171 ms with 16, 1411 ms with 24.
+int64_t parts_for(int64_t n, int64_t work, int64_t total, bool unit) {
+    const int64_t cap = total < (int64_t(1) << 20) ? 32 : unit ? 16 : 24;
     return std::max<int64_t>(4, std::min<int64_t>(cap, std::max<int64_t>(n / 2048, work / 32768)));
 }
 
@@ -1206,7 +1209,7 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
         J.narrow = jobs[(size_t)j].stuck ? 1 : 0;
         J.hi_bound = jobs[(size_t)j].hi;
         const int64_t n = jobs[(size_t)j].ne;
-        J.target_n = std::max<int64_t>(512, n / parts_for(n, jobs[(size_t)j].work, m));
+        J.target_n = std::max<int64_t>(512, n / parts_for(n, jobs[(size_t)j].work, m, ask.unit));
         first[(size_t)j] = SplitPart{ask.min_level, ask.min_level, j, 1};
     }
     if (nj == 1) {
@@ -1554,6 +1557,7 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         ask.min_level = 0;
         ask.sup_out = nullptr;
     }
+    if (turn) turn->leaves_only();
     if (leaves) leaves->finish(levels, max_level, pc);
     pc.launches += 1 + pc.yields;
     pc.max_phi = max_level;

@@ -16,6 +16,7 @@ struct Gate {
     std::condition_variable cv;
     uint64_t next = 0;
     bool busy = false;
+    bool leaves = false;  // the holder runs kernels without grid barriers only
     int64_t holder_weight = 0;
     std::map<uint64_t, int64_t> waiting;
     int32_t *word = nullptr;  // pinned, coherent: [0] yield request, [1] always 1
@@ -54,6 +55,7 @@ void take_turn(Gate &g, std::unique_lock<std::mutex> &lk, uint64_t ticket, int64
     g.cv.wait(lk, [&] { return !g.busy && g.waiting.begin()->first == ticket; });
     g.waiting.erase(ticket);
     g.busy = true;
+    g.leaves = false;
     g.holder_weight = weight;
     update_yield(g);
 }
@@ -66,7 +68,7 @@ thread_local int64_t t_turn_weight = -1;
 
 void set_turn_weight(int64_t w) { t_turn_weight = w; }
 
-CoopTurn::CoopTurn(int64_t weight) : weight_(t_turn_weight >= 0 ? t_turn_weight : weight) {
+CoopTurn::CoopTurn(int64_t weight, bool barriers) : weight_(t_turn_weight >= 0 ? t_turn_weight : weight) {
     Gate &g = gate();
     std::unique_lock<std::mutex> lk(g.mu);
     if (!g.word) {
@@ -81,10 +83,35 @@ CoopTurn::CoopTurn(int64_t weight) : weight_(t_turn_weight >= 0 ? t_turn_weight 
     }
     ticket_ = g.next++;
     g.waiting[ticket_] = weight_;
-    take_turn(g, lk, ticket_, weight_);
+    if (barriers) {
+        take_turn(g, lk, ticket_, weight_);
+        return;
+    }
+    update_yield(g);
+    g.cv.wait(lk, [&] {
+        return g.busy ? g.leaves : g.waiting.begin()->first == ticket_;
+    });
+    if (g.busy) {
+        held_ = false;
+        g.waiting.erase(ticket_);
+        update_yield(g);
+        g.cv.notify_all();  // the oldest waiter may be another now
+    } else {
+        take_turn(g, lk, ticket_, weight_);
+        g.leaves = true;
+        g.cv.notify_all();
+    }
+}
+
+void CoopTurn::leaves_only() {
+    Gate &g = gate();
+    std::lock_guard<std::mutex> lk(g.mu);
+    g.leaves = true;
+    g.cv.notify_all();
 }
 
 CoopTurn::~CoopTurn() {
+    if (!held_) return;
     Gate &g = gate();
     std::lock_guard<std::mutex> lk(g.mu);
     g.busy = false;
