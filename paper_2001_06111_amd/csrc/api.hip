@@ -773,10 +773,11 @@ static void decompose_batch_once(const bt_csr *gs, int32_t n, int64_t *const *su
                                  int64_t *const *phi_out, bt_stats *stats, Workspace &ws,
                                  hipStream_t s, bool plain, const SizedHook *on_sized) {
     if (stats) std::memset(stats, 0, sizeof *stats);
-    // Unions are cut from the graphs in decreasing edge count: a union peels
-    // for as many rounds as its slowest graph needs, so the large graphs,
-    // which need the most rounds, share a union instead of each stretching
-    // one (whole 4,096-graph pool: 62k rounds instead of 103k, 7% faster).
+    // Unions are cut from the graphs in decreasing edge count: a union takes
+    // as long as its slowest graph, so the large graphs, which need the most
+    // rounds, share a union instead of each stretching one (whole 4,096-graph
+    // pool, when it was peeled level by level: 62k rounds instead of 103k, 7%
+    // faster).
     std::vector<int32_t> ord((size_t)n);
     for (int32_t i = 0; i < n; ++i) ord[(size_t)i] = i;
     std::stable_sort(ord.begin(), ord.end(),
