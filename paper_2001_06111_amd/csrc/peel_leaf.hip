@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
     int32_t *const sup = reinterpret_cast<int32_t *>(li + items_lds);
     uint8_t *const stt = reinterpret_cast<uint8_t *>(sup + K.ecap);
     __shared__ LeafJob s_job;
-    __shared__ int32_t s_min;
+    __shared__ int32_t s_min[2];  // the next level, by the level's parity
     __shared__ uint32_t s_nf[2], s_ni[2], s_multi[2];
     __shared__ u64 s_mask[kLeafBlock / kWave][kAhead];
     __shared__ uint16_t s_cross[kLeafBlock / kWave][kCross];
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
         // Edges past the end, up to a multiple of four, are removed ones.
         if (tid < 4 && ne + tid < ((ne + 3) & ~3)) stt[ne + tid] = kRemoved;
         if (tid == 0) {
-            s_min = INT_MAX;
+            s_min[0] = INT_MAX;
             s_nf[0] = s_nf[1] = s_ni[0] = s_ni[1] = s_multi[0] = s_multi[1] = 0;
         }
         __syncthreads();
@@ -334,9 +334,15 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
                 mn = min(mn, min(min(v.x, v.y), min(v.z, v.w)));
             }
             mn = wave_min(mn);
-            if (lane_id() == 0 && mn != INT_MAX) atomicMin(&s_min, mn);
+            // The other word is cleared for the level after this one.  It was
+            // last read before the barrier that ended the last level's queueing,
+            // and is next lowered after the one below: a level whose edges have
+            // no links runs no round, so no barrier but these two lies between
+            // one level's minimum and the next one's.
+            if (tid == 0) s_min[(levels & 1) ^ 1] = INT_MAX;
+            if (lane_id() == 0 && mn != INT_MAX) atomicMin(&s_min[levels & 1], mn);
             __syncthreads();
-            const int32_t level = s_min;
+            const int32_t level = s_min[levels & 1];
             if (level == INT_MAX) break;
             if (mn == level) {  // only waves that hold such an edge look again
                 for (int i0 = 0; i0 < ne; i0 += 4 * nthr) {
@@ -349,7 +355,6 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
                 }
             }
             __syncthreads();
-            if (tid == 0) s_min = INT_MAX;
             ++levels;
             if (level > max_level) max_level = level;
             uint32_t nf = s_nf[r & 1];

@@ -48,3 +48,24 @@ def test_batch_of_mixed_sizes():
         if g.m:
             wedges += binding.bt_decompose(upload(g), stats=True)[2]["bloom_wedges"]
     assert st["bloom_wedges"] == wedges
+
+
+def test_levels_that_run_no_round():
+    """Edges without butterflies are a level whose edges have no links, so no
+    round comes between its minimum and the next level's: graphs of all three
+    launch sizes with many such edges, several times over."""
+    gs = []
+    for i, m in enumerate([60, 300, 900, 2000, 5000, 7000, 12000] * 12):
+        # A dense core, and as many pendant edges as it has.
+        core = graphs.random_dense(max(4, int(m ** 0.5) // 2), max(4, int(m ** 0.5) // 2), 0.8, i)
+        u, v = core.edges()
+        k = m - core.m if m > 2 * core.m else core.m
+        keys = [(int(a), int(b)) for a, b in zip(u, v)]
+        keys += [(core.n_upper + j // 40, core.n_lower + j) for j in range(k)]
+        gs.append(synth.from_edges(core.n_upper + (k + 39) // 40, core.n_lower + k, keys))
+    want = [oracle_all(g)[2] for g in gs]
+    assert all((w == 0).any() and (w > 0).any() for w in want)
+    ds = [upload(g) for g in gs]
+    for _ in range(20):
+        for w, p in zip(want, binding.bt_decompose_batch(ds)[1]):
+            assert np.array_equal(p.cpu().numpy(), w)
