@@ -68,7 +68,7 @@ struct LeafArgs {
     uint32_t *ends;     // end of each edge's links in its job's
     // Work lists past their part in LDS.
     uint2 *front[2];    // {edge | (links - 1) << 16, first link}
-    uint2 *items;       // {bloom | multi << 31, first wedge << 6 | (wedges - 1)}
+    uint2 *items;       // {bloom | multi << 31, first wedge << 6 | (wedges - 1)}; kLeafJobWedges
     const int32_t *oid;  // where an edge's number goes in phi_out (null: at the edge)
     int64_t *phi_out;
     int32_t *glevels;  // levels per graph
@@ -782,6 +782,9 @@ void LeafRun::take() {
     std::vector<int32_t> order(n);
     for (size_t j = 0; j < n; ++j) order[j] = (int32_t)j;
     const auto leaf = [&](int32_t j) -> const SplitJob & { return pool_.leaves[S.taken + (size_t)j]; };
+    for (size_t j = S.taken; j < pool_.jobs.size(); ++j)
+        if (pool_.jobs[j].nw >= kLeafJobWedges)
+            throw Error{BT_EDEVICE, "a leaf holds more wedges than its work items can name"};
     std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
         const int cx = leaf_class(leaf(x).ne), cy = leaf_class(leaf(y).ne);
         if (cx != cy) return cx < cy;

@@ -1536,10 +1536,13 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         if (depth == 0) pool.place(ix.link, ix.n_w, m, ws);
         Regrouped g;
         regroup(cur, sw, jobs, depth, phi_out, levels, max_level, g, pool, ws, s);
-        if (verbose)
-            std::fprintf(stderr, "[peel] regrouped: %zu jobs (%lld edges, %lld wedges); %zu leaves (%lld edges, %lld wedges) in all\n",
+        if (verbose) {
+            uint32_t top = 0;
+            for (const SplitJob &l : pool.leaves) top = std::max(top, l.work);
+            std::fprintf(stderr, "[peel] regrouped: %zu jobs (%lld edges, %lld wedges); %zu leaves (%lld edges, %lld wedges, up to %u in one) in all\n",
                          g.jobs.size(), (long long)g.m, (long long)g.n_w, pool.leaves.size(),
-                         (long long)pool.m, (long long)pool.n_w);
+                         (long long)pool.m, (long long)pool.n_w, top);
+        }
         jobs = g.jobs;
         if (!leaves && !pool.leaves.empty())
             leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, unit, ng, ws, s));

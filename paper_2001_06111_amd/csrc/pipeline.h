@@ -205,6 +205,9 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
 constexpr int64_t kLeafEdges = int64_t(1) << 14;
 // A part of a larger graph may have up to this many (what fits LDS).
 constexpr int64_t kLeafCap = 28672;
+// A job's wedges must be fewer than this (its work items hold 26-bit positions).
+// A graph of m edges has at most 2 m^(3/2) (Lemma 6), so 2^22 below kLeafEdges.
+constexpr int64_t kLeafJobWedges = int64_t(1) << 26;
 struct LeafJob {
     int32_t e0, ne;       // edges [e0, e0 + ne)
     uint32_t w0, nw;      // wedges [w0, w0 + nw)

@@ -21,6 +21,8 @@ namespace bt {
 namespace {
 
 constexpr uint32_t kLeafWedges = 500000;
+constexpr int kLeafMostLog2 = 22;  // of the wedges of any leaf
+static_assert((int64_t(1) << kLeafMostLog2) <= kLeafJobWedges, "a leaf's work items hold them");
 constexpr int kTile = 2048;  // wedges per tile of the order-keeping compactions
 
 __global__ void k_edge_keys(const EdgeMark *mark, int64_t m, int32_t n_parts, uint64_t *keys,
@@ -290,8 +292,23 @@ __global__ void k_job_links(const int32_t *wea, const int32_t *web, const int32_
 // Whether a part is peeled by one workgroup.  A leaf takes about 60 ns a
 // wedge, which a sweep that splits it further must beat; parts that a sweep
 // took whole, or that several have not brought down, are left to it as well.
-bool leaf_part(const SplitJob &c, int depth) {
-    return c.ne < kLeafCap && (c.work <= kLeafWedges || c.ne < 512 || c.stuck || depth > 5);
+// Above `most` wedges a part goes on to the next sweep whatever it is: its
+// positions must fit the work items, and one workgroup would take seconds.  A
+// part that a sweep took whole is cut by levels, whose range shrinks by 16 a
+// depth, down to single ones, so it ends.  Bounds of 2^20, 2^22 and 2^25: 2M-edge
+// request graph 514, 527 and 543 ms (its largest leaves 0.7, 2.6 and 4.2 million
+// wedges), 20M-edge hub graph 2.94, 2.91 and 2.92 s (1.0, 1.6 and 1.6 million);
+// 5M-edge graph, 400,000-edge hub graph by BiT-PC: no leaf above 2^20.
+bool leaf_part(const SplitJob &c, int depth, uint32_t most) {
+    return c.ne < kLeafCap && c.work <= most &&
+           (c.work <= kLeafWedges || c.ne < 512 || c.stuck || depth > 5);
+}
+
+// BT_LEAF_WEDGES_LOG2 (0..25) sets another bound, for tests and measurements.
+uint32_t leaf_most() {
+    const char *v = std::getenv("BT_LEAF_WEDGES_LOG2");
+    const int l = v ? std::atoi(v) : -1;
+    return uint32_t(1) << (l >= 0 && l <= 25 ? l : kLeafMostLog2);
 }
 
 // Workspace names of one of the two sets.
@@ -313,6 +330,7 @@ void regroup(const SplitIndex &ix, const SweepResult &sw, const std::vector<Spli
     const int32_t np = sw.n_parts;
     out.jobs.clear();
     std::vector<SplitJob> leaves;
+    const uint32_t most = leaf_most();
     // Edges by part.
     uint64_t *ekeys = ws.get<uint64_t>("rg_ekeys", m);
     uint32_t *evals = ws.get<uint32_t>("rg_evals", m);
@@ -367,7 +385,7 @@ void regroup(const SplitIndex &ix, const SweepResult &sw, const std::vector<Spli
         c.hi = std::min(P.hi, J.hi);
         c.stuck = n == J.ne;
         c.work = wcnt[(size_t)p];
-        (leaf_part(c, depth) ? leaves : out.jobs).push_back(c);
+        (leaf_part(c, depth, most) ? leaves : out.jobs).push_back(c);
     }
     const int32_t nj = (int32_t)out.jobs.size(), nl = (int32_t)leaves.size();
     const uint32_t n_ranks = (uint32_t)(nj + nl);

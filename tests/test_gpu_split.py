@@ -5,6 +5,7 @@ unions whose graphs differ in size and in depth, the level-by-level form and
 the two-kernel rounds.  Bit-exact against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2001_06111_amd import binding, synth
 from tests import graphs
@@ -117,3 +118,41 @@ def test_few_levels(m, mode, monkeypatch):
     assert st["max_phi"] == int(ophi.max()) and st["levels"] == np.unique(ophi).size
     _, phi, _ = binding.bt_decompose_pc(upload(g), 0.05)
     assert np.array_equal(phi.cpu().numpy(), ophi)
+
+
+@pytest.mark.parametrize("log2", ["0", "6", "11", "15"])
+@pytest.mark.parametrize("g", [_cl(30000), _cl(60000), synth.complete(170, 180),
+                               graphs.random_dense(220, 210, 0.8, 5),
+                               graphs.disjoint_union(_cl(20000), synth.complete(130, 140))],
+                         ids=lambda g: g.name)
+def test_leaves_of_bounded_wedges(g, log2, monkeypatch):
+    """Parts of more wedges than a leaf may hold go on to the next sweep,
+    whatever their edges and depth, down to parts of one level."""
+    ophi = oracle_all(g)[2]
+    monkeypatch.setenv("BT_LEAF_WEDGES_LOG2", log2)
+    monkeypatch.setenv("BT_PEEL_MODE", "split")
+    phi = binding.bt_decompose(upload(g))[1]
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+    phi = binding.bt_decompose_pc(upload(g), tau=0.3)[1]
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+
+
+def test_few_edges_of_many_wedges(monkeypatch):
+    """2,500 hubs on 20 common lower vertices (and 5,000 of their own each)
+    and 2,800 upper vertices on ten of them: 28,000 edges, fewer than a leaf
+    takes, that hold 7.0e7 wedges and stay together at the next depth."""
+    hubs, own, common, small, ten = 2500, 5000, 20, 2800, 10
+    lower = np.concatenate([np.broadcast_to(np.arange(common), (hubs, common)),
+                            common + own * np.arange(hubs)[:, None] + np.arange(own)], axis=1)
+    some = np.sort(np.argsort(np.random.default_rng(7).random((small, 12)), axis=1)[:, :ten], axis=1)
+    row_ptr = np.concatenate([np.arange(hubs + 1) * (common + own),
+                              hubs * (common + own) + ten * np.arange(1, small + 1)])
+    g = synth.Graph(hubs + small, common + own * hubs, row_ptr.astype(np.int64),
+                    np.concatenate([lower.ravel(), some.ravel()]).astype(np.int32), "hubs")
+    d = upload(g)
+    sup, phi, st = binding.bt_decompose(d, stats=True)
+    monkeypatch.setenv("BT_PEEL_MODE", "plain")
+    sup0, phi0, st0 = binding.bt_decompose(d, stats=True)
+    assert torch.equal(phi, phi0) and torch.equal(sup, sup0)
+    for k in ("butterflies", "max_phi", "levels", "bloom_wedges"):
+        assert st[k] == st0[k], k
