@@ -663,7 +663,9 @@ void add_stats(bt_stats &t, const bt_stats &s) {
     t.peel_yields += s.peel_yields;
 }
 
-// Graphs [a, b) as one union; splits the range if the union is too large.
+// Graphs [a, b) as one union; splits the range if the union is too large (its
+// halves' sizes are not reported, so with on_sized they peel in the form that
+// needs the least).
 void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out,
                  int64_t *const *phi_out, bt_stats *stats, Workspace &ws, hipStream_t s,
                  bool plain, const SizedHook *on_sized) {
@@ -690,8 +692,8 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     const bool splittable = b - a > 1;
     if (splittable && (nu + nl >= INT32_MAX || m >= INT32_MAX)) {
         const int32_t mid = a + (b - a) / 2;
-        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain, nullptr);
-        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain, nullptr);
+        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
+        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
         return;
     }
     BatchEntry *dtab = ws.get<BatchEntry>("batch_tab", b - a);
@@ -744,8 +746,8 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     } catch (const Error &e) {
         if (e.status != BT_EOVERFLOW || !splittable) throw;
         const int32_t mid = a + (b - a) / 2;
-        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain, nullptr);
-        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain, nullptr);
+        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
+        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
         return;
     }
     k_batch_scatter<<<grid, 256, 0, s>>>(dtab, b - a, sup_u, phi_u, perm, flags);

@@ -339,13 +339,14 @@ void bt_engine::run_batch(int slot, const Batch &b, Workspace &ws, hipStream_t s
                              s, &on_sized);
         for (auto &r : b.reqs) out.push_back(Done{r.id, BT_OK});
     } catch (const Error &) {
-        // Isolate the failure: run the requests of the batch one by one.
+        // Isolate the failure: run the requests of the batch one by one, each
+        // within the batch's admission as the batch was.
         for (auto &r : b.reqs) {
             bt_status st = BT_OK;
             try {
                 bt_csr g = r.g;
                 int64_t *sp = r.sup, *pp = r.phi;
-                decompose_batch_impl(&g, 1, &sp, &pp, nullptr, ws, s);
+                decompose_batch_impl(&g, 1, &sp, &pp, nullptr, ws, s, &on_sized);
             } catch (const Error &e) {
                 st = e.status;
             } catch (...) {
