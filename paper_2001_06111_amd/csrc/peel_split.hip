@@ -151,6 +151,7 @@ struct SweepArgs {
     uint32_t m;
     int32_t unit;       // one decrement per kill (no batch bloom processing)
     int32_t short_a, short_b;  // items that fill a wave in phases A, B; 0: most are long
+    uint32_t reserve;   // slots that a wave may leave over in a phase
     FrontItem *front[2];  // {edge, part, links [lo, hi)}
     SweepBloomItem *tc[2];
     SweepGatherItem *gth[2];
@@ -189,6 +190,13 @@ __device__ __forceinline__ void set_front_flags(const SweepArgs &P, bool on, int
 // (up to kReserve) and fills what it leaves over with null items, at most half
 // as many as the round had.
 constexpr uint32_t kReserve = 128;
+// Slots that the waves of a phase may leave over in all.  Their lists take 80
+// bytes a slot, 30 MB at kReserve a wave, which a caller short of memory has
+// not counted on for a small graph: at most 64 bytes an edge there.
+int64_t spare_slots(int64_t m, int64_t waves, bool least) {
+    const int64_t all = waves * kReserve;
+    return least ? std::min(all, m * 4 / 5) : all;
+}
 struct Reserve {
     uint32_t base = 0, left = 0;  // lists hold fewer than 2^32 items
 };
@@ -682,7 +690,7 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
     const int q = p ^ 1;
     const int32_t now = (int32_t)r;
     const uint32_t per = items_per_step(nf, nwaves, P.short_a);
-    const uint32_t grow = per > 1 ? 2 * per : 0u;
+    const uint32_t grow = per > 1 ? min(2 * per, P.reserve) : 0u;
     Reserve rb, rf;
     int32_t flagged = -1;
     for (int64_t g0 = wid * per; g0 < (int64_t)nf; g0 += nwaves * per) {
@@ -771,7 +779,7 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
     const uint32_t per = items_per_step(ntc, nwaves, P.short_b);
-    const uint32_t grow = per > 1 ? 2 * per : 0u;
+    const uint32_t grow = per > 1 ? min(2 * per, P.reserve) : 0u;
     Reserve rf;
     int32_t flagged = -1;
     for (int64_t g0 = wid * per; g0 < (int64_t)ntc; g0 += nwaves * per) {
@@ -1119,6 +1127,7 @@ struct SweepAsk {
     const int32_t *fixed = nullptr;
     int32_t min_level = 0;
     bool unit = false, plain = false;
+    bool least = false;          // with the least memory
     int64_t *sup_out = nullptr;
     int64_t *scratch = nullptr;  // plain: m places that the caller writes afterwards
 };
@@ -1147,9 +1156,9 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     if (2 * ix.n_w >= (int64_t)UINT32_MAX)
         throw Error{BT_EOVERFLOW, "edge-to-wedge links must be below 2^32"};
     const int64_t nb = ix.n_b > 0 ? ix.n_b : 1;
-    // A phase's waves leave at most kReserve slots each; a round's frontier
-    // list takes those of two phases.
-    const int64_t spare = (int64_t)pblocks * (kPBlock / kWave) * kReserve;
+    // A round's frontier list takes the slots that two phases leave over.
+    const int64_t waves = (int64_t)pblocks * (kPBlock / kWave);
+    const int64_t spare = spare_slots(m, waves, ask.least);
     const int64_t max_tc = nb + ix.n_w / kWedgeChunk + 1 + spare;
     const int64_t max_front = m + 2 * ix.n_w / kLinkChunk + 1 + 2 * spare;
     const int64_t max_gth = m / kGatherChunk + nj + 1;
@@ -1178,6 +1187,7 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     P.link = ix.link;
     P.n_w = (uint32_t)ix.n_w;
     P.unit = ask.unit ? 1 : 0;
+    P.reserve = (uint32_t)(spare / waves);
     P.front[0] = ws.get<FrontItem>("peel_front0", max_front);
     P.front[1] = ws.get<FrontItem>("peel_front1", max_front);
     P.tc[0] = ws.get<SweepBloomItem>("peel_tc0", max_tc);
@@ -1440,7 +1450,7 @@ void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn 
 }
 
 int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bool plain) {
-    const int64_t spare = 256 * 16 * (int64_t)kReserve;  // one wave's, on a card of 256 CUs
+    const int64_t spare = spare_slots(m, 256 * 16, plain);  // waves of a card of 256 CUs
     // Sweep: edges, blooms, wedges, work lists.  The deeper sweeps' blooms
     // are parts of the first's, at most one a wedge.
     const int64_t nb = plain ? n_b : std::max(n_b, n_w);
@@ -1497,6 +1507,7 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
     ask.fixed = opt ? opt->fixed : nullptr;
     ask.min_level = opt ? opt->min_level : 0;
     ask.unit = unit;
+    ask.least = opt && opt->plain;
     // Few levels: level by level as well, as splitting passes over the graph
     // once more.
     ask.plain = opt && (opt->plain || few_levels(std::min(ix.max_sup, opt->levels), ix.n_w));

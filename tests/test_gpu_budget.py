@@ -37,3 +37,22 @@ def test_batch_with_a_request_that_fails():
     assert done == {0: binding.BT_EINVAL, 1: binding.BT_OK}
     assert np.array_equal(eng.results[1][2].cpu().numpy(), oracle_all(good)[2])
     assert mem["peak_held"] <= budget and mem["peak_committed"] <= budget, mem
+
+
+@pytest.mark.parametrize("g", [synth.uniform(1200, 1800, 16500, 1), synth.scaled_chunglu(17000, seed=1),
+                               synth.uniform(5000, 7000, 117248, 2), synth.complete(150, 150),
+                               synth.scaled_chunglu(60000, seed=1)], ids=lambda g: g.name)
+def test_budget_of_one_request(g):
+    """A budget of just the estimate admits the request and holds it."""
+    budget = estimate(g)
+    eng = binding.BtEngine(hbm_budget=budget, slots=-1)
+    try:
+        d = upload(g)
+        eng.bt_engine_submit(d, 0)
+        assert eng.bt_engine_step() == 1
+        done, mem = dict(eng.bt_engine_poll()), eng.bt_engine_memory()
+    finally:
+        eng.bt_engine_destroy()
+    assert done == {0: binding.BT_OK}
+    assert np.array_equal(eng.results[0][2].cpu().numpy(), oracle_all(g)[2])
+    assert mem["peak_held"] <= budget and mem["peak_committed"] <= budget, mem
