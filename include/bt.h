@@ -40,7 +40,8 @@
  *     bt_decompose_batch, bt_bitruss_components, bt_tune) serialise on an
  *     internal lock; engines use workspaces of their own.  Cooperative peel
  *     launches (all of the above that peel, and engine batches) run one at
- *     a time in the process.
+ *     a time in the process; peels of graphs below 2^14 edges alone make none
+ *     and go beside another's.
  */
 #ifndef BT_H
 #define BT_H
@@ -343,10 +344,12 @@ bt_status bt_decompose_batch(const bt_csr *gs, int32_t n_graphs, int64_t *const 
  *   peels of different slots take turns; a second slot counts and builds
  *   the index of the next batch while one slot's batch peels, and when that
  *   batch is of a smaller size class, the running peel ends its launch
- *   between two rounds (within 16 rounds), lets the smaller batch peel,
- *   and resumes where it stopped.  With two or more slots one is kept for
- *   the small class: a slot starts a larger class's batch only while fewer
- *   than slots - 1 others run one, and not while requests still come in
+ *   between two rounds (within 16 rounds or 50 us, whichever comes first; where
+ *   it peels parts of a graph in single workgroups, when those begun are
+ *   done), lets the smaller batch peel, which begins beside it at once if it
+ *   is of the smallest class, and resumes where it stopped.  With two or more
+ *   slots one is kept for the small class: a slot starts a larger class's
+ *   batch only while fewer than slots - 1 others run one, and not while requests still come in
  *   (none for 1 ms, or the oldest of the class waiting 10 ms).
  *   Memory: the budget covers every slot's cached workspace plus what its
  *   running batch may still allocate (the submit-time estimate, replaced by

@@ -20,16 +20,16 @@ namespace bt {
 // a grid barrier for blocks the other keeps from being scheduled.  They
 // therefore take turns in the process, in the order they asked.  While a
 // turn is held, a waiter that weighs under 1/8 of the holder raises the
-// holder's yield word (pinned host memory that the kernel reads every few
-// rounds); the peel kernel then ends its launch between two rounds, and its
-// host thread queues again and relaunches from the state left in device
-// memory.
+// holder's yield word (pinned host memory that its kernels read); a sweep then
+// ends its launch between two rounds, a launch of leaves when the leaves begun
+// are done, and the host thread queues again and relaunches from the state
+// left in device memory.
 class CoopTurn {
   public:
     // Blocks until this turn comes.  The turn weighs `weight` (the peel's
     // edges) unless the calling thread set another weight for its turns.
-    // With barriers false the peel launches no cooperative kernel: it also
-    // goes beside a holder that has said leaves_only().
+    // With barriers false the peel launches no cooperative kernel: it goes
+    // beside the holder at once, which it makes yield as a waiter does.
     explicit CoopTurn(int64_t weight, bool barriers = true);
     ~CoopTurn();
     CoopTurn(const CoopTurn &) = delete;
@@ -38,15 +38,14 @@ class CoopTurn {
     // With force, a word that always reads 1, for tests of the resume path.
     const int32_t *yield_word(bool force) const;
     // Gives the device up, queues behind every current waiter and returns
-    // when the turn comes again.
+    // when the turn comes again and the much lighter peels that went beside
+    // have ended.
     void requeue();
-    // The holder launches no cooperative kernel any more.
-    void leaves_only();
 
   private:
     uint64_t ticket_ = 0;
     int64_t weight_ = 0;
-    bool held_ = true;  // false: beside another holder
+    bool held_ = true;  // false: beside the holder
 };
 
 namespace {

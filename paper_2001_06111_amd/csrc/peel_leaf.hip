@@ -60,6 +60,10 @@ struct LeafArgs {
     LeafList list[kLeafLists];  // taken in turn
     int32_t n_lists;
     int32_t once;  // a workgroup takes one job
+    // Nullable: the word that asks the launch to end early.  Workgroups from
+    // `sure` on then take no job, and none takes another.
+    const int32_t *yield;
+    int32_t sure;
     const int32_t *wea, *web, *wbl;
     const uint32_t *bwoff;
     const int32_t *bk;  // initial bloom numbers
@@ -186,12 +190,16 @@ __global__ __launch_bounds__(kLeafBlock) void k_peel_leaf(LeafArgs A, LeafClass 
     u64 rounds = 0;  // thread 0's
     int32_t max_level = 0;
     int32_t list = 0;  // thread 0's
+    bool done_one = false;
 
-    for (bool more = true; more; more = !A.once) {
+    for (bool more = true; more; more = !A.once, done_one = true) {
         __syncthreads();
         if (tid == 0) {
             s_job.ne = -1;
-            for (; list < A.n_lists; ++list) {
+            const bool stop = A.yield && (done_one || (int32_t)blockIdx.x >= A.sure) &&
+                              __hip_atomic_load(A.yield, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_SYSTEM) != 0;
+            for (; !stop && list < A.n_lists; ++list) {
                 const LeafList &L = A.list[list];
                 const int32_t i = L.j0 + atomicAdd(L.queue, 1);
                 if (i >= L.j1) continue;
@@ -606,20 +614,25 @@ void leaf_state(const LeafArgs &A, int64_t b0, int64_t n, hipStream_t s) {
     BT_CHECK_LAUNCH();
 }
 
-// Launches class c over A's lists by at most `most` workgroups.
-void launch_leaves(LeafArgs A, int c, bool unit_updates, int most, hipStream_t s) {
+// Workgroups of a launch that take a job whatever the yield word says, so that
+// a launch between two yields gets on; the other CUs are free for who asked.
+constexpr int kSureLeaves = 64;
+
+// Launches class c over A's lists, in which n jobs are left, by at most `most`
+// workgroups.
+void launch_leaves(LeafArgs A, int c, int64_t n, bool unit_updates, int most, hipStream_t s) {
     const auto kern = unit_updates ? k_peel_leaf<true> : k_peel_leaf<false>;
     const LeafClass &K = kLeafClasses[c];
     BT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kLeafClasses[0].lds()));
-    int64_t n = 0;
-    for (int l = 0; l < A.n_lists; ++l) n += A.list[l].j1 - A.list[l].j0;
     // Without a limit each job has a workgroup: one that took job after job
     // would hold its CU, and small requests' peels on other streams would wait
     // for the last of a large graph's leaves (small requests served beside
-    // 2M-edge graphs: 30 ms in the middle, 12 ms so).
+    // 2M-edge graphs: 30 ms in the middle, 12 to 28 ms so, and 2.1 to 2.5 ms
+    // since those leaves that have not begun make room for them).
     const int64_t grid = std::min<int64_t>(n, most);
     A.once = grid == n ? 1 : 0;
+    A.sure = kSureLeaves;
     if (grid <= 0) return;
     kern<<<(unsigned)grid, K.threads, K.lds(), s>>>(A, K);
     BT_CHECK_LAUNCH();
@@ -627,10 +640,10 @@ void launch_leaves(LeafArgs A, int c, bool unit_updates, int most, hipStream_t s
 
 // Runs lists of jobs (lists[l][c]: list l's jobs of class c) to their end and
 // reads the counters back.  `early` (nullable): the end of a launch that has
-// taken from them already.
+// taken from them already.  `turn` (nullable): held, with A.yield its word.
 void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hipEvent_t early,
                 bool unit_updates, int32_t n_roots, std::vector<int32_t> &levels, int32_t &max_level, PeelCounters &pc,
-                LeafCtl &done, Workspace &ws, hipStream_t s) {
+                LeafCtl &done, CoopTurn *turn, Workspace &ws, hipStream_t s) {
     hipEvent_t ev0, ev1;
     BT_HIP(hipEventCreate(&ev0));
     BT_HIP(hipEventCreate(&ev1));
@@ -647,47 +660,66 @@ void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hip
                 if (e[c]) (void)hipEventDestroy(e[c]);
         }
     } ev_free{ev0, ev1, joins};
-    BT_HIP(hipEventRecord(ev0, s));
-    int last = -1;
-    int64_t n_jobs = 0;
-    const auto jobs_of = [&](int c) {
-        int64_t n = 0;
-        for (const auto &l : lists) n += l[(size_t)c].j1 - l[(size_t)c].j0;
-        return n;
-    };
-    for (int c = 0; c < kNumLeafClasses; ++c) {
-        if (jobs_of(c)) last = c;
-        n_jobs += jobs_of(c);
-    }
-    for (int c = 0; c < kNumLeafClasses; ++c) {
-        if (!jobs_of(c)) continue;
-        A.n_lists = 0;
-        for (const auto &l : lists)
-            if (l[(size_t)c].j1 > l[(size_t)c].j0) A.list[A.n_lists++] = l[(size_t)c];
-        const hipStream_t cs = c == last ? s : ws.side(c);  // the last class stays on s
-        if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
-        launch_leaves(A, c, unit_updates, INT_MAX, cs);
-        if (cs != s) {
-            BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
-            BT_HIP(hipEventRecord(joins[c], cs));
-        }
-    }
-    for (hipEvent_t e : joins)
-        if (e) BT_HIP(hipStreamWaitEvent(s, e, 0));
-    if (early) BT_HIP(hipStreamWaitEvent(s, early, 0));
-    BT_HIP(hipEventRecord(ev1, s));
     LeafCtl *hc =
         reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (n_roots + 1) / 2)));
     int32_t *hl = reinterpret_cast<int32_t *>(hc + 1);
-    BT_HIP(hipMemcpyAsync(hc, A.ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));
+    // Jobs of class c that no workgroup has taken.
+    const auto left = [&](int c, bool begun) {
+        int64_t n = 0;
+        for (const auto &L : lists) {
+            const LeafList &l = L[(size_t)c];
+            const int32_t taken = begun ? hc->queue[&L - lists.data()][c] : 0;
+            n += std::max(l.j1 - l.j0 - taken, 0);
+        }
+        return n;
+    };
+    float ms = 0.f;
+    int64_t n_jobs = 0;
+    for (bool begun = false;; begun = true) {
+        int64_t n[kNumLeafClasses], all = 0;
+        int last = -1;
+        for (int c = 0; c < kNumLeafClasses; ++c) {
+            all += n[c] = left(c, begun);
+            if (n[c]) last = c;
+        }
+        if (begun) {
+            if (all == 0) break;
+            if (!turn) throw Error{BT_EDEVICE, "leaves were left over"};
+            pc.yields += 1;
+            turn->requeue();
+        } else {
+            n_jobs = all;
+        }
+        BT_HIP(hipEventRecord(ev0, s));
+        for (int c = 0; c < kNumLeafClasses; ++c) {
+            if (!n[c]) continue;
+            A.n_lists = 0;
+            for (const auto &l : lists)
+                if (l[(size_t)c].j1 > l[(size_t)c].j0) A.list[A.n_lists++] = l[(size_t)c];
+            const hipStream_t cs = c == last ? s : ws.side(c);  // the last class stays on s
+            if (cs != s) BT_HIP(hipStreamWaitEvent(cs, ev0, 0));
+            launch_leaves(A, c, n[c], unit_updates, INT_MAX, cs);
+            if (cs != s) {
+                if (!joins[c]) BT_HIP(hipEventCreateWithFlags(&joins[c], hipEventDisableTiming));
+                BT_HIP(hipEventRecord(joins[c], cs));
+            }
+        }
+        for (int c = 0; c < kNumLeafClasses; ++c)
+            if (n[c] && c != last) BT_HIP(hipStreamWaitEvent(s, joins[c], 0));
+        if (early && !begun) BT_HIP(hipStreamWaitEvent(s, early, 0));
+        BT_HIP(hipEventRecord(ev1, s));
+        BT_HIP(hipMemcpyAsync(hc, A.ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));
+        BT_HIP(hipStreamSynchronize(s));
+        float t = 0.f;
+        BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
+        ms += t;
+    }
     BT_HIP(hipMemcpyAsync(hl, A.glevels, sizeof(int32_t) * n_roots, hipMemcpyDeviceToHost, s));
     BT_HIP(hipStreamSynchronize(s));
-    float t = 0.f;
-    BT_HIP(hipEventElapsedTime(&t, ev0, ev1));
     if (std::getenv("BT_PEEL_VERBOSE"))
         std::fprintf(stderr, "[peel] leaves: %lld: %.2f ms, %llu rounds\n", (long long)n_jobs,
-                     (double)t, hc->rounds);
-    pc.kernel_ms += t;
+                     (double)ms, hc->rounds);
+    pc.kernel_ms += ms;
     pc.rounds += (int64_t)hc->rounds;
     pc.updates += (int64_t)hc->updates;
     pc.updates_unbatched += (int64_t)(hc->updates + hc->unbatched);
@@ -718,9 +750,8 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
     k_leaf_jobs<<<grid_for(ng, 256, 256), 256, 0, s>>>(doff, ng, ix.base, ix.cursor, jobs, A.ctl);
     BT_CHECK_LAUNCH();
     if (sup_out) supl_to_sup(ix.supl, sup_out, m, s);
-    // This peel needs no co-resident workgroups, but it takes its turn like
-    // the others, so that a running sweep of a much larger graph gives way;
-    // it runs beside another peel's leaves.
+    // This peel needs no co-resident workgroups, so it begins at once, beside
+    // another that holds the turn; one of a much larger graph gives way.
     CoopTurn turn(m, false);
     std::vector<int32_t> levels((size_t)ng, 0);
     int32_t max_level = 0;
@@ -733,7 +764,7 @@ void peel_leaf(IndexArrays &ix, const std::vector<int64_t> &off, const int64_t *
         lists[0].push_back(LeafList{jobs, nullptr, &A.ctl->queue[0][c], a, b});
         a = b;
     }
-    run_leaves(A, lists, nullptr, unit_updates, ng, levels, max_level, pc, done, ws, s);
+    run_leaves(A, lists, nullptr, unit_updates, ng, levels, max_level, pc, done, nullptr, ws, s);
     pc.launches += 1;
     pc.max_phi = max_level;
     for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);
@@ -752,8 +783,9 @@ struct LeafRun::State {
 };
 
 LeafRun::LeafRun(const LeafPool &pool, int64_t m, int64_t n_w, int64_t *phi_out, bool unit_updates,
-                 int32_t n_roots, Workspace &ws, hipStream_t s)
-    : pool_(pool), unit_(unit_updates), roots_(n_roots), ws_(ws), s_(s), st_(new State()) {
+                 int32_t n_roots, CoopTurn *turn, const int32_t *yield_word, Workspace &ws,
+                 hipStream_t s)
+    : pool_(pool), unit_(unit_updates), roots_(n_roots), turn_(turn), ws_(ws), s_(s), st_(new State()) {
     LeafArgs &A = st_->A;
     // A leaf holds an edge or more, a bloom a wedge or more; a depth's blooms
     // have a slot more than there are.
@@ -765,6 +797,7 @@ LeafRun::LeafRun(const LeafPool &pool, int64_t m, int64_t n_w, int64_t *phi_out,
     A.bwoff = pool.bwoff;
     A.oid = pool.oid;
     A.phi_out = phi_out;
+    A.yield = yield_word;
 }
 
 LeafRun::~LeafRun() {
@@ -832,7 +865,7 @@ void LeafRun::start(int groups) {
     LeafArgs A = S.A;
     A.n_lists = 1;
     A.list[0] = S.lists.back()[0];
-    launch_leaves(A, 0, unit_, groups, S.stream);
+    launch_leaves(A, 0, A.list[0].j1 - A.list[0].j0, unit_, groups, S.stream);
     BT_HIP(hipEventRecord(S.early, S.stream));
 }
 
@@ -841,7 +874,7 @@ void LeafRun::finish(std::vector<int32_t> &levels, int32_t &max_level, PeelCount
     if (pool_.leaves.size() > S.taken) take();
     if (S.lists.empty()) return;
     LeafCtl done;
-    run_leaves(S.A, S.lists, S.early, unit_, roots_, levels, max_level, pc, done, ws_, s_);
+    run_leaves(S.A, S.lists, S.early, unit_, roots_, levels, max_level, pc, done, turn_, ws_, s_);
 }
 
 }  // namespace bt

@@ -93,9 +93,11 @@ void regroup(const SplitIndex &ix, const SweepResult &sw, const std::vector<Spli
 // parts, so leaves that a depth finds may start beside the deeper sweeps.
 class LeafRun {
   public:
-    // For a pool of up to m edges and n_w wedges.
+    // For a pool of up to m edges and n_w wedges.  With `turn` (and its yield
+    // word) the launches end early to give the device to a much lighter peel.
     LeafRun(const LeafPool &pool, int64_t m, int64_t n_w, int64_t *phi_out, bool unit_updates,
-            int32_t n_roots, Workspace &ws, hipStream_t s);
+            int32_t n_roots, CoopTurn *turn, const int32_t *yield_word, Workspace &ws,
+            hipStream_t s);
     ~LeafRun();  // waits for what was started
     LeafRun(const LeafRun &) = delete;
     LeafRun &operator=(const LeafRun &) = delete;
@@ -112,6 +114,7 @@ class LeafRun {
     const LeafPool &pool_;
     bool unit_;
     int32_t roots_;
+    CoopTurn *turn_;
     Workspace &ws_;
     hipStream_t s_;
     std::unique_ptr<State> st_;

@@ -111,12 +111,18 @@ struct SweepCtl {
     u64 round_b;       // two-kernel rounds: the round of phase B
     u64 prof[5];       // BT_PEEL_PROFILE=1: block-0 clock ticks (decide, A, bar, B, bar)
     u64 yield_src;     // address of the host-written yield word (0: none)
-    int32_t yield_req;  // the yield word as the lead last read it
     int32_t yielded;    // set when the launch ended early to give way
+    int32_t pad;
 };
 
-// Every kYieldEvery rounds the lead reads the host's yield word.
+// The lead reads the host's yield word every kYieldEvery rounds, and after
+// kYieldTicks of the 100 MHz clock (50 us): the first rounds of a large graph's
+// sweep take up to milliseconds each.
 constexpr int64_t kYieldEvery = 16;
+constexpr u64 kYieldTicks = 5000;
+// In the count of the next round's selects, which every block reads between
+// two rounds anyway: all of them end the launch there.
+constexpr u64 kYieldBit = u64(1) << 63;
 
 // Parts a job may begin in one sweep; the last takes everything left.
 constexpr int32_t kMaxParts = 64;
@@ -926,12 +932,16 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         s_left = 1;  // a launch has something to do (see below)
         s_nf = ld(&C->nf[s_r0 & 1].v);
         s_ngth = ld(&C->ngth[s_r0 & 1].v);
-        s_nsel = ld(&C->nsel[s_r0 & 1].v);
+        s_nsel = ld(&C->nsel[s_r0 & 1].v) & ~kYieldBit;
         s_ys = reinterpret_cast<const int32_t *>(ld(&C->yield_src));
         s_ok = 1;
         s_y = 0;
     }
-    if (lead) st(&C->yielded, 0);
+    u64 looked = 0;  // the lead's, at the yield word
+    if (lead) {
+        st(&C->yielded, 0);
+        looked = wall_clock64();
+    }
     __syncthreads();
     int64_t r = (int64_t)s_r0;
     for (; r < max_rounds && s_left > 0 && s_ok; ++r) {
@@ -977,20 +987,22 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         drain_memory();
         __syncthreads();
         if (threadIdx.x == 0) {
-            // Every kYieldEvery rounds the lead publishes the host's yield
-            // word before the barrier and every block reads it after, so all
-            // blocks stop after the same round.
-            const bool chk = s_ys && ((r + 1) % kYieldEvery) == 0;
-            if (chk && lead) {
-                st(&C->yield_req, __hip_atomic_load(s_ys, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_SYSTEM));
+            // The lead publishes the host's yield word before the barrier and
+            // every block reads it after, so all blocks stop after the same
+            // round.
+            if (lead && s_ys &&
+                ((r + 1) % kYieldEvery == 0 || wall_clock64() - looked >= kYieldTicks)) {
+                if (__hip_atomic_load(s_ys, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))
+                    atomicOr(&C->nsel[q].v, kYieldBit);
+                looked = wall_clock64();
                 drain_memory();
             }
             s_ok = grid_arrive_wait(B, gen_local);
             s_nf = ld(&C->nf[q].v);
             s_ngth = ld(&C->ngth[q].v);
-            s_nsel = ld(&C->nsel[q].v);
-            s_y = s_ok && chk && ld(&C->yield_req) != 0;
+            const u64 ns = ld(&C->nsel[q].v);
+            s_nsel = ns & ~kYieldBit;
+            s_y = s_ok && (ns & kYieldBit) != 0;
         }
         __syncthreads();
         if (prof && lead) {
@@ -1255,6 +1267,13 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     return P;
 }
 
+// BT_PEEL_YIELD=1 makes every launch stop at its first check (a test of the
+// resume path).
+const int32_t *yield_word(const CoopTurn *turn) {
+    const char *yv = std::getenv("BT_PEEL_YIELD");
+    return turn ? turn->yield_word(yv && std::atoi(yv) == 1) : nullptr;
+}
+
 // One sweep over the jobs of a depth; `turn` is held.
 SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const SweepAsk &ask,
                   const TuneParams &tp, CoopTurn *turn, PeelCounters &pc, Workspace &ws,
@@ -1269,11 +1288,7 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
                         : tp.peel_blocks == 0 && m >= kAllCusEdges
                             ? std::max(1, std::min(cus, occ * cus))
                             : peel_grid(tp, cus, occ * cus);
-    // BT_PEEL_YIELD=1 makes every launch stop at its first check (a test of
-    // the resume path).
-    const char *yv = std::getenv("BT_PEEL_YIELD");
-    SweepArgs P = sweep_setup(ix, jobs, ask, pblocks,
-                              turn ? turn->yield_word(yv && std::atoi(yv) == 1) : nullptr, ws, s);
+    SweepArgs P = sweep_setup(ix, jobs, ask, pblocks, yield_word(turn), ws, s);
     hipEvent_t ev0, ev1;
     BT_HIP(hipEventCreate(&ev0));
     BT_HIP(hipEventCreate(&ev1));
@@ -1556,7 +1571,8 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         }
         jobs = g.jobs;
         if (!leaves && !pool.leaves.empty())
-            leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, unit, ng, ws, s));
+            leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, unit, ng, turn.get(),
+                                     yield_word(turn.get()), ws, s));
         if (jobs.empty()) break;
         // The compute units that the next sweep leaves peel the heaviest
         // leaves meanwhile: one of a few hundred thousand wedges takes tens of
@@ -1583,7 +1599,6 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         ask.min_level = 0;
         ask.sup_out = nullptr;
     }
-    if (turn) turn->leaves_only();
     if (leaves) leaves->finish(levels, max_level, pc);
     pc.launches += 1 + pc.yields;
     pc.max_phi = max_level;

@@ -110,3 +110,58 @@ def test_engine_small_batches_run_while_a_large_request_peels():
     want = gold["big:1"]["per_graph"][0]["phi_sha256"]
     got = hashlib.sha256(eng.results[0][2].cpu().numpy().astype("<i8").tobytes()).hexdigest()
     assert got == want
+
+
+def test_small_requests_do_not_wait_for_a_large_one():
+    """Small requests that come one by one while 2M-edge requests peel: they
+    go beside the large peel at once and it gives way in every phase (sweeps
+    and parts), so half of them take less than 8 ms (about 2.5 ms, as measured;
+    13 to 28 ms where they waited for workgroups of the large peel)."""
+    small = [g for g in (synth.batch_graph(i) for i in range(64)) if g.m < (1 << 14)][:16]
+    ds = [upload(g) for g in small]
+    want = [binding.bt_decompose(d, want_sup=False)[1] for d in ds]
+    bigs = [upload(synth.big_serving_graph(i)) for i in range(2)]
+    eng = binding.BtEngine(slots=2)
+    took, done = [], set()
+    try:
+        for i, d in enumerate(bigs):
+            eng.bt_engine_submit(d, 1_000_000 + i)
+        time.sleep(0.02)
+        n = 0
+        while len(done) < len(bigs):
+            t0 = time.perf_counter()
+            eng.bt_engine_submit(ds[n % len(ds)], n)
+            while True:
+                new = [r for r, _ in eng.bt_engine_poll()]
+                done.update(r for r in new if r >= 1_000_000)
+                if n in new:
+                    break
+                time.sleep(0.0002)
+            took.append(time.perf_counter() - t0)
+            n += 1
+            time.sleep(0.005)
+        st = eng.bt_engine_stats()
+        for i in range(n):
+            assert eng.results[i][0] == binding.BT_OK
+            assert torch.equal(eng.results[i][2], want[i % len(ds)])
+    finally:
+        eng.bt_engine_destroy()
+    assert n >= 20 and st["peel_yields"] >= 1
+    assert np.median(took) < 0.008, sorted(took)
+
+
+@pytest.mark.parametrize("seed", [31, 32])
+def test_forced_yields_of_parts(monkeypatch, seed):
+    """Every launch that peels parts in single workgroups ends after the
+    workgroups that take a part whatever is asked (64 a launch size); the
+    parts left over are peeled by later launches."""
+    g = synth.scaled_chunglu(900_000, seed=seed)
+    dg = upload(g)
+    _, phi0, st0 = binding.bt_decompose(dg, want_sup=False, stats=True)
+    monkeypatch.setenv("BT_PEEL_YIELD", "1")
+    _, phi1, st1 = binding.bt_decompose(dg, want_sup=False, stats=True)
+    monkeypatch.delenv("BT_PEEL_YIELD")
+    assert st1["peel_yields"] >= 2
+    for k in SAME:
+        assert st1[k] == st0[k], k
+    assert torch.equal(phi0, phi1)
