@@ -349,8 +349,9 @@ bt_status bt_decompose_batch(const bt_csr *gs, int32_t n_graphs, int64_t *const 
  *   done), lets the smaller batch peel, which begins beside it at once if it
  *   is of the smallest class, and resumes where it stopped.  With two or more
  *   slots one is kept for the small class: a slot starts a larger class's
- *   batch only while fewer than slots - 1 others run one, and not while requests still come in
- *   (none for 1 ms, or the oldest of the class waiting 10 ms).
+ *   batch only while fewer than slots - 1 others run one, and not while
+ *   requests come in one after another (a bt_engine_submit under way, or a
+ *   request of the last 0.25 ms), unless the class's oldest has waited 10 ms.
  *   Memory: the budget covers every slot's cached workspace plus what its
  *   running batch may still allocate (the submit-time estimate, replaced by
  *   the exact peel state once the batch's index is built); a slot frees its

@@ -72,12 +72,15 @@ constexpr int32_t kLargePerBatch = 2;
 // waited this long (so a steady stream of small requests cannot starve
 // larger ones).
 constexpr double kLargeWaitS = 10.0;
-// A worker's batch of a larger class waits until no request has come for
-// kGatherS, as requests that come together should share their batch (24 pool
-// graphs submitted at once: 93 ms where the last of nine medium ones just
-// missed its batch and ran alone after it, 70 ms so); the oldest waits kGatherMostS
-// at most.  Small batches, of a millisecond or little more, start at once.
-constexpr double kGatherS = 0.001, kGatherMostS = 0.010;
+// A worker's batch of a larger class waits for requests that come together with
+// its own, as they should share their batch (24 pool graphs submitted at once:
+// 93 ms where the last of nine medium ones just missed its batch and ran alone
+// after it, 74 ms so): while a call of bt_engine_submit is under way, and for
+// kGatherS after the last one (a caller's way from one call to the next); the
+// oldest waits kGatherMostS at most.  A request that comes alone waits kGatherS
+// (1 ms, before calls under way were counted).  Small batches, of a millisecond
+// or little more, start at once.
+constexpr double kGatherS = 0.00025, kGatherMostS = 0.010;
 constexpr int kDefaultSlots = 2;
 // Weights of a batch's turns on the device, by size class (each class's
 // bound on its graphs' edges; the large one well above 8x the medium): a
@@ -121,6 +124,7 @@ struct bt_engine {
     std::vector<Done> done;
     std::vector<Slot> slots;
     int64_t running = 0;  // requests now running
+    int32_t submitting = 0;  // calls of bt_engine_submit under way
     bool stop = false;
     std::vector<std::thread> workers;
     // submit-time estimates run on their own stream and workspace
@@ -252,8 +256,10 @@ bool bt_engine::take_batch(int slot, std::unique_lock<std::mutex> &lk, bool bloc
             const auto now = std::chrono::steady_clock::now();
             const std::chrono::duration<double> since_last = now - queue.back().t,
                                                 oldest = now - first_of(cls)->t;
-            if (since_last.count() < kGatherS && oldest.count() < kGatherMostS) {
-                cv_work.wait_for(lk, std::chrono::duration<double>(kGatherS) - since_last);
+            if ((submitting > 0 || since_last.count() < kGatherS) &&
+                oldest.count() < kGatherMostS) {
+                // Woken by the next request; looks again by itself otherwise.
+                cv_work.wait_for(lk, std::chrono::duration<double>(kGatherS));
                 continue;
             }
         }
@@ -443,6 +449,17 @@ bt_status bt_engine_submit(bt_engine *E, const bt_csr *g, int64_t *sup_out, int6
         set_error("engine is NULL");
         return BT_EINVAL;
     }
+    struct Submitting {
+        bt_engine *E;
+        explicit Submitting(bt_engine *e) : E(e) {
+            std::lock_guard<std::mutex> lk(E->mu);
+            E->submitting += 1;
+        }
+        ~Submitting() {
+            std::lock_guard<std::mutex> lk(E->mu);
+            E->submitting -= 1;
+        }
+    } submitting(E);
     Request r{};
     try {
         check_graph(g);
