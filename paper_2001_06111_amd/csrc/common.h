@@ -69,8 +69,12 @@ public:
     size_t bytes() const;
     // Side stream k (0 to 2), made on first use and kept: for launches that
     // may run beside each other.  Work on it is ordered after and before the
-    // caller's stream by events, so nothing outlives a call on it.
+    // caller's stream by events, so nothing outlives a call on it.  release()
+    // gives the streams back.
     hipStream_t side(int k);
+    // Waits for all side streams: for a call that ends in an error before it
+    // has ordered its stream after them, since the buffers may be reused.
+    void sync_sides();
     // Arena mode: buffers are carved from [base, base + cap), device memory
     // the caller owns, and host scratch is `host` (n_host int64); nothing is
     // allocated, and a request that does not fit throws BT_ENOMEM.  Every

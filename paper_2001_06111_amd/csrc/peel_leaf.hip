@@ -653,13 +653,16 @@ void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hip
     hipEvent_t joins[kNumLeafClasses] = {};
     struct EvFree {
         hipEvent_t a, b, *e;
+        Workspace &ws;
+        bool joined;  // nothing runs on a side stream that s does not wait for
         ~EvFree() {
+            if (!joined) ws.sync_sides();
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
             for (int c = 0; c < kNumLeafClasses; ++c)
                 if (e[c]) (void)hipEventDestroy(e[c]);
         }
-    } ev_free{ev0, ev1, joins};
+    } ev_free{ev0, ev1, joins, ws, true};
     LeafCtl *hc =
         reinterpret_cast<LeafCtl *>(ws.host((int)(sizeof(LeafCtl) / 8 + 1 + (n_roots + 1) / 2)));
     int32_t *hl = reinterpret_cast<int32_t *>(hc + 1);
@@ -691,6 +694,7 @@ void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hip
             n_jobs = all;
         }
         BT_HIP(hipEventRecord(ev0, s));
+        ev_free.joined = false;
         for (int c = 0; c < kNumLeafClasses; ++c) {
             if (!n[c]) continue;
             A.n_lists = 0;
@@ -706,6 +710,7 @@ void run_leaves(LeafArgs A, const std::vector<std::vector<LeafList>> &lists, hip
         }
         for (int c = 0; c < kNumLeafClasses; ++c)
             if (n[c] && c != last) BT_HIP(hipStreamWaitEvent(s, joins[c], 0));
+        ev_free.joined = true;
         if (early && !begun) BT_HIP(hipStreamWaitEvent(s, early, 0));
         BT_HIP(hipEventRecord(ev1, s));
         BT_HIP(hipMemcpyAsync(hc, A.ctl, sizeof(LeafCtl), hipMemcpyDeviceToHost, s));

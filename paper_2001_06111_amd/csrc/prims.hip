@@ -114,12 +114,13 @@ hipStream_t Workspace::side(int k) {
     return side_[k];
 }
 
+void Workspace::sync_sides() {
+    for (hipStream_t t : side_)
+        if (t) (void)hipStreamSynchronize(t);
+}
+
 void Workspace::close() {
     release();
-    for (hipStream_t &t : side_) {
-        if (t) (void)hipStreamDestroy(t);
-        t = nullptr;
-    }
     if (!stream_) return;
     (void)hipStreamSynchronize(stream_);
     for (int64_t *h : old_host_) (void)hipHostFree(h);
@@ -192,6 +193,10 @@ void Workspace::release() {
     graphs.clear();
     for (auto &b : bufs_) device_free(b.ptr);
     bufs_.clear();
+    for (hipStream_t &t : side_) {
+        if (t) (void)hipStreamDestroy(t);
+        t = nullptr;
+    }
     if (stream_) return;  // host scratch stays until the destructor
     if (host_) (void)hipHostFree(host_);
     host_ = nullptr;

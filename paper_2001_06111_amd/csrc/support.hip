@@ -625,6 +625,7 @@ class SideStreams {
   public:
     SideStreams(Workspace &ws, hipStream_t s) : ws_(ws), s_(s) {}
     ~SideStreams() {
+        if (!joined_) ws_.sync_sides();
         for (hipEvent_t e : ev_)
             if (e) (void)hipEventDestroy(e);
     }
@@ -645,6 +646,7 @@ class SideStreams {
             BT_HIP(hipEventRecord(ev_[k], ws_.side(k - 1)));
             BT_HIP(hipStreamWaitEvent(s_, ev_[k], 0));
         }
+        joined_ = true;
     }
 
   private:
@@ -652,6 +654,7 @@ class SideStreams {
     hipStream_t s_;
     hipEvent_t ev_[4] = {};
     int n_ = 0;
+    bool joined_ = false;
 };
 
 }  // namespace

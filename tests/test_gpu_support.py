@@ -125,3 +125,16 @@ def test_orders_by_one_workgroup(nu, nl):
     assert np.array_equal(got.cpu().numpy(), osup) and np.array_equal(phi.cpu().numpy(), ophi)
     assert st["butterflies"] == obf
     assert np.array_equal(binding.bt_support(upload(g))[0].cpu().numpy(), osup)
+
+
+def test_side_streams_go_with_the_workspace():
+    """Walks of several tiers and leaves of several sizes, whose launches run
+    beside each other, before and after the workspace is given back."""
+    g = synth.chung_lu(9000, 15000, 100000, 2.1, 2.3, 9000, 9000, 12)
+    osup, obf, ophi = oracle_all(g)
+    d = upload(g)
+    for _ in range(3):
+        sup, bf = binding.bt_support(d)
+        assert np.array_equal(sup.cpu().numpy(), osup) and bf == obf
+        assert np.array_equal(binding.bt_decompose(d)[1].cpu().numpy(), ophi)
+        binding.bt_release_workspace()
