@@ -145,6 +145,13 @@ template <> __device__ __forceinline__ uint32_t wave_inclusive_sum<uint32_t>(uin
     return v;
 }
 
+// Orders a wave's LDS accesses before it ahead of those after it, over all its
+// lanes (which run in step, so it costs no instruction).  All lanes call.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Lane 63's value in every lane.
 __device__ __forceinline__ uint32_t wave_last(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);

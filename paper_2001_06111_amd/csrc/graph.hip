@@ -304,10 +304,11 @@ __global__ __launch_bounds__(kRankBlock) void k_rank_small(const int32_t *deg, i
                 peers &= bit ? bal : ~bal;
             }
             const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-            if (ok) {
-                out[mine[d] + rank] = k;
-                if (rank == 0) mine[d] += (uint32_t)__popcll(peers);
-            }
+            const uint32_t at = mine[d] + rank;
+            if (ok) out[at] = k;
+            wave_fence();  // all lanes have read the position
+            if (ok && rank == 0) mine[d] = at + (uint32_t)__popcll(peers);
+            wave_fence();
         }
         __syncthreads();
         done += bits;

@@ -535,12 +535,14 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_scatter(const uint64_t *kin, co
             peers &= bit ? bal : ~bal;
         }
         const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
+        const uint32_t pos = mine[d] + rank;
         if (valid) {
-            const uint32_t pos = mine[d] + rank;
             kout[pos] = k[i];
             vout[pos] = v[i];
-            if (rank == 0) mine[d] += (uint32_t)__popcll(peers);
         }
+        wave_fence();  // all lanes have read the position
+        if (valid && rank == 0) mine[d] = pos + (uint32_t)__popcll(peers);
+        wave_fence();
     }
 }
 
