@@ -734,21 +734,27 @@ void batch_range(const bt_csr *gs, int32_t a, int32_t b, int64_t *const *sup_out
     comps.l_off = dvoff;
     comps.u_off = dvoff + (b - a + 1);
     // BT_BATCH_REORDER=0 keeps the union in the callers' numbering.  Graphs
-    // that peel in LDS gain nothing from the order.
+    // that peel in LDS gain nothing from the order, but it also takes rows whose
+    // ids do not increase (each id once), which no union without it does; so
+    // such a union is put in order when it has been refused.
     const char *ro = std::getenv("BT_BATCH_REORDER");
-    const uint32_t *perm = (ro && std::atoi(ro) == 0) || leaf_peel(max_m, ws)
-                               ? nullptr
-                               : reorder_union(u, dvoff, b - a, ws, s);
+    const bool may = !(ro && std::atoi(ro) == 0);
+    const uint32_t *perm = nullptr;
     bt_stats st;
-    try {
-        decompose_union_impl(u, off, comps, sup_u, phi_u, stats ? &st : nullptr, ws, s, plain,
-                             on_sized);
-    } catch (const Error &e) {
-        if (e.status != BT_EOVERFLOW || !splittable) throw;
-        const int32_t mid = a + (b - a) / 2;
-        batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
-        batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
-        return;
+    for (bool order = may && !leaf_peel(max_m, ws);; order = true) {
+        if (order) perm = reorder_union(u, dvoff, b - a, ws, s);
+        try {
+            decompose_union_impl(u, off, comps, sup_u, phi_u, stats ? &st : nullptr, ws, s, plain,
+                                 on_sized);
+            break;
+        } catch (const Error &e) {
+            if (e.status == BT_EINVAL && may && !order) continue;
+            if (e.status != BT_EOVERFLOW || !splittable) throw;
+            const int32_t mid = a + (b - a) / 2;
+            batch_range(gs, a, mid, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
+            batch_range(gs, mid, b, sup_out, phi_out, stats, ws, s, plain || on_sized, nullptr);
+            return;
+        }
     }
     k_batch_scatter<<<grid, 256, 0, s>>>(dtab, b - a, sup_u, phi_u, perm, flags);
     BT_CHECK_LAUNCH();
