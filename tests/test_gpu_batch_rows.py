@@ -18,7 +18,7 @@ def _any_order(g, seed):
     return synth.Graph(g.n_upper, g.n_lower, g.row_ptr, g.col[at], g.name), at
 
 
-@pytest.mark.parametrize("sizes", [(2000,), (3000, 9000), (3000, 16383, 2500), (3000, 20000)])
+@pytest.mark.parametrize("sizes", [(3000,), (3000, 9000), (3500, 16383, 4000), (3000, 20000)])
 def test_rows_in_any_order(sizes):
     gs = [synth.scaled_chunglu(m, seed=m) for m in sizes]
     want = [oracle_all(g) for g in gs]
