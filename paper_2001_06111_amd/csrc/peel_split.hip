@@ -73,25 +73,40 @@ struct alignas(128) JobState {
     float rem_n;        // edges it saw remaining
     int32_t narrow;     // split by levels, not by edges (a job that came back whole)
     int32_t hi_bound;   // its bitruss numbers are at most this
-    // P.plain: the list of remaining edges that gathers scan.
-    int32_t n_list;     // its length; -1: the job's range of edges
-    int32_t which;      // of the two halves of P.list
-    int32_t packing;    // the scheduled gather writes the next list
-    int32_t gathers;    // so far
-    u64 n_next;         // edges the next list has so far
+    // Level by level: the list of the remaining edges below a threshold, which
+    // gathers at levels below it scan.
+    int32_t thresh;     // -1: none yet
+    int32_t delta;      // how far the next threshold lies above its level
+    int32_t listed;     // the last gather scanned the list
+    uint32_t n_list;    // its entries
 };
 
-// With P.plain every kPackEvery-th gather of a job also lists the edges that
-// remain, and later ones scan that list: most edges go at the lowest of a
-// graph's thousands of levels (5M-edge graph level by level: 1851 -> 1542 ms).
-// Short lists are not listed anew: their scan costs a round as it is.
-constexpr int32_t kPackEvery = 32;
-constexpr uint32_t kPackLeast = 1u << 17;
+// Level by level, a gather that scanned all that remains at each of a graph's
+// thousands of levels would take as long as the rounds in between (5M-edge
+// graph: 10,500 levels, 40 us a gather).  A gather at or above the threshold
+// scans the job's edges, sets a new threshold and lists the edges below it;
+// later ones scan the list, to which decrements add the edges that they take
+// below the threshold (5M-edge graph 1.44 -> 1.27 s, 2M-edge request graph 2.71
+// -> 2.22 s).  Thresholds are moved so that a list holds some kListTarget edges
+// in all (2^13, 2^15, 2^17 and 2^19: 1.30, 1.27, 1.27 and 1.30 s).  Ranges below
+// kListLeast are scanned as they are (250,000 edges 94 ms, with lists 97), and
+// those of graphs of few levels, whose edges would join a list in masses (1.5M
+// uniform edges 22.5 ms, with lists 45).
+constexpr uint32_t kListLeast = 1u << 18, kListTarget = 1u << 15;
+
+// What a sweep kernel is made for.  A form each, as all together keep more
+// values than the 128 registers that 16 waves have (level by level, 5M edges
+// 1.55 -> 1.46 s; split 242 -> 240 ms).
+enum SweepForm : int {
+    kSplit,  // parts
+    kMany,   // level by level, many jobs
+    kOne,    // level by level, one job: its level is known without a load
+};
 
 // A piece of at most 64 wedges of a touched bloom; b < 0: none.
 struct alignas(8) SweepBloomItem {
     int32_t b;
-    uint32_t chunk;
+    uint32_t lo;  // its first wedge
 };
 
 struct SweepGatherItem {
@@ -100,7 +115,7 @@ struct SweepGatherItem {
     uint32_t lo, hi;  // edges, or places of P.list
 };
 constexpr int32_t kGatherList = 1;  // scans places of P.list
-constexpr int32_t kGatherPack = 2;  // lists the edges it leaves
+constexpr int32_t kGatherPack = 2;  // lists the edges below the threshold
 
 struct SweepCtl {
     Counter nf[2], ntc[2], ngth[2], nsel[2];
@@ -115,7 +130,7 @@ struct SweepCtl {
     int32_t pad;
 };
 
-// The lead reads the host's yield word every kYieldEvery rounds, and after
+// A wave reads the host's yield word every kYieldEvery rounds, and after
 // kYieldTicks of the 100 MHz clock (50 us): the first rounds of a large graph's
 // sweep take up to milliseconds each.
 constexpr int64_t kYieldEvery = 16;
@@ -134,7 +149,7 @@ constexpr int64_t kSelSamples = 4096;  // edges a select looks at
 struct alignas(8) BloomRec {
     u64 kc;           // (live wedges at the round's start << 32) | kills of this round
     uint32_t w0, w1;  // its wedges
-    int32_t part;     // the last part that touched it (with P.plain: the last job)
+    int32_t part;     // the last part that touched it (level by level: the last job)
     int32_t done;     // chunks of it that phase B has finished
 };
 
@@ -152,10 +167,7 @@ struct SweepArgs {
     const int64_t *link_off;
     const uint3 *link;
     uint32_t n_w;
-    int32_t plain;      // level by level, each edge's mark its number
-    int32_t *list;      // with plain: two lists of remaining edges, 2 * m places
-    uint32_t m;
-    int32_t unit;       // one decrement per kill (no batch bloom processing)
+    int32_t *list;      // level by level: the jobs' lists, each where its edges are
     int32_t short_a, short_b;  // items that fill a wave in phases A, B; 0: most are long
     uint32_t reserve;   // slots that a wave may leave over in a phase
     FrontItem *front[2];  // {edge, part, links [lo, hi)}
@@ -177,9 +189,10 @@ __device__ __forceinline__ void set_front_flag(const SweepArgs &P, int32_t job, 
 // address queue at the memory side, so a wave sets a job's flag once (a
 // uniform graph of 4M edges, whose every step takes edges: 152 -> 93 ms).
 // All 64 lanes call.
+template <SweepForm F>
 __device__ __forceinline__ void set_front_flags(const SweepArgs &P, bool on, int32_t part, int q,
                                                 int32_t &last) {
-    const int32_t job = on ? ld(&P.parts[part].job) : -1;
+    const int32_t job = !on ? -1 : F != kSplit ? part : ld(&P.parts[part].job);
     unsigned long long who = __ballot(on && job != last);
     while (who) {
         last = __shfl(job, __ffsll(who) - 1, kWave);
@@ -246,31 +259,33 @@ __device__ __forceinline__ void reserve2(Reserve &R0, uint32_t n0, u64 *k0, Rese
     }
 }
 
-// Each lane's cnt chunks of bloom b as items at slots S(at), ...: a lane writes its first, the whole wave the others of a longer range.  All
-// 64 lanes call.
+// Each lane's cnt pieces of bloom b, whose wedges begin at lo, as items at slots
+// S(at), ...: a lane writes its first, the whole wave the others of a longer
+// range.  All 64 lanes call.
 __device__ __forceinline__ void put_blooms(SweepBloomItem *list, const Slots &S, uint32_t cnt,
-                                           uint32_t at, int32_t b) {
-    const auto put = [&](uint32_t slot, int32_t bloom, uint32_t c) {
-        st(reinterpret_cast<u64 *>(&list[slot]), ((u64)c << 32) | (uint32_t)bloom);
+                                           uint32_t at, int32_t b, uint32_t lo) {
+    const auto put = [&](uint32_t slot, int32_t bloom, uint32_t w) {
+        st(reinterpret_cast<u64 *>(&list[slot]), ((u64)w << 32) | (uint32_t)bloom);
     };
-    if (cnt) put(S(at), b, 0);
+    if (cnt) put(S(at), b, lo);
     unsigned long long big = __ballot(cnt > 1);
     while (big) {
         const int l = __ffsll(big) - 1;
         big &= big - 1;
-        const uint32_t n = __shfl(cnt, l, kWave), a = __shfl(at, l, kWave);
+        const uint32_t n = __shfl(cnt, l, kWave), a = __shfl(at, l, kWave), w = __shfl(lo, l, kWave);
         const int32_t lb = __shfl(b, l, kWave);
-        for (uint32_t c = 1 + lane_id(); c < n; c += kWave) put(S(a + c), lb, c);
+        for (uint32_t c = 1 + lane_id(); c < n; c += kWave) put(S(a + c), lb, w + c * kWedgeChunk);
     }
 }
 
 // The same for the links of an edge that joins a part and goes at `round`
 // (lanes with take); an edge without links needs no item.
+template <SweepForm F>
 __device__ __forceinline__ void put_fronts(const SweepArgs &P, FrontItem *list, const Slots &S,
                                            bool take, uint32_t cnt, uint32_t at, int32_t e,
                                            int32_t part, int32_t level, int32_t round,
                                            uint32_t lo, uint32_t hi) {
-    if (take) st(&P.mark[e].v, edge_mark(P.plain ? level : part, round));
+    if (take) st(&P.mark[e].v, edge_mark(F != kSplit ? level : part, round));
     if (cnt) st_item(&list[S(at)], FrontItem{e, part, lo, min(lo + (uint32_t)kWave, hi)});
     unsigned long long big = __ballot(cnt > 1);
     while (big) {
@@ -298,13 +313,13 @@ __device__ __forceinline__ void fill_fronts(FrontItem *list, const Reserve &R) {
         st_item(&list[R.base + i], FrontItem{-1, 0, 0u, 1u});
 }
 
-// Gather items over edges (or places) [e0, e0 + n) for the round of parity q;
-// each lane with n > 0 has its own.  All 64 lanes call.
-__device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t part, uint32_t e0,
+// Gather items over edges (or places) [e0, e0 + n) for phase B of this round, of
+// parity p; each lane with n > 0 has its own.  All 64 lanes call.
+__device__ __forceinline__ void put_gather(const SweepArgs &P, int p, int32_t part, uint32_t e0,
                                            uint32_t n, int32_t how) {
     const uint32_t cnt = (n + kGatherChunk - 1) / kGatherChunk;
     u64 base[3];
-    wave_alloc3(cnt, &P.ctl->ngth[q].v, 0u, nullptr, 0u, nullptr, base);
+    wave_alloc3(cnt, &P.ctl->ngth[p].v, 0u, nullptr, 0u, nullptr, base);
     unsigned long long who = __ballot(cnt != 0);
     while (who) {
         const int l = __ffsll(who) - 1;
@@ -316,7 +331,7 @@ __device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t pa
         const int32_t lh = __shfl(how, l, kWave);
         for (uint32_t c = lane_id(); c < nc; c += kWave) {
             const uint32_t a = c * kGatherChunk;
-            st_item(&P.gth[q][b + c], SweepGatherItem{lp, lh, le + a, le + min(a + kGatherChunk, ln)});
+            st_item(&P.gth[p][b + c], SweepGatherItem{lp, lh, le + a, le + min(a + kGatherChunk, ln)});
         }
     }
 }
@@ -324,7 +339,11 @@ __device__ __forceinline__ void put_gather(const SweepArgs &P, int q, int32_t pa
 // What each of this thread's jobs does next, decided at the start of round r
 // (parity p) from what the last round left: rounds while there is a
 // frontier; after a gather that took nothing, a gather at the smallest
-// support it saw; else a select for the next part.
+// support it saw; else a select for the next part.  A gather runs in phase B
+// of this round, where nothing else touches its job: one in the next round's
+// phase A cost each level and part a round more (level by level, 250,000 edges
+// 8,145 -> 7,155 rounds, 105 -> 99 ms).
+template <SweepForm F>
 __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, int64_t nthreads) {
     const int q = p ^ 1;
     for (int64_t g0 = tid - lane_id(); g0 < P.n_jobs; g0 += nthreads) {
@@ -344,11 +363,13 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
             n = (uint32_t)ld(&J->e1) - e0;
             if (state != kJobDone) {
                 if (fr) st(&J->fr[p], 0);
-                if (!fr && sr != r && gr != r) {
+                if (!fr && sr != r) {
                     int32_t next = INT_MAX;
                     if (gr == r - 1) {
                         next = gm;
-                        if (gm == INT_MAX) {  // nothing remains
+                        // Nothing is left in the list.
+                        if (F != kSplit && gm == INT_MAX && ld(&J->listed)) next = ld(&J->thresh);
+                        if (next == INT_MAX) {  // nothing remains
                             st(&J->state, (int32_t)kJobDone);
                             atomicAdd(&P.ctl->left.v, ~0ull);
                         }
@@ -356,7 +377,7 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
                         // the part took everything
                         st(&J->state, (int32_t)kJobDone);
                         atomicAdd(&P.ctl->left.v, ~0ull);
-                    } else if (P.plain) {
+                    } else if (F != kSplit) {
                         next = level + 1;
                         atomicAdd(&J->n_parts, 1);
                     } else {
@@ -367,35 +388,36 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
                         gather = true;
                         st(&J->level, next);
                         st(&P.parts[part].hi, next);
-                        st(&J->gather_round, r + 1);
-                        st(&J->gmin[q], (int32_t)INT_MAX);
-                        if (P.plain) {
-                            const int32_t ng = ld(&J->gathers);
-                            int32_t which = ld(&J->which);
-                            int32_t nl = ld(&J->n_list);
-                            if (ld(&J->packing)) {  // the last gather wrote the next list
-                                which ^= 1;
-                                nl = (int32_t)ld(&J->n_next);
-                                st(&J->which, which);
-                                st(&J->n_list, nl);
+                        st(&J->gather_round, r);
+                        st(&J->gmin[p], (int32_t)INT_MAX);
+                        if (F != kSplit) {
+                            if (P.list && n >= kListLeast) {
+                                const int32_t t = ld(&J->thresh);
+                                const uint32_t held = ld(&J->n_list);
+                                if (next < t) {
+                                    how = kGatherList;
+                                    n = held;
+                                } else {
+                                    how = kGatherPack;
+                                    int32_t d = ld(&J->delta);
+                                    if (t >= 0 && held > 2 * kListTarget) d /= 2;
+                                    else if (t >= 0 && held < kListTarget) d = min(2 * d + 1, 1 << 29);
+                                    const int32_t t1 =
+                                        (int32_t)min((int64_t)next + 1 + d, (int64_t)INT_MAX);
+                                    st(&J->delta, d);
+                                    st(&J->thresh, t1);
+                                    st(&J->n_list, 0u);
+                                    st(&P.parts[part].lo, t1);
+                                }
                             }
-                            const bool pack = ng % kPackEvery == kPackEvery - 1 &&
-                                              (nl >= 0 ? (uint32_t)nl : n) >= kPackLeast;
-                            if (pack) st(&J->n_next, (u64)0);
-                            st(&J->packing, pack ? 1 : 0);
-                            st(&J->gathers, ng + 1);
-                            how = (nl >= 0 ? kGatherList : 0) | (pack ? kGatherPack : 0);
-                            if (nl >= 0) {
-                                e0 += which ? P.m : 0u;
-                                n = (uint32_t)nl;
-                            }
+                            st(&J->listed, how & kGatherList);
                         }
                     }
                 }
             }
         }
         if (!__any(gather || select)) continue;
-        put_gather(P, q, part, e0, gather ? n : 0u, how);
+        put_gather(P, p, part, e0, gather ? n : 0u, how);
         const u64 slot = wave_alloc(select ? 1u : 0u, &P.ctl->nsel[q].v);
         if (select) st(&P.sel[q][slot], (int32_t)g);
     }
@@ -415,11 +437,11 @@ __device__ __forceinline__ int64_t sel_end(int b) {
 
 // Begins a job's next part: from a sample of its remaining supports, the
 // largest level below which no more than the targets lie (at least the
-// smallest support sampled), and the gather at it for round r + 1.  A job
+// smallest support sampled), and the gather at it in phase B of this round.  A job
 // that came back whole from the last sweep (some range's cascade took all of
 // it) is cut into sixteenths of its range of levels instead, down to single
 // levels.  One workgroup; all its threads call.
-__device__ void sweep_select(const SweepArgs &P, int32_t g, int64_t r, int q) {
+__device__ void sweep_select(const SweepArgs &P, int32_t g, int64_t r, int p) {
     __shared__ uint32_t s_n[kSelBins];
     __shared__ int32_t s_mn, s_mx;
     JobState *J = &P.js[g];
@@ -559,14 +581,14 @@ __device__ void sweep_select(const SweepArgs &P, int32_t g, int64_t r, int q) {
             st(&J->n_parts, np + 1);
             st(&J->level, hi);
             st(&J->part, part);
-            st(&J->gather_round, r + 1);
-            st(&J->gmin[q], (int32_t)INT_MAX);
+            st(&J->gather_round, r);
+            st(&J->gmin[p], (int32_t)INT_MAX);
             s_mn = part;
         }
     }
     __syncthreads();
     if (threadIdx.x < kWave)  // one wave writes the gather's items
-        put_gather(P, q, s_mn, (uint32_t)e0, threadIdx.x == 0 ? (uint32_t)n : 0u, 0);
+        put_gather(P, p, s_mn, (uint32_t)e0, threadIdx.x == 0 ? (uint32_t)n : 0u, 0);
     __syncthreads();
 }
 
@@ -581,6 +603,7 @@ __device__ __forceinline__ void flush_min(const SweepArgs &P, int p, int32_t job
 // frontier; the smallest support above it is kept for a jump, the smallest
 // taken as the part's lower bound.  The smallest is kept by the wave until its
 // items' job changes: one counter takes an atomic every few nanoseconds.
+template <SweepForm F>
 __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int p,
                                              const SweepGatherItem it, int32_t &mn_job,
                                              int32_t &mn_all, int32_t &flagged) {
@@ -593,7 +616,7 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
     for (int k = 0; k < kGatherPerLane; ++k) {
         const uint32_t i = it.lo + k * kWave + lane_id();
         ed[k] = i;
-        if ((it.how & kGatherList) && i < it.hi) ed[k] = (uint32_t)ld(&P.list[i]);
+        if (F != kSplit && (it.how & kGatherList) && i < it.hi) ed[k] = (uint32_t)ld(&P.list[i]);
     }
 #pragma unroll
     for (int k = 0; k < kGatherPerLane; ++k) {
@@ -636,27 +659,33 @@ __device__ __forceinline__ void sweep_gather(const SweepArgs &P, int64_t r, int 
 #pragma unroll
         for (int k = 0; k < kGatherPerLane; ++k) {
             const uint32_t cnt = chunks_of(lo[k], hi[k]);
-            put_fronts(P, P.front[q], S, (take >> k) & 1u, cnt, at,
+            put_fronts<F>(P, P.front[q], S, (take >> k) & 1u, cnt, at,
                        (int32_t)ed[k], it.part, level, (int32_t)(r + 1), lo[k], hi[k]);
             at += cnt;
         }
         lowest = wave_min(lowest);
         if (lane_id() == 0) {
             if (job != flagged) set_front_flag(P, job, q);
-            if (!P.plain) atomicMin(&P.parts[it.part].lo, lowest);
+            if (F == kSplit) atomicMin(&P.parts[it.part].lo, lowest);
         }
         flagged = job;
     }
-    if (it.how & kGatherPack) {
+    if (F != kSplit && (it.how & kGatherPack)) {
+        const int32_t t = ld(&P.js[job].thresh);
         uint32_t keep = 0;
 #pragma unroll
-        for (int k = 0; k < kGatherPerLane; ++k) keep += ph[k] < 0 && sv[k] > level ? 1u : 0u;
-        u64 at = wave_alloc(keep, &P.js[job].n_next);
-        // The half of P.list that the job's current list is not in.
-        at += (uint64_t)(uint32_t)ld(&P.js[job].e0) + (ld(&P.js[job].which) ? 0u : P.m);
-#pragma unroll
         for (int k = 0; k < kGatherPerLane; ++k)
-            if (ph[k] < 0 && sv[k] > level) st(&P.list[at++], (int32_t)ed[k]);
+            keep += ph[k] < 0 && sv[k] > level && sv[k] < t ? 1u : 0u;
+        if (__ballot(keep != 0)) {
+            const uint32_t inc = wave_inclusive_sum<uint32_t>(keep);
+            uint32_t base = 0;
+            if (lane_id() == 0) base = atomicAdd(&P.js[job].n_list, wave_last(inc));
+            uint32_t at = (uint32_t)ld(&P.js[job].e0) +
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + inc - keep;
+#pragma unroll
+            for (int k = 0; k < kGatherPerLane; ++k)
+                if (ph[k] < 0 && sv[k] > level && sv[k] < t) st(&P.list[at++], (int32_t)ed[k]);
+        }
     }
     mn = wave_min(mn);
     if (job != mn_job) {
@@ -682,6 +711,109 @@ __device__ __forceinline__ uint32_t items_per_step(u64 n, int64_t nwaves, int32_
     return per < 1 ? 1u : per > kWave ? (uint32_t)kWave : (uint32_t)per;
 }
 
+// Whether an edge's removal kills a link's wedge: the twin is still there, or
+// goes in the same round and is the larger of the two.
+__device__ __forceinline__ bool kills(bool has, int32_t e, int32_t twin, int32_t tround, int32_t now) {
+    return has && e >= 0 && tround >= now && !(tround == now && twin < e);
+}
+
+// Level by level: edges that fell below their job's threshold (lanes with on)
+// join its list.  All 64 lanes call.
+__device__ __forceinline__ void list_edges(const SweepArgs &P, bool on, int32_t job, int32_t e) {
+    unsigned long long who = __ballot(on);
+    while (who) {
+        const int l = __ffsll(who) - 1;
+        const int32_t j = __shfl(job, l, kWave);
+        const unsigned long long same = __ballot(on && job == j);
+        uint32_t base = 0;
+        if (lane_id() == l) base = atomicAdd(&P.js[j].n_list, (uint32_t)__popcll(same));
+        base = (uint32_t)__shfl((int)base, l, kWave) + (uint32_t)ld(&P.js[j].e0);
+        if ((same >> lane_id()) & 1)
+            st(&P.list[base + (uint32_t)__popcll(same & lanemask_lt())], e);
+        who &= ~same;
+    }
+}
+
+// A part's level, and level by level its threshold (INT_MIN: no list).
+template <SweepForm F>
+__device__ __forceinline__ int2 part_level(const SweepArgs &P, int32_t part, int2 one) {
+    if (F == kSplit) return make_int2(ld(&P.parts[part].hi), 0);
+    if (F == kOne) return one;
+    const u64 v = ld(reinterpret_cast<const u64 *>(&P.parts[part].hi));
+    return make_int2((int32_t)(uint32_t)v, (int32_t)(v >> 32));
+}
+
+// Phase A of the only job of a level-by-level peel, with few items: one a wave
+// and step.  Such a round is a chain of waits for memory, so what does not
+// depend on each other is asked for together: the item; its links; all that a
+// link may need (the twin's mark and links, the bloom's record); the kill and
+// the twin's decrement; the slots (250,000 edges 94.5 -> 89 ms, 5M 1.27 -> 1.23 s).
+// Where many items hide the waits that only costs requests (split, 192 pool
+// graphs: 144 -> 148 ms).
+__device__ __forceinline__ void sweep_phase_a_few(const SweepArgs &P, int64_t r, int p, u64 nf,
+                                                  int2 one, int64_t wid, int64_t nwaves,
+                                                  uint32_t &upd) {
+    SweepCtl *C = P.ctl;
+    const int q = p ^ 1;
+    const int32_t now = (int32_t)r, level = one.x, thresh = one.y;
+    bool flagged = false;
+    FrontItem it{};
+    if (wid < (int64_t)nf) it = ld_item(&P.front[p][wid]);
+    for (int64_t i = wid; i < (int64_t)nf; i += nwaves) {
+        const FrontItem cur = it;
+        if (i + nwaves < (int64_t)nf) it = ld_item(&P.front[p][i + nwaves]);  // loaded early
+        const int32_t e = cur.e;
+        const uint32_t j = cur.lo + lane_id();
+        const bool has = j < cur.hi;
+        uint3 lk = make_uint3(0, 0, kFixedBit);
+        if (has) lk = P.link[j];
+        const bool tfix = (lk.z & kFixedBit) != 0;
+        const int32_t twin = (int32_t)(lk.z & kEdgeMask);
+        BloomRec *const B = &P.bloom[lk.y];
+        int32_t tround = INT_MAX;
+        u64 kc = 0;
+        uint2 w01 = make_uint2(0, 0);
+        uint32_t tlo = 0, thi = 0;
+        if (has) {
+            kc = ld(&B->kc);
+            w01 = *reinterpret_cast<const uint2 *>(&B->w0);
+            if (!tfix) {
+                tround = mark_round(ld(&P.mark[twin].v));
+                tlo = (uint32_t)P.link_off[twin];
+                thi = (uint32_t)P.link_off[(int64_t)twin + 1];
+            }
+        }
+        const bool kill = kills(has, e, twin, tround, now);
+        const int32_t d = (int32_t)(kc >> 32) - 1;
+        const bool dec = kill && d > 0 && !tfix && tround != now;
+        u64 old = 1;
+        int32_t otw = 0;
+        if (kill) {  // both atomics issue before either result is used
+            old = atomicAdd(&B->kc, (u64)1);
+            if (dec) otw = atomicSub(&P.sup[twin], d);
+            st(&P.dead[lk.x], (uint8_t)1);
+        }
+        const bool first = kill && d > 0 && (uint32_t)old == 0;
+        const bool tf = dec && otw > level && otw - d <= level;
+        if (__ballot(first || tf)) {
+            const uint32_t nch = first ? (w01.y - w01.x + kWedgeChunk - 1) / kWedgeChunk : 0u;
+            const uint32_t tk = tf ? chunks_of(tlo, thi) : 0u;
+            u64 base[3];
+            wave_alloc3(nch, &C->ntc[p].v, tk, &C->nf[q].v, 0u, nullptr, base);
+            const Slots S{0, 0, 0xffffffffu};
+            put_blooms(P.tc[p], S, nch, (uint32_t)base[0], (int32_t)lk.y, w01.x);
+            put_fronts<kOne>(P, P.front[q], S, tf, tk, (uint32_t)base[1], twin, 0, level, now + 1,
+                             tlo, thi);
+            if (!flagged && __ballot(tf)) {
+                if (lane_id() == 0) set_front_flag(P, 0, q);
+                flagged = true;
+            }
+        }
+        list_edges(P, dec && otw >= thresh && otw - d < thresh && otw - d > level, 0, twin);
+        upd += dec ? 1 : 0;
+    }
+}
+
 // Phase A: the frontier's wedges are killed; each kill counts in its bloom,
 // and the twin edge loses all of its butterflies in the bloom.  A wedge is
 // alive unless its twin was removed in an earlier round; where both edges are
@@ -689,23 +821,26 @@ __device__ __forceinline__ uint32_t items_per_step(u64 n, int64_t nwaves, int32_
 // is killed for nothing: the bloom has no butterfly left to take.)  Bound by
 // random accesses: a link reads its twin's mark; a kill adds two atomics and
 // a byte, a bloom's first kill one read of its record.
-__device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int p, u64 nf,
-                                              u64 ngth, int64_t wid, int64_t nwaves, u64 *mask,
+template <SweepForm F>
+__device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int p, u64 nf, int2 one,
+                                              int64_t wid, int64_t nwaves, u64 *mask,
                                               uint32_t &upd) {
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
     const int32_t now = (int32_t)r;
     const uint32_t per = items_per_step(nf, nwaves, P.short_a);
+    if (F == kOne && per == 1)
+        return sweep_phase_a_few(P, r, p, nf, one, wid, nwaves, upd);
     const uint32_t grow = per > 1 ? min(2 * per, P.reserve) : 0u;
     Reserve rb, rf;
     int32_t flagged = -1;
     for (int64_t g0 = wid * per; g0 < (int64_t)nf; g0 += nwaves * per) {
         const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)nf;
         FrontItem it{0, 0, 0, 0};
-        int32_t level_l = 0;
+        int2 level_l = make_int2(0, 0);
         if (ok) {
             it = ld_item(&P.front[p][g0 + lane_id()]);
-            level_l = ld(&P.parts[it.part].hi);
+            level_l = part_level<F>(P, it.part, one);
         }
         const uint32_t n = ok ? it.hi - it.lo : 0u;
         const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
@@ -717,7 +852,6 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
             const bool has = x < total;
             const uint32_t j = __shfl(it.lo - start, src, kWave) + x;
             const int32_t e = __shfl(it.e, src, kWave), part = __shfl(it.part, src, kWave);
-            const int32_t level = __shfl(level_l, src, kWave);
             uint3 lk = make_uint3(0, 0, kFixedBit);
             int32_t tround = INT_MAX;
             if (has) {
@@ -726,7 +860,7 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
             }
             const bool tfix = (lk.z & kFixedBit) != 0;
             const int32_t twin = (int32_t)(lk.z & kEdgeMask);
-            const bool kill = has && e >= 0 && tround >= now && !(tround == now && twin < e);
+            const bool kill = kills(has, e, twin, tround, now);
             BloomRec *const B = &P.bloom[lk.y];
             u64 old = 1;
             if (kill) {
@@ -743,12 +877,17 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
             if (dec) otw = atomicSub(&P.sup[twin], d);
             if (first) {
                 w01 = *reinterpret_cast<const uint2 *>(&B->w0);
-                if (ld(&B->part) != part) {
+                if (F != kOne && ld(&B->part) != part) {
                     st(&B->part, part);
-                    if (!P.plain) P.wedge_k[lk.x] = kb;
+                    if (F == kSplit) P.wedge_k[lk.x] = kb;
                 }
             }
+            const int32_t level = __shfl(level_l.x, src, kWave);
             const bool tf = dec && otw > level && otw - d <= level;
+            if (F != kSplit) {
+                const int32_t t = __shfl(level_l.y, src, kWave);
+                list_edges(P, dec && otw >= t && otw - d < t && otw - d > level, part, twin);
+            }
             if (__ballot(first || tf)) {
                 uint32_t tlo = 0, thi = 0;
                 if (tf) {
@@ -762,25 +901,137 @@ __device__ __forceinline__ void sweep_phase_a(const SweepArgs &P, int64_t r, int
                 Slots sb, sf;
                 reserve2(rb, wave_last(ib), &C->ntc[p].v, rf, wave_last(jf), &C->nf[q].v, grow, sb,
                          sf);
-                put_blooms(P.tc[p], sb, nch, ib - nch, (int32_t)lk.y);
-                put_fronts(P, P.front[q], sf, tf, tk, jf - tk, twin, part, level, now + 1, tlo, thi);
-                set_front_flags(P, tf, part, q, flagged);
+                put_blooms(P.tc[p], sb, nch, ib - nch, (int32_t)lk.y, w01.x);
+                put_fronts<F>(P, P.front[q], sf, tf, tk, jf - tk, twin, part, level, now + 1, tlo, thi);
+                set_front_flags<F>(P, tf, part, q, flagged);
             }
             upd += dec ? 1 : 0;
         }
     }
     fill_blooms(P.tc[p], rb);
     fill_fronts(P.front[q], rf);
-    int32_t mn_job = -1, mn_all = INT_MAX;
-    for (int64_t i = wid; i < (int64_t)ngth; i += nwaves)
-        sweep_gather(P, r, p, ld_item(&P.gth[p][i]), mn_job, mn_all, flagged);
-    flush_min(P, p, mn_job, mn_all);
+}
+
+// A wedge's two edges lose the kills c of its bloom (lanes with da, db): whether
+// they cross the level (f), and level by level the threshold t.
+template <SweepForm F, bool UNIT>
+__device__ __forceinline__ void take_kills(const SweepArgs &P, bool da, bool db, int32_t ea, int32_t eb,
+                                           int32_t c, int32_t level, int32_t t, bool &f1, bool &f2,
+                                           bool &t1, bool &t2) {
+    f1 = f2 = t1 = t2 = false;
+    if (UNIT) {
+        // Ablation: one unit per kill; the step from level + 1 crosses (from
+        // the threshold, crosses that).  A sweep's blooms lose many wedges a
+        // round, so eight kills' atomics are in flight together (5M-edge graph
+        // 1,780 -> 668 ms).
+        constexpr int kUnits = 8;
+        for (int32_t x = 0; x < (da || db ? c : 0); x += kUnits) {
+            int32_t o1[kUnits], o2[kUnits];
+#pragma unroll
+            for (int k = 0; k < kUnits; ++k) {
+                o1[k] = o2[k] = -1;
+                if (da && x + k < c) o1[k] = atomicSub(&P.sup[ea], 1);
+                if (db && x + k < c) o2[k] = atomicSub(&P.sup[eb], 1);
+            }
+#pragma unroll
+            for (int k = 0; k < kUnits; ++k) {
+                f1 |= da && x + k < c && o1[k] == level + 1;
+                f2 |= db && x + k < c && o2[k] == level + 1;
+                if (F != kSplit) {
+                    t1 |= da && x + k < c && o1[k] == t;
+                    t2 |= db && x + k < c && o2[k] == t;
+                }
+            }
+        }
+    } else {
+        int32_t o1 = 0, o2 = 0;
+        if (da) o1 = atomicSub(&P.sup[ea], c);
+        if (db) o2 = atomicSub(&P.sup[eb], c);
+        f1 = da && o1 > level && o1 - c <= level;
+        f2 = db && o2 > level && o2 - c <= level;
+        if (F != kSplit) {
+            t1 = da && o1 >= t && o1 - c < t && o1 - c > level;
+            t2 = db && o2 >= t && o2 - c < t && o2 - c > level;
+        }
+    }
+}
+
+// Phase B likewise.
+template <bool UNIT>
+__device__ __forceinline__ void sweep_phase_b_few(const SweepArgs &P, int64_t r, int p, u64 ntc,
+                                                  int2 one, int64_t wid, int64_t nwaves,
+                                                  uint32_t &upd, uint32_t &visits, uint32_t &touch,
+                                                  uint32_t &unb) {
+    SweepCtl *C = P.ctl;
+    const int q = p ^ 1;
+    const int32_t level = one.x, thresh = one.y;
+    const u64 *const items = reinterpret_cast<const u64 *>(P.tc[p]);
+    bool flagged = false;
+    u64 item = 0;
+    if (wid < (int64_t)ntc) item = ld(&items[wid]);
+    for (int64_t i = wid; i < (int64_t)ntc; i += nwaves) {
+        const u64 cur = item;
+        if (i + nwaves < (int64_t)ntc) item = ld(&items[i + nwaves]);  // loaded early
+        const int32_t b = (int32_t)(uint32_t)cur;
+        if (b < 0) continue;
+        BloomRec *const B = &P.bloom[b];
+        const uint32_t w = (uint32_t)(cur >> 32) + lane_id();
+        const u64 kc = ld(&B->kc);
+        const uint2 w01 = *reinterpret_cast<const uint2 *>(&B->w0);
+        // The piece's end is not known yet: its loads stay below the index's
+        // end, and what lies past the bloom's is left out.
+        const uint32_t at = min(w, P.n_w);
+        const uint32_t ra = (uint32_t)P.wea[at], rb = (uint32_t)P.web[at];
+        const uint8_t gone = ld(&P.dead[at]);
+        const int32_t c = (int32_t)(uint32_t)kc, kn = (int32_t)(kc >> 32) - c;
+        const uint32_t nch = (w01.y - w01.x + kWedgeChunk - 1) / kWedgeChunk;
+        const bool live = w < w01.y && kn > 0 && !gone;
+        const bool da = live && !(ra & kFixedBit), db = live && !(rb & kFixedBit);
+        const int32_t ea = (int32_t)(ra & kEdgeMask), eb = (int32_t)(rb & kEdgeMask);
+        uint32_t lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
+        if (da) {
+            lo1 = (uint32_t)P.link_off[ea];
+            hi1 = (uint32_t)P.link_off[(int64_t)ea + 1];
+        }
+        if (db) {
+            lo2 = (uint32_t)P.link_off[eb];
+            hi2 = (uint32_t)P.link_off[(int64_t)eb + 1];
+        }
+        bool f1, f2, t1, t2;
+        take_kills<kOne, UNIT>(P, da, db, ea, eb, c, level, thresh, f1, f2, t1, t2);
+        if (__ballot(f1 || f2)) {
+            const uint32_t k1 = f1 ? chunks_of(lo1, hi1) : 0u, k2 = f2 ? chunks_of(lo2, hi2) : 0u;
+            u64 base[3];
+            wave_alloc3(k1 + k2, &C->nf[q].v, 0u, nullptr, 0u, nullptr, base);
+            const Slots S{0, 0, 0xffffffffu};
+            put_fronts<kOne>(P, P.front[q], S, f1, k1, (uint32_t)base[0], ea, 0, level,
+                             (int32_t)(r + 1), lo1, hi1);
+            put_fronts<kOne>(P, P.front[q], S, f2, k2, (uint32_t)base[0] + k1, eb, 0, level,
+                             (int32_t)(r + 1), lo2, hi2);
+            if (!flagged && lane_id() == 0) set_front_flag(P, 0, q);
+            flagged = true;
+        }
+        list_edges(P, t1, 0, ea);
+        list_edges(P, t2, 0, eb);
+        const int32_t each = UNIT ? c : 1;
+        upd += (uint32_t)((da ? each : 0) + (db ? each : 0));
+        if (!UNIT) unb += (uint32_t)((da ? c - 1 : 0) + (db ? c - 1 : 0));
+        touch += live ? 1 : 0;
+        // (See sweep_phase_b.)
+        if (lane_id() == 0 && kn != INT_MIN &&
+            (nch == 1 || atomicAdd(&B->done, 1) == (int32_t)nch - 1)) {
+            st(&B->kc, (u64)(uint32_t)kn << 32);
+            if (nch > 1) st(&B->done, 0);
+            visits += 1;
+        }
+    }
 }
 
 // Phase B: the survivors of every touched bloom lose its kills; the last
-// chunk of a bloom to finish settles it.
-__device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int p, u64 ntc, int64_t wid,
-                                              int64_t nwaves, u64 *mask, uint32_t &upd,
+// chunk of a bloom to finish settles it.  Then the round's gathers.
+template <SweepForm F, bool UNIT>
+__device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int p, u64 ntc, u64 ngth, int2 one,
+                                              int64_t wid, int64_t nwaves, u64 *mask, uint32_t &upd,
                                               uint32_t &visits, uint32_t &touch, uint32_t &unb) {
     SweepCtl *C = P.ctl;
     const int q = p ^ 1;
@@ -788,9 +1039,12 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
     const uint32_t grow = per > 1 ? min(2 * per, P.reserve) : 0u;
     Reserve rf;
     int32_t flagged = -1;
-    for (int64_t g0 = wid * per; g0 < (int64_t)ntc; g0 += nwaves * per) {
+    const bool few = F == kOne && per == 1;
+    if (few) sweep_phase_b_few<UNIT>(P, r, p, ntc, one, wid, nwaves, upd, visits, touch, unb);
+    for (int64_t g0 = wid * per; !few && g0 < (int64_t)ntc; g0 += nwaves * per) {
         const bool ok = (uint32_t)lane_id() < per && g0 + lane_id() < (int64_t)ntc;
-        int32_t b_l = -1, level_l = 0, part_l = 0, c_l = 0, k_l = 0;
+        int32_t b_l = -1, part_l = 0, c_l = 0, k_l = 0;
+        int2 level_l = make_int2(0, 0);
         uint32_t lo_l = P.n_w, n = ok ? 1u : 0u, nch = 0;
         if (ok) {
             const u64 item = ld(reinterpret_cast<const u64 *>(&P.tc[p][g0 + lane_id()]));
@@ -799,13 +1053,13 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
                 const BloomRec *B = &P.bloom[b_l];
                 const u64 kc = ld(&B->kc);
                 const uint2 w01 = *reinterpret_cast<const uint2 *>(&B->w0);
-                part_l = ld(&B->part);
+                part_l = F == kOne ? 0 : ld(&B->part);
                 c_l = (int32_t)(uint32_t)kc;
                 k_l = (int32_t)(kc >> 32);
-                lo_l = w01.x + (uint32_t)(item >> 32) * kWedgeChunk;
+                lo_l = (uint32_t)(item >> 32);
                 n = min(w01.y - lo_l, (uint32_t)kWedgeChunk);
                 nch = (w01.y - w01.x + kWedgeChunk - 1) / kWedgeChunk;
-                level_l = ld(&P.parts[part_l].hi);
+                level_l = part_level<F>(P, part_l, one);
             }
         }
         const uint32_t inc = wave_inclusive_sum<uint32_t>(n);
@@ -824,37 +1078,17 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
                 gone = ld(&P.dead[w]);
             }
             const int32_t part = __shfl(part_l, src, kWave);
-            const int32_t level = __shfl(level_l, src, kWave);
             const int32_t c = __shfl(c_l, src, kWave), kn = __shfl(k_l, src, kWave) - c;
             const bool live = kn > 0 && !gone;
             const bool da = live && !(ra & kFixedBit), db = live && !(rb & kFixedBit);
             const int32_t ea = (int32_t)(ra & kEdgeMask), eb = (int32_t)(rb & kEdgeMask);
-            bool f1 = false, f2 = false;
-            if (P.unit) {
-                // Ablation: one unit per kill; the step from level + 1 crosses.
-                // A sweep's blooms lose many wedges a round, so eight kills'
-                // atomics are in flight together (5M-edge graph 1,780 -> 668 ms).
-                constexpr int kUnits = 8;
-                for (int32_t t = 0; t < (live ? c : 0); t += kUnits) {
-                    int32_t o1[kUnits], o2[kUnits];
-#pragma unroll
-                    for (int k = 0; k < kUnits; ++k) {
-                        o1[k] = o2[k] = 0;
-                        if (da && t + k < c) o1[k] = atomicSub(&P.sup[ea], 1);
-                        if (db && t + k < c) o2[k] = atomicSub(&P.sup[eb], 1);
-                    }
-#pragma unroll
-                    for (int k = 0; k < kUnits; ++k) {
-                        f1 |= da && t + k < c && o1[k] == level + 1;
-                        f2 |= db && t + k < c && o2[k] == level + 1;
-                    }
-                }
-            } else {
-                int32_t o1 = 0, o2 = 0;
-                if (da) o1 = atomicSub(&P.sup[ea], c);
-                if (db) o2 = atomicSub(&P.sup[eb], c);
-                f1 = da && o1 > level && o1 - c <= level;
-                f2 = db && o2 > level && o2 - c <= level;
+            const int32_t level = __shfl(level_l.x, src, kWave);
+            const int32_t t = F != kSplit ? __shfl(level_l.y, src, kWave) : 0;
+            bool f1, f2, t1, t2;
+            take_kills<F, UNIT>(P, da, db, ea, eb, c, level, t, f1, f2, t1, t2);
+            if (F != kSplit) {
+                list_edges(P, t1, part, ea);
+                list_edges(P, t2, part, eb);
             }
             if (__ballot(f1 || f2)) {
                 uint32_t lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
@@ -871,15 +1105,15 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
                 Slots sf, none;
                 Reserve no;
                 reserve2(rf, wave_last(i1), &C->nf[q].v, no, 0u, nullptr, grow, sf, none);
-                put_fronts(P, P.front[q], sf, f1, k1, i1 - k1 - k2, ea, part, level, (int32_t)(r + 1),
+                put_fronts<F>(P, P.front[q], sf, f1, k1, i1 - k1 - k2, ea, part, level, (int32_t)(r + 1),
                            lo1, hi1);
-                put_fronts(P, P.front[q], sf, f2, k2, i1 - k2, eb, part, level, (int32_t)(r + 1), lo2,
+                put_fronts<F>(P, P.front[q], sf, f2, k2, i1 - k2, eb, part, level, (int32_t)(r + 1), lo2,
                            hi2);
-                set_front_flags(P, f1 || f2, part, q, flagged);
+                set_front_flags<F>(P, f1 || f2, part, q, flagged);
             }
-            const int32_t each = P.unit ? c : 1;
+            const int32_t each = UNIT ? c : 1;
             upd += (uint32_t)((da ? each : 0) + (db ? each : 0));
-            if (!P.unit) unb += (uint32_t)((da ? c - 1 : 0) + (db ? c - 1 : 0));
+            if (!UNIT) unb += (uint32_t)((da ? c - 1 : 0) + (db ? c - 1 : 0));
             touch += live ? 1 : 0;
         }
         // A chunk counts itself done once its reads of the bloom's counts
@@ -896,6 +1130,10 @@ __device__ __forceinline__ void sweep_phase_b(const SweepArgs &P, int64_t r, int
         }
     }
     fill_fronts(P.front[q], rf);
+    int32_t mn_job = -1, mn_all = INT_MAX;
+    for (int64_t i = wid; i < (int64_t)ngth; i += nwaves)
+        sweep_gather<F>(P, r, p, ld_item(&P.gth[p][i]), mn_job, mn_all, flagged);
+    flush_min(P, p, mn_job, mn_all);
 }
 
 // Adds the lanes' statistics to the control block and clears them.
@@ -912,18 +1150,22 @@ __device__ __forceinline__ void sweep_flush(SweepCtl *C, uint32_t &upd, uint32_t
     upd = visits = touch = unb = 0;
 }
 
+template <SweepForm F, bool UNIT>
 __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int64_t max_rounds,
                                                    int prof) {
     SweepCtl *C = P.ctl;
     __shared__ u64 s_nf, s_ngth, s_nsel, s_ntc, s_left, s_r0;
     __shared__ int s_ok, s_y;
+    __shared__ int2 s_level;  // of the only job (level by level; else -1)
     __shared__ u64 s_mask[kPBlock / kWave];
     __shared__ const int32_t *s_ys;
     u64 gen_local = 0;
     // Wave ids run across blocks first: a small round spreads over many CUs.
     const int64_t wid = (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x;
     const int64_t nwaves = (int64_t)gridDim.x * (kPBlock / kWave);
-    const int64_t tid = wid * kWave + lane_id();
+    // Decisions are made by the last waves, as phase A's items go to the first
+    // ones (a round of few items is a chain of waits for memory).
+    const int64_t tid = (nwaves - 1 - wid) * kWave + lane_id();
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     uint32_t upd = 0, visits = 0, touch = 0, unb = 0;
     if (threadIdx.x == 0) {
@@ -931,34 +1173,47 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         s_r0 = ld(&C->rounds);
         s_left = 1;  // a launch has something to do (see below)
         s_nf = ld(&C->nf[s_r0 & 1].v);
-        s_ngth = ld(&C->ngth[s_r0 & 1].v);
+        const int2 none = make_int2(-1, 0);
+        s_level = F == kOne ? part_level<kMany>(P, 0, none) : none;
         s_nsel = ld(&C->nsel[s_r0 & 1].v) & ~kYieldBit;
         s_ys = reinterpret_cast<const int32_t *>(ld(&C->yield_src));
         s_ok = 1;
         s_y = 0;
     }
-    u64 looked = 0;  // the lead's, at the yield word
-    if (lead) {
-        st(&C->yielded, 0);
-        looked = wall_clock64();
-    }
+    u64 looked = tid == 0 ? wall_clock64() : 0;  // at the yield word
+    if (lead) st(&C->yielded, 0);
     __syncthreads();
     int64_t r = (int64_t)s_r0;
     for (; r < max_rounds && s_left > 0 && s_ok; ++r) {
         const int p = (int)(r & 1), q = p ^ 1;
-        const u64 nf = s_nf, ngth = s_ngth, nsel = s_nsel;
+        const u64 nf = s_nf, nsel = s_nsel;
+        // It changes in rounds without a frontier only (gathers read it anew).
+        const int2 one = s_level;
         u64 t0 = 0, t1 = 0, t2 = 0, t3 = 0, t4 = 0;
         if (prof && lead) t0 = wall_clock64();
-        if (lead) st(&C->ntc[q].v, (u64)0);
-        sweep_decide(P, r, p, tid, nwaves * kWave);
+        if (lead) {
+            st(&C->ntc[q].v, (u64)0);
+            st(&C->ngth[q].v, (u64)0);
+        }
+        // The host's yield word is passed on before a barrier and read by every
+        // block after it, so all blocks stop after the same round.  One of the
+        // last waves looks, which have no items in small rounds: the read takes
+        // about 2 us.
+        if (tid == 0 && s_ys &&
+            (r % kYieldEvery == kYieldEvery - 1 || wall_clock64() - looked >= kYieldTicks)) {
+            if (__hip_atomic_load(s_ys, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))
+                atomicOr(&C->nsel[q].v, kYieldBit);
+            looked = wall_clock64();
+        }
+        sweep_decide<F>(P, r, p, tid, nwaves * kWave);
         // Selects take their blocks out of phase A (they are chains of waits
         // behind its traffic), unless there are too many.
         const u64 busy = nsel <= gridDim.x / 2 ? nsel : 0;
-        for (u64 i = blockIdx.x; i < nsel; i += gridDim.x)
-            sweep_select(P, ld(&P.sel[p][i]), r, q);
+        for (u64 i = blockIdx.x; F == kSplit && i < nsel; i += gridDim.x)
+            sweep_select(P, ld(&P.sel[p][i]), r, p);
         if (prof && lead) t1 = wall_clock64();
         if (blockIdx.x >= busy)
-            sweep_phase_a(P, r, p, nf, ngth,
+            sweep_phase_a<F>(P, r, p, nf, one,
                           (int64_t)(threadIdx.x / kWave) * (gridDim.x - busy) + blockIdx.x - busy,
                           (int64_t)(gridDim.x - busy) * (kPBlock / kWave),
                           &s_mask[threadIdx.x / kWave], upd);
@@ -968,6 +1223,7 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         if (threadIdx.x == 0) {
             s_ok = grid_arrive_wait(B, gen_local);
             s_ntc = ld(&C->ntc[p].v);
+            s_ngth = ld(&C->ngth[p].v);
             // Jobs end in sweep_decide alone, so this count is the same for
             // every block between the round's barriers.  Past the second one a
             // faster block may already decide on the next round: a block that
@@ -979,27 +1235,16 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
         if (prof && lead) t3 = wall_clock64();
         if (lead) {
             st(&C->nf[p].v, (u64)0);
-            st(&C->ngth[p].v, (u64)0);
             st(&C->nsel[p].v, (u64)0);
         }
-        sweep_phase_b(P, r, p, s_ntc, wid, nwaves, &s_mask[threadIdx.x / kWave], upd, visits, touch,
+        sweep_phase_b<F, UNIT>(P, r, p, s_ntc, s_ngth, one, wid, nwaves, &s_mask[threadIdx.x / kWave], upd, visits, touch,
                       unb);
         drain_memory();
         __syncthreads();
         if (threadIdx.x == 0) {
-            // The lead publishes the host's yield word before the barrier and
-            // every block reads it after, so all blocks stop after the same
-            // round.
-            if (lead && s_ys &&
-                ((r + 1) % kYieldEvery == 0 || wall_clock64() - looked >= kYieldTicks)) {
-                if (__hip_atomic_load(s_ys, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))
-                    atomicOr(&C->nsel[q].v, kYieldBit);
-                looked = wall_clock64();
-                drain_memory();
-            }
             s_ok = grid_arrive_wait(B, gen_local);
             s_nf = ld(&C->nf[q].v);
-            s_ngth = ld(&C->ngth[q].v);
+            if (F == kOne) s_level = part_level<kMany>(P, 0, make_int2(-1, 0));
             const u64 ns = ld(&C->nsel[q].v);
             s_nsel = ns & ~kYieldBit;
             s_y = s_ok && (ns & kYieldBit) != 0;
@@ -1025,13 +1270,13 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
 
 // The same rounds as two kernels each, replayed from a captured HIP graph or
 // launched directly (a job list that is done makes them empty).
+template <SweepForm F>
 __global__ __launch_bounds__(kPBlock) void k_sweep_a(SweepArgs P, int p) {
     SweepCtl *C = P.ctl;
-    __shared__ u64 s_r, s_nf, s_ngth, s_nsel, s_mask[kPBlock / kWave];
+    __shared__ u64 s_r, s_nf, s_nsel, s_mask[kPBlock / kWave];
     if (threadIdx.x == 0) {
         s_r = ld(&C->rounds);
         s_nf = ld(&C->nf[p].v);
-        s_ngth = ld(&C->ngth[p].v);
         s_nsel = ld(&C->nsel[p].v);
     }
     __syncthreads();
@@ -1040,34 +1285,36 @@ __global__ __launch_bounds__(kPBlock) void k_sweep_a(SweepArgs P, int p) {
     const int64_t nwaves = (int64_t)gridDim.x * (kPBlock / kWave);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st(&C->ntc[q].v, (u64)0);
+        st(&C->ngth[q].v, (u64)0);
         st(&C->round_b, s_r);
     }
-    sweep_decide(P, (int64_t)s_r, p, wid * kWave + lane_id(), nwaves * kWave);
-    for (u64 i = blockIdx.x; i < s_nsel; i += gridDim.x)
-        sweep_select(P, ld(&P.sel[p][i]), (int64_t)s_r, q);
+    sweep_decide<F>(P, (int64_t)s_r, p, (nwaves - 1 - wid) * kWave + lane_id(), nwaves * kWave);
+    for (u64 i = blockIdx.x; F == kSplit && i < s_nsel; i += gridDim.x)
+        sweep_select(P, ld(&P.sel[p][i]), (int64_t)s_r, p);
     uint32_t upd = 0, none = 0;
-    sweep_phase_a(P, (int64_t)s_r, p, s_nf, s_ngth, wid, nwaves, &s_mask[threadIdx.x / kWave], upd);
+    sweep_phase_a<F>(P, (int64_t)s_r, p, s_nf, make_int2(-1, 0), wid, nwaves, &s_mask[threadIdx.x / kWave], upd);
     sweep_flush(C, upd, none, none, none);
 }
 
+template <SweepForm F, bool UNIT>
 __global__ __launch_bounds__(kPBlock) void k_sweep_b(SweepArgs P, int p) {
     SweepCtl *C = P.ctl;
-    __shared__ u64 s_ntc, s_r, s_mask[kPBlock / kWave];
+    __shared__ u64 s_ntc, s_ngth, s_r, s_mask[kPBlock / kWave];
     if (threadIdx.x == 0) {
         s_ntc = ld(&C->ntc[p].v);
+        s_ngth = ld(&C->ngth[p].v);
         s_r = ld(&C->round_b);
     }
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st(&C->nf[p].v, (u64)0);
-        st(&C->ngth[p].v, (u64)0);
         st(&C->nsel[p].v, (u64)0);
         // Phase B reads round_b, phase A rounds: each is set where the other
         // kernel runs.
         if (ld(&C->left.v) > 0) st(&C->rounds, s_r + 1);
     }
     uint32_t upd = 0, visits = 0, touch = 0, unb = 0;
-    sweep_phase_b(P, (int64_t)s_r, p, s_ntc, (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x,
+    sweep_phase_b<F, UNIT>(P, (int64_t)s_r, p, s_ntc, s_ngth, make_int2(-1, 0), (int64_t)(threadIdx.x / kWave) * gridDim.x + blockIdx.x,
                   (int64_t)gridDim.x * (kPBlock / kWave), &s_mask[threadIdx.x / kWave], upd, visits,
                   touch, unb);
     sweep_flush(C, upd, visits, touch, unb);
@@ -1141,7 +1388,7 @@ struct SweepAsk {
     bool unit = false, plain = false;
     bool least = false;          // with the least memory
     int64_t *sup_out = nullptr;
-    int64_t *scratch = nullptr;  // plain: m places that the caller writes afterwards
+    int64_t *scratch = nullptr;  // plain: m words that the caller writes afterwards
 };
 
 // The state of a sweep over one job.
@@ -1186,19 +1433,16 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     P.dead = ws.get<uint8_t>("sw_dead", dead_bytes);
     P.bloom = ws.get<BloomRec>("sw_bloom", nb);
     P.wedge_k = ask.plain ? nullptr : ws.get<int32_t>("sw_wedge_k", ix.n_w);
-    P.plain = ask.plain ? 1 : 0;
     // Links of an edge, wedges of a bloom, on average.
     const int64_t links = 2 * ix.n_w / m + 1, wedges = ix.n_w / nb + 1;
     P.short_a = links <= 16 ? (int32_t)(kWave / links) : 0;
     P.short_b = wedges <= 3 ? (int32_t)(kWave / wedges) : 0;
     P.list = reinterpret_cast<int32_t *>(ask.scratch);
-    P.m = (uint32_t)m;
     P.wea = ix.wea;
     P.web = ix.web;
     P.link_off = ix.link_off;
     P.link = ix.link;
     P.n_w = (uint32_t)ix.n_w;
-    P.unit = ask.unit ? 1 : 0;
     P.reserve = (uint32_t)(spare / waves);
     P.front[0] = ws.get<FrontItem>("peel_front0", max_front);
     P.front[1] = ws.get<FrontItem>("peel_front1", max_front);
@@ -1238,13 +1482,14 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
         J.select_round = -8;
         J.level = -1;
         J.part = j;
-        J.n_list = -1;
+        J.thresh = -1;
+        J.delta = 7;
         J.scale = 1.f;
         J.narrow = jobs[(size_t)j].stuck ? 1 : 0;
         J.hi_bound = jobs[(size_t)j].hi;
         const int64_t n = jobs[(size_t)j].ne;
         J.target_n = std::max<int64_t>(512, n / parts_for(n, jobs[(size_t)j].work, m));
-        first[(size_t)j] = SplitPart{ask.min_level, ask.min_level, j, 1};
+        first[(size_t)j] = SplitPart{ask.min_level, ask.plain ? INT_MIN : ask.min_level, j, 1};
     }
     if (nj == 1) {
         // By value: copies from the host's arrays and the wait for them took 50
@@ -1267,6 +1512,14 @@ SweepArgs sweep_setup(const SplitIndex &ix, const std::vector<SplitJob> &jobs, c
     return P;
 }
 
+using SweepKernel = void (*)(SweepArgs, GridBar *, int64_t, int);
+SweepKernel sweep_kernel(SweepForm form, bool unit) {
+    static const SweepKernel k[3][2] = {{k_sweep<kSplit, false>, k_sweep<kSplit, true>},
+                                        {k_sweep<kMany, false>, k_sweep<kMany, true>},
+                                        {k_sweep<kOne, false>, k_sweep<kOne, true>}};
+    return k[form][unit ? 1 : 0];
+}
+
 // BT_PEEL_YIELD=1 makes every launch stop at its first check (a test of the
 // resume path).
 const int32_t *yield_word(const CoopTurn *turn) {
@@ -1283,7 +1536,8 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
     int dev = 0, cus = 0, occ = 0;
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_sweep, kPBlock, 0));
+    const auto kern = sweep_kernel(ask.plain ? (nj == 1 ? kOne : kMany) : kSplit, ask.unit);
+    BT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kPBlock, 0));
     const int pblocks = !turn ? cus
                         : tp.peel_blocks == 0 && m >= kAllCusEdges
                             ? std::max(1, std::min(cus, occ * cus))
@@ -1310,7 +1564,7 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
         for (;;) {
             zero_bytes(bar, sizeof(GridBar), s);
             BT_HIP(hipEventRecord(ev0, s));
-            BT_HIP(hipLaunchCooperativeKernel((const void *)k_sweep, dim3(pblocks), dim3(kPBlock),
+            BT_HIP(hipLaunchCooperativeKernel((const void *)kern, dim3(pblocks), dim3(kPBlock),
                                               args, 0, s));
             BT_HIP(hipEventRecord(ev1, s));
             int32_t fail = 0;
@@ -1335,10 +1589,13 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
         const char *gv = std::getenv("BT_PEEL_GRAPH");
         const bool use_graph = !(gv && std::atoi(gv) == 0);
         constexpr int kChunk = 32;
+        const auto kern_a = ask.plain ? k_sweep_a<kMany> : k_sweep_a<kSplit>;
+        const auto kern_b = ask.plain ? (ask.unit ? k_sweep_b<kMany, true> : k_sweep_b<kMany, false>)
+                                      : (ask.unit ? k_sweep_b<kSplit, true> : k_sweep_b<kSplit, false>);
         const auto rounds = [&](hipStream_t t) {
             for (int k = 0; k < kChunk; ++k) {
-                k_sweep_a<<<cus, kPBlock, 0, t>>>(P, k & 1);
-                k_sweep_b<<<cus, kPBlock, 0, t>>>(P, k & 1);
+                kern_a<<<cus, kPBlock, 0, t>>>(P, k & 1);
+                kern_b<<<cus, kPBlock, 0, t>>>(P, k & 1);
             }
         };
         hipGraphExec_t ex = nullptr;
@@ -1435,8 +1692,8 @@ void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn 
     std::vector<EdgeMark> mark((size_t)m);
     for (int64_t r = 0;; ++r) {
         if (r > 8 * m + 1024) throw Error{BT_EDEVICE, "peel made no progress"};
-        k_sweep_a<<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
-        k_sweep_b<<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
+        k_sweep_a<kMany><<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
+        k_sweep_b<kMany, false><<<blocks, kPBlock, 0, s>>>(P, (int)(r & 1));
         BT_CHECK_LAUNCH();
         if (ix.n_b) k_blooms_live<<<grid_for(ix.n_b, 256, 4096), 256, 0, s>>>(P.bloom, ix.n_b, live);
         BT_CHECK_LAUNCH();
@@ -1525,9 +1782,10 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
     ask.least = opt && opt->plain;
     // Few levels: level by level as well, as splitting passes over the graph
     // once more.
-    ask.plain = opt && (opt->plain || few_levels(std::min(ix.max_sup, opt->levels), ix.n_w));
+    const bool few = opt && few_levels(std::min(ix.max_sup, opt->levels), ix.n_w);
+    ask.plain = few || (opt && opt->plain);
     ask.sup_out = sup_out;
-    ask.scratch = phi_out;
+    ask.scratch = few ? nullptr : phi_out;
     if (ask.plain) {
         // Level by level, with the memory of the index alone.
         const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);

@@ -156,3 +156,30 @@ def test_few_edges_of_many_wedges(monkeypatch):
     assert torch.equal(phi, phi0) and torch.equal(sup, sup0)
     for k in ("butterflies", "max_phi", "levels", "bloom_wedges"):
         assert st[k] == st0[k], k
+
+
+@pytest.mark.parametrize("unit", [False, True])
+@pytest.mark.parametrize("mode", ["plain", "graph"])
+def test_thresholds_of_long_ranges(mode, unit, monkeypatch):
+    """Ranges of 2^18 edges and more, whose level-by-level gathers scan a list of
+    the edges below a threshold: alone, beside others, and resumed after
+    yields; with batch bloom processing and without."""
+    g = synth.chung_lu(6000, 40000, 300001, 2.0, 2.3, 4000, 4000, 7)
+    ophi = oracle_all(g)[2]
+    d = upload(g)
+    monkeypatch.setenv("BT_PEEL_MODE", mode)
+    variant = binding.BT_PEEL_BATCH_EDGE if unit else binding.BT_PEEL_BATCH_BLOOM
+    _, phi, st = binding.bt_decompose_variant(d, variant, stats=True)
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+    assert mode == "graph" or st["levels"] == np.unique(ophi).size
+    if mode == "plain":
+        monkeypatch.setenv("BT_PEEL_YIELD", "1")
+        _, phi, st1 = binding.bt_decompose_variant(d, variant, stats=True)
+        assert st1["peel_yields"] >= 1 and st1["rounds"] == st["rounds"]
+        assert np.array_equal(phi.cpu().numpy(), ophi)
+        monkeypatch.delenv("BT_PEEL_YIELD")
+    if not unit:
+        h = _cl(280000, 5)
+        phis = binding.bt_decompose_batch([d, upload(h), upload(_cl(20000))])[1]
+        assert np.array_equal(phis[0].cpu().numpy(), ophi)
+        assert np.array_equal(phis[1].cpu().numpy(), oracle_all(h)[2])
