@@ -175,9 +175,11 @@ bool peel_mode(const char *v) {
     return mv && std::strcmp(mv, v) == 0;
 }
 
-// Runs a decomposition with the peel that splits; where that does not fit the
-// device's memory, again with the one that needs the least (level by level).
-// BT_PEEL_MODE=plain takes that one at once.
+// Runs a decomposition with the peel that splits (which goes on level by level
+// where only the split's own buffers do not fit); where the device's memory does
+// not hold even that beside what the workspace has cached, again from an empty
+// workspace in the form that needs the least.  BT_PEEL_MODE=plain takes that one
+// at once.
 template <class F> void with_plain_fallback(Workspace &ws, F &&run) {
     if (peel_mode("plain")) return run(true);
     try {

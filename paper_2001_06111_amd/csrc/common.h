@@ -66,6 +66,8 @@ public:
     }
     int64_t *host(int n);  // pinned, at least n int64; valid until a larger request
     void release();
+    // Frees the buffers whose names begin with one of these (NULL ends them).
+    void drop(const char *const *prefixes);
     size_t bytes() const;
     // Side stream k (0 to 2), made on first use and kept: for launches that
     // may run beside each other.  Work on it is ordered after and before the

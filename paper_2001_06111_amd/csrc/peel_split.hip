@@ -1753,68 +1753,49 @@ bool few_levels(int64_t levels, int64_t n_w) {
     return levels <= 24 + n_w / 65536;
 }
 
-void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
-                int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,
-                const PeelOptions *opt) {
-    const int32_t ng = (int32_t)off.size() - 1;
-    const int64_t m = off[(size_t)ng];
-    if (m == 0) return;
-    const bool unit = opt && opt->unit_updates;
-    const char *mv = std::getenv("BT_PEEL_MODE");
-    const bool coop = ws.coop && !(mv && std::strcmp(mv, "graph") == 0);
+const char *const kSplitBuffers[] = {"sw_wedge_k", "rg_", "sp_", "lf_", "pool_", "rs_", nullptr};
+
+// The peel level by level.
+static void peel_levels(const SplitIndex &cur, const std::vector<SplitJob> &jobs, const SweepAsk &ask,
+                        const TuneParams &tp, CoopTurn *turn, int64_t *phi_out, PeelCounters &pc,
+                        Workspace &ws, hipStream_t s) {
+    const int64_t m = cur.m;
+    // Level by level, with the memory of the index alone.
+    const SweepResult sw = sweep(cur, jobs, ask, tp, turn, pc, ws, s);
+    k_marks_out<<<grid_for(m, 256, 16384), 256, 0, s>>>(sw.mark, m, phi_out);
+    BT_CHECK_LAUNCH();
+    unsigned long long *mx = ws.get<unsigned long long>("sp_max", 1);
+    zero_bytes(mx, sizeof *mx, s);
+    k_max_mark<<<grid_for(m, 256, 4096), 256, 0, s>>>(sw.mark, m, mx);
+    BT_CHECK_LAUNCH();
+    static_assert(sizeof(JobState) % sizeof(int64_t) == 0, "copied as words");
+    int64_t *h = ws.host(1 + (int)(jobs.size() * (sizeof(JobState) / sizeof(int64_t))));
+    BT_HIP(hipMemcpyAsync(h, mx, sizeof *mx, hipMemcpyDeviceToHost, s));
+    BT_HIP(hipMemcpyAsync(h + 1, ws.get<JobState>("sw_jobs", (int64_t)jobs.size()),
+                          sizeof(JobState) * jobs.size(), hipMemcpyDeviceToHost, s));
+    BT_HIP(hipStreamSynchronize(s));
+    pc.launches += 1 + pc.yields;
+    pc.max_phi = h[0];
+    const JobState *js = reinterpret_cast<const JobState *>(h + 1);
+    for (size_t j = 0; j < jobs.size(); ++j)
+        pc.levels = std::max<int64_t>(pc.levels, js[j].n_parts);
+}
+
+// The peel that splits; the index's links are lost.
+static void peel_parts(const IndexArrays &ix, SplitIndex cur, std::vector<SplitJob> jobs, SweepAsk ask,
+                       int32_t ng, const TuneParams &tp, bool coop, CoopTurn *turn, int64_t *phi_out,
+                       PeelCounters &pc, Workspace &ws, hipStream_t s) {
+    const int64_t m = cur.m;
     const bool verbose = std::getenv("BT_PEEL_VERBOSE") != nullptr;
-    std::vector<SplitJob> jobs;
-    for (int32_t g = 0; g < ng; ++g)
-        if (off[(size_t)g + 1] > off[(size_t)g])
-            jobs.push_back(SplitJob{0, (int32_t)off[(size_t)g],
-                                    (int32_t)(off[(size_t)g + 1] - off[(size_t)g]), g, kLevelMax,
-                                    (uint32_t)(ix.n_w * (off[(size_t)g + 1] - off[(size_t)g]) / m), false});
     std::vector<int32_t> levels((size_t)ng, 0);
     int32_t max_level = 0;
-    std::unique_ptr<CoopTurn> turn;
-    if (coop) turn.reset(new CoopTurn(m));
-    SplitIndex cur = view_of(ix, m);
-    SweepAsk ask;
-    ask.supl = ix.supl;
-    ask.fixed = opt ? opt->fixed : nullptr;
-    ask.min_level = opt ? opt->min_level : 0;
-    ask.unit = unit;
-    ask.least = opt && opt->plain;
-    // Few levels: level by level as well, as splitting passes over the graph
-    // once more.
-    const bool few = opt && few_levels(std::min(ix.max_sup, opt->levels), ix.n_w);
-    ask.plain = few || (opt && opt->plain);
-    ask.sup_out = sup_out;
-    ask.scratch = few ? nullptr : phi_out;
-    if (ask.plain) {
-        // Level by level, with the memory of the index alone.
-        const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);
-        k_marks_out<<<grid_for(m, 256, 16384), 256, 0, s>>>(sw.mark, m, phi_out);
-        BT_CHECK_LAUNCH();
-        unsigned long long *mx = ws.get<unsigned long long>("sp_max", 1);
-        zero_bytes(mx, sizeof *mx, s);
-        k_max_mark<<<grid_for(m, 256, 4096), 256, 0, s>>>(sw.mark, m, mx);
-        BT_CHECK_LAUNCH();
-        static_assert(sizeof(JobState) % sizeof(int64_t) == 0, "copied as words");
-        int64_t *h = ws.host(1 + (int)(jobs.size() * (sizeof(JobState) / sizeof(int64_t))));
-        BT_HIP(hipMemcpyAsync(h, mx, sizeof *mx, hipMemcpyDeviceToHost, s));
-        BT_HIP(hipMemcpyAsync(h + 1, ws.get<JobState>("sw_jobs", (int64_t)jobs.size()),
-                              sizeof(JobState) * jobs.size(), hipMemcpyDeviceToHost, s));
-        BT_HIP(hipStreamSynchronize(s));
-        pc.launches += 1 + pc.yields;
-        pc.max_phi = h[0];
-        const JobState *js = reinterpret_cast<const JobState *>(h + 1);
-        for (size_t j = 0; j < jobs.size(); ++j)
-            pc.levels = std::max<int64_t>(pc.levels, js[j].n_parts);
-        return;
-    }
     LeafPool pool;
     std::unique_ptr<LeafRun> leaves;
     int dev = 0, cus = 0;
     BT_HIP(hipGetDevice(&dev));
     BT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     for (int depth = 0; !jobs.empty(); ++depth) {
-        const SweepResult sw = sweep(cur, jobs, ask, r.tp, turn.get(), pc, ws, s);
+        const SweepResult sw = sweep(cur, jobs, ask, tp, turn, pc, ws, s);
         // The links are not needed after the first sweep; their memory (24
         // bytes a wedge) takes the leaves' wedges and blooms (20).
         if (depth == 0) pool.place(ix.link, ix.n_w, m, ws);
@@ -1829,14 +1810,14 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
         }
         jobs = g.jobs;
         if (!leaves && !pool.leaves.empty())
-            leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, unit, ng, turn.get(),
-                                     yield_word(turn.get()), ws, s));
+            leaves.reset(new LeafRun(pool, m, ix.n_w, phi_out, ask.unit, ng, turn,
+                                     yield_word(turn), ws, s));
         if (jobs.empty()) break;
         // The compute units that the next sweep leaves peel the heaviest
         // leaves meanwhile: one of a few hundred thousand wedges takes tens of
         // milliseconds, all of them together little more.  5M-edge graph 262
         // and 247 ms, 192 pool graphs 151 and 142 ms.
-        if (leaves && coop && g.m < kAllCusEdges) leaves->start(cus - peel_grid(r.tp, cus, cus));
+        if (leaves && coop && g.m < kAllCusEdges) leaves->start(cus - peel_grid(tp, cus, cus));
         uint64_t *supl2 = ws.get<uint64_t>("sp_supl", g.m + 1);
         int64_t *loff2 = ws.get<int64_t>("sp_loff", g.m + 1);
         uint3 *link2 = ws.get<uint3>("sp_link", 2 * g.n_w + 1);
@@ -1861,6 +1842,54 @@ void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &o
     pc.launches += 1 + pc.yields;
     pc.max_phi = max_level;
     for (int32_t l : levels) pc.levels = std::max<int64_t>(pc.levels, l);
+}
+
+void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
+                int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,
+                const PeelOptions *opt) {
+    const int32_t ng = (int32_t)off.size() - 1;
+    const int64_t m = off[(size_t)ng];
+    if (m == 0) return;
+    const bool unit = opt && opt->unit_updates;
+    const char *mv = std::getenv("BT_PEEL_MODE");
+    const bool coop = ws.coop && !(mv && std::strcmp(mv, "graph") == 0);
+    std::vector<SplitJob> jobs;
+    for (int32_t g = 0; g < ng; ++g)
+        if (off[(size_t)g + 1] > off[(size_t)g])
+            jobs.push_back(SplitJob{0, (int32_t)off[(size_t)g],
+                                    (int32_t)(off[(size_t)g + 1] - off[(size_t)g]), g, kLevelMax,
+                                    (uint32_t)(ix.n_w * (off[(size_t)g + 1] - off[(size_t)g]) / m), false});
+    std::unique_ptr<CoopTurn> turn;
+    if (coop) turn.reset(new CoopTurn(m));
+    const SplitIndex cur = view_of(ix, m);
+    SweepAsk ask;
+    ask.supl = ix.supl;
+    ask.fixed = opt ? opt->fixed : nullptr;
+    ask.min_level = opt ? opt->min_level : 0;
+    ask.unit = unit;
+    ask.least = opt && opt->plain;
+    // Few levels: level by level as well, as splitting passes over the graph
+    // once more.
+    const bool few = opt && few_levels(std::min(ix.max_sup, opt->levels), ix.n_w);
+    ask.plain = few || (opt && opt->plain);
+    ask.sup_out = sup_out;
+    ask.scratch = few ? nullptr : phi_out;
+    if (ask.plain) return peel_levels(cur, jobs, ask, r.tp, turn.get(), phi_out, pc, ws, s);
+    const PeelCounters before = pc;
+    try {
+        peel_parts(ix, cur, jobs, ask, ng, r.tp, coop, turn.get(), phi_out, pc, ws, s);
+    } catch (const Error &e) {
+        // What the split takes does not fit: level by level on the same index.
+        if (e.status != BT_ENOMEM) throw;
+        if (std::getenv("BT_PEEL_VERBOSE"))
+            std::fprintf(stderr, "[peel] %s: level by level\n", e.msg.c_str());
+        BT_HIP(hipStreamSynchronize(s));
+        ws.drop(kSplitBuffers);
+        rebuild_links(ix, m, s);
+        pc = before;
+        ask.plain = ask.least = true;
+        peel_levels(cur, jobs, ask, r.tp, turn.get(), phi_out, pc, ws, s);
+    }
 }
 
 }  // namespace bt

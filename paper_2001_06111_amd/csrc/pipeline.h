@@ -151,6 +151,10 @@ int64_t count_support(const RankCSR &r, uint64_t *supl, int64_t *bf, Workspace &
 void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspace &ws,
                  hipStream_t s, const Components *comps = nullptr);
 
+// The link lists once more, from the wedges (whose edges may carry fixed marks)
+// and link_off: for a peel that has used their memory and starts over.
+void rebuild_links(IndexArrays &ix, int64_t m, hipStream_t s);
+
 // Counters of a peel.
 struct PeelCounters {
     int64_t levels = 0, rounds = 0, max_phi = 0, updates = 0, bloom_visits = 0;
@@ -196,6 +200,9 @@ void peel_trace(IndexArrays &ix, int64_t m, int64_t *phi_out, const PeelTraceFn 
 // off[g+1])): split into ranges of bitruss numbers by grid-wide sweeps, the
 // ranges then finished by themselves.
 // Device bytes it allocates, an upper bound with the workspace's growth slack.
+// What the split takes beyond the level-by-level form (names of workspace
+// buffers): freed where it does not fit, and after a call that leaves much.
+extern const char *const kSplitBuffers[];
 int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bool plain);
 void peel_split(const RankCSR &r, IndexArrays &ix, const std::vector<int64_t> &off,
                 int64_t *sup_out, int64_t *phi_out, PeelCounters &pc, Workspace &ws, hipStream_t s,

@@ -1,6 +1,8 @@
 // prims.hip - device-wide scans, stable radix sort, fills, workspace, the
 // device-memory allocator hook.
 
+#include <algorithm>
+#include <cstring>
 #include <mutex>
 #include <unordered_map>
 
@@ -201,6 +203,18 @@ void Workspace::release() {
     if (host_) (void)hipHostFree(host_);
     host_ = nullptr;
     host_cap_ = 0;
+}
+
+void Workspace::drop(const char *const *prefixes) {
+    if (arena_) return;
+    const auto named = [&](const Buf &b) {
+        for (const char *const *p = prefixes; *p; ++p)
+            if (b.name.compare(0, std::strlen(*p), *p) == 0) return true;
+        return false;
+    };
+    for (Buf &b : bufs_)
+        if (named(b)) device_free(b.ptr);
+    bufs_.erase(std::remove_if(bufs_.begin(), bufs_.end(), named), bufs_.end());
 }
 
 size_t Workspace::bytes() const {

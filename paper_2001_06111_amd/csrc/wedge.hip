@@ -388,6 +388,28 @@ __global__ void k_link_scatter(const int32_t *wea, const int32_t *web, const int
     }
 }
 
+// The counts that the first scatter consumed, from the offsets that it left.
+__global__ void k_link_counts_again(const int64_t *link_off, int64_t m, uint64_t *supl) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x)
+        supl[e] |= (uint64_t)(link_off[e + 1] - link_off[e]) << 32;
+}
+
+// k_link_scatter of wedges whose edges may carry marks, which the twins keep.
+__global__ void k_link_again(const int32_t *wea, const int32_t *web, const int32_t *wbl, int64_t nw,
+                             uint64_t *supl, const int64_t *link_off, uint3 *link) {
+    const unsigned long long one = (unsigned long long)(-(int64_t)(uint64_t(1) << 32));
+    for (int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; w < nw;
+         w += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t a = (uint32_t)wea[w], b = (uint32_t)web[w], bl = (uint32_t)wbl[w];
+        const uint32_t ea = a & 0x7fffffffu, eb = b & 0x7fffffffu;
+        const uint64_t oa = atomicAdd((unsigned long long *)&supl[ea], one);
+        link[link_off[ea] + (int64_t)(oa >> 32) - 1] = make_uint3((uint32_t)w, bl, b);
+        const uint64_t ob = atomicAdd((unsigned long long *)&supl[eb], one);
+        link[link_off[eb] + (int64_t)(ob >> 32) - 1] = make_uint3((uint32_t)w, bl, a);
+    }
+}
+
 __global__ void k_bloom_sentinel(const uint64_t *cursor, int32_t n, uint32_t *bwoff) {
     for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n; g += gridDim.x * blockDim.x) {
         const uint64_t c = cursor[g];
@@ -513,6 +535,15 @@ void build_index(const RankCSR &r, const TaskLists &t, IndexArrays &ix, Workspac
     scan_exclusive_i32_to_i64(cnt, ix.link_off, m, ws, s);
     k_link_scatter<<<grid_for(ix.cap_w, 256, 65536), 256, 0, s>>>(
         ix.wea, ix.web, ix.wbl, ix.cursor, ix.supl, ix.link_off, ix.link);
+    BT_CHECK_LAUNCH();
+}
+
+void rebuild_links(IndexArrays &ix, int64_t m, hipStream_t s) {
+    if (m == 0 || ix.n_w == 0) return;
+    k_link_counts_again<<<grid_for(m, 256, 16384), 256, 0, s>>>(ix.link_off, m, ix.supl);
+    BT_CHECK_LAUNCH();
+    k_link_again<<<grid_for(ix.n_w, 256, 65536), 256, 0, s>>>(ix.wea, ix.web, ix.wbl, ix.n_w,
+                                                             ix.supl, ix.link_off, ix.link);
     BT_CHECK_LAUNCH();
 }
 

@@ -1,0 +1,78 @@
+"""Calls short of device memory: a split that does not fit goes on level by
+level with the index it has."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2001_06111_amd import binding, synth
+from tests.gpu_util import oracle_all, upload
+
+pytestmark = pytest.mark.gpu
+
+
+class Budget:
+    """Device memory of at most so many bytes at a time, and the largest sum."""
+
+    def __init__(self, most=None):
+        self.most, self.held, self.peak, self.sizes, self.refused = most, 0, 0, [], 0
+
+    def alloc(self, n):
+        if self.most is not None and self.held + n > self.most:
+            self.refused += 1
+            return None
+        self.held += n
+        self.peak = max(self.peak, self.held)
+        self.sizes.append(n)
+        return torch.cuda.caching_allocator_alloc(n)
+
+    def free(self, p, n):
+        self.held -= n
+        torch.cuda.caching_allocator_delete(p)
+
+
+@pytest.fixture(autouse=True)
+def _default_allocator():
+    binding.bt_release_workspace()
+    yield
+    binding.bt_release_workspace()
+    binding.bt_set_allocator()
+
+
+def _run(call, most=None):
+    b = Budget(most)
+    binding.bt_set_allocator(b.alloc, b.free)
+    out = call()
+    torch.cuda.synchronize()
+    binding.bt_release_workspace()
+    assert b.held == 0
+    return out, b
+
+
+@pytest.mark.parametrize("call", ["plain", "unit", "pc", "batch"])
+def test_split_that_does_not_fit_keeps_the_index(call, monkeypatch):
+    g = synth.chung_lu(3000, 8000, 60001, 2.1, 2.3, 2000, 2000, 3)
+    d, small = upload(g), upload(synth.scaled_chunglu(5000, seed=2))
+    ophi = oracle_all(g)[2]
+    calls = {"plain": lambda: binding.bt_decompose(d)[1],
+             "unit": lambda: binding.bt_decompose_variant(d, binding.BT_PEEL_BATCH_EDGE)[1],
+             "pc": lambda: binding.bt_decompose_pc(d, 0.3)[1],
+             "batch": lambda: binding.bt_decompose_batch([d, small])[1][0]}
+    run = calls[call]
+    phi, free = _run(run)
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+    monkeypatch.setenv("BT_PEEL_MODE", "plain")
+    phi, least = _run(run)
+    assert np.array_equal(phi.cpu().numpy(), ophi)
+    monkeypatch.delenv("BT_PEEL_MODE")
+    assert least.peak < free.peak
+    links = max(least.sizes)  # the index's links, its largest buffer
+    kept = 0
+    for k in range(1, 12):
+        most = least.peak + (free.peak - least.peak) * k // 12
+        phi, b = _run(run, most)
+        assert np.array_equal(phi.cpu().numpy(), ophi), (k, b.refused)
+        assert b.peak <= most
+        # Made once (by BiT-PC once a pass that needs a larger one).
+        if b.refused and b.sizes.count(links) == least.sizes.count(links):
+            kept += 1
+    assert kept >= 5
