@@ -32,7 +32,11 @@
  *   Ownership: the caller owns the graph and every output buffer.  The
  *     library owns its scratch memory (a device workspace cached between
  *     calls, released by bt_release_workspace) and the bt_index handles
- *     until bt_index_free.
+ *     until bt_index_free.  A call that peels takes up to about 215 bytes per
+ *     wedge stored in the index (bt_stats bloom_wedges) and keeps them for the
+ *     next; of these, some 150 are given back after a call that would leave less
+ *     than a quarter of the device's memory free.  Where they cannot be had at
+ *     all the peel goes on without them, more slowly (about 65 bytes).
  *   Errors: a non-zero bt_status leaves outputs unspecified;
  *     bt_last_error() returns a thread-local message for the last failure.
  *   Threading: calls that use the shared workspace (bt_support,

@@ -1,5 +1,6 @@
 """Calls short of device memory: a split that does not fit goes on level by
-level with the index it has."""
+level with the index it has, and what a split takes is given back after a
+call that would keep much."""
 import numpy as np
 import pytest
 import torch
@@ -76,3 +77,23 @@ def test_split_that_does_not_fit_keeps_the_index(call, monkeypatch):
         if b.refused and b.sizes.count(links) == least.sizes.count(links):
             kept += 1
     assert kept >= 5
+
+
+def test_what_a_split_takes_is_given_back(monkeypatch):
+    g = synth.chung_lu(3000, 8000, 60001, 2.1, 2.3, 2000, 2000, 3)
+    d = upload(g)
+    ophi = oracle_all(g)[2]
+    b = Budget()
+    binding.bt_set_allocator(b.alloc, b.free)
+    binding.bt_decompose(d)
+    all_kept = b.held
+    monkeypatch.setenv("BT_WORKSPACE_KEEP_MB", "1")
+    for _ in range(2):
+        phi = binding.bt_decompose(d)[1]
+        assert np.array_equal(phi.cpu().numpy(), ophi)
+        assert b.held < 0.75 * all_kept
+    monkeypatch.setenv("BT_WORKSPACE_KEEP_MB", "100000")
+    phi = binding.bt_decompose(d)[1]
+    assert np.array_equal(phi.cpu().numpy(), ophi) and b.held > 0.9 * all_kept
+    binding.bt_release_workspace()
+    assert b.held == 0
