@@ -136,7 +136,8 @@ struct SweepCtl {
 constexpr int64_t kYieldEvery = 16;
 constexpr u64 kYieldTicks = 5000;
 // In the count of the next round's selects, which every block reads between
-// two rounds anyway: all of them end the launch there.
+// two rounds anyway: all of them end the launch there.  It may be set while the
+// count still grows.
 constexpr u64 kYieldBit = u64(1) << 63;
 
 // Parts a job may begin in one sweep; the last takes everything left.
@@ -418,7 +419,7 @@ __device__ void sweep_decide(const SweepArgs &P, int64_t r, int p, int64_t tid, 
         }
         if (!__any(gather || select)) continue;
         put_gather(P, p, part, e0, gather ? n : 0u, how);
-        const u64 slot = wave_alloc(select ? 1u : 0u, &P.ctl->nsel[q].v);
+        const u64 slot = wave_alloc(select ? 1u : 0u, &P.ctl->nsel[q].v) & ~kYieldBit;
         if (select) st(&P.sel[q][slot], (int32_t)g);
     }
 }
