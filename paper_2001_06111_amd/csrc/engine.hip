@@ -75,7 +75,7 @@ constexpr double kLargeWaitS = 10.0;
 // A worker's batch of a larger class waits for requests that come together with
 // its own, as they should share their batch (24 pool graphs submitted at once:
 // 93 ms where the last of nine medium ones just missed its batch and ran alone
-// after it, 74 ms so): while a call of bt_engine_submit is under way, and for
+// after it, 72 to 80 ms so): while a call of bt_engine_submit is under way, and for
 // kGatherS after the last one (a caller's way from one call to the next); the
 // oldest waits kGatherMostS at most.  A request that comes alone waits kGatherS
 // (1 ms, before calls under way were counted).  Small batches, of a millisecond

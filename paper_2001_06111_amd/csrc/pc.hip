@@ -27,7 +27,6 @@ __global__ void k_low32(const uint64_t *supl, int64_t m, int32_t *sup0) {
         sup0[e] = (int32_t)(supl[e] & 0xffffffffu);
 }
 
-// Number of edges with support >= k.
 // cnt[j]: edges whose support is from lo + (j + 1) * step up and below the next
 // threshold (the last: from there up).
 constexpr int kCuts = 64;

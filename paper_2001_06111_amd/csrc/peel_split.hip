@@ -29,16 +29,18 @@
 // summed support lies below it), gather (the edges at or below hi become the
 // frontier), rounds until no edge falls to hi.
 //
-// Whole calls, level by level and split: 5M-edge Chung-Lu graph (75,000
-// rounds, bound by the 9 us a round's two grid barriers and chains take)
-// 1.115 s and 0.239 s; 200k-edge graph 66.4 and 17.5 ms; 400k-edge hub graph
-// by BiT-PC 436 and 99 ms; 192 pool graphs in one batch 620 and 143 ms.
+// Whole calls, level by level (by the kernel that did only that) and split:
+// 5M-edge Chung-Lu graph (75,000 rounds, bound by the 9 us a round's two grid
+// barriers and chains take) 1.115 s and 0.239 s; 200k-edge graph 66.4 and 17.5
+// ms; 400k-edge hub graph by BiT-PC 436 and 98 ms; 192 pool graphs in one batch
+// 620 and 143 ms.
 // The 5M graph's first sweep is now bound by memory-side requests (about
 // 2e10/s of support atomics and random reads), a small graph's by the 10 to
 // 15 us of a round.  The level-by-level form (the same kernel, its parts single
 // levels) stays for graphs of few levels (few_levels below) and for callers
 // whose memory does not hold the second copy of the index that the split
-// needs.
+// needs (5M-edge graph 1.23 s, 250k 88 ms, 2M-edge request graph 2.17 s; the
+// kernel that did only that took 1.10 s, 80 ms and 1.92 s).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -54,7 +56,10 @@ enum : int32_t { kJobActive = 0, kJobDone = 1 };
 constexpr int kGatherPerLane = 8;  // edges per lane of a gather item
 constexpr uint32_t kGatherChunk = kWave * kGatherPerLane;
 // Sweeps of at least this many edges run on every CU by default: they are
-// bound by atomic throughput more than by the latency of their rounds.
+// bound by atomic throughput more than by the latency of their rounds (three of
+// four CUs and all: 20M-edge hub graph 2.99 and 2.91 s, 17M-edge Chung-Lu graph
+// 900 and 886 ms, 12M 635 and 623, 5M 229 and 229).  Below, the CUs left over
+// peel leaves beside the sweep, and lighter peels of others.
 constexpr int64_t kAllCusEdges = int64_t(1) << 24;
 constexpr int32_t kLevelMax = INT_MAX - 1;  // above every support
 
@@ -124,7 +129,7 @@ struct SweepCtl {
     Counter n_parts;   // parts begun
     u64 rounds;        // rounds run so far (a resumed launch starts at this round)
     u64 round_b;       // two-kernel rounds: the round of phase B
-    u64 prof[5];       // BT_PEEL_PROFILE=1: block-0 clock ticks (decide, A, bar, B, bar)
+    u64 prof[4];       // BT_PEEL_PROFILE=1: block-0 clock ticks (decide, A, bar, B with bar)
     u64 yield_src;     // address of the host-written yield word (0: none)
     int32_t yielded;    // set when the launch ended early to give way
     int32_t pad;
@@ -1256,7 +1261,7 @@ __global__ __launch_bounds__(kPBlock) void k_sweep(SweepArgs P, GridBar *B, int6
             C->prof[0] += t1 - t0;
             C->prof[1] += t2 - t1;
             C->prof[2] += t3 - t2;
-            C->prof[4] += t4 - t3;
+            C->prof[3] += t4 - t3;
         }
         if ((r & 1023) == 1023) sweep_flush(C, upd, visits, touch, unb);  // 32-bit per lane
         if (s_y) {
@@ -1631,7 +1636,7 @@ SweepResult sweep(const SplitIndex &ix, const std::vector<SplitJob> &jobs, const
                      hc.n_parts.v, (double)hc.updates.v);
     if (prof)
         std::fprintf(stderr, "[peel] block0 us: decide %.0f phaseA %.0f bar1 %.0f phaseB+bar2 %.0f\n",
-                     hc.prof[0] / 100.0, hc.prof[1] / 100.0, hc.prof[2] / 100.0, hc.prof[4] / 100.0);
+                     hc.prof[0] / 100.0, hc.prof[1] / 100.0, hc.prof[2] / 100.0, hc.prof[3] / 100.0);
     return SweepResult{P.mark, P.wedge_k, P.parts, (int32_t)hc.n_parts.v};
 }
 
@@ -1745,8 +1750,8 @@ int64_t peel_split_bytes(int64_t m, int64_t n_b, int64_t n_w, int64_t graphs, bo
 // and 0.5 ns a wedge for the first sweep (which a graph of few levels falls
 // to as a whole) and the regrouping.  Uniform graphs of 17,000, 117,248,
 // 400,000, 1.5M and 4M edges (largest supports 8, 22, 58, about 150 and 350)
-// take 0.79, 2.8, 9.8, 41.9 and 190 ms split and 0.57, 2.5, 5.3, 22.9 and 92 ms
-// level by level; a Chung-Lu graph of 20,000 edges (thousands) 4.1 and 13.9 ms.
+// take 0.79, 2.8, 9.8, 41.9 and 190 ms split and 0.55, 2.4, 5.2, 21.7 and 88 ms
+// level by level; a Chung-Lu graph of 20,000 edges (thousands) 4.1 and 11.6 ms.
 // BT_PEEL_MODE=split splits whatever the levels.
 bool few_levels(int64_t levels, int64_t n_w) {
     const char *mv = std::getenv("BT_PEEL_MODE");

@@ -290,8 +290,14 @@ __global__ void k_job_links(const int32_t *wea, const int32_t *web, const int32_
 }
 
 // Whether a part is peeled by one workgroup.  A leaf takes about 60 ns a
-// wedge, which a sweep that splits it further must beat; parts that a sweep
-// took whole, or that several have not brought down, are left to it as well.
+// wedge, which a sweep that splits it further must beat: with 250,000 and
+// 1,000,000 wedges in place of kLeafWedges 249 and 223 ms (5M-edge graph, 229 as
+// it is), 150 and 131 (192 pool graphs, 135), 102 and 103 (400,000-edge hub graph
+// by BiT-PC, 98), 225 and 220 (2M-edge hub graph, 214).  Parts that a sweep took
+// whole, or that several have not brought down, are left to it as well; so are
+// parts of a few hundred edges, which a sweep's rounds and launches would cost
+// more (each of these two changes none of the above by 1%, at 0 to 8,192 edges
+// and depths 2 to 100).
 // Above `most` wedges a part goes on to the next sweep whatever it is: its
 // positions must fit the work items, and one workgroup would take seconds.  A
 // part that a sweep took whole is cut by levels, whose range shrinks by 16 a

@@ -49,7 +49,9 @@ constexpr uint32_t kWaveMax = 256, kMidMax = 2048, kBigMax = 16384;
 // rows, so only what would hold up the rest is cut.
 constexpr int64_t kPartLeast = int64_t(1) << 15, kPartMost = int64_t(1) << 21;
 constexpr uint32_t kMaxParts = 4096;
-constexpr int64_t kFirst = int64_t(1) << 19;  // starts from here up go first
+// Starts from here up go first, cut into parts (from 2^18 and 2^20 up: 20M-edge
+// hub graph 21.7 and 21.1 ms, 21.1 so; 5M-edge graph 4.73 and 4.70, 4.7 so).
+constexpr int64_t kFirst = int64_t(1) << 19;
 constexpr int32_t kEmpty = -1;
 constexpr uint32_t kByteMax = 255;
 enum Table { kHash, kDense32, kDense };
@@ -152,7 +154,8 @@ __device__ __forceinline__ uint32_t rows_of(const WalkArgs &A, int32_t s, bool u
 
 // Row j of the walk: entries [st, st + len).  Rows of more than `least`
 // entries are clipped to the window; the others are left whole, and their
-// entries outside the window are passed over one by one.
+// entries outside the window are passed over one by one (clipped from 16 and from
+// 256 entries up: 20M-edge hub graph 21.6 and 22.9 ms, 21.1 with 64).
 constexpr uint32_t kClipLeast = 64;
 __device__ __forceinline__ void load_row(const WalkArgs &A, const Walk &w, uint32_t os, uint32_t j,
                                          uint32_t least, uint32_t &st, uint32_t &len) {

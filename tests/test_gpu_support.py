@@ -138,3 +138,11 @@ def test_side_streams_go_with_the_workspace():
         assert np.array_equal(sup.cpu().numpy(), osup) and bf == obf
         assert np.array_equal(binding.bt_decompose(d)[1].cpu().numpy(), ophi)
         binding.bt_release_workspace()
+
+
+@pytest.mark.parametrize("a,b", [(760, 790), (1100, 500)])
+def test_starts_cut_into_parts(a, b):
+    """Starts of more than 2^19 wedges, which several workgroups share (closed
+    form: an edge of K(a, b) lies in (a - 1)(b - 1) butterflies)."""
+    sup, bf = binding.bt_support(upload(synth.complete(a, b)))
+    assert bool((sup == (a - 1) * (b - 1)).all()) and bf == a * (a - 1) // 2 * (b * (b - 1) // 2)
